@@ -223,7 +223,7 @@ def run_workload(args, wid: int, cold_sets: int = 0) -> dict:
         torch.cuda.synchronize()
         scan_ms = float(np.mean([e[0].elapsed_time(e[1]) for e in sev]))
         out["phases_ms"]["segment_scan"] = scan_ms
-        out["segment_scan"] = dict(roofline_block("scan_apply_kernel (+ scan_tail_kernel, scan_chain_kernel)",
+        out["segment_scan"] = dict(roofline_block("scan_direct_kernel or scan_staged_kernel (+ scan_clear_kernel)",
                                                   bytes_scan, scan_ms,
                                                   measured_traffic(w.wid, "scan") if whole else None), decay=0.9)
         del scan_out, scan_ws

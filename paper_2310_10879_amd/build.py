@@ -1,5 +1,6 @@
-"""Build libbload.so (the C-ABI HIP library) and libbload_yardsticks.so (plain streaming
-kernels that a benchmark times beside it) in-tree for gfx950.
+"""Build libbload.so (the C-ABI HIP library), libbload_yardsticks.so (plain streaming
+kernels that a benchmark times beside it) and libbload_scan_nowait.so (the scan with a bound of 0
+on its wait, for a test) in-tree for gfx950.
 
     python -m paper_2310_10879_amd.build
 
@@ -20,6 +21,7 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libbload.so")
 YS_SRC = os.path.join(PKG, "yardsticks", "bload_yardsticks.hip")
 YS_LIB = os.path.join(PKG, "libbload_yardsticks.so")
+NOWAIT_LIB = os.path.join(PKG, "libbload_scan_nowait.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -41,6 +43,11 @@ def build(verbose: bool = True) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
     cmd = [HIPCC] + FLAGS + ["-o", YS_LIB, YS_SRC]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    cmd = [HIPCC] + FLAGS + ["-DBLOAD_SCAN_POLLS=0", "-o", NOWAIT_LIB] + \
+        [os.path.join(CSRC, f) for f in ("bload_scan.hip", "bload_api.hip")]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)

@@ -4,55 +4,88 @@
 // Per feature:  h = x at the first frame of a sequence,  h = decay * h + x afterwards;
 // padding slots yield 0.  Output float32 [B, t_blk, feat_dim].
 //
-// HBM bound, and write heavy (4 output bytes per element).  The recurrence runs along time,
-// so parallelism comes from blocks, features and chunks of time.  A slot that is padding or
-// starts a sequence ("boundary") depends on nothing before it; only a sequence that runs
-// across a chunk border hands a state on.  Three kernels, all deterministic:
-//   scan_tail_kernel   per chunk (but the block's last): the state it would hand on if it
-//                      received none - the recurrence from the chunk's last boundary (or its
-//                      first slot) to its end - and whether it holds a boundary at all
-//   scan_chain_kernel  per block and feature, along the chunks: state handed to chunk c+1 =
-//                      the tail state of chunk c, plus decay^chunk * (state handed to c) when
-//                      chunk c holds no boundary
-//   scan_apply_kernel  per chunk: the recurrence over its own slots from the state handed in
-// Every slot is read and written once by scan_apply; scan_tail re-reads only the open ends
-// of the chunks.  With one chunk per block only scan_apply runs.
+// HBM bound, and write heavy (4 output bytes per element): what a plain copy in tile order
+// reaches (6.3-6.4 TB/s) is the mark, and a wave that walks a row of its own from end to end
+// stays at 5 (it keeps thousands of far-apart places open at a time).  So the tensor is cut into
+// tiles of a few hundred slots that short workgroups take nearly in memory order, every slot read
+// once and written once, and the state travels from tile to tile:
+//   - a tile computes its recurrence from a state of 0.  If it holds a boundary (a slot that
+//     starts a sequence, or padding: nothing in front of it matters) the state it ends in is
+//     final and is published, a word per feature
+//   - a tile whose first slot continues a sequence looks for the state in front of it: the final
+//     one of the tile before, or, going back over the tiles of its block as many at a time as it
+//     has groups of lanes, the nearest final one and the partial ones behind it: state =
+//     decay^chunk * state + partial.  It publishes its own end state: partial while it waits, final then
+//   - the recurrence over the tile's own slots from that state, kept in registers meanwhile, is
+//     what leaves for the output
+// A state and its mark (partial / final) are one 8-byte word, written and read by atomics of
+// device scope, so no order between different words is needed.  The states are combined in the
+// same order whichever tile finishes first: equal inputs give equal bits.
+// Tiles that wait hold their registers, so the order of the tiles is that of memory only in
+// the large: 32 blocks are taken side by side, chunk by chunk, and the tile in front has mostly
+// finished (6900 blocks of 3000 slots x 320 bytes: 3.75 ms block by block, 2.75 with 8 side by
+// side, 2.41 with 32 as with 128; without any hand-over, which is not the right result, 2.39).
 //
-// A row of lanes (16 input bytes per lane where the frame allows it, taken as quads of 4
-// elements laid out so that every load and store instruction of the row is contiguous; else
-// one element per lane) covers the features; a wavefront holds 64 / row-width rows, each on
-// a chunk of its own.  All loads of a step (8 slots) are issued together; a step of nothing but
-// padding issues none.
+// The wait ends.  A tile waits only for tiles in front of it in the same block, which publish
+// their partial state without waiting for anything and have lower workgroup numbers on the same
+// XCD (or, with few blocks, lower numbers in all), so they were started before.  Should one not
+// have been heard of after BLOAD_SCAN_POLLS looks (some ten milliseconds), the workgroup computes
+// all tiles in front of it in its block itself, the same way, and gets the same bits.
+//
+// Two kernels:
+//   scan_direct_kernel  frames of 64 elements or more.  A lane holds 32 slots of one quad (4
+//                       elements); up to 64 quads side by side, 4 to 16 groups of lanes one
+//                       behind the other in time
+//   scan_staged_kernel  smaller frames, whose rows are too short to be read lane by lane: the
+//                       tile goes through LDS in both directions, whole 16-byte vectors to
+//                       and from memory
+// Measured against the form before (a row of lanes walking a stretch of time, behind a pass over
+// the open ends of the stretches): 6900 blocks of 3000 x 80 floats 3.05 -> 2.21 ms (5.3 TB/s),
+// 79 blocks of 3000 x 2048 halfs 0.62 -> 0.49 ms, 300 videos of 37632 bytes a frame 1.34 -> 1.04 ms,
+// 1.5 * 10^8 slots of one float 6.9 -> 0.26 ms, 37 halfs a frame 0.74 -> 0.63 ms.
 #include "bload_common.hpp"
 
 #include <hip/hip_fp16.h>
 #include <math.h>
 
+#include <algorithm>
+
 namespace bload {
 
-constexpr int kScanBatch = 8;          // slots per step and row: their loads are in flight together
-constexpr uint32_t kScanAll = (1u << kScanBatch) - 1u;
-static_assert(kScanBatch % 8 == 0 && kScanBatch <= 24, "flags come eight to a load");
+#ifndef BLOAD_SCAN_POLLS
+#define BLOAD_SCAN_POLLS 16384         // looks at the tiles in front before a workgroup computes them itself
+#endif
+
+constexpr int kScanSmallFrame = 64;    // frames of fewer elements go through LDS
+constexpr int kScanRow = 64;           // units (quads or elements) of a frame side by side in a workgroup
+constexpr int kStagedElems = 8448;     // elements of a staged tile: 33 KiB of LDS, four workgroups per CU
+constexpr int kScanLong = 32, kScanShort = 8;                  // slots per lane, and where tiles are few
+constexpr int kScanStagedLong = 33, kScanStagedShort = 9;      // odd, see scan_staged_kernel
+constexpr int kScanGroup = 32;         // blocks whose tiles are taken side by side
 
 struct ScanArgs {
     const uint8_t* packed;
     const uint8_t* reset;
     const uint8_t* valid;
     float* out;
-    float* carry;                      // [B, chunks_per_block - 1, feat_dim]: tail states, then states handed on
-    uint8_t* has_boundary;             // [B, chunks_per_block - 1]
+    unsigned long long* words;         // [B, chunks - 1, feat_dim]: published states (null: chunks == 1)
     int64_t num_blocks;
-    int64_t total_slots;               // num_blocks * t_blk
+    int64_t n_units;                   // blocks, or groups of blocks_per_tile blocks
     int32_t t_blk;
     int32_t feat_dim;
-    int32_t chunk;                     // slots per chunk
-    int32_t chunks_per_block;
-    int32_t row_lanes;                 // lanes per row: a power of two <= 64
-    int32_t feat_tiles;                // rows needed to cover the features (1 unless row_lanes == 64)
-    int32_t n_vec;                     // quads (4 elements) of a frame, or elements where a frame
-                                       // is not a whole number of 16-byte pieces
+    int32_t chunk;                     // slots per tile = subs * K
+    int32_t chunks;                    // tiles per block
+    int32_t blocks_per_tile;           // chunks == 1: whole blocks per tile
+    int32_t row;                       // units side by side: lanes of a group
+    int32_t subs;                      // groups of lanes one behind the other in time
+    int32_t slices;                    // rows needed to cover a frame
+    int32_t frame_units;               // units of a frame
+    int32_t group;                     // units whose tiles are taken side by side
+    int32_t by_xcd;                    // every XCD takes whole blocks of its own
+    uint32_t polls;
     float decay;
-    float decay_chunk;                 // decay ^ chunk
+    double decay_sub[8];               // decay ^ (K * 2^i)
+    double decay_chunk;                // decay ^ chunk
 };
 
 template <typename ElemT> struct ScanElem;
@@ -68,306 +101,568 @@ template <> struct ScanElem<float> {
 };
 
 typedef float float4v __attribute__((ext_vector_type(4)));
+typedef float4v __attribute__((aligned(4))) float4v_any;
+typedef vec16 __attribute__((aligned(1))) vec16_any;
 
-// Four consecutive elements ("quad") as loaded: 4, 8 or 16 bytes in one instruction.
+// Four consecutive elements ("quad") as loaded: 4, 8 or 16 bytes in one instruction, at any address.
 typedef unsigned int vec8 __attribute__((ext_vector_type(2)));
 template <int BYTES> struct ScanBits;
-template <> struct ScanBits<4> { typedef unsigned int T; };
-template <> struct ScanBits<8> { typedef vec8 T; };
-template <> struct ScanBits<16> { typedef vec16 T; };
+template <> struct ScanBits<4> { typedef unsigned int T; typedef T __attribute__((aligned(1))) Any; };
+template <> struct ScanBits<8> { typedef vec8 T; typedef T __attribute__((aligned(1))) Any; };
+template <> struct ScanBits<16> { typedef vec16 T; typedef T __attribute__((aligned(1))) Any; };
 template <typename ElemT> union ScanQuad {
     typename ScanBits<sizeof(ElemT) * 4>::T bits;
     ElemT e[4];
 };
 
-// Flags of the 8 consecutive slots from global slot g on (`plane` covers `total` slots): bit u set
-// iff the flag of slot g + u is non-zero; slots at or behind `total` read as 0.  One 8-byte load
-// that never leaves the plane; a non-zero byte becomes a 1, and two byte-wise dot products with
-// the weights 1, 2, 4, ... gather the eight 1s into eight bits.  TINY: the plane holds fewer than
-// 8 slots, which are read one by one.
-template <bool TINY>
-__device__ __forceinline__ uint32_t scan_flags8(const uint8_t* __restrict__ plane, int64_t g, int64_t total)
+// The state `n` slots on: own = what those slots make of a state of 0, power = decay^n.  In 64
+// bits, so that a power that float32 cannot hold does no harm.  A state of exactly 0 leaves
+// `own` whatever the power is; an infinite one stays infinite when the power has become 0.
+__device__ __forceinline__ float scan_join(double power, float handed, float own)
 {
-    typedef uint64_t word_any __attribute__((aligned(1)));
-    uint64_t w;
-    if (!TINY) {
-        const int64_t from = min(g, total - 8);
-        w = *reinterpret_cast<const word_any*>(plane + from) >> (8 * (int)(g - from));
-    } else {
-        w = 0;
-        for (int u = 0; u < 8; ++u)
-            if (g + u < total) w |= (uint64_t)plane[g + u] << (8 * u);
-    }
-    const uint32_t lo = (uint32_t)w, hi = (uint32_t)(w >> 32);
-    const uint32_t lo1 = ((((lo & 0x7f7f7f7fu) + 0x7f7f7f7fu) | lo) >> 7) & 0x01010101u;
-    const uint32_t hi1 = ((((hi & 0x7f7f7f7fu) + 0x7f7f7f7fu) | hi) >> 7) & 0x01010101u;
-    return __builtin_amdgcn_udot4(hi1, 0x80402010u, __builtin_amdgcn_udot4(lo1, 0x08040201u, 0u, false), false);
+    if (handed == 0.0f) return own;
+    if (power == 0.0 && __builtin_isinf(handed)) power = __builtin_copysign(1.0, power);
+    return (float)__builtin_fma(power, (double)handed, (double)own);
 }
 
-// Flags of the kScanBatch slots from slot t of a block on (g = the same slot counted over all
-// blocks), and which of them are boundaries: padding, a start flag, the block's first slot, or
-// the slot after padding.  Slots behind the block's end read as 0.  `before`: was slot t - 1 valid.
-struct ScanFlags { uint32_t valid, boundary; };
-template <bool TINY>
-__device__ __forceinline__ ScanFlags scan_flags(const uint8_t* __restrict__ valid,
-                                                const uint8_t* __restrict__ reset, int64_t g, int64_t total,
-                                                int32_t t, int32_t T, uint32_t before)
-{
-    const uint32_t in_range = T - t >= kScanBatch ? kScanAll : (1u << (T - t)) - 1u;
-    uint32_t vm = 0, rm = 0;
-#pragma unroll
-    for (int part = 0; part < kScanBatch; part += 8) {
-        if (part == 0 || t + part < T) {
-            vm |= scan_flags8<TINY>(valid, g + part, total) << part;
-            rm |= scan_flags8<TINY>(reset, g + part, total) << part;
-        }
-    }
-    vm &= in_range;
-    const uint32_t prev_valid = (vm << 1) | before;
-    return ScanFlags{vm, in_range & (~vm | rm | ~prev_valid | (t == 0 ? 1u : 0u))};
-}
-
-// What a lane works on.  It holds QUADS quads of a frame: quad g of lane r in a row of
-// `row_lanes` lanes is quad number tile_base + g * row_lanes + r, so that each load and each
-// store instruction of a row covers one contiguous stretch of the frame.
-template <typename ElemT, int QUADS, bool VEC, bool TINY>
-struct ScanLane {
-    static constexpr int EPL = VEC ? QUADS * 4 : 1;      // elements per lane
-    bool idle;
-    int64_t block;
-    int32_t chunk;
-    int32_t t0, t1;                    // the chunk's slots inside the block
-    int64_t first_elem;                // first element of the lane inside a frame
-    int32_t quad_stride;               // elements between the lane's quads
-    bool quad_on[QUADS];
-
-    __device__ __forceinline__ ScanLane(const ScanArgs& a, int32_t chunks_used)
-    {
-        const int lane = lane_id();
-        const int rows_per_wave = kWave / a.row_lanes;
-        const int64_t wave = (int64_t)xcd_contiguous(blockIdx.x, gridDim.x) * (kThreads / kWave) + wave_id();
-        const int32_t feat_tile = (int32_t)(wave % a.feat_tiles);
-        const int64_t item = (wave / a.feat_tiles) * rows_per_wave + lane / a.row_lanes;
-        const int32_t r = lane & (a.row_lanes - 1);
-        const int32_t first = VEC ? feat_tile * a.row_lanes * QUADS + r : feat_tile * a.row_lanes + r;
-        idle = item >= a.num_blocks * chunks_used || first >= a.n_vec;
-        block = idle ? 0 : item / chunks_used;
-        chunk = idle ? 0 : (int32_t)(item - block * chunks_used);
-        t0 = chunk * a.chunk;
-        t1 = min(a.t_blk, t0 + a.chunk);
-        if (t0 >= a.t_blk) idle = true;
-        first_elem = (int64_t)first * (VEC ? 4 : 1);
-        quad_stride = a.row_lanes * 4;
-#pragma unroll
-        for (int g = 0; g < QUADS; ++g) quad_on[g] = !VEC || first + g * a.row_lanes < a.n_vec;
-    }
-
-    // kScanBatch slots from t on: the recurrence goes on in h; the first `keep` slots are handed
-    // to `emit(u, g, quad)`.  `at`: the lane's first byte of slot t.  FULL: all kScanBatch slots
-    // lie in the block and all are kept, which spares every clamp and test; otherwise slots
-    // behind the block's end re-read its last slot.  A batch of nothing but padding (block
-    // tails) costs no read: every state ends there and every output is 0.  h = decay * h + x is
-    // one fused multiply-add (one rounding), the state of a boundary slot being replaced by 0
-    // first (never multiplied: it may be infinite).
-    template <bool FULL, typename Emit>
-    __device__ __forceinline__ void step(const ScanArgs& a, const uint8_t* __restrict__ at, int32_t t,
-                                         ScanFlags f, float (&h)[EPL], int keep, Emit emit) const
-    {
-        const int64_t frame_bytes = (int64_t)a.feat_dim * (int64_t)sizeof(ElemT);
-        if (f.valid == 0) {
-#pragma unroll
-            for (int k = 0; k < EPL; ++k) h[k] = 0.0f;
-            const float4v zero = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int u = 0; u < kScanBatch; ++u) {
-#pragma unroll
-                for (int g = 0; g < (VEC ? QUADS : 1); ++g)
-                    if ((FULL || u < keep) && quad_on[g]) emit(u, g, zero);
-            }
-            return;
-        }
-        const int32_t last = a.t_blk - 1 - t;              // the block's last slot, counted from t
-        if (VEC) {
-            ScanQuad<ElemT> x[kScanBatch][QUADS];
-#pragma unroll
-            for (int u = 0; u < kScanBatch; ++u) {
-                const uint8_t* frame = at + (int64_t)(FULL ? u : min(u, last)) * frame_bytes;
-#pragma unroll
-                for (int g = 0; g < QUADS; ++g) {
-                    const int64_t off = quad_on[g] ? (int64_t)g * quad_stride * (int64_t)sizeof(ElemT) : 0;
-                    x[u][g].bits = __builtin_nontemporal_load(
-                        reinterpret_cast<const typename ScanBits<sizeof(ElemT) * 4>::T*>(frame + off));
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kScanBatch; ++u) {
-                const bool is_valid = (f.valid >> u) & 1u, starts = (f.boundary >> u) & 1u;
-#pragma unroll
-                for (int g = 0; g < QUADS; ++g) {
-                    float4v o;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float xv = is_valid ? ScanElem<ElemT>::get(x[u][g].e[j]) : 0.0f;
-                        h[g * 4 + j] = __builtin_fmaf(a.decay, starts ? 0.0f : h[g * 4 + j], xv);
-                        o[j] = h[g * 4 + j];
-                    }
-                    if ((FULL || u < keep) && quad_on[g]) emit(u, g, o);
-                }
-            }
-        } else {
-            ElemT x[kScanBatch];
-#pragma unroll
-            for (int u = 0; u < kScanBatch; ++u)
-                x[u] = *reinterpret_cast<const ElemT*>(at + (int64_t)(FULL ? u : min(u, last)) * frame_bytes);
-#pragma unroll
-            for (int u = 0; u < kScanBatch; ++u) {
-                const bool is_valid = (f.valid >> u) & 1u, starts = (f.boundary >> u) & 1u;
-                const float xv = is_valid ? ScanElem<ElemT>::get(x[u]) : 0.0f;
-                h[0] = __builtin_fmaf(a.decay, starts ? 0.0f : h[0], xv);
-                float4v o = {h[0], 0.0f, 0.0f, 0.0f};
-                if (FULL || u < keep) emit(u, 0, o);
-            }
-        }
-    }
-
-    // The recurrence over the slots [from, t1) of the lane's block from the state in h, batch by
-    // batch.  `emit(t, n, u, g, quad)`: slot t + u of a batch of n slots that begins at slot t.
-    template <typename Emit>
-    __device__ __forceinline__ void recur(const ScanArgs& a, int32_t from, int32_t t1, float (&h)[EPL], Emit emit) const
-    {
-        const int64_t frame_bytes = (int64_t)a.feat_dim * (int64_t)sizeof(ElemT);
-        const int64_t slot0 = block * a.t_blk;
-        const uint8_t* at = a.packed + ((slot0 + from) * a.feat_dim + first_elem) * (int64_t)sizeof(ElemT);
-        uint32_t before = from > 0 ? (a.valid[slot0 + from - 1] != 0) : 0u;
-        for (int32_t t = from; t < t1; t += kScanBatch, at += (int64_t)kScanBatch * frame_bytes) {
-            const ScanFlags f = scan_flags<TINY>(a.valid, a.reset, slot0 + t, a.total_slots, t, a.t_blk, before);
-            const int n = min(kScanBatch, t1 - t);
-            auto out = [&](int u, int g, float4v o) { emit(t, n, u, g, o); };
-            if (n == kScanBatch) step<true>(a, at, t, f, h, n, out);
-            else step<false>(a, at, t, f, h, n, out);
-            before = (f.valid >> (n - 1)) & 1u;
-        }
-    }
+// Where a workgroup's tile lies: `unit` = block (or group of blocks), tile `c` of it, feature slice.
+struct ScanTile {
+    int64_t unit;
+    int32_t c, slice;
 };
 
-// The state a chunk hands on when it receives none, and whether it holds a boundary.
-template <typename ElemT, int QUADS, bool VEC, bool TINY>
-__global__ __launch_bounds__(kThreads) void scan_tail_kernel(ScanArgs a)
+__device__ __forceinline__ ScanTile scan_tile(const ScanArgs& a)
 {
-    typedef ScanLane<ElemT, QUADS, VEC, TINY> Lane;
-    const Lane me(a, a.chunks_per_block - 1);                 // the block's last chunk hands nothing on
-    if (me.idle) return;
-    const int64_t slot0 = me.block * a.t_blk;
-
-    // the chunk's last boundary
-    int32_t last = -1;
-    uint32_t before = me.t0 > 0 ? (a.valid[slot0 + me.t0 - 1] != 0) : 0u;
-    for (int32_t t = me.t0; t < me.t1; t += kScanBatch) {
-        const ScanFlags f = scan_flags<TINY>(a.valid, a.reset, slot0 + t, a.total_slots, t, a.t_blk, before);
-        const int n = min(kScanBatch, me.t1 - t);
-        const uint32_t mine = f.boundary & ((1u << n) - 1u);
-        if (mine) last = t + 31 - __builtin_clz(mine);
-        before = (f.valid >> (n - 1)) & 1u;
+    const uint32_t slices = (uint32_t)a.slices, per_unit = (uint32_t)a.chunks * slices;
+    uint32_t y = blockIdx.x, first = 0, units = (uint32_t)a.n_units;
+    if (a.by_xcd) {
+        // workgroup b runs on XCD b mod 8: every XCD takes units of its own
+        const uint32_t x = y % kXcds, most = (units + kXcds - 1) / kXcds;
+        y /= kXcds;
+        first = x * most;
+        units = first < units ? min(most, units - first) : 0u;
     }
+    const uint32_t G = (uint32_t)a.group;
+    const uint32_t g = y / (G * per_unit), in_group = y - g * (G * per_unit);
+    if (g * G >= units) return ScanTile{a.n_units, 0, 0};
+    const uint32_t here = min(G, units - g * G);                 // units of this group
+    const uint32_t c = in_group / (here * slices), rest = in_group - c * (here * slices);
+    if (c >= (uint32_t)a.chunks) return ScanTile{a.n_units, 0, 0};
+    const uint32_t u = rest / slices;
+    return ScanTile{(int64_t)(first + g * G + u), (int32_t)c, (int32_t)(rest - u * slices)};
+}
 
-    // the recurrence from there (from the chunk's first slot if there is none) to the chunk's end
-    const int32_t from = last >= 0 ? last : me.t0;
-    float h[Lane::EPL];
+// Slots of tile c of a unit: first slot (counted over all blocks), slots, place in its block.
+struct ScanSpan {
+    int64_t g0;
+    int32_t n, rem0;
+};
+
+__device__ __forceinline__ ScanSpan scan_span(const ScanArgs& a, int64_t unit, int32_t c)
+{
+    ScanSpan s;
+    if (a.chunks > 1) {
+        s.rem0 = c * a.chunk;
+        s.g0 = unit * (int64_t)a.t_blk + s.rem0;
+        s.n = min(a.chunk, a.t_blk - s.rem0);
+    } else {
+        const int64_t b0 = unit * a.blocks_per_tile;
+        s.rem0 = 0;
+        s.g0 = b0 * (int64_t)a.t_blk;
+        s.n = (int32_t)min((int64_t)a.blocks_per_tile, a.num_blocks - b0) * a.t_blk;
+    }
+    return s;
+}
+
+// What the lanes of a workgroup exchange.  Lane `tid` = group s, place q in the row.
+template <int UNIT> struct ScanShared {
+    alignas(16) float value[2][kThreads][UNIT];
+    uint32_t mark[2][kThreads];
+};
+
+// Inclusive scan over the groups: in, v = what the lane's own slots make of a state of 0 and
+// `closed` = they hold a boundary; out, the same for all slots of the tile up to the lane's last
+// (left in sh.value / sh.mark [return value], with a barrier behind it).
+template <int UNIT>
+__device__ __forceinline__ int scan_groups(const ScanArgs& a, ScanShared<UNIT>& sh, int s, float (&v)[UNIT],
+                                           uint32_t closed)
+{
+    const int tid = (int)threadIdx.x;
+    int buf = 0;
 #pragma unroll
-    for (int k = 0; k < Lane::EPL; ++k) h[k] = 0.0f;
-    float* carry = a.carry + (me.block * (a.chunks_per_block - 1) + me.chunk) * (int64_t)a.feat_dim + me.first_elem;
-    me.recur(a, from, me.t1, h, [&](int32_t t, int n, int u, int g, float4v o) {
-        if (t + n >= me.t1 && u == n - 1) {
-            if (VEC) *reinterpret_cast<float4v*>(carry + g * me.quad_stride) = o;
-            else carry[0] = o[0];
+    for (int i = 0; i < 8; ++i) {
+        const int step = 1 << i;
+        if (step >= a.subs) break;
+#pragma unroll
+        for (int k = 0; k < UNIT; ++k) sh.value[buf][tid][k] = v[k];
+        sh.mark[buf][tid] = closed;
+        __syncthreads();
+        if (s >= step && s < a.subs) {
+            const int other = tid - step * a.row;
+            if (!closed) {
+#pragma unroll
+                for (int k = 0; k < UNIT; ++k) v[k] = scan_join(a.decay_sub[i], sh.value[buf][other][k], v[k]);
+                closed = sh.mark[buf][other];
+            }
         }
-    });
-    if (me.first_elem == 0) a.has_boundary[me.block * (a.chunks_per_block - 1) + me.chunk] = last >= 0;
+        buf ^= 1;
+    }
+#pragma unroll
+    for (int k = 0; k < UNIT; ++k) sh.value[buf][tid][k] = v[k];
+    sh.mark[buf][tid] = closed;
+    __syncthreads();
+    return buf;
 }
 
-// Along the chunks of a block: what chunk c + 1 is handed = the tail state of chunk c, plus
-// decay^chunk times what chunk c was handed if chunk c holds no boundary.  In place.
-__global__ __launch_bounds__(kThreads) void scan_chain_kernel(ScanArgs a)
+constexpr uint32_t kPartial = 1, kFinal = 2;
+
+__device__ __forceinline__ void scan_publish(unsigned long long* word, float v, uint32_t mark)
 {
-    const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (idx >= a.num_blocks * a.feat_dim) return;
-    const int64_t block = idx / a.feat_dim, d = idx - block * a.feat_dim;
-    const int32_t links = a.chunks_per_block - 1;
-    float handed = 0.0f;
-    for (int32_t c = 0; c < links; ++c) {
-        const int64_t at = (block * links + c) * (int64_t)a.feat_dim + d;
-        const float tail = a.carry[at];
-        // a state of exactly 0 stays 0 whatever decay^chunk is (it may have overflowed to inf)
-        handed = (a.has_boundary[block * links + c] || handed == 0.0f) ? tail : a.decay_chunk * handed + tail;
-        a.carry[at] = handed;
+    __hip_atomic_store(word, ((unsigned long long)mark << 32) | __float_as_uint(v), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// What group s sees of tile c - 1 - s: the words of the lane's features.
+template <int UNIT> struct ScanSeen {
+    unsigned long long w[UNIT];
+};
+
+template <int UNIT>
+__device__ __forceinline__ void scan_look(const ScanArgs& a, const unsigned long long* words, int s, bool looks,
+                                          ScanSeen<UNIT>& seen)
+{
+#pragma unroll
+    for (int k = 0; k < UNIT; ++k) seen.w[k] = 0;
+    if (looks) {
+        const unsigned long long* from = words - (int64_t)(1 + s) * a.feat_dim;
+#pragma unroll
+        for (int k = 0; k < UNIT; ++k) seen.w[k] = __hip_atomic_load(from + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
-// The recurrence over a chunk's own slots, from the state handed in.
-template <typename ElemT, int QUADS, bool VEC, bool TINY>
-__global__ __launch_bounds__(kThreads) void scan_apply_kernel(ScanArgs a)
+// The state tile c is handed, for the features of place q: true if it was found.  `words` = the
+// tile's own words at the lane's first feature.  The first look is at tile c - 1 alone, whose state
+// is final most of the time; where it is not, `not_yet` is called before the wait begins.  Uses
+// sh.value / sh.mark [buf]; all lanes of the workgroup call it together and get the same answer.
+template <int UNIT, typename NotYet>
+__device__ __forceinline__ bool scan_look_back(const ScanArgs& a, ScanShared<UNIT>& sh, int buf,
+                                               const unsigned long long* words, int s, int q, int window, bool active,
+                                               float (&handed)[UNIT], NotYet not_yet)
 {
-    typedef ScanLane<ElemT, QUADS, VEC, TINY> Lane;
-    const Lane me(a, a.chunks_per_block);
-    if (me.idle) return;
-    float h[Lane::EPL];
+    const int tid = (int)threadIdx.x;
+    for (uint32_t look = 0; look < a.polls; ++look) {
+        ScanSeen<UNIT> seen;
+        scan_look<UNIT>(a, words, s, active && s < (look == 0 ? 1 : window), seen);
+        // words that are seen half way from partial to final are none yet
+        uint32_t mark = (uint32_t)(seen.w[0] >> 32);
 #pragma unroll
-    for (int k = 0; k < Lane::EPL; ++k) h[k] = 0.0f;
-    if (me.chunk > 0) {
-        const float* handed = a.carry + (me.block * (a.chunks_per_block - 1) + me.chunk - 1) * (int64_t)a.feat_dim +
-                              me.first_elem;
+        for (int k = 1; k < UNIT; ++k) mark = (uint32_t)(seen.w[k] >> 32) == mark ? mark : 0u;
 #pragma unroll
-        for (int g = 0; g < QUADS; ++g) {
-            if (me.quad_on[g]) {
-                if (VEC) {
-                    const float4v v = *reinterpret_cast<const float4v*>(handed + g * me.quad_stride);
+        for (int k = 0; k < UNIT; ++k) sh.value[buf][tid][k] = __uint_as_float((uint32_t)seen.w[k]);
+        sh.mark[buf][tid] = mark;
+        __syncthreads();
+        int found = -1;
+        if (active) {
+            for (int j = 0; j < window; ++j) {
+                const uint32_t m = sh.mark[buf][j * a.row + q];
+                if (m == kFinal) found = j;
+                if (m != kPartial) break;
+            }
+        }
+        if (__syncthreads_and(!active || found >= 0)) {
+            if (active) {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) h[g * 4 + j] = v[j];
-                } else {
-                    h[0] = handed[0];
+                for (int k = 0; k < UNIT; ++k) handed[k] = sh.value[buf][found * a.row + q][k];
+                for (int j = found - 1; j >= 0; --j) {
+#pragma unroll
+                    for (int k = 0; k < UNIT; ++k)
+                        handed[k] = scan_join(a.decay_chunk, handed[k], sh.value[buf][j * a.row + q][k]);
                 }
+            }
+            __syncthreads();
+            return true;
+        }
+        if (look == 0) not_yet();
+        else __builtin_amdgcn_s_sleep(1);
+    }
+    return false;
+}
+
+// decay ^ (K * s)
+__device__ __forceinline__ double scan_power(const ScanArgs& a, int s)
+{
+    double p = 1.0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        if ((s >> i) & 1) p *= a.decay_sub[i];
+    return p;
+}
+
+// What the lane's slots of tile c, read one after another from memory, make of a state of 0, and
+// whether they hold a boundary: the arithmetic of the kernels below, for the rare case that a
+// workgroup computes tiles that are not its own.
+template <typename ElemT, int UNIT, int K>
+__device__ __forceinline__ uint32_t scan_slots_again(const ScanArgs& a, const ScanSpan& span, int s, int64_t feature,
+                                                     bool active, float (&v)[UNIT])
+{
+    uint32_t closed = 0;
+#pragma unroll
+    for (int k = 0; k < UNIT; ++k) v[k] = 0.0f;
+#pragma nounroll
+    for (int t = s * K; active && t < min((s + 1) * K, span.n); ++t) {
+        const int64_t g = span.g0 + t;
+        const bool valid = a.valid[g] != 0;
+        const bool first = span.rem0 + t == 0;                   // only blocks cut into tiles come here
+        const bool starts = !valid || a.reset[g] != 0 || first || a.valid[g - (first ? 0 : 1)] == 0;
+        closed |= starts ? 1u : 0u;
+        const ElemT* x = reinterpret_cast<const ElemT*>(a.packed) + g * a.feat_dim + feature;
+#pragma unroll
+        for (int k = 0; k < UNIT; ++k)
+            v[k] = __builtin_fmaf(a.decay, starts ? 0.0f : v[k], valid ? ScanElem<ElemT>::get(x[k]) : 0.0f);
+    }
+    return closed;
+}
+
+// The part both kernels share: from what the lane's slots make of a state of 0 (v), whether they
+// hold a boundary (closed) and whether the tile's first slot is one (starts_closed, the same in
+// all lanes), the state in front of the lane's first slot (h).
+template <typename ElemT, int UNIT, int K>
+__device__ __forceinline__ void scan_carry_in(const ScanArgs& a, ScanShared<UNIT>& sh, const ScanTile& tile, int s,
+                                              int q, int64_t feature, bool active, float (&v)[UNIT], uint32_t closed,
+                                              bool starts_closed, float (&h)[UNIT])
+{
+    const int tid = (int)threadIdx.x;
+    const int last = (a.subs - 1) * a.row + q;         // the lane that ends the tile at this place
+    const bool open_front = tile.c > 0 && !starts_closed;
+    const int buf = scan_groups(a, sh, s, v, closed);
+    // what the groups in front make of a state of 0
+    const bool front = s > 0 && s < a.subs;
+    const bool front_closed = front && sh.mark[buf][tid - a.row] != 0;
+#pragma unroll
+    for (int k = 0; k < UNIT; ++k) h[k] = front ? sh.value[buf][tid - a.row][k] : 0.0f;
+    if (a.chunks == 1) return;
+
+    const bool publishes = tile.c + 1 < a.chunks && active && s == 0;
+    const bool tile_closed = sh.mark[buf][last] != 0;
+    float total[UNIT], handed[UNIT];
+#pragma unroll
+    for (int k = 0; k < UNIT; ++k) total[k] = sh.value[buf][last][k];
+    unsigned long long* words = a.words + (tile.unit * (int64_t)(a.chunks - 1) + tile.c) * a.feat_dim + feature;
+    if (publishes && tile_closed) {
+#pragma unroll
+        for (int k = 0; k < UNIT; ++k) scan_publish(words + k, total[k], kFinal);
+    }
+    if (!open_front) return;
+    if (!scan_look_back<UNIT>(a, sh, buf ^ 1, words, s, q, min(a.subs, tile.c), active, handed, [&] {
+            if (publishes && !tile_closed) {
+#pragma unroll
+                for (int k = 0; k < UNIT; ++k) scan_publish(words + k, total[k], kPartial);
+            }
+        })) {
+        // not heard of in time: all tiles of the block in front of this one, one after another
+#pragma unroll
+        for (int k = 0; k < UNIT; ++k) handed[k] = 0.0f;
+#pragma nounroll
+        for (int32_t c = 0; c < tile.c; ++c) {
+            __syncthreads();
+            const uint32_t any = scan_slots_again<ElemT, UNIT, K>(a, scan_span(a, tile.unit, c), s, feature, active, v);
+            const int at = scan_groups(a, sh, s, v, any);
+#pragma unroll
+            for (int k = 0; k < UNIT; ++k) {
+                const float t = sh.value[at][last][k];
+                handed[k] = sh.mark[at][last] ? t : scan_join(a.decay_chunk, handed[k], t);
             }
         }
     }
-    float* dst = a.out + me.block * a.t_blk * (int64_t)a.feat_dim + me.first_elem;
-    me.recur(a, me.t0, me.t1, h, [&](int32_t t, int, int u, int g, float4v o) {
-        float* to = dst + (int64_t)(t + u) * a.feat_dim;
-        if (VEC) __builtin_nontemporal_store(o, reinterpret_cast<float4v*>(to + g * me.quad_stride));
-        else __builtin_nontemporal_store(o[0], to);
-    });
+    if (publishes && !tile_closed) {
+#pragma unroll
+        for (int k = 0; k < UNIT; ++k) scan_publish(words + k, scan_join(a.decay_chunk, handed[k], total[k]), kFinal);
+    }
+    if (!front_closed) {
+        const double p = scan_power(a, s);
+#pragma unroll
+        for (int k = 0; k < UNIT; ++k) h[k] = scan_join(p, handed[k], h[k]);
+    }
+}
+
+// Frames of 64 elements or more.
+template <typename ElemT, int K>
+__global__ __launch_bounds__(kThreads, sizeof(ElemT) == 4 ? 2 : 3) void scan_direct_kernel(ScanArgs a)
+{
+    constexpr int UNIT = 4;
+    constexpr int kMostSlots = kThreads / (kScanSmallFrame / 4) * K;     // groups of at least 16 lanes
+    constexpr int kWords = (kMostSlots + 63) / 64;
+    constexpr uint32_t ALL = K == 32 ? ~0u : (1u << (K & 31)) - 1u;
+    static_assert(64 % K == 0, "the flags of a lane lie in one 64-bit word");
+    __shared__ ScanShared<UNIT> sh;
+    __shared__ unsigned long long s_valid[kWords], s_bound[kWords];
+    const ScanTile tile = scan_tile(a);
+    if (tile.unit >= a.n_units) return;
+    const int tid = (int)threadIdx.x;
+    const int s = (int)((uint32_t)tid / (uint32_t)a.row), q = tid - s * a.row;
+    const int32_t unit = tile.slice * a.row + q;
+    const bool active = s < a.subs && unit < a.frame_units;
+    // a frame that is no whole number of quads: the last one lies over the end of the one before
+    // (both lanes compute and store the same)
+    const int64_t feature = active ? min((int64_t)unit * UNIT, (int64_t)a.feat_dim - UNIT) : 0;
+    const int64_t D = a.feat_dim;
+    const uint32_t lane_at = active ? (uint32_t)(s * K) * (uint32_t)a.feat_dim + (uint32_t)feature : 0u;
+
+    ScanQuad<ElemT> x[K];
+    uint32_t vm = 0, bm = 0;           // the lane's slots: valid, boundary
+    const ScanSpan span = scan_span(a, tile.unit, tile.c);
+    float v[UNIT], h[UNIT];
+    {
+        for (int t0 = 0; t0 < a.chunk; t0 += kThreads) {
+            const int t = t0 + tid;
+            bool valid = false, bound = false;
+            if (t < span.n) {
+                const int64_t g = span.g0 + t;
+                const uint32_t pos = a.chunks > 1 ? (uint32_t)(span.rem0 + t) : (uint32_t)t % (uint32_t)a.t_blk;
+                const bool before = pos != 0 && a.valid[g - (pos != 0 ? 1 : 0)] != 0;
+                valid = a.valid[g] != 0;
+                bound = !valid || !before || a.reset[g] != 0;
+            }
+            const unsigned long long v64 = __ballot(valid), b64 = __ballot(bound);
+            const int word = (t0 >> 6) + wave_id();
+            if (lane_id() == 0 && word < kWords) { s_valid[word] = v64; s_bound[word] = b64; }
+        }
+        __syncthreads();
+        vm = bm = 0;
+        if (active) {
+            vm = (uint32_t)(s_valid[(s * K) >> 6] >> ((s * K) & 63)) & ALL;
+            bm = (uint32_t)(s_bound[(s * K) >> 6] >> ((s * K) & 63)) & ALL;
+        }
+        // wave-uniform frame addresses, 32-bit offsets of the lanes
+        const int64_t frame_bytes = D * (int64_t)sizeof(ElemT);
+        const uint8_t* from = a.packed + span.g0 * frame_bytes;
+        const uint32_t at = lane_at * (uint32_t)sizeof(ElemT);
+        typedef typename ScanBits<sizeof(ElemT) * 4>::T Bits;
+        typedef typename ScanBits<sizeof(ElemT) * 4>::Any BitsAny;
+        if (vm == ALL) {
+#pragma unroll
+            for (int u = 0; u < K; ++u)
+                x[u].bits = __builtin_nontemporal_load(reinterpret_cast<const BitsAny*>(from + u * frame_bytes + at));
+        } else {
+#pragma unroll
+            for (int u = 0; u < K; ++u) {
+                x[u].bits = Bits{};
+                if ((vm >> u) & 1u)
+                    x[u].bits = __builtin_nontemporal_load(reinterpret_cast<const BitsAny*>(from + u * frame_bytes + at));
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < UNIT; ++k) v[k] = 0.0f;
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+            const bool starts = (bm >> u) & 1u;
+#pragma unroll
+            for (int k = 0; k < UNIT; ++k)
+                v[k] = __builtin_fmaf(a.decay, starts ? 0.0f : v[k], ScanElem<ElemT>::get(x[u].e[k]));
+        }
+    }
+    scan_carry_in<ElemT, UNIT, K>(a, sh, tile, s, q, feature, active, v, bm != 0u ? 1u : 0u, (s_bound[0] & 1ull) != 0, h);
+    if (!active) return;
+    // the payload stays packed until here: not the floats made of it above, four times as many registers
+    if constexpr (sizeof(ElemT) < 4) {
+#pragma unroll
+        for (int u = 0; u < K; ++u) asm volatile("" : "+v"(x[u].bits));
+    }
+
+    uint8_t* to = reinterpret_cast<uint8_t*>(a.out + span.g0 * D);
+    const uint32_t at = lane_at * 4u;
+    const int left = span.n - s * K;
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+        const bool starts = (bm >> u) & 1u;
+#pragma unroll
+        for (int k = 0; k < UNIT; ++k)
+            h[k] = __builtin_fmaf(a.decay, starts ? 0.0f : h[k], ScanElem<ElemT>::get(x[u].e[k]));
+        if (u < left) {
+            const float4v o = {h[0], h[1], h[2], h[3]};
+            __builtin_nontemporal_store(o, reinterpret_cast<float4v_any*>(to + u * D * 4 + at));
+        }
+    }
+}
+
+// Bit j: byte j of the 16 flag bytes is non-zero.
+__device__ __forceinline__ uint32_t scan_nonzero16(vec16 w)
+{
+    uint32_t t[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) t[k] = ((((w[k] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w[k]) >> 7) & 0x01010101u;
+    const uint32_t lo = __builtin_amdgcn_udot4(t[1], 0x80402010u, __builtin_amdgcn_udot4(t[0], 0x08040201u, 0u, false), false);
+    const uint32_t hi = __builtin_amdgcn_udot4(t[3], 0x80402010u, __builtin_amdgcn_udot4(t[2], 0x08040201u, 0u, false), false);
+    return lo | (hi << 8);
+}
+
+// The flags of the 16 slots from g on, of which `left` lie in the tile: one load that stays inside
+// the plane of `total` slots (a plane of fewer than 16 is read byte by byte).
+__device__ __forceinline__ uint32_t scan_flags16(const uint8_t* __restrict__ plane, int64_t g, int32_t left, int64_t total)
+{
+    if (left <= 0) return 0;
+    const uint32_t in_tile = left >= 16 ? 0xffffu : (1u << left) - 1u;
+    if (total >= 16) {
+        const int64_t from = min(g, total - 16);
+        return (scan_nonzero16(*reinterpret_cast<const vec16_any*>(plane + from)) >> (int)(g - from)) & in_tile;
+    }
+    uint32_t m = 0;
+    for (int j = 0; j < left && j < 16; ++j) m |= (uint32_t)(plane[g + j] != 0) << j;
+    return m;
+}
+
+// Smaller frames.  K is odd, so that lanes K frames apart in LDS spread over the banks.
+template <typename ElemT, int K>
+__global__ __launch_bounds__(kThreads, 4) void scan_staged_kernel(ScanArgs a)
+{
+    static_assert(K % 2 == 1 && K * kThreads <= kStagedElems && K < 34, "a lane's flags fit behind a 31-bit shift");
+    constexpr int kGroups = kStagedElems / 16 + 4;     // groups of 16 flags, the last ones zero
+    __shared__ ScanShared<1> sh;
+    __shared__ alignas(16) float s_x[K * kThreads];
+    __shared__ alignas(16) uint16_t s_valid[kGroups], s_reset[kGroups];
+    const ScanTile tile = scan_tile(a);
+    if (tile.unit >= a.n_units) return;
+    const int tid = (int)threadIdx.x;
+    const int D = a.feat_dim;
+    const int s = (int)((uint32_t)tid / (uint32_t)D), q = tid - s * D;
+    const bool active = s < a.subs;
+
+    float x[K];
+    uint64_t bm = 0;                   // the lane's slots: boundary
+    const ScanSpan span = scan_span(a, tile.unit, tile.c);
+    float v[1], h[1];
+    bool starts_closed;
+    {
+        // the payload as whole vectors, all asked for before anything is waited for
+        constexpr int EPV = 16 / (int)sizeof(ElemT);
+        constexpr int NV = (K + EPV - 1) / EPV;
+        const int elems = span.n * D, vecs = elems / EPV;
+        const uint8_t* from = a.packed + span.g0 * D * (int64_t)sizeof(ElemT);
+        vec16 in[NV];
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            const int i = tid + k * kThreads;
+            in[k] = vec16{0u, 0u, 0u, 0u};
+            if (i < vecs) in[k] = __builtin_nontemporal_load(reinterpret_cast<const vec16_any*>(from) + i);
+        }
+        const int64_t total = a.num_blocks * (int64_t)a.t_blk;
+        for (int i = tid; i < (a.chunk + 15) / 16 + 4; i += kThreads) {
+            s_valid[i] = (uint16_t)scan_flags16(a.valid, span.g0 + 16 * i, span.n - 16 * i, total);
+            s_reset[i] = (uint16_t)scan_flags16(a.reset, span.g0 + 16 * i, span.n - 16 * i, total);
+        }
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            const int i = tid + k * kThreads;
+            union { vec16 v; ElemT e[EPV]; } u;
+            u.v = in[k];
+            if (i < vecs) {
+#pragma unroll
+                for (int j = 0; j < EPV; j += 4) {
+                    const float4v o = {ScanElem<ElemT>::get(u.e[j]), ScanElem<ElemT>::get(u.e[j + 1]),
+                                       ScanElem<ElemT>::get(u.e[j + 2]), ScanElem<ElemT>::get(u.e[j + 3])};
+                    *reinterpret_cast<float4v*>(s_x + i * EPV + j) = o;
+                }
+            }
+        }
+        for (int i = vecs * EPV + tid; i < elems; i += kThreads)
+            s_x[i] = ScanElem<ElemT>::get(reinterpret_cast<const ElemT*>(from)[i]);
+        const bool before_tile = span.rem0 > 0 && a.valid[span.g0 - (span.rem0 > 0 ? 1 : 0)] != 0;
+        __syncthreads();
+
+        const int o = s * K, left = active ? min(K, span.n - o) : 0;
+        uint64_t vm = 0;
+        bm = 0;
+        if (left > 0) {
+            const uint32_t* v32 = reinterpret_cast<const uint32_t*>(s_valid) + (o >> 5);
+            const uint32_t* r32 = reinterpret_cast<const uint32_t*>(s_reset) + (o >> 5);
+            const uint64_t in_range = ~0ull >> (64 - left);
+            vm = (((uint64_t)v32[1] << 32 | v32[0]) >> (o & 31)) & in_range;
+            const uint64_t rm = ((uint64_t)r32[1] << 32 | r32[0]) >> (o & 31);
+            const uint64_t before = o > 0 ? (s_valid[(o - 1) >> 4] >> ((o - 1) & 15)) & 1u : (uint32_t)before_tile;
+            const uint32_t T = (uint32_t)a.t_blk, pos = (uint32_t)(span.rem0 + o) % T;
+            uint64_t first = 0;
+            for (uint32_t k = pos == 0 ? 0 : T - pos; k < (uint32_t)left; k += T) first |= 1ull << k;
+            bm = (~vm | rm | first | ~(vm << 1 | before)) & in_range;
+        }
+#pragma unroll
+        for (int u = 0; u < K; ++u) x[u] = (vm >> u) & 1u ? s_x[(o + u) * D + q] : 0.0f;
+        float t = 0.0f;
+#pragma unroll
+        for (int u = 0; u < K; ++u) t = __builtin_fmaf(a.decay, (bm >> u) & 1u ? 0.0f : t, x[u]);
+        v[0] = t;
+        starts_closed = !before_tile || (s_reset[0] & 1u) || !(s_valid[0] & 1u);
+    }
+    scan_carry_in<ElemT, 1, K>(a, sh, tile, s, q, q, active, v, bm != 0 ? 1u : 0u, starts_closed, h);
+
+    const int left = active ? span.n - s * K : 0;
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+        h[0] = __builtin_fmaf(a.decay, (bm >> u) & 1u ? 0.0f : h[0], x[u]);
+        if (u < left) s_x[(s * K + u) * D + q] = h[0];
+    }
+    __syncthreads();
+    const int elems = span.n * D, quads = elems / 4;
+    float* to = a.out + span.g0 * D;
+    for (int i = tid; i < quads; i += kThreads)
+        __builtin_nontemporal_store(*reinterpret_cast<const float4v*>(s_x + 4 * i), reinterpret_cast<float4v_any*>(to) + i);
+    for (int i = quads * 4 + tid; i < elems; i += kThreads) __builtin_nontemporal_store(s_x[i], to + i);
+}
+
+// No state is published yet.
+__global__ __launch_bounds__(kThreads) void scan_clear_kernel(unsigned long long* words, int64_t n)
+{
+    const int64_t stride = (int64_t)gridDim.x * kThreads;
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride) words[i] = 0;
 }
 
 struct ScanPlan {
-    int32_t epv, n_vec, row_lanes, feat_tiles, chunk, chunks_per_block;
-    int64_t rows_per_wave;
-    bool tiny;
-    size_t carry_bytes, bytes;         // workspace: the states handed on, then the boundary marks
+    bool staged;
+    int32_t k;                         // slots per lane
+    int32_t row, subs, slices, frame_units;
+    int32_t chunk, chunks, blocks_per_tile;
+    int64_t n_units, grid;
+    bool by_xcd;
+    size_t bytes;                      // workspace: the published states
 };
 
 static ScanPlan scan_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, size_t elem)
 {
     ScanPlan p{};
-    // whole 16-byte pieces per frame: a lane takes 16 / elem elements as quads; else one element
-    p.epv = (feat_dim * (int64_t)elem) % 16 == 0 ? (int32_t)(16 / elem) : 1;
-    p.tiny = num_blocks * t_blk < 8;               // flags cannot be read eight at a time
-    if (p.tiny) p.epv = 1;
-    p.n_vec = p.epv > 1 ? (int32_t)(feat_dim / 4) : (int32_t)feat_dim;      // quads, or elements
-    const int64_t per_lane = p.epv > 1 ? p.epv / 4 : 1;
-    p.row_lanes = 1;
-    while (p.row_lanes < kWave && p.row_lanes * per_lane < p.n_vec) p.row_lanes *= 2;
-    p.feat_tiles = (int32_t)ceil_div(p.n_vec, p.row_lanes * per_lane);
-    p.rows_per_wave = kWave / p.row_lanes;
-    // enough wavefronts to fill the chip several times over, chunks not shorter than 64 slots
-    const int64_t want_waves = 6144;
-    int64_t chunks = ceil_div(want_waves * p.rows_per_wave, (num_blocks > 0 ? num_blocks : 1) * p.feat_tiles);
-    const int64_t most = t_blk / 64 > 1 ? t_blk / 64 : 1;
-    if (chunks > most) chunks = most;
-    if (chunks < 1) chunks = 1;
-    p.chunk = (int32_t)round_up((size_t)ceil_div(t_blk, chunks), kScanBatch);
-    p.chunks_per_block = (int32_t)ceil_div(t_blk, p.chunk);
-    const size_t links = (size_t)(num_blocks > 0 ? num_blocks : 0) * (size_t)(p.chunks_per_block - 1);
-    p.carry_bytes = round_up(links * (size_t)feat_dim * sizeof(float), 16);
-    p.bytes = p.carry_bytes + round_up(links, 16);
+    p.staged = feat_dim < kScanSmallFrame;
+    p.frame_units = (int32_t)(p.staged ? feat_dim : ceil_div(feat_dim, 4));
+    // slices of equal width; a width of which the workgroup's 256 lanes hold a whole number
+    p.slices = p.staged ? 1 : (int32_t)ceil_div(p.frame_units, kScanRow);
+    p.row = (int32_t)ceil_div(p.frame_units, p.slices);
+    int32_t most_subs = kThreads / p.row;
+    // slots per lane: 64 registers of payload; fewer where that leaves the chip without enough tiles
+    p.k = p.staged ? kScanStagedLong : kScanLong;
+    const int32_t small_k = p.staged ? kScanStagedShort : kScanShort;
+    // shorter tiles where the long ones are too few to fill the chip, but none that cut a block (a
+    // chain of hand-overs costs more than idle CUs: 82 blocks of 109 slots x 874 bytes took 28 us in
+    // four tiles per block, 20 us in one)
+    if (t_blk <= most_subs * small_k && num_blocks / (most_subs * p.k / t_blk) * p.slices < 512) p.k = small_k;
+    // the lanes' places in a tile are 32-bit byte offsets from its first slot
+    if (!p.staged) most_subs = (int32_t)std::min<int64_t>(most_subs, std::max<int64_t>(1, ((int64_t)1 << 32) / (4 * p.k * feat_dim)));
+    const int64_t most = (int64_t)most_subs * p.k;
+    if (t_blk > most) {
+        p.chunks = (int32_t)ceil_div(t_blk, most);
+        p.subs = (int32_t)ceil_div(ceil_div(t_blk, p.chunks), p.k);
+        p.chunk = p.subs * p.k;
+        p.chunks = (int32_t)ceil_div(t_blk, p.chunk);
+        p.blocks_per_tile = 1;
+        p.n_units = num_blocks;
+    } else {
+        p.chunks = 1;
+        p.subs = most_subs;
+        p.chunk = (int32_t)most;
+        p.blocks_per_tile = (int32_t)(most / t_blk);
+        p.n_units = ceil_div(num_blocks, p.blocks_per_tile);
+    }
+    const int64_t per_unit = (int64_t)p.chunks * p.slices;
+    // every XCD gets whole blocks where there are enough of them for equal shares
+    p.by_xcd = p.n_units >= 256;
+    p.grid = p.by_xcd ? ceil_div(p.n_units, kXcds) * kXcds * per_unit : p.n_units * per_unit;
+    p.bytes = round_up((size_t)num_blocks * (size_t)(p.chunks - 1) * (size_t)feat_dim * sizeof(unsigned long long), 16);
     return p;
 }
 
@@ -379,23 +674,17 @@ static size_t scan_elem_bytes(bload_dtype dtype)
 template <typename ElemT>
 static void scan_launch(const ScanArgs& a, const ScanPlan& p, hipStream_t stream)
 {
-    constexpr int kQuads = 4 / (int)sizeof(ElemT);           // quads in 16 input bytes
-    const dim3 block(kThreads);
-    const int waves_per_group = kThreads / kWave;
-    if (p.chunks_per_block > 1) {
-        const int64_t waves = ceil_div(a.num_blocks * (p.chunks_per_block - 1), p.rows_per_wave) * p.feat_tiles;
-        const dim3 grid((uint32_t)ceil_div(waves, waves_per_group));
-        if (p.epv > 1) hipLaunchKernelGGL((scan_tail_kernel<ElemT, kQuads, true, false>), grid, block, 0, stream, a);
-        else if (!p.tiny) hipLaunchKernelGGL((scan_tail_kernel<ElemT, 1, false, false>), grid, block, 0, stream, a);
-        else hipLaunchKernelGGL((scan_tail_kernel<ElemT, 1, false, true>), grid, block, 0, stream, a);
-        hipLaunchKernelGGL(scan_chain_kernel, dim3((uint32_t)ceil_div(a.num_blocks * a.feat_dim, kThreads)),
-                           block, 0, stream, a);
+    const dim3 grid((uint32_t)p.grid), block(kThreads);
+    if (p.chunks > 1) {
+        const int64_t words = (int64_t)(p.bytes / sizeof(unsigned long long));
+        const int64_t groups = ceil_div(words, kThreads);
+        hipLaunchKernelGGL(scan_clear_kernel, dim3((uint32_t)(groups < 4096 ? groups : 4096)), block, 0, stream,
+                           a.words, words);
     }
-    const int64_t waves = ceil_div(a.num_blocks * p.chunks_per_block, p.rows_per_wave) * p.feat_tiles;
-    const dim3 grid((uint32_t)ceil_div(waves, waves_per_group));
-    if (p.epv > 1) hipLaunchKernelGGL((scan_apply_kernel<ElemT, kQuads, true, false>), grid, block, 0, stream, a);
-    else if (!p.tiny) hipLaunchKernelGGL((scan_apply_kernel<ElemT, 1, false, false>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((scan_apply_kernel<ElemT, 1, false, true>), grid, block, 0, stream, a);
+    if (p.staged && p.k == kScanStagedLong) hipLaunchKernelGGL((scan_staged_kernel<ElemT, kScanStagedLong>), grid, block, 0, stream, a);
+    else if (p.staged) hipLaunchKernelGGL((scan_staged_kernel<ElemT, kScanStagedShort>), grid, block, 0, stream, a);
+    else if (p.k == kScanLong) hipLaunchKernelGGL((scan_direct_kernel<ElemT, kScanLong>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((scan_direct_kernel<ElemT, kScanShort>), grid, block, 0, stream, a);
 }
 
 }  // namespace bload
@@ -428,29 +717,32 @@ extern "C" bload_status bload_segment_scan(const void* d_packed, const uint8_t* 
         if (!aligned_to(d_workspace, 16)) return BLOAD_EALIGN;
         if (workspace_bytes < p.bytes) return BLOAD_EWORKSPACE;
     }
-    const int64_t most_waves = ceil_div(num_blocks * p.chunks_per_block, p.rows_per_wave) * p.feat_tiles;
-    if (ceil_div(most_waves, kThreads / kWave) > 0x7fffffffLL ||
-        ceil_div(num_blocks * feat_dim, kThreads) > 0x7fffffffLL)
-        return BLOAD_EOVERFLOW;
+    if (p.grid > 0x7fffffffLL) return BLOAD_EOVERFLOW;
 
     ScanArgs a{};
     a.packed = static_cast<const uint8_t*>(d_packed);
     a.reset = d_reset;
     a.valid = d_valid;
     a.out = d_out;
-    a.carry = static_cast<float*>(d_workspace);
-    a.has_boundary = static_cast<uint8_t*>(d_workspace) + p.carry_bytes;
+    a.words = static_cast<unsigned long long*>(d_workspace);
     a.num_blocks = num_blocks;
-    a.total_slots = num_blocks * (int64_t)t_blk;
+    a.n_units = p.n_units;
     a.t_blk = t_blk;
     a.feat_dim = (int32_t)feat_dim;
     a.chunk = p.chunk;
-    a.chunks_per_block = p.chunks_per_block;
-    a.row_lanes = p.row_lanes;
-    a.feat_tiles = p.feat_tiles;
-    a.n_vec = p.n_vec;
+    a.chunks = p.chunks;
+    a.blocks_per_tile = p.blocks_per_tile;
+    a.row = p.row;
+    a.subs = p.subs;
+    a.slices = p.slices;
+    a.frame_units = p.frame_units;
+    a.by_xcd = p.by_xcd ? 1 : 0;
+    a.group = p.chunks > 1 ? (int32_t)std::min<int64_t>(kScanGroup, p.n_units) : 1;
+    a.polls = BLOAD_SCAN_POLLS;
     a.decay = decay;
-    a.decay_chunk = (float)pow((double)decay, (double)p.chunk);
+    double power = pow((double)decay, (double)p.k);
+    for (int i = 0; i < 8; ++i, power *= power) a.decay_sub[i] = power;
+    a.decay_chunk = pow((double)decay, (double)p.chunk);
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (dtype == BLOAD_U8) scan_launch<uint8_t>(a, p, stream);

@@ -137,7 +137,7 @@ def main() -> None:
     families = {"pack": ("pack", "bload::pack_", ("bload::pack_prepare",), "bload_pack.hip"),
                 "reduce": ("segment_reduce", "bload::reduce_", ("bload::reduce_wide", "bload::reduce_narrow"),
                            "bload_reduce.hip"),
-                "scan": ("segment_scan", "bload::scan_", ("bload::scan_apply",), "bload_scan.hip")}
+                "scan": ("segment_scan", "bload::scan_", ("bload::scan_direct", "bload::scan_staged"), "bload_scan.hip")}
     totals = {k: [0.0, 0.0, 0] for k in families}          # read bytes, written bytes, calls
     names = sorted({k[0] for k in fetch} | {k[0] for k in write})
     for name in names:

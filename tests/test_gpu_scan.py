@@ -94,6 +94,72 @@ def test_scan_of_packed_workloads(wid):
         assert_scan_close(got, ref, scale, f"workload {wid} block {b}")
 
 
+# Where the tiles of the two kernels end: frames of 63 / 64 / 65 elements (through LDS, whole quads, a
+# last quad that lies over its neighbour), more than one slice of 64 quads, blocks of a tile's
+# length and one slot more, enough blocks that every XCD takes whole ones, and single long blocks.
+TILE_EDGES = [(3, 132, 63, "f16"), (3, 133, 63, "f32"), (2, 528, 64, "u8"), (2, 129, 64, "f32"), (5, 513, 65, "f16"),
+              (300, 140, 66, "u8"), (1, 3000, 131, "f32"), (2, 300, 259, "u8"), (3, 130, 1031, "f16"),
+              (1, 8448, 1, "f32"), (1, 20000, 1, "u8"), (2, 2305, 1, "f16"), (700, 2400, 1, "u8"), (290, 800, 7, "f32"),
+              (257, 1100, 64, "u8"), (1, 2, 64, "u8"), (1, 15, 1, "f32"), (1, 17, 1, "f16")]
+
+
+@pytest.mark.parametrize("B,T,D,dtype", TILE_EDGES)
+def test_scan_tile_edges(B, T, D, dtype):
+    """Flags with long runs that cross several tiles and flags without a start at all."""
+    rng = np.random.default_rng(B + 3 * T + D)
+    for p_valid, p_reset, decay in [(1.0, 0.0, 1.0), (0.999, 0.004, 0.9)]:
+        print(f"scan edges B={B} T={T} D={D} {dtype} valid {p_valid} reset {p_reset}", flush=True)
+        valid, reset, _, _ = random_flags(rng, B, T, p_valid, p_reset)
+        src = draw_source(rng, B * T, D, dtype)
+        ref, scale = oracle.segment_scan_packed(src, reset, valid, D, dtype, decay)
+        got = gpu_scan(src, reset, valid, D, dtype, decay)
+        assert not got[valid == 0].any()
+        assert_scan_close(got, ref, scale, f"{dtype} B={B} T={T} D={D}")
+
+
+@pytest.mark.parametrize("B,T,D,dtype", [(3, 700, 80, "f32"), (2, 600, 70, "u8"), (2, 9000, 1, "f16"), (5, 400, 33, "f32")])
+def test_scan_without_a_word_from_the_tiles_in_front(B, T, D, dtype):
+    """A library whose wait for other workgroups ends at once: every tile computes the ones in front
+    of it itself, and gets the same bits."""
+    import ctypes
+    import os
+    bl = binding()
+    lib = ctypes.CDLL(os.path.join(os.path.dirname(bl.LIB_PATH), "libbload_scan_nowait.so"))
+    fn = lib.bload_segment_scan
+    fn.restype, fn.argtypes = ctypes.c_int, bl._lib.bload_segment_scan.argtypes
+    rng = np.random.default_rng(B + T + D)
+    for p_valid, p_reset in [(1.0, 0.0), (0.999, 0.004)]:
+        valid, reset, _, _ = random_flags(rng, B, T, p_valid, p_reset)
+        src = draw_source(rng, B * T, D, dtype)
+        want = gpu_scan(src, reset, valid, D, dtype, 0.99)
+        x, r, v = to_dev(src.view(np.uint8).reshape(-1)), to_dev(reset), to_dev(valid)
+        out = torch.full((B, T, D), float("nan"), dtype=torch.float32, device="cuda")
+        ws = torch.empty(max(16, bl.bload_segment_scan_workspace_bytes(B, T, D, dtype)), dtype=torch.uint8, device="cuda")
+        assert fn(x.data_ptr(), r.data_ptr(), v.data_ptr(), B, T, D, bl.DTYPES[dtype], 0.99, out.data_ptr(),
+                  ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy(), want)
+
+
+def test_scan_state_beyond_float_powers():
+    """decay^chunk overflows float32 while the state does not, underflows it under an infinite
+    state, and a state of 0 meets an infinite power."""
+    T = 20000
+    valid, reset = np.ones((1, T), np.uint8), np.zeros((1, T), np.uint8)
+    x = np.zeros((1, T, 1), np.float32)
+    x[0, 1, 0] = np.float32(1e-30)
+    got = gpu_scan(x, reset, valid, 1, "f32", 1.0125)
+    ref, _ = oracle.segment_scan_packed(x.reshape(T, 1), reset, valid, 1, "f32", float(np.float32(1.0125)))
+    k = np.arange(1, T + 1)
+    fine = np.abs(ref[0, :, 0]) < 1e38
+    assert np.all(np.abs(got[0, fine, 0].astype(np.float64) - ref[0, fine, 0]) <= (3 * k[fine] + 4) * EPS * np.abs(ref[0, fine, 0]))
+    x[0, 1, 0] = np.inf
+    got = gpu_scan(x, reset, valid, 1, "f32", 0.5)
+    assert got[0, 0, 0] == 0 and np.isposinf(got[0, 1:, 0]).all()
+    x[0, 1, 0] = 0
+    assert not gpu_scan(x, reset, valid, 1, "f32", 1e9).any()
+
+
 def test_scan_closed_forms_and_determinism():
     bl = binding()
     B, T, D = 7, 200, 64
