@@ -461,6 +461,37 @@ __device__ __forceinline__ uint32_t nonzero_bytes16(vec16 w)
 
 typedef vec16 __attribute__((aligned(1))) vec16_any;      // a 16-byte vector at any address
 
+// The flag bytes of 16 consecutive slots, asked for with loads that stay inside the planes of
+// `total` slots wherever the slots lie (planes of fewer than 16 slots are read byte by byte).
+struct FlagBytes {
+    vec16 valid, reset;
+    int64_t g, from;
+    uint8_t before;                    // the valid flag of the slot in front (of the first slot: its own)
+
+    __device__ __forceinline__ void load(const ReduceArgs& a, int64_t first, int32_t left)
+    {
+        g = first;
+        from = max(min(g, a.total_slots - 16), (int64_t)0);
+        valid = reset = vec16{0u, 0u, 0u, 0u};
+        before = 0;
+        if (left < 0) return;
+        before = a.valid[max(min(g, a.total_slots) - 1, (int64_t)0)];
+        if (a.total_slots >= 16) {
+            valid = *reinterpret_cast<const vec16_any*>(a.valid + from);
+            reset = *reinterpret_cast<const vec16_any*>(a.reset + from);
+        }
+    }
+    // bit j: the flag of slot g + j is set, for the `left` slots that count
+    __device__ __forceinline__ uint32_t mask(vec16 bytes, const uint8_t* plane, int32_t left, int64_t total) const
+    {
+        const uint32_t counts = left >= 16 ? 0xffffu : (1u << max(left, 0)) - 1u;
+        if (total >= 16) return g - from < 16 ? (nonzero_bytes16(bytes) >> (int)(g - from)) & counts : 0u;
+        uint32_t m = 0;
+        for (int j = 0; j < left && j < 16; ++j) m |= (uint32_t)(plane[g + j] != 0) << j;
+        return m;
+    }
+};
+
 // Where a workgroup's tile lies.  Tiles never straddle a block: a tile is a piece of one block
 // (blocks of at least a tile's length) or a whole number of blocks.
 struct NarrowTile {
@@ -663,29 +694,24 @@ struct NarrowRows {
     }
 };
 
-// The lane's 16 elements of feature d where they do not come as rows; only those of valid slots
-// mean anything.  ONE: a frame is one element, so they are contiguous and come as 16-byte
-// vectors.  Otherwise one load per slot, all issued together.  `left` = slots from the lane's
-// first one to the tile's end.
-template <typename ElemT, bool ONE>
-__device__ __forceinline__ void narrow_load(const ReduceArgs& a, int64_t s0, int32_t left, int d,
-                                            ElemT (&raw)[kSlotsPerLane])
+// The lane's 16 elements where they do not come as rows; only those of valid slots mean anything.
+// `left` = slots from the lane's first one to the tile's end.
+template <typename ElemT>
+__device__ __forceinline__ void narrow_load(const ReduceArgs& a, int64_t s0, int32_t left, ElemT (&raw)[kSlotsPerLane])
 {
     constexpr int SPL = kSlotsPerLane;
     constexpr int NV = NarrowStage<ElemT>::NV;
-    if (ONE && left >= SPL) {
+    const uint8_t* from = a.packed + s0 * (int64_t)sizeof(ElemT);
+    if (left >= SPL) {
         union { vec16 v[NV > 0 ? NV : 1]; ElemT e[SPL]; } u;
-        const vec16_any* from = reinterpret_cast<const vec16_any*>(a.packed + s0 * (int64_t)sizeof(ElemT));
 #pragma unroll
-        for (int k = 0; k < NV; ++k) u.v[k] = __builtin_nontemporal_load(from + k);
+        for (int k = 0; k < NV; ++k) u.v[k] = __builtin_nontemporal_load(reinterpret_cast<const vec16_any*>(from) + k);
 #pragma unroll
         for (int j = 0; j < SPL; ++j) raw[j] = u.e[j];
     } else if (left > 0) {
         // slots past the tile's end re-read its last slot (their valid bits are 0)
-        const int64_t stride = (int64_t)(ONE ? 1 : a.feat_dim) * (int64_t)sizeof(ElemT);
-        const uint8_t* from = a.packed + (s0 * (ONE ? 1 : a.feat_dim) + d) * (int64_t)sizeof(ElemT);
 #pragma unroll
-        for (int j = 0; j < SPL; ++j) raw[j] = *reinterpret_cast<const ElemT*>(from + min(j, left - 1) * stride);
+        for (int j = 0; j < SPL; ++j) raw[j] = reinterpret_cast<const ElemT*>(from)[min(j, left - 1)];
     } else {
 #pragma unroll
         for (int j = 0; j < SPL; ++j) raw[j] = ElemT{};
@@ -702,29 +728,28 @@ __device__ __forceinline__ long long masked(long long x, uint32_t mask, int j)
     return (long long)((int32_t)x & (int32_t)__builtin_amdgcn_sbfe(mask, j, 1));     // x holds an int32 here
 }
 
-// Hand one finished piece on: to the output row of its sequence, or to the
-// partial buffers when the tile border cuts its segment.  `seq` is the sequence
-// id at the first slot of the piece when the segment starts in this tile
-// (`started`), as in the wide layout.
+// Hand one finished piece on: to the output row of its sequence, or to the partial buffers when the
+// tile border cuts its segment.  `seq` is the sequence id at the first slot of the piece when the
+// segment starts in this tile (`started`), as in the wide layout; `value` is finished (a mean is
+// divided) where the piece is a whole segment.
 template <typename Acc>
-__device__ __forceinline__ void narrow_emit(const ReduceArgs& a, int64_t q, int d, int32_t seq,
-                                            bool is_end, bool started, Acc sum, int32_t cnt,
-                                            ChunkDesc* s_desc)
+__device__ __forceinline__ void emit_piece(const ReduceArgs& a, int64_t q, int d, int32_t seq,
+                                           bool is_end, bool started, Acc value, int32_t cnt,
+                                           ChunkDesc* s_desc)
 {
     typedef typename OutOf<Acc>::T Out;
     const int D = a.feat_dim;
     if (is_end && started) {
-        if ((uint32_t)seq < (uint32_t)a.n_seq)
-            static_cast<Out*>(a.out)[(int64_t)seq * D + d] = finish<Acc>(sum, cnt, a.mean);
+        if ((uint32_t)seq < (uint32_t)a.n_seq) static_cast<Out*>(a.out)[(int64_t)seq * D + d] = value;
     } else if (!started) {
         // continues a segment of the previous tile; closed here or running through
-        if (a.head_part) static_cast<Acc*>(a.head_part)[q * D + d] = sum;
+        if (a.head_part) static_cast<Acc*>(a.head_part)[q * D + d] = value;
         if (d == 0) {
             s_desc->head_state = is_end ? kHeadClosed : kHeadThrough;
             s_desc->cnt_head = cnt;
         }
     } else {
-        if (a.tail_part) static_cast<Acc*>(a.tail_part)[q * D + d] = sum;
+        if (a.tail_part) static_cast<Acc*>(a.tail_part)[q * D + d] = value;
         if (d == 0) {
             s_desc->cnt_tail = cnt;
             s_desc->seq_tail = seq;
@@ -732,7 +757,7 @@ __device__ __forceinline__ void narrow_emit(const ReduceArgs& a, int64_t q, int 
     }
 }
 
-template <typename ElemT, bool ONE>
+template <typename ElemT>
 __global__ __launch_bounds__(kThreads) void reduce_narrow_kernel(ReduceArgs a)
 {
     typedef typename Elem<ElemT>::Acc Acc;
@@ -743,7 +768,7 @@ __global__ __launch_bounds__(kThreads) void reduce_narrow_kernel(ReduceArgs a)
     __shared__ unsigned long long s_wave_breaks[NW];   // which lanes of the wave hold a break
     __shared__ int32_t s_last_break[kThreads];         // position of a lane's last break (lanes that have one)
     __shared__ int32_t s_break_seq[kThreads];          // and the sequence id found there
-    __shared__ vec16 s_stage[ONE ? NarrowStage<ElemT>::kVectors : 1];
+    __shared__ vec16 s_stage[NarrowStage<ElemT>::kVectors];
     __shared__ ChunkDesc s_desc;
 
     const int tid = (int)threadIdx.x;
@@ -759,7 +784,7 @@ __global__ __launch_bounds__(kThreads) void reduce_narrow_kernel(ReduceArgs a)
     // its rows now, before the flags are looked at
     const bool wave_valid = !bytes.wave_blank;
     const int32_t left = tile.n - pos0;
-    const bool by_rows = ONE && NarrowStage<ElemT>::NV > 1 && left - (kWave - 1 - lane) * SPL >= SPL;
+    const bool by_rows = NarrowStage<ElemT>::NV > 1 && left - (kWave - 1 - lane) * SPL >= SPL;
     NarrowRows<ElemT> rows;
     if (wave_valid && by_rows) rows.issue(a, s0 - lane * SPL);
     const LaneFlags f = narrow_lane_flags(a, tile, bytes);
@@ -778,55 +803,49 @@ __global__ __launch_bounds__(kThreads) void reduce_narrow_kernel(ReduceArgs a)
     int32_t prev_start = -1;           // position of the last break in front of this lane, -1: none in the tile
     int32_t prev_seq = -1;             // and the sequence id found there
 
-    const int n_feat = ONE ? 1 : a.feat_dim;
-    for (int d = 0; d < n_feat; ++d) {
-        SegState<Acc> scan, carry;
-        Acc tail = 0;                  // the lane's slots from its last break on (all of them if it has none)
-        Acc head = 0;                  // the lane's slots in front of its first break
-        if (!wave_valid) {
-            // nothing but padding: every slot is a break, nothing to add
-            scan = SegState<Acc>{0, 1u};
-            carry = SegState<Acc>{0, lane == 0 ? 0u : 1u};
+    SegState<Acc> scan, carry;
+    Acc tail = 0;                      // the lane's slots from its last break on (all of them if it has none)
+    Acc head = 0;                      // the lane's slots in front of its first break
+    if (!wave_valid) {
+        // nothing but padding: every slot is a break, nothing to add
+        scan = SegState<Acc>{0, 1u};
+        carry = SegState<Acc>{0, lane == 0 ? 0u : 1u};
+    } else {
+        ElemT raw[SPL];
+        if (by_rows) rows.finish(s_stage, raw);
+        else narrow_load<ElemT>(a, s0, left, raw);
+        if (wave_breaks == 0) {
+            // no break in the whole wave (so every slot is valid): plain sums
+#pragma unroll
+            for (int j = 0; j < SPL; ++j) tail += Elem<ElemT>::get(raw[j]);
+            scan = SegState<Acc>{wave_scan(tail, PlainSum<Acc>(), PlainMove<Acc>()), 0u};
+            carry = SegState<Acc>{dpp_move<kDppWaveShr1>(scan.sum, (Acc)0), 0u};
         } else {
-            ElemT raw[SPL];
-            if (by_rows) rows.finish(s_stage, raw);
-            else narrow_load<ElemT, ONE>(a, s0, left, d, raw);
-            if (wave_breaks == 0) {
-                // no break in the whole wave (so every slot is valid): plain sums
 #pragma unroll
-                for (int j = 0; j < SPL; ++j) tail += Elem<ElemT>::get(raw[j]);
-                scan = SegState<Acc>{wave_scan(tail, PlainSum<Acc>(), PlainMove<Acc>()), 0u};
-                carry = SegState<Acc>{dpp_move<kDppWaveShr1>(scan.sum, (Acc)0), 0u};
-            } else {
-#pragma unroll
-                for (int j = 0; j < SPL; ++j) {
-                    tail += masked((Acc)Elem<ElemT>::get(raw[j]), from_last_break, j);
-                    head += masked((Acc)Elem<ElemT>::get(raw[j]), to_first_break, j);
-                }
-                scan = wave_scan(SegState<Acc>{tail, bmask != 0 ? 1u : 0u}, SegCombine<Acc>(), SegMove<Acc>());
-                carry = SegMove<Acc>().template at<kDppWaveShr1, 0xF>(scan);      // the lanes before this one
+            for (int j = 0; j < SPL; ++j) {
+                tail += masked((Acc)Elem<ElemT>::get(raw[j]), from_last_break, j);
+                head += masked((Acc)Elem<ElemT>::get(raw[j]), to_first_break, j);
             }
+            scan = wave_scan(SegState<Acc>{tail, bmask != 0 ? 1u : 0u}, SegCombine<Acc>(), SegMove<Acc>());
+            carry = SegMove<Acc>().template at<kDppWaveShr1, 0xF>(scan);      // the lanes before this one
         }
-        if (d > 0) __syncthreads();                  // the previous feature's wave sums are consumed
-        if (lane == kWave - 1) { s_wave_sum[wave] = scan.sum; s_wave_any[wave] = scan.any; }
-        if (d == 0 && bmask) { s_last_break[tid] = pos0 + last_break; s_break_seq[tid] = own_seq; }
-        __syncthreads();
-        if (!finishes) continue;
-
+    }
+    if (lane == kWave - 1) { s_wave_sum[wave] = scan.sum; s_wave_any[wave] = scan.any; }
+    if (bmask) { s_last_break[tid] = pos0 + last_break; s_break_seq[tid] = own_seq; }
+    __syncthreads();
+    if (finishes) {
         // the segments that end in this lane, and the open tail of the tile
         SegState<Acc> before{0, 0};
         for (int w = 0; w < wave; ++w)
             before = SegCombine<Acc>()(before, SegState<Acc>{s_wave_sum[w], s_wave_any[w]});
         carry = SegCombine<Acc>()(before, carry);
-        if (d == 0) {
-            const unsigned long long lower = wave_breaks & ((1ull << lane) - 1ull);
-            int holder = lower ? wave * kWave + 63 - __clzll((long long)lower) : -1;
-            for (int w = wave - 1; w >= 0 && holder < 0; --w) {
-                const unsigned long long b = s_wave_breaks[w];
-                if (b) holder = w * kWave + 63 - __clzll((long long)b);
-            }
-            if (holder >= 0) { prev_start = s_last_break[holder]; prev_seq = s_break_seq[holder]; }
+        const unsigned long long lower = wave_breaks & ((1ull << lane) - 1ull);
+        int holder = lower ? wave * kWave + 63 - __clzll((long long)lower) : -1;
+        for (int w = wave - 1; w >= 0 && holder < 0; --w) {
+            const unsigned long long b = s_wave_breaks[w];
+            if (b) holder = w * kWave + 63 - __clzll((long long)b);
         }
+        if (holder >= 0) { prev_start = s_last_break[holder]; prev_seq = s_break_seq[holder]; }
         // One piece per end (usually one per lane).  The piece that closes what the lanes before
         // left open ends in front of the lane's first break: carry + head.  The piece that the
         // lane's last break opened ends at its last slot: tail (plus the carry if the lane has no
@@ -849,16 +868,229 @@ __global__ __launch_bounds__(kThreads) void reduce_narrow_kernel(ReduceArgs a)
                 if (by_rows) {
                     for (int k = lb; k <= j; ++k) sum += Elem<ElemT>::get(NarrowRows<ElemT>::again(s_stage, k));
                 } else {
-                    const int64_t stride = (int64_t)(ONE ? 1 : a.feat_dim) * (int64_t)sizeof(ElemT);
-                    const uint8_t* from = a.packed + ((s0 + lb) * (ONE ? 1 : a.feat_dim) + d) * (int64_t)sizeof(ElemT);
-                    for (int k = lb; k <= j; ++k, from += stride) sum += Elem<ElemT>::get(*reinterpret_cast<const ElemT*>(from));
+                    const ElemT* from = reinterpret_cast<const ElemT*>(a.packed) + s0;
+                    for (int k = lb; k <= j; ++k) sum += Elem<ElemT>::get(from[k]);
                 }
             }
             const int32_t start = lb >= 0 ? pos0 + lb : prev_start;
             const int32_t cnt = start >= 0 ? pos0 + j - start + 1 : pos0 + j + 1;
             const int32_t seq = lb < 0 ? prev_seq : (lb == last_break ? own_seq : a.seq_id[s0 + lb]);
-            narrow_emit<Acc>(a, q, d, seq, (f.ends >> j) & 1u, start >= 0, sum, cnt, &s_desc);
+            const bool is_end = (f.ends >> j) & 1u;
+            emit_piece<Acc>(a, q, 0, seq, is_end, start >= 0, finish<Acc>(sum, is_end && start >= 0 ? cnt : 1, a.mean), cnt, &s_desc);
         }
+    }
+    __syncthreads();
+    if (tid == 0 && a.desc) a.desc[q] = s_desc;
+}
+
+// ----------------------------------------------------------------- staged
+//
+// Frames of 2 to 63 elements.  A tile of whole frames (a piece of one block, or several whole
+// blocks) comes into LDS as whole 16-byte vectors, because rows this short read lane by lane
+// would touch a cache line per lane; then lanes take one feature each and kStagedSlots
+// consecutive slots, D lanes side by side and 256 / D groups of them one behind the other in
+// time.  As in the narrow layout a lane contributes the sum of its slots from its last break on
+// to a segmented scan over the groups, and then hands on the pieces that end in its slots.
+// A lane's sum is of at most 17 frames, in two halves; the sums of the lanes are added in 64
+// bits.  The sequence ids are read at the starts only, all at once, and wait in
+// LDS.  Bound by HBM where the sequences are long, by the pieces of the lanes where they are of
+// a few frames.
+// Measured against a loop over the features of lanes across time (the narrow layout before): see
+// the launch rule.
+
+constexpr int kStagedSlots = 17;       // odd, so that the groups' places in LDS spread over the banks
+constexpr int kStagedSlotsShort = 9;   // where long lanes would leave the chip without enough tiles
+constexpr int kStagedFrame = 64;       // frames of fewer elements are staged
+
+template <typename Acc> struct WideSum { typedef double T; };
+template <> struct WideSum<long long> { typedef long long T; };
+
+// v where bit j of `mask` is set, 0 elsewhere (v: a float, or an int32 on its way into a 64-bit sum)
+__device__ __forceinline__ float kept(float v, uint32_t mask, int j) { return masked(v, mask, j); }
+__device__ __forceinline__ long long kept(long long v, uint32_t mask, int j) { return masked(v, mask, j); }
+
+template <typename ElemT, int K>
+__global__ __launch_bounds__(kThreads) void reduce_staged_kernel(ReduceArgs a)
+{
+    typedef typename Elem<ElemT>::Acc Acc;
+    typedef typename WideSum<Acc>::T Sum;
+    static_assert(K % 2 == 1 && K < 32, "a lane's flags fit a word");
+    constexpr int kElems = K * kThreads;
+    constexpr int kMostSlots = kElems / 2;
+    constexpr int kGroups = (kMostSlots + 15) / 16 + 6;      // groups of 16 flags, the last ones zero
+    constexpr int EPV = 16 / (int)sizeof(ElemT);
+    constexpr int NV = (K + EPV - 1) / EPV;
+    __shared__ alignas(16) ElemT s_x[kElems];
+    __shared__ int32_t s_seq[kMostSlots];                    // at starts: the sequence id
+    __shared__ alignas(16) uint16_t s_valid[kGroups], s_break[kGroups];
+    __shared__ Sum s_sum[2][kThreads];
+    __shared__ int32_t s_pos[2][kThreads];                   // last break up to there, -1: none in the tile
+    __shared__ ChunkDesc s_desc;
+
+    const int tid = (int)threadIdx.x;
+    const int D = a.feat_dim;
+    const int s = (int)((uint32_t)tid / (uint32_t)D), d = tid - s * D;
+    const int subs = a.chunk / K;
+    const bool active = s < subs;
+    const int64_t q = blockIdx.x;
+    // the tile: a piece of one block, or blocks_per_tile whole ones
+    int64_t g0;
+    int32_t n, rem0;
+    if (a.n_chunks > 1) {
+        const int64_t b = (int64_t)((uint32_t)q / (uint32_t)a.n_chunks);
+        rem0 = (int32_t)(q - b * a.n_chunks) * a.chunk;
+        g0 = b * (int64_t)a.t_blk + rem0;
+        n = min(a.chunk, a.t_blk - rem0);
+    } else {
+        const int64_t b0 = q * a.blocks_per_tile;
+        rem0 = 0;
+        g0 = b0 * (int64_t)a.t_blk;
+        n = (int32_t)min((int64_t)a.blocks_per_tile, a.num_blocks - b0) * a.t_blk;
+    }
+    if (tid == 0) s_desc = ChunkDesc{kHeadNone, 0, 0, -1};
+
+    // payload: all vectors asked for before anything is waited for
+    const int elems = n * D, vecs = elems / EPV;
+    const uint8_t* from = a.packed + g0 * D * (int64_t)sizeof(ElemT);
+    vec16 in[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        const int i = tid + k * kThreads;
+        in[k] = vec16{0u, 0u, 0u, 0u};
+        if (i < vecs) in[k] = __builtin_nontemporal_load(reinterpret_cast<const vec16_any*>(from) + i);
+    }
+    // flags, 16 slots to a lane: which slots are valid, and which cannot continue the segment of the slot
+    // in front (padding, a start flag, a block's first slot, a slot behind padding)
+    const uint32_t T = (uint32_t)a.t_blk;
+    // (every load unconditional, at an address inside the planes, so that none waits for another)
+    constexpr int kRounds = (kGroups + kThreads - 1) / kThreads;
+    FlagBytes fb[kRounds];
+    const bool more_behind = rem0 + n < a.t_blk && a.n_chunks > 1;
+    const int64_t behind = min(g0 + n, a.total_slots - 1);
+    const uint8_t behind_valid = a.valid[behind], behind_reset = a.reset[behind];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) fb[r].load(a, g0 + 16 * (tid + r * kThreads), n - 16 * (tid + r * kThreads));
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const int i = tid + r * kThreads;
+        if (i >= kGroups) break;
+        uint32_t vm16 = 0, brk = 0xffffu;                    // behind the tile: breaks
+        const int32_t left16 = n - 16 * i;
+        if (left16 >= 0) {
+            const uint32_t pos = (uint32_t)(rem0 + 16 * i) % T;
+            const uint32_t before = pos != 0 && fb[r].before != 0 ? 1u : 0u;
+            vm16 = fb[r].mask(fb[r].valid, a.valid, left16, a.total_slots);
+            const uint32_t rm16 = fb[r].mask(fb[r].reset, a.reset, left16, a.total_slots);
+            uint32_t first = 0;
+            for (uint32_t k = pos == 0 ? 0 : T - pos; k < 16; k += T) first |= 1u << k;
+            brk = (~vm16 | rm16 | first | ~(vm16 << 1 | before)) & 0xffffu;
+            if (left16 < 16) {                               // the slot behind the tile
+                const bool goes_on = more_behind && behind_valid != 0 && behind_reset == 0 &&
+                                     ((left16 == 0 ? before : vm16 >> (left16 - 1)) & 1u);
+                brk = goes_on ? brk & ~(1u << left16) : brk | 1u << left16;
+            }
+        }
+        s_valid[i] = (uint16_t)vm16;
+        s_break[i] = (uint16_t)brk;
+    }
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        const int i = tid + k * kThreads;
+        if (i < vecs) *reinterpret_cast<vec16*>(s_x + i * EPV) = in[k];
+    }
+    for (int i = vecs * EPV + tid; i < elems; i += kThreads) s_x[i] = reinterpret_cast<const ElemT*>(from)[i];
+    __syncthreads();
+    // the sequence ids at the starts: the first two per lane are on their way while the lane adds up
+    auto starts_at = [&](int t) { return t < n && ((s_valid[t >> 4] & s_break[t >> 4]) >> (t & 15)) & 1u; };
+    const bool start0 = starts_at(tid), start1 = starts_at(tid + kThreads);
+    int32_t seq0 = -1, seq1 = -1;
+    if (start0) seq0 = a.seq_id[g0 + tid];
+    if (start1) seq1 = a.seq_id[g0 + tid + kThreads];
+
+    const int o = s * K, left = active ? min(K, n - o) : 0;
+    uint32_t vm = 0, bm = 0, next_brk = 0;
+    Acc tail = 0, head = 0;            // the slots from the last break on, and those in front of the first one
+    if (left > 0) {
+        const uint32_t* v32 = reinterpret_cast<const uint32_t*>(s_valid) + (o >> 5);
+        const uint32_t* b32 = reinterpret_cast<const uint32_t*>(s_break) + (o >> 5);
+        const uint32_t in_lane = (1u << left) - 1u;
+        vm = (uint32_t)(((uint64_t)v32[1] << 32 | v32[0]) >> (o & 31)) & in_lane;
+        const uint32_t brk = (uint32_t)(((uint64_t)b32[1] << 32 | b32[0]) >> (o & 31));
+        bm = brk & in_lane;
+        next_brk = brk >> 1;                                 // also of the slot behind the lane's last
+        ElemT x[K];
+#pragma unroll
+        for (int u = 0; u < K; ++u) x[u] = s_x[(o + u) * D + d];             // only valid slots count below
+        const uint32_t open = bm ? vm & (~0u << (31 - __clz((int)bm))) : vm;
+        const uint32_t front = bm ? vm & ((bm & -bm) - 1u) : vm;
+        Acc odd = 0;                   // (two sums, so that one addition does not wait for the other)
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+            const Acc v = kept((Acc)Elem<ElemT>::get(x[u]), open, u);
+            if (u & 1) odd += v; else tail += v;
+        }
+        tail += odd;
+        head = tail;
+        if (bm) {
+            head = 0;
+#pragma unroll
+            for (int u = 0; u < K; ++u) head += kept((Acc)Elem<ElemT>::get(x[u]), front, u);
+        }
+    }
+    if (start0) s_seq[tid] = seq0;
+    if (start1) s_seq[tid + kThreads] = seq1;
+    for (int t = tid + 2 * kThreads; t < n; t += kThreads)
+        if (starts_at(t)) s_seq[t] = a.seq_id[g0 + t];
+    // segmented scan over the groups
+    Sum sum = (Sum)tail;
+    int32_t pos = bm ? o + 31 - __clz((int)bm) : -1;
+    int buf = 0;
+    for (int step = 1; step < subs; step <<= 1) {
+        s_sum[buf][tid] = sum;
+        s_pos[buf][tid] = pos;
+        __syncthreads();
+        if (active && s >= step && pos < 0) {
+            sum = s_sum[buf][tid - step * D] + sum;
+            pos = s_pos[buf][tid - step * D];
+        }
+        buf ^= 1;
+    }
+    s_sum[buf][tid] = sum;
+    s_pos[buf][tid] = pos;
+    __syncthreads();
+
+    // One piece per end in the lane's slots, and the open one at the tile's end
+    const uint32_t ends = vm & next_brk;
+    uint32_t todo = ends;
+    if (left > 0 && o + left == n) todo |= vm & (1u << (left - 1));
+    while (todo) {
+        const int j = __ffs((int)todo) - 1;
+        todo &= todo - 1u;
+        const uint32_t upto = bm & ((2u << j) - 1u);
+        int32_t start = -1;
+        Sum piece;
+        if (upto == 0) {
+            // it closes what the groups in front left open
+            piece = (Sum)head;
+            if (s > 0) {
+                piece = s_sum[buf][tid - D] + piece;
+                start = s_pos[buf][tid - D];
+            }
+        } else {
+            const int from = 31 - __clz((int)upto);
+            start = o + from;
+            if (upto == bm) {
+                piece = (Sum)tail;
+            } else {                   // a segment between two breaks of the lane is read again
+                Acc again = 0;
+                for (int k = from; k <= j; ++k) again += Elem<ElemT>::get(s_x[(o + k) * D + d]);
+                piece = (Sum)again;
+            }
+        }
+        const bool started = start >= 0, is_end = (ends >> j) & 1u;
+        const int32_t cnt = o + j - (started ? start : 0) + 1;
+        if (started && is_end && a.mean) piece = piece / (Sum)cnt;
+        emit_piece<Acc>(a, q, d, started ? s_seq[start] : -1, is_end, started, (Acc)piece, cnt, &s_desc);
     }
     __syncthreads();
     if (tid == 0 && a.desc) a.desc[q] = s_desc;
@@ -909,12 +1141,13 @@ __global__ __launch_bounds__(kThreads) void reduce_stitch_kernel(ReduceArgs a, i
 // ------------------------------------------------------------------- host
 
 struct ReducePlan {
-    bool wide;
+    bool wide, staged;
     int vec;                 // wide: elements per lane (16 / elem size, or 1)
     int row_lanes_log2;
     int n_vec;
     int32_t chunk, n_chunks;
-    int32_t blocks_per_tile;  // narrow, t_blk < the tile: whole blocks per tile
+    int32_t blocks_per_tile;  // narrow and staged, t_blk < the tile: whole blocks per tile
+    int32_t slots;           // staged: slots per lane
     int64_t total_chunks;
     bool partials;           // can a chunk border cut a segment
     size_t desc_off, head_off, tail_off, bytes;
@@ -929,7 +1162,8 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
     const int64_t frame_bytes = feat_dim * es;
     const size_t acc = dtype == BLOAD_I32 ? 8 : 4;
     const bool vectors = frame_bytes % 16 == 0 && frame_bytes >= 64;
-    p.wide = vectors || feat_dim >= 64;
+    p.staged = feat_dim > 1 && feat_dim < kStagedFrame && !vectors;
+    p.wide = !p.staged && feat_dim > 1;
     if (p.wide) {
         p.vec = vectors ? 16 / es : 1;
         p.n_vec = (int)ceil_div(feat_dim, p.vec);
@@ -968,13 +1202,23 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
     } else {
         // tiles never straddle a block: pieces of one block, or several whole blocks
         p.chunk = kNarrowTile;
-        if (t_blk >= kNarrowTile) {
-            p.n_chunks = (int32_t)ceil_div(t_blk, kNarrowTile);
+        if (p.staged) {
+            const int32_t groups = kThreads / (int32_t)feat_dim;
+            p.slots = kStagedSlots;
+            if (num_blocks * t_blk / ((int64_t)groups * kStagedSlots) < 512) p.slots = kStagedSlotsShort;
+            p.chunk = groups * p.slots;
+            if (t_blk > p.chunk) {         // equal pieces
+                const int32_t pieces = (int32_t)ceil_div(t_blk, p.chunk);
+                p.chunk = (int32_t)ceil_div(ceil_div(t_blk, pieces), p.slots) * p.slots;
+            }
+        }
+        if (t_blk >= p.chunk) {
+            p.n_chunks = (int32_t)ceil_div(t_blk, p.chunk);
             p.blocks_per_tile = 1;
             p.total_chunks = num_blocks * p.n_chunks;
         } else {
             p.n_chunks = 1;
-            p.blocks_per_tile = kNarrowTile / t_blk;
+            p.blocks_per_tile = p.chunk / t_blk;
             p.total_chunks = ceil_div(num_blocks, p.blocks_per_tile);
         }
         // only a block cut into several tiles can have a segment across a tile border
@@ -1019,12 +1263,13 @@ static void launch_reduce(const ReducePlan& p, const ReduceArgs& a, hipStream_t 
     if (p.wide) {
         launch_wide<ElemT>(p, a, stream);
     } else {
-        if (a.feat_dim == 1)
-            hipLaunchKernelGGL((reduce_narrow_kernel<ElemT, true>), dim3((uint32_t)p.total_chunks),
-                               dim3(kThreads), 0, stream, a);
+        const dim3 grid((uint32_t)p.total_chunks), block(kThreads);
+        if (!p.staged)
+            hipLaunchKernelGGL(reduce_narrow_kernel<ElemT>, grid, block, 0, stream, a);
+        else if (p.slots == kStagedSlots)
+            hipLaunchKernelGGL((reduce_staged_kernel<ElemT, kStagedSlots>), grid, block, 0, stream, a);
         else
-            hipLaunchKernelGGL((reduce_narrow_kernel<ElemT, false>), dim3((uint32_t)p.total_chunks),
-                               dim3(kThreads), 0, stream, a);
+            hipLaunchKernelGGL((reduce_staged_kernel<ElemT, kStagedSlotsShort>), grid, block, 0, stream, a);
     }
     if (p.partials) {
         const int32_t feat_tiles = (int32_t)ceil_div(a.feat_dim, kThreads);

@@ -263,3 +263,13 @@ def test_reduce_follows_the_flags(B, T, D, dtype, op):
         bound = REL_TOL * np.maximum(np.abs(want.astype(np.float64)), scale.astype(np.float64)) + 1e-30
         err = np.abs(got.astype(np.float64) - want.astype(np.float64))
         assert np.all(err <= bound), f"max err {err.max()} at {np.unravel_index(np.argmax(err - bound), err.shape)}"
+
+
+# Frames of 2 to 63 elements go through LDS in tiles of 256 / D groups of lanes: the widest and the
+# narrowest of them, blocks of a tile's length and one slot more, many blocks per tile, planes of
+# fewer than 16 slots, enough tiles for the longer lanes and too few for them.
+@pytest.mark.parametrize("dtype,op", [("f32", "mean"), ("i32", "sum"), ("u8", "mean"), ("f16", "sum")])
+@pytest.mark.parametrize("B,T,D", [(2, 4224, 2), (700, 4225, 2), (3, 1153, 2), (40, 132, 63), (600, 133, 63), (300, 36, 57),
+                                   (5000, 37, 37), (900, 700, 7), (1, 2, 5), (1, 15, 3), (1, 17, 3), (4000, 19, 33)])
+def test_reduce_staged_edges(B, T, D, dtype, op):
+    test_reduce_follows_the_flags(B, T, D, dtype, op)
