@@ -15,7 +15,7 @@
 // fixed order make the float32 result bit-reproducible.
 //
 // Two layouts of the work:
-//   wide   (a frame is >= 64 bytes): lanes across the features of a frame, each
+//   wide   (a frame is >= 64 bytes): lanes across the features of a frame, 16 bytes each, each
 //          row of lanes (at most one wave) walks one chunk of time serially
 //          with several loads in flight, restarting its accumulators at every
 //          start flag.
@@ -98,16 +98,30 @@ template <> struct Elem<int32_t> {
     __device__ static long long get(int32_t v) { return (long long)v; }
 };
 
-// VEC elements of one lane: a 16-byte vector (VEC = 16 / sizeof(ElemT)) or one element.
-template <typename ElemT, int VEC>
+typedef vec16 __attribute__((aligned(1))) vec16_any;      // a 16-byte vector at any address
+
+// The elements of one lane, 16 bytes or fewer, in one load at any address.
+template <int BYTES> struct LaneBits;
+template <> struct LaneBits<16> { typedef vec16 T; typedef vec16_any Any; };
+template <> struct LaneBits<4> { typedef uint32_t T; typedef uint32_t __attribute__((aligned(1))) Any; };
+template <> struct LaneBits<2> { typedef uint16_t T; typedef uint16_t __attribute__((aligned(1))) Any; };
+template <> struct LaneBits<1> { typedef uint8_t T; typedef uint8_t Any; };
+
+// STREAM: a streaming load, for tensors that do not fit the memory-side cache.  Rows of narrow lanes
+// share cache lines with the rows beside them, which a streaming load would fetch again (78 slots x
+// 271 int32: 174 us, 143 us with plain loads), and what fits the cache is worth keeping there (4300
+// blocks of 30 slots x 113 bytes 108 us streamed, 89 plain; 800 MB of 320-byte frames 279 and 305).
+template <typename ElemT, int VEC, bool STREAM>
 struct LaneData {
-    union { vec16 v; ElemT e[VEC > 1 ? VEC : 1]; } u;
+    typedef LaneBits<VEC * (int)sizeof(ElemT)> Bits;
+    union { typename Bits::T v; ElemT e[VEC]; } u;
     __device__ __forceinline__ void load(const uint8_t* p)
     {
-        if (VEC > 1) u.v = load_stream(reinterpret_cast<const vec16*>(p));
-        else u.e[0] = *reinterpret_cast<const ElemT*>(p);
+        if (STREAM) u.v = __builtin_nontemporal_load(reinterpret_cast<const typename Bits::Any*>(p));
+        else u.v = *reinterpret_cast<const typename Bits::Any*>(p);
     }
 };
+constexpr int64_t kMemorySideCache = (int64_t)256 << 20;
 
 template <typename Acc> struct OutOf;
 template <> struct OutOf<float> { typedef float T; };
@@ -190,18 +204,19 @@ __host__ __device__ constexpr int kScratchStride() { return sizeof(Acc) == 4 ? V
 // writes 16-byte pieces 16 * VEC bytes apart; when a whole wave belongs to one
 // row the values go through the wave's LDS scratch instead and leave as runs
 // of 64 consecutive elements.  `scratch` is null for rows narrower than a wave.
+// The last lane of a frame that is no whole number of vectors holds its last VEC
+// features, some of them its neighbour's as well: it stores its own.
 template <typename Acc, int VEC>
 __device__ __forceinline__ void store_row(Acc* dst_row, int64_t feat0, const Acc (&v)[VEC],
                                           bool lane_stores, Acc* scratch, int64_t wave_feat0,
                                           int32_t feat_dim)
 {
-    if (VEC == 1 || scratch == nullptr) {
-        if (lane_stores) {
+    const int32_t whole = feat_dim - feat_dim % VEC;      // features of whole vectors
+    if (lane_stores && (VEC == 1 || scratch == nullptr || feat0 + VEC > whole)) {
 #pragma unroll
-            for (int k = 0; k < VEC; ++k) dst_row[feat0 + k] = v[k];
-        }
-        return;
+        for (int k = 0; k < VEC; ++k) dst_row[feat0 + k] = v[k];
     }
+    if (VEC == 1 || scratch == nullptr) return;
     const int lane = lane_id();
     constexpr int S = kScratchStride<Acc, VEC>();
     // element e of the wave's 64 * VEC span lives in lane e / VEC, register e % VEC
@@ -220,7 +235,7 @@ __device__ __forceinline__ void store_row(Acc* dst_row, int64_t feat0, const Acc
             const int e = j * kWave * 4 + lane * 4;
             const float4v q = *reinterpret_cast<const float4v*>(reinterpret_cast<const float*>(scratch) +
                                                                 (e / VEC) * S + (e % VEC));
-            if (wave_feat0 + e < feat_dim)
+            if (wave_feat0 + e < whole)
                 *reinterpret_cast<float4v*>(reinterpret_cast<float*>(dst_row) + wave_feat0 + e) = q;
         }
         __builtin_amdgcn_wave_barrier();
@@ -234,7 +249,7 @@ __device__ __forceinline__ void store_row(Acc* dst_row, int64_t feat0, const Acc
     for (int j = 0; j < VEC; ++j) {
         const int e = j * kWave + lane;
         const Acc x = scratch[(e / VEC) * S + (e % VEC)];
-        if (wave_feat0 + e < feat_dim) dst_row[wave_feat0 + e] = x;
+        if (wave_feat0 + e < whole) dst_row[wave_feat0 + e] = x;
     }
     __builtin_amdgcn_wave_barrier();
 }
@@ -243,7 +258,7 @@ __device__ __forceinline__ void store_row(Acc* dst_row, int64_t feat0, const Acc
 // addresses of the frames are then the same for all lanes of the wave, and saying so (the row
 // index goes through readfirstlane) lets the compiler keep them in scalar registers and address
 // the loads as scalar base + lane offset.
-template <typename ElemT, int VEC, bool WAVE_ROW>
+template <typename ElemT, int VEC, bool WAVE_ROW, bool STREAM>
 __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
 {
     typedef typename Elem<ElemT>::Acc Acc;
@@ -292,8 +307,10 @@ __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
     const uint8_t* flags = s_flags + row * stride + 1;      // flags[-1] = the slot before the chunk
     const int64_t frame_bytes = (int64_t)a.feat_dim * (int64_t)sizeof(ElemT);
     const uint8_t* chunk_src = a.packed + g * frame_bytes;                 // the chunk's first frame
-    const uint32_t lane_off = (uint32_t)fv * VEC * (uint32_t)sizeof(ElemT);  // the lane's place in a frame
-    const int64_t feat0 = (int64_t)fv * VEC;
+    // a frame that is no whole number of vectors: its last vector lies over the end of the one before
+    // (both lanes compute the same)
+    const int64_t feat0 = min((int64_t)fv * VEC, (int64_t)a.feat_dim - VEC);
+    const uint32_t lane_off = (uint32_t)feat0 * (uint32_t)sizeof(ElemT);     // the lane's place in a frame
     const bool writes_desc = (col == 0 && feat_tile == 0 && a.desc != nullptr);
     typedef typename OutOf<Acc>::T Out;
     Out* out = static_cast<Out*>(a.out);
@@ -334,7 +351,7 @@ __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
         int32_t s = t;
         static_assert(kWideUnroll == 8, "the tree below adds eight frames");
         for (; s + kWideUnroll <= e; s += kWideUnroll) {
-            LaneData<ElemT, VEC> x[kWideUnroll];
+            LaneData<ElemT, VEC, STREAM> x[kWideUnroll];
 #pragma unroll
             for (int u = 0; u < kWideUnroll; ++u) x[u].load(p + (int64_t)u * frame_bytes + lane_off);
 #pragma unroll
@@ -350,7 +367,7 @@ __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
             // the last, partial batch: all loads are issued at once as well (those
             // past the piece re-read its last slot and count as 0)
             const int32_t left = e - s;
-            LaneData<ElemT, VEC> x[kWideUnroll];
+            LaneData<ElemT, VEC, STREAM> x[kWideUnroll];
 #pragma unroll
             for (int u = 0; u < kWideUnroll; ++u)
                 x[u].load(p + (int64_t)min(u, left - 1) * frame_bytes + lane_off);
@@ -458,8 +475,6 @@ __device__ __forceinline__ uint32_t nonzero_bytes16(vec16 w)
     const uint32_t hi = __builtin_amdgcn_udot4(t[3], 0x80402010u, __builtin_amdgcn_udot4(t[2], 0x08040201u, 0u, false), false);
     return (lo >> 7) | ((hi >> 7) << 8);
 }
-
-typedef vec16 __attribute__((aligned(1))) vec16_any;      // a 16-byte vector at any address
 
 // The flag bytes of 16 consecutive slots, asked for with loads that stay inside the planes of
 // `total` slots wherever the slots lie (planes of fewer than 16 slots are read byte by byte).
@@ -1142,7 +1157,7 @@ __global__ __launch_bounds__(kThreads) void reduce_stitch_kernel(ReduceArgs a, i
 
 struct ReducePlan {
     bool wide, staged;
-    int vec;                 // wide: elements per lane (16 / elem size, or 1)
+    int vec;                 // wide: elements per lane (16 / elem size)
     int row_lanes_log2;
     int n_vec;
     int32_t chunk, n_chunks;
@@ -1161,11 +1176,14 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
     const int es = elem_size(dtype);
     const int64_t frame_bytes = feat_dim * es;
     const size_t acc = dtype == BLOAD_I32 ? 8 : 4;
-    const bool vectors = frame_bytes % 16 == 0 && frame_bytes >= 64;
-    p.staged = feat_dim > 1 && feat_dim < kStagedFrame && !vectors;
-    p.wide = !p.staged && feat_dim > 1;
-    if (p.wide) {
-        p.vec = vectors ? 16 / es : 1;
+    p.wide = frame_bytes >= 64;
+    // Lanes of 16 bytes, unless that leaves fewer than two workgroups per compute unit (four where the
+    // vectors are not aligned) or many lanes of a row idle: then lanes of 4 bytes, then of one element, which spread a frame over more waves (15
+    // blocks of 830 slots x 342 bytes: 23 us with 16 bytes a lane, 14 with one; 78 slots x 271 int32,
+    // whose rows of 16-byte lanes are half idle: 160 and 143 us).
+    const int widths[3] = {16, 4, es};
+    for (int w = 0; p.wide && w < 3; ++w) {
+        p.vec = widths[w] / es;
         p.n_vec = (int)ceil_div(feat_dim, p.vec);
         // a row is at most one wave wide: the last lane-slice of a frame then idles at most 63
         // lanes, and the four waves of a workgroup walk four different chunks
@@ -1199,7 +1217,17 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
         p.n_chunks = (int32_t)ceil_div(t_blk, chunk);
         p.total_chunks = num_blocks * p.n_chunks;
         p.partials = p.n_chunks > 1;
-    } else {
+        const int64_t groups = ceil_div(p.total_chunks, rows) * feat_tiles;
+        // Small frames in rows of a few lanes: a workgroup walks many chunks, and where that leaves too
+        // few workgroups the staged tiles are the more (13 blocks of 1580 slots x 128 bytes: 33 -> 15 us,
+        // 2900 blocks of 245 slots x 64 bytes: 90 -> 48 us); with enough of them the rows read better
+        // (2.5-4.9 TB/s against 2.0-2.8).
+        if (feat_dim < kStagedFrame && groups < 512) p.wide = false;
+        const bool half_idle = p.n_vec * 5 < (feat_tiles << p.row_lanes_log2) * 3;
+        if (groups >= (frame_bytes % 16 == 0 ? 512 : 1024) && !(w == 0 && half_idle && es == 4)) break;
+    }
+    if (!p.wide) {
+        p.staged = feat_dim > 1;
         // tiles never straddle a block: pieces of one block, or several whole blocks
         p.chunk = kNarrowTile;
         if (p.staged) {
@@ -1234,26 +1262,19 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
     return p;
 }
 
-template <typename ElemT>
+template <typename ElemT, int VEC, bool STREAM>
 static void launch_wide(const ReducePlan& p, const ReduceArgs& a, hipStream_t stream)
 {
+    typedef typename Elem<ElemT>::Acc Acc;
     const int rows = kThreads >> p.row_lanes_log2;
     const dim3 grid((uint32_t)(ceil_div(p.total_chunks, rows) * a.feat_tiles));
     size_t lds = (size_t)rows * (size_t)(p.chunk + 2);
-    if (p.vec > 1 && p.row_lanes_log2 >= 6)     // + the per-wave scratch of the transposed stores
-        lds = round_up(lds, 16) + (size_t)(kThreads / kWave) * kWave *
-                                      kScratchStride<typename Elem<ElemT>::Acc, 16 / (int)sizeof(ElemT)>() *
-                                      sizeof(typename Elem<ElemT>::Acc);
-    constexpr int kVec = 16 / (int)sizeof(ElemT);
-    const bool wave_row = p.row_lanes_log2 == 6;
-    if (p.vec > 1 && wave_row)
-        hipLaunchKernelGGL((reduce_wide_kernel<ElemT, kVec, true>), grid, dim3(kThreads), lds, stream, a);
-    else if (p.vec > 1)
-        hipLaunchKernelGGL((reduce_wide_kernel<ElemT, kVec, false>), grid, dim3(kThreads), lds, stream, a);
-    else if (wave_row)
-        hipLaunchKernelGGL((reduce_wide_kernel<ElemT, 1, true>), grid, dim3(kThreads), lds, stream, a);
+    if (VEC > 1 && p.row_lanes_log2 >= 6)     // + the per-wave scratch of the transposed stores
+        lds = round_up(lds, 16) + (size_t)(kThreads / kWave) * kWave * kScratchStride<Acc, VEC>() * sizeof(Acc);
+    if (p.row_lanes_log2 == 6)
+        hipLaunchKernelGGL((reduce_wide_kernel<ElemT, VEC, true, STREAM>), grid, dim3(kThreads), lds, stream, a);
     else
-        hipLaunchKernelGGL((reduce_wide_kernel<ElemT, 1, false>), grid, dim3(kThreads), lds, stream, a);
+        hipLaunchKernelGGL((reduce_wide_kernel<ElemT, VEC, false, STREAM>), grid, dim3(kThreads), lds, stream, a);
 }
 
 template <typename ElemT>
@@ -1261,7 +1282,12 @@ static void launch_reduce(const ReducePlan& p, const ReduceArgs& a, hipStream_t 
 {
     typedef typename Elem<ElemT>::Acc Acc;
     if (p.wide) {
-        launch_wide<ElemT>(p, a, stream);
+        constexpr int kVec = 16 / (int)sizeof(ElemT), kSmallVec = 4 / (int)sizeof(ElemT);
+        const bool fits_cache = a.total_slots * a.feat_dim * (int64_t)sizeof(ElemT) <= kMemorySideCache;
+        if (p.vec == kVec && fits_cache) launch_wide<ElemT, kVec, false>(p, a, stream);
+        else if (p.vec == kVec) launch_wide<ElemT, kVec, true>(p, a, stream);
+        else if (p.vec == kSmallVec) launch_wide<ElemT, kSmallVec, false>(p, a, stream);
+        else launch_wide<ElemT, 1, false>(p, a, stream);
     } else {
         const dim3 grid((uint32_t)p.total_chunks), block(kThreads);
         if (!p.staged)

@@ -270,6 +270,9 @@ def test_reduce_follows_the_flags(B, T, D, dtype, op):
 # fewer than 16 slots, enough tiles for the longer lanes and too few for them.
 @pytest.mark.parametrize("dtype,op", [("f32", "mean"), ("i32", "sum"), ("u8", "mean"), ("f16", "sum")])
 @pytest.mark.parametrize("B,T,D", [(2, 4224, 2), (700, 4225, 2), (3, 1153, 2), (40, 132, 63), (600, 133, 63), (300, 36, 57),
-                                   (5000, 37, 37), (900, 700, 7), (1, 2, 5), (1, 15, 3), (1, 17, 3), (4000, 19, 33)])
+                                   (5000, 37, 37), (900, 700, 7), (1, 2, 5), (1, 15, 3), (1, 17, 3), (4000, 19, 33),
+                                   # rows of 16 bytes per lane whose last vector lies over its neighbour, in rows
+                                   # of a few lanes, of a wave, and of several
+                                   (3000, 140, 17), (800, 300, 65), (60, 300, 271), (30, 70, 1025), (20, 40, 2061)])
 def test_reduce_staged_edges(B, T, D, dtype, op):
     test_reduce_follows_the_flags(B, T, D, dtype, op)
