@@ -107,7 +107,8 @@ int bload_last_hip_error(void);
  * gives B = 0, BLOAD_OK, and writes nothing to the device.  Synchronises the
  * stream before returning.  The library keeps 64 bytes of pinned host memory per
  * calling thread (taken at that thread's first call, never freed) into which the
- * device writes B and the frame total; bload_plan_shard uses the same bytes.
+ * device writes B and the frame total; bload_plan_random_fit and bload_plan_shard use
+ * the same bytes.
  */
 size_t bload_plan_workspace_bytes(int64_t n_seq);
 

@@ -32,13 +32,12 @@ constexpr int kRfGroups = kRfMaxT / kWave;            // groups of 64 lengths
 constexpr int kRfStride = kWave + 1;                  // a group's row: 65 running sums
 static_assert(kRfGroups == 2 * kWave, "two group sums per lane");
 
-// One placement, as the chain leaves it.
+// One placement, as the chain leaves it: its block is the one whose range of placements holds it.
 struct RfPick {
-    int32_t length;
-    int32_t rank;         // position inside the list of that length (the last remaining one)
-    int32_t block;
-    int32_t offset;
+    int32_t where;        // length - 1 << 16 | what was free in the block - 1
+    int32_t left;         // how many of that length were left: it takes the last of them
 };
+static_assert(kRfMaxT <= 1 << 15, "lengths and offsets, counted from 0, take 15 bits");
 
 __global__ void rf_clear_kernel(PlanResult* result)
 {
@@ -100,56 +99,70 @@ __global__ __launch_bounds__(kThreads) void rf_count_kernel(const int32_t* __res
     for (int e = tid; e < lengths_kept; e += kThreads) chunk_count[(int64_t)blockIdx.x * kRfMaxT + e] = s_fill[e];
 }
 
-// Step 2, one workgroup: the totals per length, from them first[], within[] and group_before[],
-// and in place of every chunk's counts the place where its part of each list begins.
-__global__ __launch_bounds__(kThreads) void rf_offsets_kernel(
+// Step 2, one workgroup of 16 waves: the totals per length, from them first[], within[] and
+// group_before[], and in place of every chunk's counts the place where its part of each list
+// begins.  A wave takes a group of 64 lengths at a time, a lane each (one thread per group walking its
+// lengths took 43 us at 3000 lengths, this 9).
+constexpr int kRfOffsetThreads = 1024;
+constexpr int kRfOffsetRounds = kRfGroups / (kRfOffsetThreads / kWave);
+
+struct RfSum { __device__ int32_t operator()(int32_t a, int32_t b) const { return a + b; } };
+struct RfMove {
+    template <int CTRL, int ROW_MASK>
+    __device__ __forceinline__ int32_t at(int32_t v) const { return dpp_move<CTRL, ROW_MASK>(v, 0); }
+};
+
+__global__ __launch_bounds__(kRfOffsetThreads) void rf_offsets_kernel(
     int32_t n_chunks, int32_t t_blk, int32_t* __restrict__ chunk_count, int32_t* __restrict__ first,
     int32_t* __restrict__ within, int32_t* __restrict__ group_before)
 {
-    __shared__ int32_t s_fill[kRfMaxT];
-    __shared__ int32_t s_scan[kThreads];
-    const int tid = (int)threadIdx.x;
+    __shared__ int32_t s_group[kRfGroups];
+    const int lane = lane_id(), wave = wave_id();
+    constexpr int kWaves = kRfOffsetThreads / kWave;
     const int groups = (t_blk + kWave - 1) / kWave;
-    for (int e = tid; e < groups * kWave; e += kThreads) {
-        int32_t total = 0;
-        for (int c = 0; c < n_chunks; ++c) total += chunk_count[(int64_t)c * kRfMaxT + e];
-        s_fill[e] = total;
-    }
-    __syncthreads();
-
-    // running sums inside each group of 64 lengths, one group per thread
-    int32_t mine = 0;
-    if (tid < groups) {
-        for (int j = 0; j < kWave; ++j) {
-            within[tid * kRfStride + j] = mine;
-            mine += s_fill[tid * kWave + j];
+    int32_t mine[kRfOffsetRounds], upto[kRfOffsetRounds];      // sequences of the lane's length; up to it in its group
+#pragma unroll
+    for (int r = 0; r < kRfOffsetRounds; ++r) {
+        const int g = wave + r * kWaves, e = g * kWave + lane;
+        mine[r] = upto[r] = 0;
+        if (g < groups) {
+            int32_t total = 0;
+#pragma unroll 8
+            for (int c = 0; c < n_chunks; ++c) total += chunk_count[(int64_t)c * kRfMaxT + e];
+            mine[r] = total;
+            upto[r] = wave_scan(total, RfSum(), RfMove());
+            within[g * kRfStride + lane + 1] = upto[r];
+            if (lane == 0) within[g * kRfStride] = 0;
         }
-        within[tid * kRfStride + kWave] = mine;
-    }
-    s_scan[tid] = mine;
-    __syncthreads();
-    static_assert(kRfGroups <= kThreads, "one thread per group");
-    int32_t run = 0;
-    for (int t = 0; t < tid; ++t) run += s_scan[t];
-    if (tid < kRfGroups) group_before[tid] = run;          // = all of them past the last group
-    if (tid < groups) {
-        for (int j = 0; j < kWave; ++j) {
-            const int e = tid * kWave + j;
-            const int32_t c = s_fill[e];
-            if (e < t_blk) first[e] = run;
-            s_fill[e] = run;                // start of the list of length e + 1
-            run += c;
-        }
+        if (lane == kWave - 1) s_group[g] = upto[r];
     }
     __syncthreads();
-    // a chunk's part of a list begins behind the parts of the chunks before it
-    for (int e = tid; e < groups * kWave; e += kThreads) {
-        int32_t at = s_fill[e];
-        for (int c = 0; c < n_chunks; ++c) {
-            const int64_t k = (int64_t)c * kRfMaxT + e;
-            const int32_t count = chunk_count[k];
-            chunk_count[k] = at;
-            at += count;
+    // sequences in the groups before each one: every wave adds them up for itself
+    static_assert(kRfGroups == 2 * kWave, "two groups per lane");
+    const int32_t lo = s_group[lane], hi = s_group[kWave + lane];
+    const int32_t lo_upto = wave_scan(lo, RfSum(), RfMove()), hi_upto = wave_scan(hi, RfSum(), RfMove());
+    const int32_t lo_all = __builtin_amdgcn_readlane(lo_upto, kWave - 1);
+    if (wave == 0) {
+        group_before[lane] = lo_upto - lo;
+        group_before[kWave + lane] = lo_all + hi_upto - hi;
+    }
+#pragma unroll
+    for (int r = 0; r < kRfOffsetRounds; ++r) {
+        const int g = wave + r * kWaves, e = g * kWave + lane;
+        if (g >= groups) break;
+        const int32_t before = g < kWave ? __shfl(lo_upto - lo, g & 63, kWave) : lo_all + __shfl(hi_upto - hi, g & 63, kWave);
+        int32_t at = before + upto[r] - mine[r];
+        if (e < t_blk) first[e] = at;
+        // a chunk's part of a list begins behind the parts of the chunks before it
+        for (int c0 = 0; c0 < n_chunks; c0 += 8) {
+            int32_t count[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) count[c] = c0 + c < n_chunks ? chunk_count[(int64_t)(c0 + c) * kRfMaxT + e] : 0;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                if (c0 + c < n_chunks) chunk_count[(int64_t)(c0 + c) * kRfMaxT + e] = at;
+                at += count[c];
+            }
         }
     }
 }
@@ -162,7 +175,7 @@ __global__ __launch_bounds__(kThreads) void rf_scatter_kernel(
     int32_t t_blk, int32_t per_chunk, const int32_t* __restrict__ chunk_start, int32_t* __restrict__ entry)
 {
     __shared__ int32_t s_fill[kRfMaxT];         // next free place of every list, for this chunk
-    __shared__ int32_t s_key[kThreads];
+    __shared__ alignas(16) int32_t s_key[kThreads];
     const int tid = (int)threadIdx.x;
     const int lengths_kept = ((t_blk + kWave - 1) / kWave) * kWave;
     for (int e = tid; e < lengths_kept; e += kThreads) s_fill[e] = chunk_start[(int64_t)blockIdx.x * kRfMaxT + e];
@@ -175,7 +188,20 @@ __global__ __launch_bounds__(kThreads) void rf_scatter_kernel(
         s_key[tid] = len;
         __syncthreads();
         int32_t rank = 0;
-        for (int t = 0; t < kThreads; ++t) rank += (s_key[t] == len) & (t < tid);
+        // four keys a look-up; only those of the waves up to this one can be in front
+        typedef int32_t int4v __attribute__((ext_vector_type(4)));
+        const int4v* key4 = reinterpret_cast<const int4v*>(s_key);
+        for (int w = 0; w <= wave_id(); ++w) {
+#pragma unroll
+            for (int t4 = 0; t4 < kWave / 4; ++t4) {
+                const int4v key = key4[w * (kWave / 4) + t4];
+                const int t = w * kWave + 4 * t4;
+                rank += (key[0] == len) & (t < tid);
+                rank += (key[1] == len) & (t + 1 < tid);
+                rank += (key[2] == len) & (t + 2 < tid);
+                rank += (key[3] == len) & (t + 3 < tid);
+            }
+        }
         const int32_t at = len ? s_fill[len - 1] + rank : 0;
         __syncthreads();
         if (len) {
@@ -186,116 +212,153 @@ __global__ __launch_bounds__(kThreads) void rf_scatter_kernel(
     }
 }
 
-// The chain of draws, on one wavefront, everything wave-uniform except three things
-// spread over the lanes: the 64 sums of a group (one LDS row), the sums of the groups
-// (lane j holds groups j and 64 + j) and the next 64 random numbers.
+// The chain of draws, on one wavefront, everything wave-uniform except: the running sums of a
+// group's lengths (a row: lane j holds how many of the group's first j + 1 lengths are left),
+// the sums over the groups (lane j holds groups j and 64 + j), the next 64 random numbers and the
+// last 64 placements.
 //   how many fit    = groups below the room's group (a lane read) + the row entry of the room
 //   the group of k  = the last group with "shorter sequences" <= k (compare, vote, find last)
-//   the length of k = the same inside the group's row
-//   taking it out   = one less in the row behind that length and in the groups behind
-// TWO: more than 64 groups (t_blk > 4096).
-template <bool TWO>
+//   the length of k = the first lane of the group's row above k's place in it
+//   taking it out   = one less in the lanes from there on and in the groups behind
+// A single wavefront issues a dependent instruction every seven cycles or so (3 ns), whatever it is; so
+// what counts is the number of instructions of a draw: placements kept in registers, a lane each, and stored 64 at a time without
+// their block (rf_assign_kernel finds it).  REGISTERS (t_blk <= 2048): the rows lie in 32 vector
+// registers, picked with an indexed register move, which saves the two waits for LDS of a
+// draw; more than 32 registers cannot be indexed as one, and choosing between two sets costs more
+// instructions than the waits (83 instead of 62).  GROUPS_HI: more than 64 groups (t_blk > 4096).
+constexpr int kRfRegisterRows = 32;
+typedef int32_t rf_rows __attribute__((ext_vector_type(kRfRegisterRows)));
+
+template <bool REGISTERS, bool GROUPS_HI>
 __global__ __launch_bounds__(kWave) void rf_draw_kernel(
     const int32_t* __restrict__ within, const int32_t* __restrict__ group_before, int32_t n_seq,
     int32_t t_blk, uint64_t seed, RfPick* __restrict__ pick, int32_t* __restrict__ block_first,
-    PlanResult* __restrict__ result)
+    PlanResult* __restrict__ result, PlanResult* __restrict__ host_result)
 {
-    __shared__ int32_t s_within[(TWO ? kRfGroups : kWave) * kRfStride];
+    __shared__ int32_t s_rows[REGISTERS ? 1 : (GROUPS_HI ? kRfGroups : kWave) * kWave];
     const int lane = (int)threadIdx.x;
     const int groups = (t_blk + kWave - 1) / kWave;
-    for (int k = lane; k < groups * kRfStride; k += kWave) s_within[k] = within[k];
-    int32_t before_lo = group_before[lane];
-    int32_t before_hi = TWO ? group_before[kWave + lane] : 0;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (result->bad_length) return;
-
-    // Every block takes at least one sequence (all of them fit an empty block) and every
-    // placement uses up room, so both loops end whatever the sums hold; should a draw ever
-    // land on a length that does not fit, the chain stops and says so.
-    int32_t placed = 0, block = 0;
-    bool consistent = true;
-    uint32_t u_lo = 0, u_hi = 0;
-    while (consistent && placed < n_seq && block < n_seq) {
-        int32_t room = t_blk;
-        if (lane == 0) block_first[block] = placed;
-        while (room > 0 && placed < n_seq) {
-            const int e_room = room - 1, g_room = e_room >> 6;
-            int32_t fit = s_within[g_room * kRfStride + (e_room & 63) + 1];
-            if (TWO && g_room >= kWave) fit += __builtin_amdgcn_readlane(before_hi, g_room - kWave);
-            else fit += __builtin_amdgcn_readlane(before_lo, g_room);
-            fit = __builtin_amdgcn_readfirstlane(fit);
-            if (fit <= 0) break;
-
-            if ((placed & (kWave - 1)) == 0) {          // the next 64 random numbers, one per lane
-                const uint64_t u = splitmix64_at(seed, (uint64_t)(6 + placed + lane));
-                u_lo = (uint32_t)u;
-                u_hi = (uint32_t)(u >> 32);
-            }
-            const int turn = placed & (kWave - 1);
-            const uint64_t u = ((uint64_t)__builtin_amdgcn_readlane(u_hi, turn) << 32) |
-                               (uint32_t)__builtin_amdgcn_readlane(u_lo, turn);
-            const int32_t k = (int32_t)__umul64hi(u, (uint64_t)fit);          // uniform in [0, fit)
-
-            int g_pick = 63 - __builtin_clzll(__ballot(before_lo <= k));      // lane 0 holds 0 <= k
-            int32_t below = __builtin_amdgcn_readlane(before_lo, g_pick);
-            if (TWO) {
-                const uint64_t vote_hi = __ballot(before_hi <= k);
-                if (vote_hi) {
-                    const int j = 63 - __builtin_clzll(vote_hi);
-                    g_pick = kWave + j;
-                    below = __builtin_amdgcn_readlane(before_hi, j);
-                }
-            }
-            const int row = g_pick * kRfStride + lane;
-            const int32_t shorter = s_within[row], upto = s_within[row + 1];
-            const int j = 63 - __builtin_clzll(__ballot(shorter <= k - below));   // lane 0 holds 0
-            const int32_t length = g_pick * kWave + j + 1;
-            const int32_t left = __builtin_amdgcn_readlane(upto, j) - __builtin_amdgcn_readlane(shorter, j);
-            if (length > room) {
-                consistent = false;
-                break;
-            }
-
-            // the last remaining sequence of that length leaves
-            if (lane >= j) s_within[row + 1] = upto - 1;
-            before_lo -= (lane > g_pick);
-            if (TWO) before_hi -= (kWave + lane > g_pick);
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-
-            if (lane == 0) pick[placed] = RfPick{length, left - 1, block, t_blk - room};
-            room -= length;
-            placed += 1;
-        }
-        block += 1;
+    rf_rows rows = {};
+    if (REGISTERS) {
+#pragma unroll
+        for (int k = 0; k < kRfRegisterRows; ++k)        // (behind the last group never picked; they repeat it)
+            rows[k] = within[min(k, groups - 1) * kRfStride + lane + 1];
+    } else {
+        for (int g = 0; g < groups; ++g) s_rows[g * kWave + lane] = within[g * kRfStride + lane + 1];
     }
+    int32_t before_lo = group_before[lane];
+    int32_t before_hi = GROUPS_HI ? group_before[kWave + lane] : 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const int32_t bad = result->bad_length;
+    if (bad) {
+        if (lane == 0 && host_result) host_result->bad_length = bad;
+        return;
+    }
+
+    // Every block takes at least one sequence (all of them fit an empty block), every placement
+    // uses up room, and at most n_seq blocks are begun: the loop ends whatever the sums hold.
+    int32_t placed = 0, blocks = 0;
+    int32_t last = -1;                                   // the longest length that fits, counted from 0; -1: none
+    uint32_t u_lo = 0, u_hi = 0;
+    int32_t kept_where = 0, kept_left = 0;               // placement (placed & ~63) + lane
+    while (placed < n_seq && blocks < n_seq && last >= -1) {
+      if (lane == 0) block_first[blocks] = placed;
+      blocks += 1;
+      last = t_blk - 1;
+      while (last >= 0) {
+        const int g_room = last >> 6;
+        int32_t fit = REGISTERS ? __builtin_amdgcn_readlane(rows[g_room & (kRfRegisterRows - 1)], last & 63)
+                                : __builtin_amdgcn_readfirstlane(s_rows[last]);
+        if (GROUPS_HI && g_room >= kWave) fit += __builtin_amdgcn_readlane(before_hi, g_room - kWave);
+        else fit += __builtin_amdgcn_readlane(before_lo, g_room);
+        if (fit <= 0) break;
+
+        const int turn = placed & (kWave - 1);
+        if (turn == 0) {                                 // the next 64 random numbers, one per lane
+            const uint64_t u = splitmix64_at(seed, (uint64_t)(6 + placed + lane));
+            u_lo = (uint32_t)u;
+            u_hi = (uint32_t)(u >> 32);
+            if (placed > 0) pick[placed - kWave + lane] = RfPick{kept_where, kept_left};
+        }
+        const uint64_t u = ((uint64_t)__builtin_amdgcn_readlane(u_hi, turn) << 32) |
+                           (uint32_t)__builtin_amdgcn_readlane(u_lo, turn);
+        const int32_t k = (int32_t)__umul64hi(u, (uint64_t)(uint32_t)fit);        // uniform in [0, fit)
+
+        int g = 63 - __builtin_clzll(__ballot(before_lo <= k));                   // lane 0 holds 0 <= k
+        int32_t in_row = k - __builtin_amdgcn_readlane(before_lo, g);
+        if (GROUPS_HI) {
+            const uint64_t vote_hi = __ballot(before_hi <= k);
+            if (vote_hi) {
+                const int j = 63 - __builtin_clzll(vote_hi);
+                g = kWave + j;
+                in_row = k - __builtin_amdgcn_readlane(before_hi, j);
+            }
+        }
+        const int32_t upto = REGISTERS ? rows[g & (kRfRegisterRows - 1)] : s_rows[g * kWave + lane];
+        const bool above = upto > in_row;                // running sums do not fall: the lanes from k's length on
+        const int j = __builtin_ctzll(__ballot(above));
+        // (two lane reads: a difference in the vector unit, folded into the move, comes out negated)
+        const int32_t shorter = dpp_move<kDppWaveShr1>(upto, 0);
+        const int32_t left = __builtin_amdgcn_readlane(upto, j) - __builtin_amdgcn_readlane(shorter, j);
+
+        // the last remaining sequence of that length leaves
+        if (REGISTERS) rows[g & (kRfRegisterRows - 1)] = upto - (int32_t)above;
+        else s_rows[g * kWave + lane] = upto - (int32_t)above;
+        before_lo -= (lane > g);
+        if (GROUPS_HI) before_hi -= (kWave + lane > g);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+
+        const int32_t drawn = g * kWave + j;             // its length, counted from 0
+        const int32_t where = drawn << 16 | last;
+        kept_where = lane == turn ? where : kept_where;
+        kept_left = lane == turn ? left : kept_left;
+        last -= drawn + 1;                               // (below -1 only if the sums were wrong)
+        placed += 1;
+      }
+    }
+    const int32_t rest = (placed - 1) & (kWave - 1);     // the last set of placements
+    if (placed > 0 && lane <= rest) pick[placed - 1 - rest + lane] = RfPick{kept_where, kept_left};
     if (lane == 0) {
-        if (consistent && placed == n_seq) {
-            block_first[block] = n_seq;
-            result->num_blocks = block;
+        if (last >= -1 && placed == n_seq) {
+            block_first[blocks] = n_seq;
+            result->num_blocks = blocks;
         } else {
             result->bad_length = 2;
+        }
+        if (host_result) {
+            host_result->num_blocks = blocks;
+            host_result->total_frames = result->total_frames;
+            host_result->bad_length = last >= -1 && placed == n_seq ? 0 : 2;
         }
     }
 }
 
 __global__ __launch_bounds__(kThreads) void rf_assign_kernel(
     const RfPick* __restrict__ pick, const int32_t* __restrict__ first,
-    const int32_t* __restrict__ entry, int32_t n_seq, int32_t* __restrict__ order,
-    int32_t* __restrict__ block_of_seq, int32_t* __restrict__ offset_of_seq,
-    PlanResult* __restrict__ result)
+    const int32_t* __restrict__ entry, int32_t n_seq, int32_t t_blk, const int32_t* __restrict__ block_first,
+    int32_t* __restrict__ order, int32_t* __restrict__ block_of_seq, int32_t* __restrict__ offset_of_seq,
+    PlanResult* __restrict__ result, PlanResult* __restrict__ host_result)
 {
     const int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (p >= n_seq || result->bad_length) return;
     const RfPick k = pick[p];
-    const int64_t at = (int64_t)first[k.length - 1] + k.rank;
-    if (k.rank < 0 || at >= n_seq) {                    // cannot happen with consistent sums
+    const int32_t rank = k.left - 1;
+    const int64_t at = (int64_t)first[k.where >> 16] + rank;
+    if (rank < 0 || at >= n_seq) {                      // cannot happen with consistent sums
         result->bad_length = 2;
+        if (host_result) host_result->bad_length = 2;
         return;
     }
     const int32_t i = entry[at];
+    // the last block that begins at or before placement p
+    int32_t lo = 0, hi = (int32_t)result->num_blocks;
+    while (hi - lo > 1) {
+        const int32_t mid = lo + ((hi - lo) >> 1);
+        if (block_first[mid] <= p) lo = mid; else hi = mid;
+    }
     order[p] = i;
-    block_of_seq[i] = k.block;
-    offset_of_seq[i] = k.offset;
+    block_of_seq[i] = lo;
+    offset_of_seq[i] = t_blk - 1 - (k.where & 0xffff);
 }
 
 struct RfLayout {
@@ -362,6 +425,10 @@ extern "C" bload_status bload_plan_random_fit(const int32_t* d_lengths, int64_t 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     uint8_t* ws = static_cast<uint8_t*>(d_workspace);
     PlanResult* result = reinterpret_cast<PlanResult*>(ws + l.result);
+    // the numbers the host waits for also go into pinned host memory where there is some (plain stores of
+    // the last kernels), else they are copied back from the workspace
+    static_assert(sizeof(PlanResult) <= 64, "the pinned buffer holds 64 bytes");
+    PlanResult* pinned = static_cast<PlanResult*>(host_result_buffer());
     int32_t* seeded = reinterpret_cast<int32_t*>(ws + l.seeded);
     int32_t* seeded_len = reinterpret_cast<int32_t*>(ws + l.seeded_len);
     int32_t* entry = reinterpret_cast<int32_t*>(ws + l.entry);
@@ -381,24 +448,29 @@ extern "C" bload_status bload_plan_random_fit(const int32_t* d_lengths, int64_t 
                        seeded_len, result);
     hipLaunchKernelGGL(rf_count_kernel, dim3((uint32_t)l.n_chunks), block, 0, stream, seeded_len, n, t_blk,
                        l.per_chunk, chunk_count);
-    hipLaunchKernelGGL(rf_offsets_kernel, dim3(1), block, 0, stream, l.n_chunks, t_blk, chunk_count, first,
+    hipLaunchKernelGGL(rf_offsets_kernel, dim3(1), dim3(kRfOffsetThreads), 0, stream, l.n_chunks, t_blk, chunk_count, first,
                        within, group_before);
     hipLaunchKernelGGL(rf_scatter_kernel, dim3((uint32_t)l.n_chunks), block, 0, stream, seeded, seeded_len,
                        n, t_blk, l.per_chunk, chunk_count, entry);
     // after a length outside [1, t_blk] the last two kernels return at once
-    if (t_blk > kWave * kWave)
-        hipLaunchKernelGGL(rf_draw_kernel<true>, dim3(1), dim3(kWave), 0, stream, within, group_before,
-                           n, t_blk, seed, pick, d_block_first, result);
+    const dim3 wave(kWave);
+    if (t_blk <= kRfRegisterRows * kWave)
+        hipLaunchKernelGGL((rf_draw_kernel<true, false>), dim3(1), wave, 0, stream, within, group_before, n, t_blk,
+                           seed, pick, d_block_first, result, pinned);
+    else if (t_blk <= kWave * kWave)
+        hipLaunchKernelGGL((rf_draw_kernel<false, false>), dim3(1), wave, 0, stream, within, group_before, n, t_blk,
+                           seed, pick, d_block_first, result, pinned);
     else
-        hipLaunchKernelGGL(rf_draw_kernel<false>, dim3(1), dim3(kWave), 0, stream, within,
-                           group_before, n, t_blk, seed, pick, d_block_first, result);
-    hipLaunchKernelGGL(rf_assign_kernel, per_item, block, 0, stream, pick, first, entry, n, d_order,
-                       d_block_of_seq, d_offset_of_seq, result);
+        hipLaunchKernelGGL((rf_draw_kernel<false, true>), dim3(1), wave, 0, stream, within, group_before, n, t_blk,
+                           seed, pick, d_block_first, result, pinned);
+    hipLaunchKernelGGL(rf_assign_kernel, per_item, block, 0, stream, pick, first, entry, n, t_blk, d_block_first, d_order,
+                       d_block_of_seq, d_offset_of_seq, result, pinned);
     if (launch_status() != BLOAD_OK) return BLOAD_EHIP;
     PlanResult host{};
-    if (!hip_ok(hipMemcpyAsync(&host, result, sizeof(host), hipMemcpyDeviceToHost, stream)))
+    if (!pinned && !hip_ok(hipMemcpyAsync(&host, result, sizeof(host), hipMemcpyDeviceToHost, stream)))
         return BLOAD_EHIP;
     if (!hip_ok(hipStreamSynchronize(stream))) return BLOAD_EHIP;
+    if (pinned) host = *pinned;
     if (host.bad_length == 1) return BLOAD_ELENGTH;
     if (host.bad_length) return BLOAD_EHIP;            // the chain found its sums inconsistent
     *h_num_blocks = host.num_blocks;
