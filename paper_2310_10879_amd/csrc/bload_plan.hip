@@ -15,12 +15,14 @@
 // Beyond that the scans work on tiles of 2048 positions (many small workgroups)
 // and the orbit is found on tiles of 8192 in three steps that need no launch per
 // jumping round: every tile jumps inside its own LDS until each of its positions
-// has left the tile (exit[p]); one thread follows exit[] from position 0 and
-// notes where the orbit enters each tile (one hop per tile); every tile then
-// marks its heads from its entry by jumping in LDS again.  Seven launches at any size; five
-// up to 8192 sequences, where the one tile is entered at position 0 and the first two of the
-// three steps fall away; six up to 256 tiles of 8192, where every tile follows exit[] to its own
-// entry.
+// has left the tile (exit[p]); the orbit's entry into each tile is found by following
+// exit[] from position 0 (one hop per tile; from 40 tiles on over groups of 8 tiles, whose
+// exits a small kernel composes first; beyond 1024 tiles one thread finds all entries); every
+// tile then marks its heads from its entry by jumping in LDS again.  Five launches up to 8192
+// sequences, where the one tile is entered at position 0, six up to 40 tiles, seven beyond.
+// Bound by launches and latencies: 10^4 sequences 66 -> 59 us per call with one position per
+// thread in the order kernel (10 -> 4.3 us), 10^6 sequences 154 -> 129 us with that (17 -> 11)
+// and the groups of tiles (marking kernel 46 -> 24 us, their own 4).
 #include "bload_common.hpp"
 #include "bload_order.hpp"
 
@@ -32,7 +34,10 @@ constexpr int kJumpThreads = 512;                 // workgroup size where a work
                                                   // LDS look-ups of one wave hide behind the others')
 constexpr int kJumpItems = 16;                    // positions per thread there
 constexpr int kJumpTile = kJumpThreads * kJumpItems;   // 8192
-constexpr int kWalkTiles = 256;                   // up to this many jump tiles, each finds its own entry (see plan_mark_kernel)
+constexpr int kWalkTiles = 1024;                  // up to this many jump tiles, each finds its own entry (see plan_mark_kernel),
+constexpr int kGroupFrom = 40;                    // and from this many on with the exits of groups of tiles: their launch
+                                                  // costs 5 us, a hop of the walk 0.24
+constexpr int64_t kSingleItems = (int64_t)1 << 20;     // up to this many sequences the order kernel takes one per thread
 constexpr int kJumpRounds = 13;                   // 2^13 = kJumpTile: rounds that cross a whole tile
 constexpr int kScanPerJump = kJumpTile / kTile;   // scan tiles in a jump tile
 constexpr int kWavesPerScanTile = kTile / (kWave * kJumpItems);     // waves of the marking kernel per scan tile
@@ -183,25 +188,29 @@ __device__ __forceinline__ void pad_tile(int32_t* tile, int32_t lo, int32_t coun
 
 // ---- kernels ------------------------------------------------------------------
 
-// order[p], the shuffled lengths, and per tile: the sum of its lengths, and whether one of them
-// is outside [1, t_blk].
+// order[p], the shuffled lengths, and per workgroup of ITEMS * 256 positions: the sum of its lengths, and
+// whether one of them is outside [1, t_blk].  One position per thread where that makes few sums: a
+// walk through the order is a long chain of integer operations whose length differs from lane to
+// lane, and eight in a row by few waves took 10 us at 10^4 sequences and 17 at 10^6.
+template <int ITEMS>
 __global__ __launch_bounds__(kThreads) void plan_order_kernel(
     const int32_t* __restrict__ lengths, int32_t n_seq, int32_t t_blk, OrderKey key,
     int32_t* __restrict__ order, int32_t* __restrict__ shuffled_len,
     int64_t* __restrict__ tile_sum, int32_t* __restrict__ tile_bad)
 {
-    const int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kItems;
+    const int64_t base = (int64_t)blockIdx.x * (kThreads * ITEMS) + (int64_t)threadIdx.x * ITEMS;
     int64_t sum = 0;
     int bad = 0;
 #pragma unroll
-    for (int j = 0; j < kItems; ++j) {
+    for (int j = 0; j < ITEMS; ++j) {
         const int64_t p = base + j;
         if (p < n_seq) {
             const int32_t i = order_at((uint32_t)p, (uint32_t)n_seq, key);
-            const int32_t len = lengths[i];
+            int32_t len = lengths[i];
             order[p] = i;
+            // (a length out of range is refused in the end; as a 1 it keeps next[] rising until then)
+            if ((len < 1) | (len > t_blk)) { bad = 1; len = 1; }
             shuffled_len[p] = len;
-            bad |= (len < 1) | (len > t_blk);
             sum += len;
         }
     }
@@ -212,13 +221,13 @@ __global__ __launch_bounds__(kThreads) void plan_order_kernel(
 }
 
 // P[p] = frames before shuffled position p; P[n_seq] = total.  Every tile adds up the sums
-// of the tiles before it by itself.
+// in front of it by itself (`sums_per_tile` of them to a tile).
 __global__ __launch_bounds__(kThreads) void plan_prefix_kernel(
     const int32_t* __restrict__ shuffled_len, int32_t n_seq, const int64_t* __restrict__ tile_sum,
-    int64_t* __restrict__ prefix)
+    int32_t sums_per_tile, int64_t* __restrict__ prefix)
 {
     int64_t mine = 0;
-    for (int32_t t = (int32_t)threadIdx.x; t < (int32_t)blockIdx.x; t += kThreads) mine += tile_sum[t];
+    for (int32_t t = (int32_t)threadIdx.x; t < (int32_t)blockIdx.x * sums_per_tile; t += kThreads) mine += tile_sum[t];
     int64_t before;
     block_exclusive_scan<int64_t>(mine, 0, SumI64(), &before);
 
@@ -290,6 +299,27 @@ __global__ __launch_bounds__(kJumpThreads) void plan_exit_kernel(const int32_t* 
     copy_tile<kJumpThreads>(s_jump[cur], exit_of + lo, count);
 }
 
+// The same over kGroupTiles jump tiles at a time, for the positions where an orbit can enter such a
+// group (next[] never falls, so those are at most next[the position in front of the group]; the
+// first group is entered at 0).  A tile that looks for its entry then takes a hop per group and a
+// few per tile instead of one per tile.
+constexpr int kGroupTiles = 8;
+constexpr int kGroupSpread = 16;                  // workgroups side by side over a group's entries
+
+__global__ __launch_bounds__(kThreads) void plan_group_exit_kernel(const int32_t* __restrict__ next,
+                                                                   const int32_t* __restrict__ exit_of, int32_t n_seq,
+                                                                   int32_t* __restrict__ group_exit)
+{
+    const int32_t lo = (int32_t)blockIdx.x * (kGroupTiles * kJumpTile);
+    const int32_t end = min((int64_t)lo + kGroupTiles * kJumpTile, (int64_t)n_seq);
+    const int32_t most = min(lo == 0 ? 0 : next[lo - 1], end - 1);
+    for (int64_t p = (int64_t)lo + blockIdx.y * kThreads + threadIdx.x; p <= most; p += kGroupSpread * kThreads) {
+        int32_t e = (int32_t)p;
+        while (e < end) e = exit_of[e];           // exit[e] lies in a later tile than e: at most kGroupTiles hops
+        group_exit[p] = e;
+    }
+}
+
 // Where the orbit of position 0 enters each jump tile (-1: it passes over the tile): one hop
 // per tile along exit[].  One workgroup; thread 0 walks.
 __global__ __launch_bounds__(kThreads) void plan_chain_kernel(const int32_t* __restrict__ exit_of,
@@ -308,8 +338,9 @@ __global__ __launch_bounds__(kThreads) void plan_chain_kernel(const int32_t* __r
 }
 
 // The heads inside a jump tile, from the position where the orbit enters it: tile_entry[tile],
-// or, with `tile_entry` null, found here by following exit[] from position 0 (at most one hop per
-// tile in front of this one: for few tiles that is quicker than a launch that does it for all;
+// or, with `tile_entry` null, found here by following group_exit[] and exit[] from position 0 (one hop
+// per group of tiles and per tile of the last group: quicker than a launch that does it for all;
+// `group_exit` null: exit[] alone;
 // `exit_of` null as well: there is one tile only, entered at position 0).  The heads found so far are kept as a list in
 // orbit order, h_0 = the entry: round r jumps every position of the tile from next^(2^r) to
 // next^(2^(r+1)) as the exit kernel does, and before that the first 2^r heads look up theirs,
@@ -319,7 +350,7 @@ __global__ __launch_bounds__(kThreads) void plan_chain_kernel(const int32_t* __r
 // and the last head.
 __global__ __launch_bounds__(kJumpThreads) void plan_mark_kernel(
     const int32_t* __restrict__ next, const int32_t* __restrict__ tile_entry,
-    const int32_t* __restrict__ exit_of, int32_t n_seq,
+    const int32_t* __restrict__ exit_of, const int32_t* __restrict__ group_exit, int32_t n_seq,
     uint8_t* __restrict__ mark, int32_t* __restrict__ tile_cnt, int32_t* __restrict__ tile_head)
 {
     __shared__ __attribute__((aligned(16))) int32_t s_jump[2][kJumpTile];
@@ -338,7 +369,10 @@ __global__ __launch_bounds__(kJumpThreads) void plan_mark_kernel(
         if (tile_entry) {
             e = tile_entry[blockIdx.x];
         } else if (exit_of) {
-            while (e < lo) e = exit_of[e];            // exit[e] lies in a later tile than e: the walk ends
+            // group by group up to this tile's group, then tile by tile: every hop leads into a later one
+            const int32_t group_lo = group_exit ? lo - lo % (kGroupTiles * kJumpTile) : 0;
+            while (e < group_lo) e = group_exit[e];
+            while (e < lo) e = exit_of[e];
             if (e >= lo + count) e = -1;              // the orbit passes over this tile
         }
         s_entry = e;
@@ -419,7 +453,7 @@ __global__ __launch_bounds__(kJumpThreads) void plan_mark_kernel(
 __global__ __launch_bounds__(kThreads) void plan_assign_kernel(
     const uint8_t* __restrict__ mark, const int32_t* __restrict__ order,
     const int64_t* __restrict__ prefix, int32_t n_seq, const int32_t* __restrict__ tile_cnt,
-    const int32_t* __restrict__ tile_head, const int32_t* __restrict__ tile_bad,
+    const int32_t* __restrict__ tile_head, const int32_t* __restrict__ tile_bad, int32_t n_bad,
     int32_t* __restrict__ block_of_seq, int32_t* __restrict__ offset_of_seq,
     int32_t* __restrict__ block_first, PlanResult* __restrict__ result)
 {
@@ -428,10 +462,9 @@ __global__ __launch_bounds__(kThreads) void plan_assign_kernel(
     HeadPair mine{0, -1};
     int bad = 0;
     const bool last_tile = blockIdx.x == gridDim.x - 1;
-    for (int32_t t = (int32_t)threadIdx.x; t < (int32_t)gridDim.x; t += kThreads) {
-        if (t < (int32_t)blockIdx.x) mine = HeadOp()(mine, HeadPair{tile_cnt[t], tile_head[t]});
-        if (last_tile) bad |= tile_bad[t];
-    }
+    for (int32_t t = (int32_t)threadIdx.x; t < (int32_t)blockIdx.x; t += kThreads)
+        mine = HeadOp()(mine, HeadPair{tile_cnt[t], tile_head[t]});
+    for (int32_t t = (int32_t)threadIdx.x; last_tile && t < n_bad; t += kThreads) bad |= tile_bad[t];
     HeadPair before;
     block_exclusive_scan<HeadPair>(mine, HeadPair{0, -1}, HeadOp(), &before);
     if (last_tile) bad = __syncthreads_or(bad);
@@ -557,6 +590,8 @@ struct PlanLayout {
     size_t result, shuffled_len, prefix, next, exit_of, mark, tile_sum, tile_cnt, tile_head, tile_entry,
         tile_bad, bytes;
     int32_t n_tiles;           // scan tiles
+    int32_t sums_per_tile;     // workgroups of the order kernel to a scan tile
+    int32_t n_sums;
     int32_t n_jump_tiles;
 };
 
@@ -566,6 +601,8 @@ static PlanLayout plan_layout(int64_t n_seq)
     const size_t n = (size_t)(n_seq > 0 ? n_seq : 0);
     l.n_tiles = (int32_t)ceil_div((int64_t)n, kTile);
     l.n_jump_tiles = (int32_t)ceil_div((int64_t)n, kJumpTile);
+    l.sums_per_tile = (int64_t)n <= kSingleItems ? kItems : 1;
+    l.n_sums = (int32_t)ceil_div((int64_t)n, kTile / l.sums_per_tile);
     size_t off = 0;
     auto take = [&off](size_t bytes) { const size_t at = off; off += round_up(bytes, 16); return at; };
     l.result = take(sizeof(PlanResult));
@@ -574,11 +611,11 @@ static PlanLayout plan_layout(int64_t n_seq)
     l.next = take(n * 4);
     l.exit_of = take(n * 4);
     l.mark = take(n);
-    l.tile_sum = take((size_t)l.n_tiles * 8);
+    l.tile_sum = take((size_t)l.n_sums * 8);
     l.tile_cnt = take((size_t)l.n_tiles * 4);
     l.tile_head = take((size_t)l.n_tiles * 4);
     l.tile_entry = take((size_t)l.n_jump_tiles * 4);
-    l.tile_bad = take((size_t)l.n_tiles * 4);
+    l.tile_bad = take((size_t)l.n_sums * 4);
     l.bytes = off;
     return l;
 }
@@ -644,9 +681,14 @@ extern "C" bload_status bload_plan(const int32_t* d_lengths, int64_t n_seq, int3
         hipLaunchKernelGGL(plan_small_kernel, dim3(1), block, 0, stream, d_lengths, n, t_blk, key,
                            rounds, d_order, d_block_of_seq, d_offset_of_seq, d_block_first, result);
     } else {
-        hipLaunchKernelGGL(plan_order_kernel, tiles, block, 0, stream, d_lengths, n, t_blk, key,
-                           d_order, shuffled_len, tile_sum, tile_bad);
-        hipLaunchKernelGGL(plan_prefix_kernel, tiles, block, 0, stream, shuffled_len, n, tile_sum,
+        const dim3 sums((uint32_t)l.n_sums);
+        if (l.sums_per_tile == 1)
+            hipLaunchKernelGGL(plan_order_kernel<kItems>, sums, block, 0, stream, d_lengths, n, t_blk, key, d_order,
+                               shuffled_len, tile_sum, tile_bad);
+        else
+            hipLaunchKernelGGL(plan_order_kernel<1>, sums, block, 0, stream, d_lengths, n, t_blk, key, d_order,
+                               shuffled_len, tile_sum, tile_bad);
+        hipLaunchKernelGGL(plan_prefix_kernel, tiles, block, 0, stream, shuffled_len, n, tile_sum, l.sums_per_tile,
                            prefix);
         hipLaunchKernelGGL(plan_next_kernel, dim3((uint32_t)ceil_div(n_seq, kThreads)), block, 0, stream,
                            prefix, n, t_blk, next);
@@ -655,14 +697,20 @@ extern "C" bload_status bload_plan(const int32_t* d_lengths, int64_t n_seq, int3
         const bool one_jump_tile = l.n_jump_tiles == 1, tiles_walk = l.n_jump_tiles <= kWalkTiles;
         if (!one_jump_tile)
             hipLaunchKernelGGL(plan_exit_kernel, jump_tiles, dim3(kJumpThreads), 0, stream, next, n, exit_of);
+        const bool grouped = tiles_walk && l.n_jump_tiles >= kGroupFrom;
+        int32_t* group_exit = shuffled_len;       // (the shuffled lengths are not needed any more)
+        if (grouped)
+            hipLaunchKernelGGL(plan_group_exit_kernel, dim3((uint32_t)ceil_div(l.n_jump_tiles, kGroupTiles), kGroupSpread),
+                               block, 0, stream, next, exit_of, n, group_exit);
         if (!tiles_walk)
             hipLaunchKernelGGL(plan_chain_kernel, dim3(1), block, 0, stream, exit_of, n, l.n_jump_tiles,
                                tile_entry);
         hipLaunchKernelGGL(plan_mark_kernel, jump_tiles, dim3(kJumpThreads), 0, stream, next,
-                           tiles_walk ? nullptr : tile_entry, one_jump_tile ? nullptr : exit_of, n, mark,
+                           tiles_walk ? nullptr : tile_entry, one_jump_tile ? nullptr : exit_of,
+                           grouped ? group_exit : nullptr, n, mark,
                            tile_cnt, tile_head);
         hipLaunchKernelGGL(plan_assign_kernel, tiles, block, 0, stream, mark, d_order, prefix, n,
-                           tile_cnt, tile_head, tile_bad, d_block_of_seq, d_offset_of_seq,
+                           tile_cnt, tile_head, tile_bad, l.n_sums, d_block_of_seq, d_offset_of_seq,
                            d_block_first, result);
     }
     if (launch_status() != BLOAD_OK) return BLOAD_EHIP;

@@ -220,12 +220,13 @@ __global__ __launch_bounds__(kThreads) void rf_scatter_kernel(
 //   the group of k  = the last group with "shorter sequences" <= k (compare, vote, find last)
 //   the length of k = the first lane of the group's row above k's place in it
 //   taking it out   = one less in the lanes from there on and in the groups behind
-// A single wavefront issues a dependent instruction every seven cycles or so (3 ns), whatever it is; so
-// what counts is the number of instructions of a draw: placements kept in registers, a lane each, and stored 64 at a time without
-// their block (rf_assign_kernel finds it).  REGISTERS (t_blk <= 2048): the rows lie in 32 vector
-// registers, picked with an indexed register move, which saves the two waits for LDS of a
-// draw; more than 32 registers cannot be indexed as one, and choosing between two sets costs more
-// instructions than the waits (83 instead of 62).  GROUPS_HI: more than 64 groups (t_blk > 4096).
+// A single wavefront issues a dependent instruction every seven cycles or so (3 ns), whatever it is;
+// so what counts is the number of instructions of a draw (75 -> 60: 273 -> 217 ns a draw at lengths
+// up to 3000): placements are kept in registers, a lane each, and stored 64 at a time without their
+// block (rf_assign_kernel finds it).  REGISTERS (t_blk <= 2048): the rows lie in 32 vector registers,
+// picked with an indexed register move, which saves the two waits for LDS of a draw (256 -> 233 ns);
+// more than 32 registers cannot be indexed as one, and choosing between two sets costs more
+// instructions than the waits (83 in all, 270 ns).  GROUPS_HI: more than 64 groups (t_blk > 4096).
 constexpr int kRfRegisterRows = 32;
 typedef int32_t rf_rows __attribute__((ext_vector_type(kRfRegisterRows)));
 

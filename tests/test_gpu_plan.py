@@ -39,6 +39,31 @@ def test_plan_random_sizes_of_several_jump_tiles(case):
     assert_plan_equal(gpu_plan(L, T, seed), oracle.plan(L, T, oracle.order(n, seed)), n)
 
 
+# From 40 jump tiles of 8192 on a tile reaches its entry over the exits of groups of
+# 8 tiles: both sides of that line, a last group of one position, blocks that pass over whole tiles and
+# whole groups, blocks of one sequence, and both sides of 2^20, where the order kernel changes.
+@pytest.mark.parametrize("n,T,kind", [(39 * 8192, 64, "mixed"), (39 * 8192 + 1, 64, "mixed"), (40 * 8192 + 1, 600, "short"),
+                                      (48 * 8192 + 1, 20000, "short"), (600000, 200000, "short"), (600000, 70000, "short"),
+                                      (400000, 1, "uniform"), (400001, 3, "long"), (1 << 20, 300, "uniform"),
+                                      ((1 << 20) + 1, 300, "short"), (3000000, 4096, "mixed")])
+def test_plan_entries_over_groups_of_tiles(n, T, kind):
+    rng = np.random.default_rng(n + T)
+    L = workloads.random_lengths(rng, n, T, kind)
+    print(f"plan n={n} T={T} kind={kind}", flush=True)
+    assert_plan_equal(gpu_plan(L, T, 5), oracle.plan(L, T, oracle.order(n, 5)), n)
+
+
+def test_plan_refuses_bad_lengths_of_many_tiles():
+    bl = binding()
+    rng = np.random.default_rng(3)
+    for bad in (0, -5, 301, 2 ** 31 - 1, -2 ** 31):
+        L = workloads.random_lengths(rng, 400000, 300, "uniform")
+        L[rng.integers(0, L.size, size=500)] = bad
+        with pytest.raises(bl.BloadError) as e:
+            gpu_plan(L, 300, 1)
+        assert e.value.status == bl.ELENGTH
+
+
 @pytest.mark.parametrize("wid", [1, 2, 3, 4, 5])
 def test_plan_workloads_full_size(wid):
     w = workloads.WORKLOADS[wid]
