@@ -623,6 +623,19 @@ __device__ __forceinline__ void narrow_general_tile(const PackArgs& a, const Run
         int32_t j = w - slot * k;
         RunCursor<kNarrowMaxRuns> cur(tab, n, slot);
         const int nvalid = min(EPV, tile_elems - w);
+        if (EPV > 1 && 2 * k >= EPV && nvalid == EPV) {
+            // most vectors lie inside one run: 16 contiguous source bytes, at any alignment, instead of
+            // one load per element (frames of 9 bytes 115 -> 91 us for 0.31 GB).  Not for frames under 8 bytes,
+            // where nearly every wave has a vector that crosses a border and would do both (2-byte
+            // frames of 120-slot sequences: 199 -> 297 us).
+            const int32_t t = cur.seek(slot);
+            if (t >= 0 && w + EPV <= cur.end * k) {
+                const E* from = src + (cur.src + t) * k + j;
+                store_stream(reinterpret_cast<vec16*>(dst_tile) + v,
+                             __builtin_nontemporal_load(reinterpret_cast<const vec16_unaligned*>(from)));
+                continue;
+            }
+        }
         Assembled<E> u;
 #pragma unroll
         for (int e = 0; e < EPV; ++e) {
