@@ -276,3 +276,24 @@ def test_reduce_follows_the_flags(B, T, D, dtype, op):
                                    (3000, 140, 17), (800, 300, 65), (60, 300, 271), (30, 70, 1025), (20, 40, 2061)])
 def test_reduce_staged_edges(B, T, D, dtype, op):
     test_reduce_follows_the_flags(B, T, D, dtype, op)
+
+
+# A sequence over many chunks is put together from its pieces eight at a time behind the second: every number of
+# pieces around those borders (chunks of 64 slots), the last chunk of a tensor among them, with shorter
+# sequences in between; sums of whole numbers, so that every order and grouping must give the same bits.
+@pytest.mark.parametrize("dtype", ["i32", "f32"])
+@pytest.mark.parametrize("T", [64, 65, 128, 129, 192, 640, 641, 704, 1152, 1153, 1217, 4696])
+def test_reduce_stitches_any_number_of_pieces(T, dtype):
+    bl = binding()
+    rng = np.random.default_rng(T)
+    for L, D in [([T], 347), ([T, 1, T - 1, T // 2, T - T // 2, T], 64), ([T, T], 1)]:
+        L = np.array(L, dtype=np.int32)
+        so = workloads.src_offsets(L)
+        src = rng.integers(-1000, 1000, size=(int(so[-1]), D)).astype(NP_OF[dtype])
+        pl = oracle.plan(L, T, np.arange(len(L), dtype=np.int32))
+        packed, seq_id, frame_idx, reset, valid = oracle.pack(src, so, L, pl, D * 4)
+        print(f"stitch T={T} D={D} {dtype} n={len(L)}", flush=True)
+        out = bl.bload_segment_reduce(to_dev(packed), to_dev(seq_id), to_dev(reset), to_dev(valid),
+                                      pl.num_blocks, T, D, dtype, "sum", len(L)).cpu().numpy()
+        want = np.add.reduceat(src.astype(np.int64), so[:-1], axis=0)
+        assert np.array_equal(out.astype(np.int64), want)
