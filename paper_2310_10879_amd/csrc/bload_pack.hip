@@ -507,19 +507,20 @@ __device__ __forceinline__ void narrow_uniform_table(const PackArgs& a, int64_t 
 }
 
 // The payload of such a tile: per step one 16-byte vector per lane.
-__device__ __forceinline__ void narrow_uniform_payload(const PackArgs& a, int64_t g0, const Run* r)
+__device__ __forceinline__ void narrow_uniform_payload(const PackArgs& a, int64_t g0, const Run* r,
+                                                       int32_t part, int32_t parts)
 {
-    const int tid = (int)threadIdx.x;
+    const int first = part * kThreads + (int)threadIdx.x, step = parts * kThreads;
     const int64_t F = a.frame_bytes;
     vec16* dst = reinterpret_cast<vec16*>(a.packed + g0 * F);      // 16-byte aligned: g0 is a multiple of 1024
     const int32_t nvec = (int32_t)(kNarrowSlots * F / 16);
     if (r) {
         const uint8_t* from = a.src + (r->src + (g0 - r->dst)) * F;
-        for (int32_t v = tid; v < nvec; v += kThreads)
+        for (int32_t v = first; v < nvec; v += step)
             store_stream(dst + v, __builtin_nontemporal_load(reinterpret_cast<const vec16_unaligned*>(from) + v));
     } else {
         const vec16 z = {0u, 0u, 0u, 0u};
-        for (int32_t v = tid; v < nvec; v += kThreads) store_stream(dst + v, z);
+        for (int32_t v = first; v < nvec; v += step) store_stream(dst + v, z);
     }
 }
 
@@ -550,14 +551,15 @@ struct Assembled<vec16> {
 template <typename E, bool FUSED, bool PAYLOAD, bool TABLE>
 __device__ __forceinline__ void narrow_general_tile(const PackArgs& a, const Run* __restrict__ runs,
                                                     RunTable<kNarrowMaxRuns>& tab, int64_t g0, int64_t g1,
-                                                    int32_t first, int32_t last)
+                                                    int32_t first, int32_t last, int32_t part, int32_t parts,
+                                                    int32_t long_runs)
 {
     const int tid = (int)threadIdx.x;
     const int nslot = (int)(g1 - g0);
     const int n = gather_runs(runs, a.n_seq, first, last, g0, g1, tab);
 
     // start table (and, FUSED, the payload): 4 consecutive slots per lane -> 16-byte / 4-byte stores
-    for (int q = tid; (TABLE || FUSED) && 4 * q < nslot; q += kThreads) {
+    for (int q = tid; (TABLE || FUSED) && part == 0 && 4 * q < nslot; q += kThreads) {
         const int32_t s0 = 4 * q;
         RunCursor<kNarrowMaxRuns> cur(tab, n, s0);
         int32_t sid[4], fid[4];
@@ -617,22 +619,28 @@ __device__ __forceinline__ void narrow_general_tile(const PackArgs& a, const Run
     const int32_t nvec = (tile_elems + EPV - 1) / EPV;
     const E* src = reinterpret_cast<const E*>(a.src);
     uint8_t* dst_tile = a.packed + g0 * a.frame_bytes;          // 16-byte aligned
-    for (int32_t v = (FUSED ? done_slots / 4 : 0) + tid; v < nvec; v += kThreads) {
+    for (int32_t v = (FUSED ? done_slots / 4 : 0) + part * kThreads + tid; v < nvec; v += parts * kThreads) {
         const int32_t w = v * EPV;
         int32_t slot = w / k;
         int32_t j = w - slot * k;
         RunCursor<kNarrowMaxRuns> cur(tab, n, slot);
         const int nvalid = min(EPV, tile_elems - w);
-        if (EPV > 1 && 2 * k >= EPV && nvalid == EPV) {
-            // most vectors lie inside one run: 16 contiguous source bytes, at any alignment, instead of
-            // one load per element (frames of 9 bytes 115 -> 91 us for 0.31 GB).  Not for frames under 8 bytes,
-            // where nearly every wave has a vector that crosses a border and would do both (2-byte
-            // frames of 120-slot sequences: 199 -> 297 us).
+        if (EPV > 1 && !FUSED && long_runs) {
+            // where every vector of the wave lies inside one run or one stretch of padding: 16 contiguous
+            // source bytes, at any alignment, instead of one load per element (9-byte frames of 500-slot
+            // sequences 1.13 -> 0.79 ms for 1.4 GB, 62-byte frames of 75-slot sequences 1.67 -> 1.09 ms, 56
+            // bytes 1.01 -> 0.97).  By the whole wave only, and only where runs are several waves long (the
+            // host's rule): a wave with a vector across a border does both (60-byte frames of 27-slot
+            // sequences 70 -> 90 us, 20-byte frames of 75 slots 91 -> 104).  A plain load, as the elements':
+            // a streaming one loses to them where the source is in the memory-side cache (60-byte frames,
+            // 0.2 GB: 84 us by elements, 111 streaming, 86 plain).
             const int32_t t = cur.seek(slot);
-            if (t >= 0 && w + EPV <= cur.end * k) {
-                const E* from = src + (cur.src + t) * k + j;
-                store_stream(reinterpret_cast<vec16*>(dst_tile) + v,
-                             __builtin_nontemporal_load(reinterpret_cast<const vec16_unaligned*>(from)));
+            const bool inside = nvalid == EPV && w + EPV <= (t >= 0 ? cur.end : min(cur.next, nslot)) * k;
+            if (__ballot(!inside) == 0) {
+                vec16 x = {0u, 0u, 0u, 0u};
+                if (t >= 0)
+                    x = *reinterpret_cast<const vec16_unaligned*>(src + (cur.src + t) * k + j);
+                store_stream(reinterpret_cast<vec16*>(dst_tile) + v, x);
                 continue;
             }
         }
@@ -676,13 +684,17 @@ __device__ __forceinline__ void narrow_general_tile(const PackArgs& a, const Run
 template <typename E, bool FUSED, bool PAYLOAD = true, bool TABLE = true, int GROUP = 1>
 __global__ __launch_bounds__(kThreads) void pack_narrow_kernel(PackArgs a, const Run* __restrict__ runs,
                                                                const int32_t* __restrict__ first_pos,
-                                                               uint32_t n_tiles)
+                                                               uint32_t n_tiles, int32_t parts, int32_t long_runs)
 {
     static_assert(PAYLOAD || !FUSED, "the fused form is about the payload");
     static_assert(PAYLOAD || TABLE, "a pass writes something");
     __shared__ RunTable<kNarrowMaxRuns> tab;
     const int tid = (int)threadIdx.x;
-    const uint32_t tile0 = xcd_contiguous(blockIdx.x, gridDim.x) * (uint32_t)GROUP;
+    constexpr bool kSplit = PAYLOAD && TABLE && !FUSED && GROUP == 1;     // else parts is 1
+    const uint32_t unit = xcd_contiguous(blockIdx.x, gridDim.x);
+    const uint32_t tile0 = !kSplit ? unit * (uint32_t)GROUP : parts == 1 ? unit : unit / (uint32_t)parts;
+    const int32_t part = kSplit ? (int32_t)(unit - tile0 * (uint32_t)parts) : 0;
+    if (!kSplit) parts = 1;
 
     // entry[u]: where tile tile0 + u starts in the run table; behind the last tile: the last run
     int32_t entry[GROUP + 1];
@@ -740,11 +752,11 @@ __global__ __launch_bounds__(kThreads) void pack_narrow_kernel(PackArgs a, const
 #pragma unroll
         for (int u = 0; u < GROUP; ++u) {
             const int64_t g0 = (int64_t)(tile0 + (uint32_t)u) * kNarrowSlots;
-            if (kind[u] == kTileOneRun) narrow_uniform_payload(a, g0, &r[u]);
-            else if (kind[u] == kTilePadding) narrow_uniform_payload(a, g0, nullptr);
+            if (kind[u] == kTileOneRun) narrow_uniform_payload(a, g0, &r[u], part, parts);
+            else if (kind[u] == kTilePadding) narrow_uniform_payload(a, g0, nullptr, part, parts);
         }
     }
-    if (TABLE) {
+    if (TABLE && part == 0) {
 #pragma unroll
         for (int u = 0; u < GROUP; ++u) {
             const int64_t g0 = (int64_t)(tile0 + (uint32_t)u) * kNarrowSlots;
@@ -760,7 +772,7 @@ __global__ __launch_bounds__(kThreads) void pack_narrow_kernel(PackArgs a, const
         const int64_t g0 = (int64_t)(tile0 + (uint32_t)u) * kNarrowSlots;
         if (table_in_use) __syncthreads();           // the tile before is done with the gathered runs
         narrow_general_tile<E, FUSED, PAYLOAD, TABLE>(a, runs, tab, g0, min(g0 + kNarrowSlots, a.total_slots),
-                                                      entry[u], entry[u + 1]);
+                                                      entry[u], entry[u + 1], part, parts, long_runs);
         table_in_use = true;
     }
 }
@@ -947,15 +959,15 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
                        dim3(kThreads), 0, stream, d_src_offsets, d_lengths, d_order, d_block_of_seq,
                        d_offset_of_seq, d_block_first, (int32_t)n_seq, num_blocks, (int64_t)t_blk, unit_bytes,
                        l.tiles, tile_units, inv_unit, inv_t, runs, first_pos, l.table_tiles, first_pos_table);
-    const dim3 grid((uint32_t)l.tiles), block(kThreads);
+    const dim3 block(kThreads);
     const uint32_t n_tiles = (uint32_t)l.tiles;
     if (l.wide) {
-        hipLaunchKernelGGL(pack_wide_kernel, grid, block, 0, stream, a, runs, first_pos, kWideTile, inv_unit,
+        hipLaunchKernelGGL(pack_wide_kernel, dim3(n_tiles), block, 0, stream, a, runs, first_pos, kWideTile, inv_unit,
                            l.table_tiles == 0 ? 1 : 0);
         if (l.table_tiles > 0)
             hipLaunchKernelGGL((pack_narrow_kernel<uint8_t, false, false, true, kPassGroup>),
                                dim3((uint32_t)ceil_div(l.table_tiles, kPassGroup)), block, 0, stream, a, runs,
-                               first_pos_table, (uint32_t)l.table_tiles);
+                               first_pos_table, (uint32_t)l.table_tiles, 1, 0);
         return launch_status();
     }
     // slot tiles: one pass; 4-byte frames (whose payload and table share a loop, so that one kernel writes
@@ -963,24 +975,34 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
     // each over the same tiles.  Measured on 1.3 * 10^9 token slots: 3.98 -> 3.72 ms; frames of 6 and 8
     // bytes, whose one pass already writes the table first and the payload after it, lose 5-7 % to the
     // second pass's look-ups and keep the one pass.
+    // A tile is 1024 frames, one workgroup's work: where that leaves compute units idle, several workgroups share
+    // a tile, towards 1024 of them, or 4096 from 64 bytes on, where a tile is 64 KiB and more; never more than
+    // one per vector of a lane.  Short sequences, before and after: 8 tiles of 62 bytes 37 -> 12 us, 59 tiles
+    // of 104 bytes 38 -> 12, 211 of 68 bytes 26 -> 15, 211 of 400 bytes 89 -> 35, 1055 of 128 bytes 50 -> 52.
+    // Towards 2048 under 64 bytes: 1055 tiles of 10 bytes 19 -> 21 us, of 48 bytes 25 -> 29.
+    const int64_t vectors = ceil_div(frame_bytes, 4);               // 1024 slots / 256 lanes / 16 bytes
+    const int64_t wanted = ceil_div(frame_bytes < 64 ? 1024 : 4096, l.tiles);
+    const int32_t parts = (int32_t)(frame_bytes == 4 && aligned_to(d_src, 4) ? 1 : wanted < vectors ? wanted : vectors);
+    const int32_t long_runs = a.total_slots * frame_bytes / n_seq >= 4096;        // four waves of vectors per run
+    const dim3 grid((uint32_t)(l.tiles * parts));
     if (frame_bytes % 16 == 0 && aligned_to(d_src, 16)) {
-        hipLaunchKernelGGL((pack_narrow_kernel<vec16, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles);
+        hipLaunchKernelGGL((pack_narrow_kernel<vec16, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts, long_runs);
     } else if (frame_bytes == 4 && aligned_to(d_src, 4)) {
         if (a.total_slots >= kTablePassFromSlots) {
             const dim3 groups((uint32_t)ceil_div(l.tiles, kPassGroup));
             hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, true, true, false, kPassGroup>), groups, block, 0, stream,
-                               a, runs, first_pos, n_tiles);
+                               a, runs, first_pos, n_tiles, parts, long_runs);
             hipLaunchKernelGGL((pack_narrow_kernel<uint8_t, false, false, true, kPassGroup>), groups, block, 0, stream,
-                               a, runs, first_pos, n_tiles);
+                               a, runs, first_pos, n_tiles, parts, long_runs);
         } else {
-            hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, true>), grid, block, 0, stream, a, runs, first_pos, n_tiles);
+            hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, true>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts, long_runs);
         }
     } else if (frame_bytes % 4 == 0 && aligned_to(d_src, 4)) {
-        hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles);
+        hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts, long_runs);
     } else if (frame_bytes % 2 == 0 && aligned_to(d_src, 2)) {
-        hipLaunchKernelGGL((pack_narrow_kernel<uint16_t, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles);
+        hipLaunchKernelGGL((pack_narrow_kernel<uint16_t, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts, long_runs);
     } else {
-        hipLaunchKernelGGL((pack_narrow_kernel<uint8_t, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles);
+        hipLaunchKernelGGL((pack_narrow_kernel<uint8_t, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts, long_runs);
     }
     return launch_status();
 }

@@ -64,6 +64,28 @@ def test_pack_middle_frames_take_either_tile_shape(F):
         assert_packed_equal(out, ref, f"F={F} n={n} T={T}: ")
 
 
+@pytest.mark.parametrize("F", [5, 8, 9, 10, 20, 36, 48, 56, 68, 128, 400, 511])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_pack_slot_tiles_vectors_inside_and_across_runs(F, shift):
+    """Slot tiles: where runs are long, a wave whose 16-byte vectors lie inside runs loads them whole and any other
+    puts them together from elements; few tiles are shared by several workgroups.  Every alignment of a run's
+    start against the vectors, runs shorter than a vector and many long, one tile and hundreds, padding
+    behind the runs, and a source that ends with its last run; bytes must be equal."""
+    for n, T, lo, hi in [(3000, 61, 1, 3), (700, 257, 1, 40), (40, 1999, 300, 1999), (30, 3000, 1600, 1900),
+                         (20000, 27, 20, 27), (1, 7, 7, 7)]:
+        rng = np.random.default_rng(F * 17 + n)
+        L = rng.integers(lo, hi + 1, size=n).astype(np.int32)
+        so = workloads.src_offsets(L)
+        src = np.ascontiguousarray(workloads.tagged_source(L, F)).view(np.uint8).reshape(-1)
+        ref_plan = oracle.plan(L, T, oracle.order(n, 3))
+        ref = oracle.pack(src.reshape(-1, F), so, L, ref_plan, F)
+        print(f"pack slot tiles F={F} n={n} T={T} shift={shift}", flush=True)
+        base = to_dev(np.concatenate([np.zeros(shift, np.uint8), src]))[shift:]
+        out = binding().bload_pack(base, to_dev(so), to_dev(L), upload_plan(ref_plan, n), F)
+        torch.cuda.synchronize()
+        assert_packed_equal(out, ref, f"F={F} n={n} T={T}: ")
+
+
 def test_pack_degenerate_blocks():
     # every block full, every block one frame, blocks of unit sequences
     for n, T, L in [(50, 8, np.full(50, 8)), (50, 8, np.ones(50)), (50, 8, np.full(50, 5)),
