@@ -1199,7 +1199,9 @@ struct ReducePlan {
 
 static int elem_size(bload_dtype dtype) { return dtype == BLOAD_U8 ? 1 : dtype == BLOAD_F16 ? 2 : 4; }
 
-static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, bload_dtype dtype)
+// `one_element`: lanes of one element, for frames that are no whole 16-byte vectors and leave the choice
+// open (takes_one_element below).
+static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, bload_dtype dtype, bool one_element)
 {
     ReducePlan p{};
     const int es = elem_size(dtype);
@@ -1207,9 +1209,17 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
     const size_t acc = dtype == BLOAD_I32 ? 8 : 4;
     p.wide = frame_bytes >= 64;
     // Lanes of 16 bytes, unless that leaves fewer than two workgroups per compute unit (four where the
-    // vectors are not aligned) or many lanes of a row idle: then lanes of 4 bytes, then of one element, which spread a frame over more waves (15
-    // blocks of 830 slots x 342 bytes: 23 us with 16 bytes a lane, 14 with one; 78 slots x 271 int32,
-    // whose rows of 16-byte lanes are half idle: 160 and 143 us).
+    // vectors are not aligned): then lanes of 4 bytes, then of one element, which spread a frame over
+    // more waves (15 blocks of 830 slots x 342 bytes: 23 us with 16 bytes a lane, 14 with one).
+    // Frames that are no whole vectors also take the narrower lanes where
+    //   - a row would be 16 lanes or fewer (up to 256 bytes): four rows and more to a wave wait for each
+    //     other's pieces, and no vector is aligned (2 GB, sequences of 1550 frames, 16 / 4 bytes a lane:
+    //     132 bytes of halfs 611 / 416 us, 140 of bytes 650 / 425; of 24 frames, 1 GB: 115 bytes 577 / 385)
+    //   - a frame is some waves of vectors and a bit, a third of the lanes idle (1028 bytes of floats in
+    //     pieces of 24 frames, 1 GB: 300 us, 240 with one a lane; of halfs 350, 262 with 4 bytes); a row
+    //     of 32 or 64 lanes in one wave keeps the vectors, half idle or not (260 bytes of floats: 266 us,
+    //     342 with one a lane)
+    // Whole vectors stay 16 bytes a lane whatever is idle (272 bytes, 2.5 GB: 484 us, one float a lane 722).
     const int widths[3] = {16, 4, es};
     for (int w = 0; p.wide && w < 3; ++w) {
         p.vec = widths[w] / es;
@@ -1252,8 +1262,10 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
         // 2900 blocks of 245 slots x 64 bytes: 90 -> 48 us); with enough of them the rows read better
         // (2.5-4.9 TB/s against 2.0-2.8).
         if (feat_dim < kStagedFrame && groups < 512) p.wide = false;
-        const bool half_idle = p.n_vec * 5 < (feat_tiles << p.row_lanes_log2) * 3;
-        if (groups >= (frame_bytes % 16 == 0 ? 512 : 1024) && !(w == 0 && half_idle && es == 4)) break;
+        const bool whole = frame_bytes % 16 == 0;
+        const bool suits = w > 0 || whole ||
+                           (frame_bytes > 256 && (feat_tiles == 1 || p.n_vec * 3 >= (feat_tiles << p.row_lanes_log2) * 2));
+        if (groups >= (whole ? 512 : 1024) && suits && !one_element) break;
     }
     if (!p.wide) {
         p.staged = feat_dim > 1;
@@ -1289,6 +1301,28 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
         p.bytes = off;
     }
     return p;
+}
+
+// Frames that are no whole vectors: does the number of rows of the result decide for lanes of one element?
+// What suits them hangs on the length of the pieces as well, of which the slots per row are the guess at hand
+// (too short for a worker's share, whose rows are those of all workers: either width gives the same sums).
+//   - floats and int32 over more than one wave, pieces of a few frames (24 frames: 1.3-8 KB a frame up to
+//     12 % slower with 16-byte lanes, 1550 frames: 2-30 % faster; equal at 53 frames and four fifths of the
+//     lanes at work), unless blocks are short (34 slots x 5012 bytes: 40 us, one float a lane 49)
+//   - bytes and halfs of which a row of 4-byte lanes holds few, none of them at a whole word, long
+//     pieces (2 GB, 1550 frames: 101 bytes 670 us, 4 bytes a lane 770; 0.8 GB, 32 frames: 447 and 266)
+static bool leaves_choice(int64_t feat_dim, int es)
+{
+    const int64_t frame_bytes = feat_dim * es;
+    if (frame_bytes < 64 || feat_dim < 33 || frame_bytes % 16 == 0) return false;
+    return es == 4 ? frame_bytes > 16 * kWave : frame_bytes % 4 != 0 && feat_dim < (es == 1 ? 128 : 96);
+}
+
+static bool takes_one_element(int64_t slots, int32_t t_blk, int64_t n_seq, int64_t feat_dim, int es)
+{
+    if (!leaves_choice(feat_dim, es)) return false;
+    const int64_t mean = slots / n_seq, vectors = ceil_div(feat_dim * es, 16);
+    return es == 4 ? t_blk >= 128 && mean * vectors < 40 * (int64_t)round_up((size_t)vectors, kWave) : mean >= 512;
 }
 
 template <typename ElemT, int VEC, bool STREAM>
@@ -1344,7 +1378,9 @@ extern "C" size_t bload_segment_reduce_workspace_bytes(int64_t num_blocks, int32
                                                        int64_t feat_dim, bload_dtype dtype)
 {
     if (num_blocks <= 0 || t_blk < 1 || feat_dim < 1 || (int)dtype < 0 || (int)dtype > 3) return 0;
-    return reduce_plan(num_blocks, t_blk, feat_dim, dtype).bytes;
+    const size_t bytes = reduce_plan(num_blocks, t_blk, feat_dim, dtype, false).bytes;
+    if (!leaves_choice(feat_dim, elem_size(dtype))) return bytes;
+    return std::max(bytes, reduce_plan(num_blocks, t_blk, feat_dim, dtype, true).bytes);
 }
 
 extern "C" bload_status bload_segment_reduce(const void* d_packed, const int32_t* d_seq_id,
@@ -1366,7 +1402,8 @@ extern "C" bload_status bload_segment_reduce(const void* d_packed, const int32_t
         !aligned_to(d_valid, 16) || !aligned_to(d_out, 8))
         return BLOAD_EALIGN;
 
-    const ReducePlan p = reduce_plan(num_blocks, t_blk, feat_dim, dtype);
+    const ReducePlan p = reduce_plan(num_blocks, t_blk, feat_dim, dtype,
+                                     takes_one_element(total_slots, t_blk, n_seq, feat_dim, elem_size(dtype)));
     if (p.total_chunks * ceil_div(feat_dim, kThreads) > INT32_MAX) return BLOAD_EOVERFLOW;
     if (p.wide && ceil_div(p.total_chunks, kThreads >> p.row_lanes_log2) *
                       ceil_div(p.n_vec, 1 << p.row_lanes_log2) > INT32_MAX)

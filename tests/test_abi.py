@@ -72,6 +72,23 @@ def test_workspace_queries(lib):
     assert f(0, 600, 8, 0) == 0 and f(5, 0, 8, 0) == 0 and f(5, 8, 8, 7) == 0
 
 
+def reduce_query(lib):
+    f = lib.bload_segment_reduce_workspace_bytes
+    f.restype = ctypes.c_size_t
+    f.argtypes = [ctypes.c_int64, ctypes.c_int32, ctypes.c_int64, ctypes.c_int]
+    return f
+
+
+@pytest.mark.parametrize("dtype", [2, 3])
+@pytest.mark.parametrize("D", [68, 72, 76])
+def test_reduce_reads_whole_vectors_whatever_lanes_idle(lib, D, dtype):
+    """Frames of 17 to 19 vectors leave 15 to 13 of a row's 32 lanes idle and still go 16 bytes a lane: eight rows to a
+    workgroup, for which 3000 blocks are cut in three (lanes of one element, two slices of a wave each,
+    would take the blocks whole and need no workspace)."""
+    chunks, acc = 3000 * 3, 8 if dtype == 3 else 4
+    assert reduce_query(lib)(3000, 3000, D, dtype) == chunks * 16 + 2 * chunks * D * acc
+
+
 def test_argument_checks_need_no_gpu(lib):
     # every call below must be refused on the host, before any HIP call
     vp, i64, i32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32

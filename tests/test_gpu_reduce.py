@@ -297,3 +297,32 @@ def test_reduce_stitches_any_number_of_pieces(T, dtype):
                                       pl.num_blocks, T, D, dtype, "sum", len(L)).cpu().numpy()
         want = np.add.reduceat(src.astype(np.int64), so[:-1], axis=0)
         assert np.array_equal(out.astype(np.int64), want)
+
+
+# Frames that are no whole 16-byte vectors choose their lane width by bytes, idle lanes and slots per row of the
+# result: each width on both sides of each line (rows of 16 lanes and of 17, a frame a vector over one and two
+# waves, a third of the lanes idle and less, short and long pieces), with room asked for by the query.
+@pytest.mark.parametrize("dtype,op", [("f32", "mean"), ("i32", "sum"), ("u8", "mean"), ("f16", "sum")])
+@pytest.mark.parametrize("B,T,frame_bytes,n_rows", [(2100, 64, 252, 0), (2100, 64, 260, 0), (600, 130, 1028, 0),
+                                                    (600, 130, 1364, 0), (600, 130, 1364, 10000), (600, 130, 1372, 0),
+                                                    (500, 520, 66, 0), (500, 520, 66, 2), (300, 700, 126, 1)])
+def test_reduce_lane_widths(B, T, frame_bytes, n_rows, dtype, op):
+    """n_rows: more rows than segments, or so few that the pieces are taken for long ones."""
+    bl = binding()
+    D = frame_bytes // bl.ELEM_BYTES[dtype] + (1 if dtype == "u8" else 0)
+    rng = np.random.default_rng(B + T + D)
+    valid, reset, seq_id, n_seg = random_flags(rng, B, T, 0.97, 0.02 if n_rows not in (1, 2) else 0.0)
+    src = draw_source(rng, B * T, D, dtype)
+    want, _ = oracle.segment_reduce_packed(src.reshape(B, T, D), seq_id, reset, valid, D, dtype, op, n_seg)
+    n = n_rows or n_seg
+    print(f"widths B={B} T={T} D={D} {dtype} {op} rows {n} of {n_seg}", flush=True)
+    got = bl.bload_segment_reduce(to_dev(src), to_dev(seq_id), to_dev(reset), to_dev(valid), B, T, D, dtype, op, n).cpu().numpy()
+    m = min(n, n_seg)
+    if dtype == "i32":
+        assert np.array_equal(got[:m], want[:m])
+        return
+    absval = np.abs(src.astype(np.float64)).astype(np.float32).reshape(B, T, D)
+    scale, _ = oracle.segment_reduce_packed(absval, seq_id, reset, valid, D, "f32", op, n_seg)
+    bound = REL_TOL * np.maximum(np.abs(want.astype(np.float64)), scale.astype(np.float64)) + 1e-30
+    assert np.all(np.abs(got[:m].astype(np.float64) - want[:m].astype(np.float64)) <= bound[:m])
+    assert not got[m:].any()
