@@ -196,7 +196,7 @@ template <int ITEMS>
 __global__ __launch_bounds__(kThreads) void plan_order_kernel(
     const int32_t* __restrict__ lengths, int32_t n_seq, int32_t t_blk, OrderKey key,
     int32_t* __restrict__ order, int32_t* __restrict__ shuffled_len,
-    int64_t* __restrict__ tile_sum, int32_t* __restrict__ tile_bad)
+    int64_t* __restrict__ sums, int32_t* __restrict__ bads)
 {
     const int64_t base = (int64_t)blockIdx.x * (kThreads * ITEMS) + (int64_t)threadIdx.x * ITEMS;
     int64_t sum = 0;
@@ -217,17 +217,25 @@ __global__ __launch_bounds__(kThreads) void plan_order_kernel(
     int64_t total;
     block_exclusive_scan<int64_t>(sum, 0, SumI64(), &total);
     bad = __syncthreads_or(bad);
-    if (threadIdx.x == 0) { tile_sum[blockIdx.x] = total; tile_bad[blockIdx.x] = bad; }
+    if (threadIdx.x == 0) { sums[blockIdx.x] = total; bads[blockIdx.x] = bad; }
 }
 
 // P[p] = frames before shuffled position p; P[n_seq] = total.  Every tile adds up the sums
-// in front of it by itself (`sums_per_tile` of them to a tile).
+// in front of it by itself (`sums_per_tile` of the `n_sums` to a tile), and keeps whether a length of its own
+// is out of range.
 __global__ __launch_bounds__(kThreads) void plan_prefix_kernel(
-    const int32_t* __restrict__ shuffled_len, int32_t n_seq, const int64_t* __restrict__ tile_sum,
-    int32_t sums_per_tile, int64_t* __restrict__ prefix)
+    const int32_t* __restrict__ shuffled_len, int32_t n_seq, const int64_t* __restrict__ sums,
+    const int32_t* __restrict__ bads, int32_t n_sums, int32_t sums_per_tile, int64_t* __restrict__ prefix,
+    int32_t* __restrict__ tile_bad)
 {
+    const int32_t first_sum = (int32_t)blockIdx.x * sums_per_tile;
+    if (wave_id() == 0) {
+        const int32_t t = first_sum + lane_id();
+        const uint64_t bad = __ballot(lane_id() < sums_per_tile && t < n_sums && bads[t] != 0);
+        if (lane_id() == 0) tile_bad[blockIdx.x] = bad != 0;
+    }
     int64_t mine = 0;
-    for (int32_t t = (int32_t)threadIdx.x; t < (int32_t)blockIdx.x * sums_per_tile; t += kThreads) mine += tile_sum[t];
+    for (int32_t t = (int32_t)threadIdx.x; t < first_sum; t += kThreads) mine += sums[t];
     int64_t before;
     block_exclusive_scan<int64_t>(mine, 0, SumI64(), &before);
 
@@ -453,7 +461,7 @@ __global__ __launch_bounds__(kJumpThreads) void plan_mark_kernel(
 __global__ __launch_bounds__(kThreads) void plan_assign_kernel(
     const uint8_t* __restrict__ mark, const int32_t* __restrict__ order,
     const int64_t* __restrict__ prefix, int32_t n_seq, const int32_t* __restrict__ tile_cnt,
-    const int32_t* __restrict__ tile_head, const int32_t* __restrict__ tile_bad, int32_t n_bad,
+    const int32_t* __restrict__ tile_head, const int32_t* __restrict__ tile_bad,
     int32_t* __restrict__ block_of_seq, int32_t* __restrict__ offset_of_seq,
     int32_t* __restrict__ block_first, PlanResult* __restrict__ result)
 {
@@ -462,9 +470,10 @@ __global__ __launch_bounds__(kThreads) void plan_assign_kernel(
     HeadPair mine{0, -1};
     int bad = 0;
     const bool last_tile = blockIdx.x == gridDim.x - 1;
-    for (int32_t t = (int32_t)threadIdx.x; t < (int32_t)blockIdx.x; t += kThreads)
-        mine = HeadOp()(mine, HeadPair{tile_cnt[t], tile_head[t]});
-    for (int32_t t = (int32_t)threadIdx.x; last_tile && t < n_bad; t += kThreads) bad |= tile_bad[t];
+    for (int32_t t = (int32_t)threadIdx.x; t < (int32_t)gridDim.x; t += kThreads) {
+        if (t < (int32_t)blockIdx.x) mine = HeadOp()(mine, HeadPair{tile_cnt[t], tile_head[t]});
+        if (last_tile) bad |= tile_bad[t];
+    }
     HeadPair before;
     block_exclusive_scan<HeadPair>(mine, HeadPair{0, -1}, HeadOp(), &before);
     if (last_tile) bad = __syncthreads_or(bad);
@@ -587,8 +596,8 @@ __global__ __launch_bounds__(kThreads) void plan_small_kernel(
 
 // Workspace layout (every part 16-byte aligned).
 struct PlanLayout {
-    size_t result, shuffled_len, prefix, next, exit_of, mark, tile_sum, tile_cnt, tile_head, tile_entry,
-        tile_bad, bytes;
+    size_t result, shuffled_len, prefix, next, exit_of, mark, tile_cnt, tile_head, tile_entry, tile_bad, bytes;
+    size_t sums, bads;         // of the order kernel's workgroups: in the bytes of exit_of, which is written after their use
     int32_t n_tiles;           // scan tiles
     int32_t sums_per_tile;     // workgroups of the order kernel to a scan tile
     int32_t n_sums;
@@ -611,12 +620,14 @@ static PlanLayout plan_layout(int64_t n_seq)
     l.next = take(n * 4);
     l.exit_of = take(n * 4);
     l.mark = take(n);
-    l.tile_sum = take((size_t)l.n_sums * 8);
     l.tile_cnt = take((size_t)l.n_tiles * 4);
     l.tile_head = take((size_t)l.n_tiles * 4);
     l.tile_entry = take((size_t)l.n_jump_tiles * 4);
-    l.tile_bad = take((size_t)l.n_sums * 4);
+    l.tile_bad = take((size_t)l.n_tiles * 4);
     l.bytes = off;
+    // (12 bytes per 256 positions and a rest, beyond 2048 positions of 4 bytes: they fit)
+    l.sums = l.exit_of;
+    l.bads = l.exit_of + (size_t)l.n_sums * 8;
     return l;
 }
 
@@ -663,7 +674,8 @@ extern "C" bload_status bload_plan(const int32_t* d_lengths, int64_t n_seq, int3
     int32_t* next = reinterpret_cast<int32_t*>(ws + l.next);
     int32_t* exit_of = reinterpret_cast<int32_t*>(ws + l.exit_of);
     uint8_t* mark = ws + l.mark;
-    int64_t* tile_sum = reinterpret_cast<int64_t*>(ws + l.tile_sum);
+    int64_t* sum_of = reinterpret_cast<int64_t*>(ws + l.sums);
+    int32_t* bad_of = reinterpret_cast<int32_t*>(ws + l.bads);
     int32_t* tile_cnt = reinterpret_cast<int32_t*>(ws + l.tile_cnt);
     int32_t* tile_head = reinterpret_cast<int32_t*>(ws + l.tile_head);
     int32_t* tile_entry = reinterpret_cast<int32_t*>(ws + l.tile_entry);
@@ -684,12 +696,12 @@ extern "C" bload_status bload_plan(const int32_t* d_lengths, int64_t n_seq, int3
         const dim3 sums((uint32_t)l.n_sums);
         if (l.sums_per_tile == 1)
             hipLaunchKernelGGL(plan_order_kernel<kItems>, sums, block, 0, stream, d_lengths, n, t_blk, key, d_order,
-                               shuffled_len, tile_sum, tile_bad);
+                               shuffled_len, sum_of, bad_of);
         else
             hipLaunchKernelGGL(plan_order_kernel<1>, sums, block, 0, stream, d_lengths, n, t_blk, key, d_order,
-                               shuffled_len, tile_sum, tile_bad);
-        hipLaunchKernelGGL(plan_prefix_kernel, tiles, block, 0, stream, shuffled_len, n, tile_sum, l.sums_per_tile,
-                           prefix);
+                               shuffled_len, sum_of, bad_of);
+        hipLaunchKernelGGL(plan_prefix_kernel, tiles, block, 0, stream, shuffled_len, n, sum_of, bad_of, l.n_sums,
+                           l.sums_per_tile, prefix, tile_bad);
         hipLaunchKernelGGL(plan_next_kernel, dim3((uint32_t)ceil_div(n_seq, kThreads)), block, 0, stream,
                            prefix, n, t_blk, next);
         // where the orbit of position 0 enters each jump tile: a single tile it enters at 0; up to
@@ -710,7 +722,7 @@ extern "C" bload_status bload_plan(const int32_t* d_lengths, int64_t n_seq, int3
                            grouped ? group_exit : nullptr, n, mark,
                            tile_cnt, tile_head);
         hipLaunchKernelGGL(plan_assign_kernel, tiles, block, 0, stream, mark, d_order, prefix, n,
-                           tile_cnt, tile_head, tile_bad, l.n_sums, d_block_of_seq, d_offset_of_seq,
+                           tile_cnt, tile_head, tile_bad, d_block_of_seq, d_offset_of_seq,
                            d_block_first, result);
     }
     if (launch_status() != BLOAD_OK) return BLOAD_EHIP;

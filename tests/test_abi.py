@@ -72,6 +72,21 @@ def test_workspace_queries(lib):
     assert f(0, 600, 8, 0) == 0 and f(5, 0, 8, 0) == 0 and f(5, 8, 8, 7) == 0
 
 
+def test_plan_workspace_never_shrinks(lib):
+    """A buffer made for the largest epoch serves every smaller one: the query rises with the number of sequences,
+    across every line at which the planner changes its kernels, and asks for no more than 21 bytes a
+    sequence and 20 per tile of 2048."""
+    w = lib.bload_plan_workspace_bytes
+    w.restype, w.argtypes = ctypes.c_size_t, [ctypes.c_int64]
+    lines = [2048, 8192, 40 * 8192, 1 << 20, 1024 * 8192, 1 << 27]
+    sizes = sorted({n + d for n in lines for d in (-4096, -257, -256, -1, 0, 1, 255, 256, 257, 2049, 4096, 70000)
+                    if 0 <= n + d <= 1 << 27} | {1 << k for k in range(28)})
+    answers = [w(n) for n in sizes]
+    assert answers == sorted(answers)
+    for n, bytes_ in zip(sizes, answers):
+        assert bytes_ <= 21 * n + 20 * -(-n // 2048) + 4 * -(-n // 8192) + 200
+
+
 def reduce_query(lib):
     f = lib.bload_segment_reduce_workspace_bytes
     f.restype = ctypes.c_size_t
