@@ -326,3 +326,25 @@ def test_reduce_lane_widths(B, T, frame_bytes, n_rows, dtype, op):
     bound = REL_TOL * np.maximum(np.abs(want.astype(np.float64)), scale.astype(np.float64)) + 1e-30
     assert np.all(np.abs(got[:m].astype(np.float64) - want[:m].astype(np.float64)) <= bound[:m])
     assert not got[m:].any()
+
+
+# A 1 in front of frames of 2^-24, half a unit in its last place: added one by one to a float32 sum that holds the 1
+# they all vanish, a unit of roundoff each.  Trees of eight lose at most three units, their sum in more than 32
+# bits none and the result one, wherever in a lane the sequence lies.  (Blocks shorter than a tile: no
+# partial sums.  Enough tiles for lanes of 17 slots, and few enough for 9.)
+@pytest.mark.parametrize("n,T,D", [(30000, 33, 7), (2000, 33, 7), (16000, 60, 32), (900, 60, 32), (12000, 40, 3), (9000, 60, 47)])
+def test_reduce_staged_lanes_lose_no_more_than_a_tree_of_eight(n, T, D):
+    bl = binding()
+    rng = np.random.default_rng(n + D)
+    L = rng.integers(1, T, size=n, endpoint=True).astype(np.int32)
+    so = workloads.src_offsets(L)
+    src = np.full((int(so[-1]), D), 2.0 ** -24, np.float32)
+    src[so[:-1]] = 1.0
+    pl = oracle.plan(L, T, oracle.order(n, 1))
+    packed, seq_id, _, reset, valid = oracle.pack(src, so, L, pl, D * 4)
+    got = bl.bload_segment_reduce(to_dev(packed), to_dev(seq_id), to_dev(reset), to_dev(valid), pl.num_blocks, T, D,
+                                  "f32", "sum", n).cpu().numpy().astype(np.float64)
+    want = 1.0 + (L - 1)[:, None] * 2.0 ** -24
+    lost = np.abs(got - want) / (U * want)
+    print(f"n={n} T={T} D={D}: {lost.max():.1f} units of roundoff", flush=True)
+    assert lost.max() <= 4
