@@ -1327,10 +1327,11 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
         p.partials = p.n_chunks > 1;
         const int64_t groups = ceil_div(p.total_chunks, rows) * feat_tiles;
         // Small frames in rows of a few lanes: a workgroup walks many chunks, and where that leaves too
-        // few workgroups the staged tiles are the more (13 blocks of 1580 slots x 128 bytes: 33 -> 15 us,
-        // 2900 blocks of 245 slots x 64 bytes: 90 -> 48 us); with enough of them the rows read better
-        // (2.5-4.9 TB/s against 2.0-2.8).
-        if (feat_dim < kStagedFrame && groups < 512) p.wide = false;
+        // few workgroups the staged tiles are the more.  The line lies at some 24 KiB of lanes' vectors at a time,
+        // at half of that for blocks of less than two chunks (13 blocks of 1580 slots x 128 bytes: 33 -> 15 us;
+        // 857 of 777 x 64: 70 us in wide rows of 16 or 4 bytes a lane 34, in tiles 16; 571 of 777 x 96: 51, 29, 24;
+        // 428 of 777 x 192: 45, 23, 31; 2500 of 110 x 192: 32, 13, 20).
+        if (w == 0 && feat_dim < kStagedFrame && groups * p.n_vec < (t_blk < 128 ? 760 : 1550)) p.wide = false;
         const bool whole = frame_bytes % 16 == 0;
         const bool suits = w > 0 || whole ||
                            (frame_bytes > 256 && (feat_tiles == 1 || p.n_vec * 3 >= (feat_tiles << p.row_lanes_log2) * 2));
@@ -1342,8 +1343,11 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
         p.chunk = kNarrowTile;
         if (p.staged) {
             const int32_t groups = kThreads / (int32_t)feat_dim;
-            p.slots = kStagedSlots;
-            if (num_blocks * t_blk / ((int64_t)groups * kStagedSlots) < 512) p.slots = kStagedSlotsShort;
+            const int32_t longest = groups * kStagedSlots;
+            // shorter lanes where tiles are few, unless only the longer ones hold a whole block (a border costs the
+            // stitching kernel: 10 blocks of 1305 slots x 2 floats 11 -> 8.5 us)
+            const bool few = num_blocks * t_blk / longest < 512;
+            p.slots = few && (t_blk <= groups * kStagedSlotsShort || t_blk > longest) ? kStagedSlotsShort : kStagedSlots;
             p.chunk = groups * p.slots;
             if (t_blk > p.chunk) {         // equal pieces
                 const int32_t pieces = (int32_t)ceil_div(t_blk, p.chunk);
