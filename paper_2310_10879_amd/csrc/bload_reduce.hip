@@ -62,6 +62,7 @@ struct ReduceArgs {
     void* out;               // [n_seq, feat_dim] float or int64
     // chunking
     int32_t chunk;           // slots per chunk
+    int32_t tile;            // staged, several tiles per workgroup: slots per tile
     int32_t n_chunks;        // wide: chunks per block
     int32_t row_lanes_log2;  // wide: lanes per row = 1 << this
     int32_t n_vec;           // wide: lanes needed to cover one frame
@@ -997,7 +998,9 @@ __device__ __forceinline__ typename TileSum<ElemT>::T masked_sum(const ElemT (&x
     return sum;
 }
 
-template <typename ElemT, int K>
+// RUN: the workgroup takes the tiles of a whole chunk one after another and carries the open segment from
+// one to the next.  No border inside the chunk, so fewer partial sums or none.
+template <typename ElemT, int K, bool RUN>
 __global__ __launch_bounds__(kThreads) void reduce_staged_kernel(ReduceArgs a)
 {
     typedef typename Elem<ElemT>::Acc Acc;
@@ -1015,14 +1018,15 @@ __global__ __launch_bounds__(kThreads) void reduce_staged_kernel(ReduceArgs a)
     __shared__ Sum s_sum[2][kThreads];
     __shared__ int32_t s_pos[2][kThreads];                   // last break up to there, -1: none in the tile
     __shared__ ChunkDesc s_desc;
+    __shared__ int32_t s_carry_seq;                          // RUN: sequence id of the segment carried from the tile before
 
     const int tid = (int)threadIdx.x;
     const int D = a.feat_dim;
     const int s = (int)((uint32_t)tid / (uint32_t)D), d = tid - s * D;
-    const int subs = a.chunk / K;
+    const int subs = (RUN ? a.tile : a.chunk) / K;
     const bool active = s < subs;
     const int64_t q = blockIdx.x;
-    // the tile: a piece of one block, or blocks_per_tile whole ones
+    // the tile (RUN: the chunk, of which `tile` slots at a time): a piece of one block, or blocks_per_tile whole ones
     int64_t g0;
     int32_t n, rem0;
     if (a.n_chunks > 1) {
@@ -1037,6 +1041,12 @@ __global__ __launch_bounds__(kThreads) void reduce_staged_kernel(ReduceArgs a)
         n = (int32_t)min((int64_t)a.blocks_per_tile, a.num_blocks - b0) * a.t_blk;
     }
     if (tid == 0) s_desc = ChunkDesc{kHeadNone, 0, 0, -1};
+    const int32_t run_n = n;
+    int32_t base = 0;                  // the tile's first slot in the chunk
+    Sum carry = 0;                     // lanes of the first group: the open segment in front of the tile,
+    int32_t carry_pos = -1;            // and where it starts in the chunk, -1: in front of it
+    for (;; __syncthreads()) {
+    if (RUN) n = min(a.tile, run_n - base);
 
     // payload: all vectors asked for before anything is waited for
     const int elems = n * D, vecs = elems / EPV;
@@ -1054,7 +1064,7 @@ __global__ __launch_bounds__(kThreads) void reduce_staged_kernel(ReduceArgs a)
     // (every load unconditional, at an address inside the planes, so that none waits for another)
     constexpr int kRounds = (kGroups + kThreads - 1) / kThreads;
     FlagBytes fb[kRounds];
-    const bool more_behind = rem0 + n < a.t_blk && a.n_chunks > 1;
+    const bool more_behind = rem0 + n < a.t_blk && (RUN || a.n_chunks > 1);
     const int64_t behind = min(g0 + n, a.total_slots - 1);
     const uint8_t behind_valid = a.valid[behind], behind_reset = a.reset[behind];
 #pragma unroll
@@ -1121,7 +1131,11 @@ __global__ __launch_bounds__(kThreads) void reduce_staged_kernel(ReduceArgs a)
         if (starts_at(t)) s_seq[t] = a.seq_id[g0 + t];
     // segmented scan over the groups
     Sum sum = (Sum)tail;
-    int32_t pos = bm ? o + 31 - __clz((int)bm) : -1;
+    int32_t pos = bm ? base + o + 31 - __clz((int)bm) : -1;
+    if (RUN && s == 0 && base > 0 && pos < 0) {
+        sum = carry + sum;
+        pos = carry_pos;
+    }
     int buf = 0;
     for (int step = 1; step < subs; step <<= 1) {
         s_sum[buf][tid] = sum;
@@ -1140,7 +1154,7 @@ __global__ __launch_bounds__(kThreads) void reduce_staged_kernel(ReduceArgs a)
     // One piece per end in the lane's slots, and the open one at the tile's end
     const uint32_t ends = vm & next_brk;
     uint32_t todo = ends;
-    if (left > 0 && o + left == n) todo |= vm & (1u << (left - 1));
+    if (left > 0 && base + o + left == run_n) todo |= vm & (1u << (left - 1));
     while (todo) {
         const int j = __ffs((int)todo) - 1;
         todo &= todo - 1u;
@@ -1153,10 +1167,13 @@ __global__ __launch_bounds__(kThreads) void reduce_staged_kernel(ReduceArgs a)
             if (s > 0) {
                 piece = s_sum[buf][tid - D] + piece;
                 start = s_pos[buf][tid - D];
+            } else if (RUN && base > 0) {
+                piece = carry + piece;
+                start = carry_pos;
             }
         } else {
             const int from = 31 - __clz((int)upto);
-            start = o + from;
+            start = base + o + from;
             if (upto == bm) {
                 piece = (Sum)tail;
             } else {                   // a segment between two breaks of the lane is read again
@@ -1166,11 +1183,23 @@ __global__ __launch_bounds__(kThreads) void reduce_staged_kernel(ReduceArgs a)
             }
         }
         const bool started = start >= 0, is_end = (ends >> j) & 1u;
-        const int32_t cnt = o + j - (started ? start : 0) + 1;
+        const int32_t cnt = base + o + j - (started ? start : 0) + 1;
         if (started && is_end && a.mean) piece = piece / (Sum)cnt;
-        emit_piece<Acc, Part>(a, q, d, started ? s_seq[start] : -1, is_end, started, (Part)piece, cnt, &s_desc);
+        int32_t seq = -1;
+        if (started) seq = RUN && start < base ? s_carry_seq : s_seq[start - base];
+        emit_piece<Acc, Part>(a, q, d, seq, is_end, started, (Part)piece, cnt, &s_desc);
     }
     __syncthreads();
+    if (!RUN || base + n >= run_n) break;
+    if (s == 0) {
+        carry = s_sum[buf][(subs - 1) * D + d];
+        carry_pos = s_pos[buf][(subs - 1) * D + d];
+        if (d == 0 && carry_pos >= base) s_carry_seq = s_seq[carry_pos - base];
+    }
+    base += n;
+    g0 += n;
+    rem0 += n;
+    }
     if (tid == 0 && a.desc) a.desc[q] = s_desc;
 }
 
@@ -1255,6 +1284,8 @@ __global__ __launch_bounds__(kThreads) void reduce_stitch_kernel(ReduceArgs a, i
 
 struct ReducePlan {
     bool wide, staged;
+    bool run;                // staged: a workgroup takes the tiles of a whole chunk one after another
+    int32_t tile;            // of this many slots
     int vec;                 // wide: elements per lane (16 / elem size)
     int row_lanes_log2;
     int n_vec;
@@ -1269,14 +1300,41 @@ struct ReducePlan {
 
 static int elem_size(bload_dtype dtype) { return dtype == BLOAD_U8 ? 1 : dtype == BLOAD_F16 ? 2 : 4; }
 
-// `one_element`: lanes of one element, for frames that are no whole 16-byte vectors and leave the choice
-// open (takes_one_element below).
-static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, bload_dtype dtype, bool one_element)
+// Which of two cuts is the faster hangs, for some frames, on the length of the pieces as well.  The guess at hand
+// is `mean`, the slots per row of the result (too short for a worker's share, whose rows are those of all
+// workers; either cut is right).
+//
+// Lanes of one element, for frames that are no whole vectors:
+//   - floats and int32 over more than one wave, pieces of a few frames (24 frames: 1.3-8 KB a frame up to
+//     12 % slower with 16-byte lanes, 1550 frames: 2-30 % faster; equal at 53 frames and four fifths of the
+//     lanes at work), unless blocks are short (34 slots x 5012 bytes: 40 us, one float a lane 49)
+//   - bytes and halfs of which a row of 4-byte lanes holds few, none of them at a whole word, long
+//     pieces (2 GB, 1550 frames: 101 bytes 670 us, 4 bytes a lane 770; 0.8 GB, 32 frames: 447 and 266)
+static bool takes_one_element(int32_t t_blk, int64_t feat_dim, int es, int64_t mean)
+{
+    const int64_t frame_bytes = feat_dim * es, vectors = ceil_div(frame_bytes, 16);
+    if (frame_bytes < 64 || feat_dim < 33 || frame_bytes % 16 == 0) return false;
+    if (es == 4) return vectors > kWave && t_blk >= 128 && mean * vectors < 40 * (int64_t)round_up((size_t)vectors, kWave);
+    return frame_bytes % 4 != 0 && feat_dim < (es == 1 ? 128 : 96) && mean >= 512;
+}
+
+// Staged tiles of frames of 2 to 5 elements, a block in two or three of them: one workgroup takes them one after
+// another, which spares the stitching kernel (2 us), where pieces are long.  255 blocks of 2828 slots x 2 floats:
+// 10.2 -> 8.5 us; two halfs in pieces of 24 frames, 17 blocks of 4243 slots: 10.4 -> 13.  With many tiles
+// only where elements are 4 bytes, of which a tile is many loads (444 blocks of 3757 x 3 floats: 17.8 -> 13.4 us;
+// 33985 sequences in blocks of 2828 x 2 bytes: 131 -> 195).
+static bool takes_run(int64_t tiles, bool few, int64_t feat_dim, int es, int64_t mean)
+{
+    return feat_dim <= 5 && mean >= 64 && (few ? tiles <= 2 : es == 4 && tiles <= 3);
+}
+
+static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, bload_dtype dtype, int64_t mean)
 {
     ReducePlan p{};
     const int es = elem_size(dtype);
     const int64_t frame_bytes = feat_dim * es;
     p.wide = frame_bytes >= 64;
+    const bool one_element = takes_one_element(t_blk, feat_dim, es, mean);
     // Lanes of 16 bytes, unless that leaves fewer than two workgroups per compute unit (four where the
     // vectors are not aligned): then lanes of 4 bytes, then of one element, which spread a frame over
     // more waves (15 blocks of 830 slots x 342 bytes: 23 us with 16 bytes a lane, 14 with one).
@@ -1349,7 +1407,12 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
             const bool few = num_blocks * t_blk / longest < 512;
             p.slots = few && (t_blk <= groups * kStagedSlotsShort || t_blk > longest) ? kStagedSlotsShort : kStagedSlots;
             p.chunk = groups * p.slots;
-            if (t_blk > p.chunk) {         // equal pieces
+            if (t_blk > longest && takes_run(ceil_div(t_blk, longest), few, feat_dim, es, mean)) {
+                p.run = true;
+                p.slots = kStagedSlots;
+                p.tile = longest;
+                p.chunk = t_blk;
+            } else if (t_blk > p.chunk) {  // equal pieces
                 const int32_t pieces = (int32_t)ceil_div(t_blk, p.chunk);
                 p.chunk = (int32_t)ceil_div(ceil_div(t_blk, pieces), p.slots) * p.slots;
             }
@@ -1383,28 +1446,6 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
     return p;
 }
 
-// Frames that are no whole vectors: does the number of rows of the result decide for lanes of one element?
-// What suits them hangs on the length of the pieces as well, of which the slots per row are the guess at hand
-// (too short for a worker's share, whose rows are those of all workers: either width gives the same sums).
-//   - floats and int32 over more than one wave, pieces of a few frames (24 frames: 1.3-8 KB a frame up to
-//     12 % slower with 16-byte lanes, 1550 frames: 2-30 % faster; equal at 53 frames and four fifths of the
-//     lanes at work), unless blocks are short (34 slots x 5012 bytes: 40 us, one float a lane 49)
-//   - bytes and halfs of which a row of 4-byte lanes holds few, none of them at a whole word, long
-//     pieces (2 GB, 1550 frames: 101 bytes 670 us, 4 bytes a lane 770; 0.8 GB, 32 frames: 447 and 266)
-static bool leaves_choice(int64_t feat_dim, int es)
-{
-    const int64_t frame_bytes = feat_dim * es;
-    if (frame_bytes < 64 || feat_dim < 33 || frame_bytes % 16 == 0) return false;
-    return es == 4 ? frame_bytes > 16 * kWave : frame_bytes % 4 != 0 && feat_dim < (es == 1 ? 128 : 96);
-}
-
-static bool takes_one_element(int64_t slots, int32_t t_blk, int64_t n_seq, int64_t feat_dim, int es)
-{
-    if (!leaves_choice(feat_dim, es)) return false;
-    const int64_t mean = slots / n_seq, vectors = ceil_div(feat_dim * es, 16);
-    return es == 4 ? t_blk >= 128 && mean * vectors < 40 * (int64_t)round_up((size_t)vectors, kWave) : mean >= 512;
-}
-
 template <typename ElemT, int VEC, bool STREAM>
 static void launch_wide(const ReducePlan& p, const ReduceArgs& a, hipStream_t stream)
 {
@@ -1435,10 +1476,12 @@ static void launch_reduce(const ReducePlan& p, const ReduceArgs& a, hipStream_t 
         const dim3 grid((uint32_t)p.total_chunks), block(kThreads);
         if (!p.staged)
             hipLaunchKernelGGL(reduce_narrow_kernel<ElemT>, grid, block, 0, stream, a);
+        else if (p.run)
+            hipLaunchKernelGGL((reduce_staged_kernel<ElemT, kStagedSlots, true>), grid, block, 0, stream, a);
         else if (p.slots == kStagedSlots)
-            hipLaunchKernelGGL((reduce_staged_kernel<ElemT, kStagedSlots>), grid, block, 0, stream, a);
+            hipLaunchKernelGGL((reduce_staged_kernel<ElemT, kStagedSlots, false>), grid, block, 0, stream, a);
         else
-            hipLaunchKernelGGL((reduce_staged_kernel<ElemT, kStagedSlotsShort>), grid, block, 0, stream, a);
+            hipLaunchKernelGGL((reduce_staged_kernel<ElemT, kStagedSlotsShort, false>), grid, block, 0, stream, a);
     }
     if (p.partials) {
         const int32_t feat_tiles = (int32_t)ceil_div(a.feat_dim, kThreads);
@@ -1461,9 +1504,9 @@ extern "C" size_t bload_segment_reduce_workspace_bytes(int64_t num_blocks, int32
                                                        int64_t feat_dim, bload_dtype dtype)
 {
     if (num_blocks <= 0 || t_blk < 1 || feat_dim < 1 || (int)dtype < 0 || (int)dtype > 3) return 0;
-    const size_t bytes = reduce_plan(num_blocks, t_blk, feat_dim, dtype, false).bytes;
-    if (!leaves_choice(feat_dim, elem_size(dtype))) return bytes;
-    return std::max(bytes, reduce_plan(num_blocks, t_blk, feat_dim, dtype, true).bytes);
+    // either end of the guess at the pieces' length
+    return std::max(reduce_plan(num_blocks, t_blk, feat_dim, dtype, 0).bytes,
+                    reduce_plan(num_blocks, t_blk, feat_dim, dtype, (int64_t)1 << 40).bytes);
 }
 
 extern "C" bload_status bload_segment_reduce(const void* d_packed, const int32_t* d_seq_id,
@@ -1485,8 +1528,7 @@ extern "C" bload_status bload_segment_reduce(const void* d_packed, const int32_t
         !aligned_to(d_valid, 16) || !aligned_to(d_out, 8))
         return BLOAD_EALIGN;
 
-    const ReducePlan p = reduce_plan(num_blocks, t_blk, feat_dim, dtype,
-                                     takes_one_element(total_slots, t_blk, n_seq, feat_dim, elem_size(dtype)));
+    const ReducePlan p = reduce_plan(num_blocks, t_blk, feat_dim, dtype, total_slots / n_seq);
     if (p.total_chunks * ceil_div(feat_dim, kThreads) > INT32_MAX) return BLOAD_EOVERFLOW;
     if (p.wide && ceil_div(p.total_chunks, kThreads >> p.row_lanes_log2) *
                       ceil_div(p.n_vec, 1 << p.row_lanes_log2) > INT32_MAX)
@@ -1513,6 +1555,7 @@ extern "C" bload_status bload_segment_reduce(const void* d_packed, const int32_t
     a.magic_t_blk = (uint32_t)std::min<uint64_t>((((uint64_t)1 << 32) + (uint64_t)t_blk - 1) / (uint64_t)t_blk, 0xFFFFFFFFull);
     a.out = d_out;
     a.chunk = p.chunk;
+    a.tile = p.tile;
     a.n_chunks = p.n_chunks;
     a.row_lanes_log2 = p.row_lanes_log2;
     a.n_vec = p.n_vec;

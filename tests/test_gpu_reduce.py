@@ -348,3 +348,36 @@ def test_reduce_staged_lanes_lose_no_more_than_a_tree_of_eight(n, T, D):
     lost = np.abs(got - want) / (U * want)
     print(f"n={n} T={T} D={D}: {lost.max():.1f} units of roundoff", flush=True)
     assert lost.max() <= 4
+
+
+# Staged blocks in two or three tiles that one workgroup takes one after another: segments that cross the borders,
+# end at them and begin behind them, the carried sequence's id and count, in pieces long enough for that cut.
+@pytest.mark.parametrize("dtype,op", [("f32", "mean"), ("i32", "sum"), ("u8", "mean"), ("f16", "sum")])
+@pytest.mark.parametrize("B,T,D", [(9, 2177, 2), (30, 4352, 2), (20, 1446, 3), (11, 1734, 5), (700, 3300, 4), (650, 2312, 4)])
+def test_reduce_runs_of_tiles(B, T, D, dtype, op):
+    bl = binding()
+    rng = np.random.default_rng(B + T + D)
+    tile = 256 // D * 17
+    valid, reset = np.ones((B, T), np.uint8), np.zeros((B, T), np.uint8)
+    for b in range(B):
+        for t in rng.choice([tile - 1, tile, tile + 1, 2 * tile - 1, 2 * tile, 2 * tile + 1, 1, T - 1, T // 2], size=rng.integers(0, 4)):
+            if t < T:
+                reset[b, t] = 1
+        if b % 4 == 3:
+            valid[b, min(T - 1, int(rng.choice([tile - 1, tile, tile + 1]))):][:int(rng.integers(1, 9))] = 0
+    reset &= valid
+    prev = np.concatenate([np.zeros((B, 1), np.uint8), valid[:, :-1]], axis=1)
+    starts = (valid == 1) & ((reset == 1) | (prev == 0))
+    seq_id = np.where(valid == 1, np.cumsum(starts.reshape(-1)).reshape(B, T) - 1, -1).astype(np.int32)
+    n_seg = int(starts.sum())
+    src = draw_source(rng, B * T, D, dtype)
+    want, counted = oracle.segment_reduce_packed(src.reshape(B, T, D), seq_id, reset, valid, D, dtype, op, n_seg)
+    assert counted == n_seg
+    got = bl.bload_segment_reduce(to_dev(src), to_dev(seq_id), to_dev(reset), to_dev(valid), B, T, D, dtype, op, n_seg).cpu().numpy()
+    if dtype == "i32":
+        assert np.array_equal(got, want)
+        return
+    absval = np.abs(src.astype(np.float64)).astype(np.float32).reshape(B, T, D)
+    scale, _ = oracle.segment_reduce_packed(absval, seq_id, reset, valid, D, "f32", op, n_seg)
+    bound = REL_TOL * np.maximum(np.abs(want.astype(np.float64)), scale.astype(np.float64)) + 1e-30
+    assert np.all(np.abs(got.astype(np.float64) - want.astype(np.float64)) <= bound)
