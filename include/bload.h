@@ -57,7 +57,8 @@ typedef enum {
     BLOAD_EINVAL = 1,      /* null pointer, negative size, t_blk < 1, frame_bytes < 1,
                               unknown dtype / op, or an unsupported dtype-op pair */
     BLOAD_ELENGTH = 2,     /* some L_i < 1 or L_i > t_blk (the method needs T_i <= T_max) */
-    BLOAD_EWORKSPACE = 3,  /* workspace smaller than the *_workspace_bytes() answer */
+    BLOAD_EWORKSPACE = 3,  /* workspace smaller than the *_workspace_bytes() answer (but see
+                              bload_segment_reduce) */
     BLOAD_EALIGN = 4,      /* a payload / workspace base is not 16-byte aligned (32-byte for
                               bload_pack's workspace), or an int32 / int64 table is not
                               naturally aligned */
@@ -299,13 +300,20 @@ bload_status bload_pack_check(const int64_t* d_src_offsets, const int32_t* d_len
  *                 count; I32 supports SUM only.  A segment's row is d_seq_id at
  *                 its first slot: row i is written iff some segment starts with
  *                 seq_id i; ids outside [0, n_seq) are skipped.  float32 sums are
- *                 compensated: whatever the length of a sequence, the result is
+ *                 formed as trees of a few frames that are added with compensation or
+ *                 in 64 bits: whatever the length of a sequence, the result is
  *                 within a few units of float32 roundoff of sum |x| (exact for U8
  *                 while the sum stays below 2^24).
  * d_workspace     device scratch of >= bload_segment_reduce_workspace_bytes(...)
- *                 bytes, 16-byte aligned.
+ *                 bytes, 16-byte aligned (may be NULL when that is 0).  The size is
+ *                 that of one cut of the work, chosen for the sizes it is asked for:
+ *                 ask again for another num_blocks, fewer blocks can need more.  Less
+ *                 is taken where a slower cut makes do with it (none at all for
+ *                 frames of 2 to 63 elements in blocks of up to 12288 slots) and else
+ *                 refused with BLOAD_EWORKSPACE (BLOAD_EINVAL without a workspace).
  *
- * Asynchronous on `hip_stream`; same inputs give bit-identical outputs.
+ * Asynchronous on `hip_stream`; same inputs and a workspace of the same size give
+ * bit-identical outputs.
  */
 size_t bload_segment_reduce_workspace_bytes(int64_t num_blocks, int32_t t_blk, int64_t feat_dim,
                                             bload_dtype dtype);

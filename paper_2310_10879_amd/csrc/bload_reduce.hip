@@ -963,6 +963,7 @@ __global__ __launch_bounds__(kThreads) void reduce_narrow_kernel(ReduceArgs a)
 constexpr int kStagedSlots = 17;       // odd, so that the groups' places in LDS spread over the banks
 constexpr int kStagedSlotsShort = 9;   // where long lanes would leave the chip without enough tiles
 constexpr int kStagedFrame = 64;       // frames of fewer elements are staged
+constexpr int32_t kLeanRun = 3 * kNarrowTile;     // lean cut: the longest chunk of tiles
 
 template <typename Acc> struct WideSum { typedef double T; };
 template <> struct WideSum<long long> { typedef long long T; };
@@ -1328,13 +1329,18 @@ static bool takes_run(int64_t tiles, bool few, int64_t feat_dim, int es, int64_t
     return feat_dim <= 5 && mean >= 64 && (few ? tiles <= 2 : es == 4 && tiles <= 3);
 }
 
-static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, bload_dtype dtype, int64_t mean)
+// `lean`: a cut that makes do with little workspace, or none, at the price of workgroups: tiles of a whole chunk
+// one after another by one workgroup, chunks as long as whole blocks and 12288 slots; lanes of one element (the
+// most workgroups per chunk) and plain partial sums for wide frames that are no whole vectors.
+static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, bload_dtype dtype, int64_t mean,
+                              bool lean = false)
 {
     ReducePlan p{};
     const int es = elem_size(dtype);
     const int64_t frame_bytes = feat_dim * es;
     p.wide = frame_bytes >= 64;
-    const bool one_element = takes_one_element(t_blk, feat_dim, es, mean);
+    const bool one_element = takes_one_element(t_blk, feat_dim, es, mean) ||
+                             (lean && feat_dim >= kStagedFrame && frame_bytes % 16 != 0);
     // Lanes of 16 bytes, unless that leaves fewer than two workgroups per compute unit (four where the
     // vectors are not aligned): then lanes of 4 bytes, then of one element, which spread a frame over
     // more waves (15 blocks of 830 slots x 342 bytes: 23 us with 16 bytes a lane, 14 with one).
@@ -1389,7 +1395,7 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
         // at half of that for blocks of less than two chunks (13 blocks of 1580 slots x 128 bytes: 33 -> 15 us;
         // 857 of 777 x 64: 70 us in wide rows of 16 or 4 bytes a lane 34, in tiles 16; 571 of 777 x 96: 51, 29, 24;
         // 428 of 777 x 192: 45, 23, 31; 2500 of 110 x 192: 32, 13, 20).
-        if (w == 0 && feat_dim < kStagedFrame && groups * p.n_vec < (t_blk < 128 ? 760 : 1550)) p.wide = false;
+        if (w == 0 && feat_dim < kStagedFrame && (lean || groups * p.n_vec < (t_blk < 128 ? 760 : 1550))) p.wide = false;
         const bool whole = frame_bytes % 16 == 0;
         const bool suits = w > 0 || whole ||
                            (frame_bytes > 256 && (feat_tiles == 1 || p.n_vec * 3 >= (feat_tiles << p.row_lanes_log2) * 2));
@@ -1407,11 +1413,11 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
             const bool few = num_blocks * t_blk / longest < 512;
             p.slots = few && (t_blk <= groups * kStagedSlotsShort || t_blk > longest) ? kStagedSlotsShort : kStagedSlots;
             p.chunk = groups * p.slots;
-            if (t_blk > longest && takes_run(ceil_div(t_blk, longest), few, feat_dim, es, mean)) {
+            if (t_blk > longest && (lean || takes_run(ceil_div(t_blk, longest), few, feat_dim, es, mean))) {
                 p.run = true;
                 p.slots = kStagedSlots;
                 p.tile = longest;
-                p.chunk = t_blk;
+                p.chunk = lean ? std::min(t_blk, kLeanRun) : t_blk;
             } else if (t_blk > p.chunk) {  // equal pieces
                 const int32_t pieces = (int32_t)ceil_div(t_blk, p.chunk);
                 p.chunk = (int32_t)ceil_div(ceil_div(t_blk, pieces), p.slots) * p.slots;
@@ -1435,7 +1441,7 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
         // of 388 frames of 66 halfs in chunks of 70 slots: root mean square error against 64 bits 2.7e-8, 2.3e-8 in
         // half as many chunks)
         p.pair_parts = (dtype == BLOAD_F16 || dtype == BLOAD_F32) &&
-                       (p.staged || (p.wide && p.vec * es < 16 && frame_bytes % 16 != 0));
+                       (p.staged || (p.wide && p.vec * es < 16 && frame_bytes % 16 != 0 && !lean));
         const size_t acc = dtype == BLOAD_I32 || p.pair_parts ? 8 : 4;
         size_t off = 0;
         p.desc_off = off; off += round_up((size_t)p.total_chunks * sizeof(ChunkDesc), 16);
@@ -1528,7 +1534,13 @@ extern "C" bload_status bload_segment_reduce(const void* d_packed, const int32_t
         !aligned_to(d_valid, 16) || !aligned_to(d_out, 8))
         return BLOAD_EALIGN;
 
-    const ReducePlan p = reduce_plan(num_blocks, t_blk, feat_dim, dtype, total_slots / n_seq);
+    ReducePlan p = reduce_plan(num_blocks, t_blk, feat_dim, dtype, total_slots / n_seq);
+    // a workspace that is smaller than the query's answer but holds what the leanest cut needs
+    const size_t room = d_workspace ? workspace_bytes : 0;
+    if (room < p.bytes) {
+        const ReducePlan lean = reduce_plan(num_blocks, t_blk, feat_dim, dtype, total_slots / n_seq, true);
+        if (lean.bytes <= room) p = lean;
+    }
     if (p.total_chunks * ceil_div(feat_dim, kThreads) > INT32_MAX) return BLOAD_EOVERFLOW;
     if (p.wide && ceil_div(p.total_chunks, kThreads >> p.row_lanes_log2) *
                       ceil_div(p.n_vec, 1 << p.row_lanes_log2) > INT32_MAX)

@@ -350,6 +350,48 @@ def test_reduce_staged_lanes_lose_no_more_than_a_tree_of_eight(n, T, D):
     assert lost.max() <= 4
 
 
+# Less room than the query answers, down to none where the leanest cut leaves no partial sums: blocks under 4096
+# slots of frames under 64 elements (one workgroup goes through a block's tiles), longer blocks in chunks of
+# 12288 slots, and wide frames that are no whole vectors in lanes of one element.  One byte less than the
+# leanest cut needs is refused.
+@pytest.mark.parametrize("dtype,op", [("f32", "mean"), ("i32", "sum"), ("u8", "mean"), ("f16", "sum")])
+@pytest.mark.parametrize("B,T,D,chunks", [(67, 777, 37, 1), (68, 777, 37, 1), (5, 4095, 2, 1), (40, 133, 63, 1), (3, 2000, 9, 1),
+                                          (2, 12288, 3, 1), (3, 12289, 5, 2), (300, 700, 65, 7), (90, 700, 201, 10)])
+def test_reduce_with_less_workspace_than_asked_for(B, T, D, chunks, dtype, op):
+    bl = binding()
+    asked = bl.bload_segment_reduce_workspace_bytes(B, T, D, dtype)
+    part = 8 if dtype == "i32" or (D < 64 and dtype in ("f16", "f32")) else 4
+    n = B * chunks
+    room = 0 if chunks == 1 else n * 16 + 2 * (-(-n * D * part // 16) * 16)
+    assert room <= asked
+    rng = np.random.default_rng(B + T + D)
+    for p_valid, p_reset in [(1.0, 0.0), (0.97, 0.01)]:
+        valid, reset, seq_id, n_seg = random_flags(rng, B, T, p_valid, p_reset)
+        src = draw_source(rng, B * T, D, dtype)
+        want, _ = oracle.segment_reduce_packed(src.reshape(B, T, D), seq_id, reset, valid, D, dtype, op, n_seg)
+        absval = np.abs(src.astype(np.float64)).astype(np.float32).reshape(B, T, D)
+        scale, _ = oracle.segment_reduce_packed(absval, seq_id, reset, valid, D, "f32", op, n_seg)
+        x, ids, r, v = to_dev(src), to_dev(seq_id), to_dev(reset), to_dev(valid)
+        print(f"room {room} of {asked}: B={B} T={T} D={D} {dtype} {op} segments={n_seg}", flush=True)
+        for take in (room, room - 1):
+            out = torch.zeros((n_seg, D), dtype=torch.int64 if dtype == "i32" else torch.float32, device="cuda")
+            ws = torch.empty(max(room, 16), dtype=torch.uint8, device="cuda")
+            st = bl._lib.bload_segment_reduce(x.data_ptr(), ids.data_ptr(), r.data_ptr(), v.data_ptr(), B, T, D,
+                                              bl.DTYPES[dtype], bl.OPS[op], n_seg, out.data_ptr(),
+                                              ws.data_ptr() if take > 0 else None, max(take, 0),
+                                              torch.cuda.current_stream().cuda_stream)
+            if take < room and room > 0:
+                assert st == bl.EWORKSPACE
+                continue
+            assert st == bl.OK
+            got = out.cpu().numpy()
+            if dtype == "i32":
+                assert np.array_equal(got, want)
+            else:
+                bound = REL_TOL * np.maximum(np.abs(want.astype(np.float64)), scale.astype(np.float64)) + 1e-30
+                assert np.all(np.abs(got.astype(np.float64) - want.astype(np.float64)) <= bound)
+
+
 # Staged blocks in two or three tiles that one workgroup takes one after another: segments that cross the borders,
 # end at them and begin behind them, the carried sequence's id and count, in pieces long enough for that cut.
 @pytest.mark.parametrize("dtype,op", [("f32", "mean"), ("i32", "sum"), ("u8", "mean"), ("f16", "sum")])
