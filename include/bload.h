@@ -341,11 +341,12 @@ bload_status bload_segment_reduce(const void* d_packed, const int32_t* d_seq_id,
  * d_reset, d_valid   in   uint8[B, t_blk]
  * decay      in   any float
  * d_out      out  float32[B, t_blk, feat_dim], 16-byte aligned; every element is
- *                 written.  float32 arithmetic in time order inside chunks of time;
- *                 a sequence that crosses a chunk border receives the state in
- *                 front of the chunk as decay^chunk * (state one chunk earlier) +
- *                 (the chunk's own part).  For the k-th frame of a sequence the
- *                 result differs from the exact one by at most (3k + 4) * 2^-24 * S,
+ *                 written.  float32 arithmetic in time order inside stretches of 8 to
+ *                 33 slots; a sequence that crosses from one stretch to the next takes
+ *                 its state along in 64 bits, as decay^length * (state in front of the
+ *                 stretch) + (the stretch's own part), which adds no rounding; a state
+ *                 beyond the range of float32 is infinite.  For the k-th frame of a
+ *                 sequence the result differs from the exact one by at most (3k + 4) * 2^-24 * S,
  *                 S being the same recurrence run on |x| with |decay|.
  * d_workspace     device scratch of >= bload_segment_scan_workspace_bytes(...)
  *                 bytes, 16-byte aligned (may be NULL when that is 0).

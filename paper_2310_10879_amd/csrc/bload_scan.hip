@@ -18,9 +18,12 @@
 //     decay^chunk * state + partial.  It publishes its own end state: partial while it waits, final then
 //   - the recurrence over the tile's own slots from that state, kept in registers meanwhile, is
 //     what leaves for the output
-// A state and its mark (partial / final) are one 8-byte word, written and read by atomics of
-// device scope, so no order between different words is needed.  The states are combined in the
-// same order whichever tile finishes first: equal inputs give equal bits.
+// A state travels as a double whose last two mantissa bits are its mark (partial / final): one 8-byte
+// word, written and read by atomics of device scope, so no order between different words is needed.
+// Every state is cut to 50 mantissa bits when it is made, and the states are combined in the
+// same order whichever tile finishes first: equal inputs give equal bits.  A hand-over in float32
+// would add a rounding at every border (10000 sequences of log-mel frames: error against 64 bits
+// 6.36e-8 instead of 6.17e-8 of the recurrence from end to end).
 // Tiles that wait hold their registers, so the order of the tiles is that of memory only in
 // the large: 32 blocks are taken side by side, chunk by chunk, and the tile in front has mostly
 // finished (6900 blocks of 3000 slots x 320 bytes: 3.75 ms block by block, 2.75 with 8 side by
@@ -115,14 +118,30 @@ template <typename ElemT> union ScanQuad {
     ElemT e[4];
 };
 
-// The state `n` slots on: own = what those slots make of a state of 0, power = decay^n.  In 64
-// bits, so that a power that float32 cannot hold does no harm.  A state of exactly 0 leaves
-// `own` whatever the power is; an infinite one stays infinite when the power has become 0.
-__device__ __forceinline__ float scan_join(double power, float handed, float own)
+// A state and its mark in one word.
+__device__ __forceinline__ unsigned long long scan_word(double v, uint32_t mark)
 {
-    if (handed == 0.0f) return own;
+    return ((unsigned long long)__double_as_longlong(v) & ~3ull) | mark;
+}
+__device__ __forceinline__ double scan_value(unsigned long long w) { return __longlong_as_double((long long)(w & ~3ull)); }
+__device__ __forceinline__ uint32_t scan_mark(unsigned long long w) { return (uint32_t)w & 3u; }
+
+// The state `n` slots on: own = what those slots make of a state of 0, power = decay^n.  In 64
+// bits, so that a power that float32 cannot hold does no harm; what leaves the range of float32 on
+// the way is infinite, as it is in the recurrence.  A state of exactly 0 leaves
+// `own` whatever the power is; an infinite one stays infinite when the power has become 0.
+__device__ __forceinline__ double scan_join(double power, double handed, double own)
+{
+    if (handed == 0.0) return own;
     if (power == 0.0 && __builtin_isinf(handed)) power = __builtin_copysign(1.0, power);
-    return (float)__builtin_fma(power, (double)handed, (double)own);
+    const double v = __builtin_fma(power, handed, own);
+    return __builtin_isinf((float)v) ? (double)(float)v : scan_value(scan_word(v, 0));
+}
+
+// The recurrence at a lane's first slot, from a state in 64 bits: rounded once.
+__device__ __forceinline__ float scan_first(float decay, double state, float x)
+{
+    return (float)__builtin_fma((double)decay, state, (double)x);
 }
 
 // Where a workgroup's tile lies: `unit` = block (or group of blocks), tile `c` of it, feature slice.
@@ -176,50 +195,49 @@ __device__ __forceinline__ ScanSpan scan_span(const ScanArgs& a, int64_t unit, i
 
 // What the lanes of a workgroup exchange.  Lane `tid` = group s, place q in the row.
 template <int UNIT> struct ScanShared {
-    alignas(16) float value[2][kThreads][UNIT];
-    uint32_t mark[2][kThreads];
+    alignas(16) unsigned long long word[2][kThreads][UNIT];
 };
 
 // Inclusive scan over the groups: in, v = what the lane's own slots make of a state of 0 and
 // `closed` = they hold a boundary; out, the same for all slots of the tile up to the lane's last
-// (left in sh.value / sh.mark [return value], with a barrier behind it).
+// (left in sh.word [return value], the mark being `closed`, with a barrier behind it).
 template <int UNIT>
-__device__ __forceinline__ int scan_groups(const ScanArgs& a, ScanShared<UNIT>& sh, int s, float (&v)[UNIT],
+__device__ __forceinline__ int scan_groups(const ScanArgs& a, ScanShared<UNIT>& sh, int s, const float (&own)[UNIT],
                                            uint32_t closed)
 {
     const int tid = (int)threadIdx.x;
     int buf = 0;
+    double v[UNIT];
+#pragma unroll
+    for (int k = 0; k < UNIT; ++k) v[k] = (double)own[k];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int step = 1 << i;
         if (step >= a.subs) break;
 #pragma unroll
-        for (int k = 0; k < UNIT; ++k) sh.value[buf][tid][k] = v[k];
-        sh.mark[buf][tid] = closed;
+        for (int k = 0; k < UNIT; ++k) sh.word[buf][tid][k] = scan_word(v[k], closed);
         __syncthreads();
         if (s >= step && s < a.subs) {
             const int other = tid - step * a.row;
             if (!closed) {
 #pragma unroll
-                for (int k = 0; k < UNIT; ++k) v[k] = scan_join(a.decay_sub[i], sh.value[buf][other][k], v[k]);
-                closed = sh.mark[buf][other];
+                for (int k = 0; k < UNIT; ++k) v[k] = scan_join(a.decay_sub[i], scan_value(sh.word[buf][other][k]), v[k]);
+                closed = scan_mark(sh.word[buf][other][0]);
             }
         }
         buf ^= 1;
     }
 #pragma unroll
-    for (int k = 0; k < UNIT; ++k) sh.value[buf][tid][k] = v[k];
-    sh.mark[buf][tid] = closed;
+    for (int k = 0; k < UNIT; ++k) sh.word[buf][tid][k] = scan_word(v[k], closed);
     __syncthreads();
     return buf;
 }
 
 constexpr uint32_t kPartial = 1, kFinal = 2;
 
-__device__ __forceinline__ void scan_publish(unsigned long long* word, float v, uint32_t mark)
+__device__ __forceinline__ void scan_publish(unsigned long long* word, double v, uint32_t mark)
 {
-    __hip_atomic_store(word, ((unsigned long long)mark << 32) | __float_as_uint(v), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(word, scan_word(v, mark), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // What group s sees of tile c - 1 - s: the words of the lane's features.
@@ -243,28 +261,27 @@ __device__ __forceinline__ void scan_look(const ScanArgs& a, const unsigned long
 // The state tile c is handed, for the features of place q: true if it was found.  `words` = the
 // tile's own words at the lane's first feature.  The first look is at tile c - 1 alone, whose state
 // is final most of the time; where it is not, `not_yet` is called before the wait begins.  Uses
-// sh.value / sh.mark [buf]; all lanes of the workgroup call it together and get the same answer.
+// sh.word[buf]; all lanes of the workgroup call it together and get the same answer.
 template <int UNIT, typename NotYet>
 __device__ __forceinline__ bool scan_look_back(const ScanArgs& a, ScanShared<UNIT>& sh, int buf,
                                                const unsigned long long* words, int s, int q, int window, bool active,
-                                               float (&handed)[UNIT], NotYet not_yet)
+                                               double (&handed)[UNIT], NotYet not_yet)
 {
     const int tid = (int)threadIdx.x;
     for (uint32_t look = 0; look < a.polls; ++look) {
         ScanSeen<UNIT> seen;
         scan_look<UNIT>(a, words, s, active && s < (look == 0 ? 1 : window), seen);
         // words that are seen half way from partial to final are none yet
-        uint32_t mark = (uint32_t)(seen.w[0] >> 32);
+        uint32_t mark = scan_mark(seen.w[0]);
 #pragma unroll
-        for (int k = 1; k < UNIT; ++k) mark = (uint32_t)(seen.w[k] >> 32) == mark ? mark : 0u;
+        for (int k = 1; k < UNIT; ++k) mark = scan_mark(seen.w[k]) == mark ? mark : 0u;
 #pragma unroll
-        for (int k = 0; k < UNIT; ++k) sh.value[buf][tid][k] = __uint_as_float((uint32_t)seen.w[k]);
-        sh.mark[buf][tid] = mark;
+        for (int k = 0; k < UNIT; ++k) sh.word[buf][tid][k] = (seen.w[k] & ~3ull) | mark;
         __syncthreads();
         int found = -1;
         if (active) {
             for (int j = 0; j < window; ++j) {
-                const uint32_t m = sh.mark[buf][j * a.row + q];
+                const uint32_t m = scan_mark(sh.word[buf][j * a.row + q][0]);
                 if (m == kFinal) found = j;
                 if (m != kPartial) break;
             }
@@ -272,11 +289,11 @@ __device__ __forceinline__ bool scan_look_back(const ScanArgs& a, ScanShared<UNI
         if (__syncthreads_and(!active || found >= 0)) {
             if (active) {
 #pragma unroll
-                for (int k = 0; k < UNIT; ++k) handed[k] = sh.value[buf][found * a.row + q][k];
+                for (int k = 0; k < UNIT; ++k) handed[k] = scan_value(sh.word[buf][found * a.row + q][k]);
                 for (int j = found - 1; j >= 0; --j) {
 #pragma unroll
                     for (int k = 0; k < UNIT; ++k)
-                        handed[k] = scan_join(a.decay_chunk, handed[k], sh.value[buf][j * a.row + q][k]);
+                        handed[k] = scan_join(a.decay_chunk, handed[k], scan_value(sh.word[buf][j * a.row + q][k]));
                 }
             }
             __syncthreads();
@@ -329,7 +346,7 @@ __device__ __forceinline__ uint32_t scan_slots_again(const ScanArgs& a, const Sc
 template <typename ElemT, int UNIT, int K>
 __device__ __forceinline__ void scan_carry_in(const ScanArgs& a, ScanShared<UNIT>& sh, const ScanTile& tile, int s,
                                               int q, int64_t feature, bool active, float (&v)[UNIT], uint32_t closed,
-                                              bool starts_closed, float (&h)[UNIT])
+                                              bool starts_closed, double (&h)[UNIT])
 {
     const int tid = (int)threadIdx.x;
     const int last = (a.subs - 1) * a.row + q;         // the lane that ends the tile at this place
@@ -337,16 +354,16 @@ __device__ __forceinline__ void scan_carry_in(const ScanArgs& a, ScanShared<UNIT
     const int buf = scan_groups(a, sh, s, v, closed);
     // what the groups in front make of a state of 0
     const bool front = s > 0 && s < a.subs;
-    const bool front_closed = front && sh.mark[buf][tid - a.row] != 0;
+    const bool front_closed = front && scan_mark(sh.word[buf][tid - a.row][0]) != 0;
 #pragma unroll
-    for (int k = 0; k < UNIT; ++k) h[k] = front ? sh.value[buf][tid - a.row][k] : 0.0f;
+    for (int k = 0; k < UNIT; ++k) h[k] = front ? scan_value(sh.word[buf][tid - a.row][k]) : 0.0;
     if (a.chunks == 1) return;
 
     const bool publishes = tile.c + 1 < a.chunks && active && s == 0;
-    const bool tile_closed = sh.mark[buf][last] != 0;
-    float total[UNIT], handed[UNIT];
+    const bool tile_closed = scan_mark(sh.word[buf][last][0]) != 0;
+    double total[UNIT], handed[UNIT];
 #pragma unroll
-    for (int k = 0; k < UNIT; ++k) total[k] = sh.value[buf][last][k];
+    for (int k = 0; k < UNIT; ++k) total[k] = scan_value(sh.word[buf][last][k]);
     unsigned long long* words = a.words + (tile.unit * (int64_t)(a.chunks - 1) + tile.c) * a.feat_dim + feature;
     if (publishes && tile_closed) {
 #pragma unroll
@@ -361,7 +378,7 @@ __device__ __forceinline__ void scan_carry_in(const ScanArgs& a, ScanShared<UNIT
         })) {
         // not heard of in time: all tiles of the block in front of this one, one after another
 #pragma unroll
-        for (int k = 0; k < UNIT; ++k) handed[k] = 0.0f;
+        for (int k = 0; k < UNIT; ++k) handed[k] = 0.0;
 #pragma nounroll
         for (int32_t c = 0; c < tile.c; ++c) {
             __syncthreads();
@@ -369,8 +386,8 @@ __device__ __forceinline__ void scan_carry_in(const ScanArgs& a, ScanShared<UNIT
             const int at = scan_groups(a, sh, s, v, any);
 #pragma unroll
             for (int k = 0; k < UNIT; ++k) {
-                const float t = sh.value[at][last][k];
-                handed[k] = sh.mark[at][last] ? t : scan_join(a.decay_chunk, handed[k], t);
+                const double t = scan_value(sh.word[at][last][k]);
+                handed[k] = scan_mark(sh.word[at][last][k]) ? t : scan_join(a.decay_chunk, handed[k], t);
             }
         }
     }
@@ -412,6 +429,7 @@ __global__ __launch_bounds__(kThreads, sizeof(ElemT) == 4 ? 2 : 3) void scan_dir
     uint32_t vm = 0, bm = 0;           // the lane's slots: valid, boundary
     const ScanSpan span = scan_span(a, tile.unit, tile.c);
     float v[UNIT], h[UNIT];
+    double in[UNIT];                   // the state in front of the lane's first slot
     {
         for (int t0 = 0; t0 < a.chunk; t0 += kThreads) {
             const int t = t0 + tid;
@@ -461,7 +479,7 @@ __global__ __launch_bounds__(kThreads, sizeof(ElemT) == 4 ? 2 : 3) void scan_dir
                 v[k] = __builtin_fmaf(a.decay, starts ? 0.0f : v[k], ScanElem<ElemT>::get(x[u].e[k]));
         }
     }
-    scan_carry_in<ElemT, UNIT, K>(a, sh, tile, s, q, feature, active, v, bm != 0u ? 1u : 0u, (s_bound[0] & 1ull) != 0, h);
+    scan_carry_in<ElemT, UNIT, K>(a, sh, tile, s, q, feature, active, v, bm != 0u ? 1u : 0u, (s_bound[0] & 1ull) != 0, in);
     if (!active) return;
     // the payload stays packed until here: not the floats made of it above, four times as many registers
     if constexpr (sizeof(ElemT) < 4) {
@@ -477,7 +495,8 @@ __global__ __launch_bounds__(kThreads, sizeof(ElemT) == 4 ? 2 : 3) void scan_dir
         const bool starts = (bm >> u) & 1u;
 #pragma unroll
         for (int k = 0; k < UNIT; ++k)
-            h[k] = __builtin_fmaf(a.decay, starts ? 0.0f : h[k], ScanElem<ElemT>::get(x[u].e[k]));
+            h[k] = u == 0 ? scan_first(a.decay, starts ? 0.0 : in[k], ScanElem<ElemT>::get(x[u].e[k]))
+                          : __builtin_fmaf(a.decay, starts ? 0.0f : h[k], ScanElem<ElemT>::get(x[u].e[k]));
         if (u < left) {
             const float4v o = {h[0], h[1], h[2], h[3]};
             __builtin_nontemporal_store(o, reinterpret_cast<float4v_any*>(to + u * D * 4 + at));
@@ -530,7 +549,8 @@ __global__ __launch_bounds__(kThreads, 4) void scan_staged_kernel(ScanArgs a)
     float x[K];
     uint64_t bm = 0;                   // the lane's slots: boundary
     const ScanSpan span = scan_span(a, tile.unit, tile.c);
-    float v[1], h[1];
+    float v[1], h;
+    double in[1];
     bool starts_closed;
     {
         // the payload as whole vectors, all asked for before anything is waited for
@@ -592,13 +612,14 @@ __global__ __launch_bounds__(kThreads, 4) void scan_staged_kernel(ScanArgs a)
         v[0] = t;
         starts_closed = !before_tile || (s_reset[0] & 1u) || !(s_valid[0] & 1u);
     }
-    scan_carry_in<ElemT, 1, K>(a, sh, tile, s, q, q, active, v, bm != 0 ? 1u : 0u, starts_closed, h);
+    scan_carry_in<ElemT, 1, K>(a, sh, tile, s, q, q, active, v, bm != 0 ? 1u : 0u, starts_closed, in);
 
     const int left = active ? span.n - s * K : 0;
 #pragma unroll
     for (int u = 0; u < K; ++u) {
-        h[0] = __builtin_fmaf(a.decay, (bm >> u) & 1u ? 0.0f : h[0], x[u]);
-        if (u < left) s_x[(s * K + u) * D + q] = h[0];
+        const bool starts = (bm >> u) & 1u;
+        h = u == 0 ? scan_first(a.decay, starts ? 0.0 : in[0], x[u]) : __builtin_fmaf(a.decay, starts ? 0.0f : h, x[u]);
+        if (u < left) s_x[(s * K + u) * D + q] = h;
     }
     __syncthreads();
     const int elems = span.n * D, quads = elems / 4;
