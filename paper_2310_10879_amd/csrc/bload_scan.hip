@@ -49,7 +49,7 @@
 #include "bload_common.hpp"
 
 #include <hip/hip_fp16.h>
-#include <math.h>
+#include <cmath>
 
 #include <algorithm>
 
@@ -63,7 +63,7 @@ constexpr int kScanSmallFrame = 64;    // frames of fewer elements go through LD
 constexpr int kScanRow = 64;           // units (quads or elements) of a frame side by side in a workgroup
 constexpr int kStagedElems = 8448;     // elements of a staged tile: 33 KiB of LDS, four workgroups per CU
 constexpr int kScanLong = 32, kScanShort = 8;                  // slots per lane, and where tiles are few
-constexpr int kScanStagedLong = 33, kScanStagedShort = 9;      // odd, see scan_staged_kernel
+constexpr int kScanStagedLong = 33, kScanStagedHalf = 17, kScanStagedShort = 9;      // odd, see scan_staged_kernel
 constexpr int kScanGroup = 32;         // blocks whose tiles are taken side by side
 
 struct ScanArgs {
@@ -89,6 +89,7 @@ struct ScanArgs {
     float decay;
     double decay_sub[8];               // decay ^ (K * 2^i)
     double decay_chunk;                // decay ^ chunk
+    uint32_t plain;                    // bit i: decay_sub[i] is finite and not 0; bit 8: decay_chunk
 };
 
 template <typename ElemT> struct ScanElem;
@@ -127,14 +128,22 @@ __device__ __forceinline__ double scan_value(unsigned long long w) { return __lo
 __device__ __forceinline__ uint32_t scan_mark(unsigned long long w) { return (uint32_t)w & 3u; }
 
 // The state `n` slots on: own = what those slots make of a state of 0, power = decay^n.  In 64
-// bits, so that a power that float32 cannot hold does no harm; what leaves the range of float32 on
-// the way is infinite, as it is in the recurrence.  A state of exactly 0 leaves
-// `own` whatever the power is; an infinite one stays infinite when the power has become 0.
-__device__ __forceinline__ double scan_join(double power, double handed, double own)
+// bits, so that a power that float32 cannot hold does no harm.  A state of exactly 0 leaves
+// `own` whatever the power is; an infinite one stays infinite when the power has become 0.  `plain`: the
+// power is finite and not 0, and the multiplication does both by itself.
+__device__ __forceinline__ double scan_join(double power, bool plain, double handed, double own)
 {
-    if (handed == 0.0) return own;
-    if (power == 0.0 && __builtin_isinf(handed)) power = __builtin_copysign(1.0, power);
-    const double v = __builtin_fma(power, handed, own);
+    if (!plain) {
+        if (handed == 0.0) return own;
+        if (power == 0.0 && __builtin_isinf(handed)) power = __builtin_copysign(1.0, power);
+    }
+    return __builtin_fma(power, handed, own);
+}
+
+// A state that leaves a tile or enters a lane: what has left the range of float32 is infinite, as it is in the
+// recurrence, and the mantissa is cut as a word cuts it.
+__device__ __forceinline__ double scan_state(double v)
+{
     return __builtin_isinf((float)v) ? (double)(float)v : scan_value(scan_word(v, 0));
 }
 
@@ -221,7 +230,8 @@ __device__ __forceinline__ int scan_groups(const ScanArgs& a, ScanShared<UNIT>& 
             const int other = tid - step * a.row;
             if (!closed) {
 #pragma unroll
-                for (int k = 0; k < UNIT; ++k) v[k] = scan_join(a.decay_sub[i], scan_value(sh.word[buf][other][k]), v[k]);
+                for (int k = 0; k < UNIT; ++k)
+                    v[k] = scan_join(a.decay_sub[i], (a.plain >> i) & 1u, scan_value(sh.word[buf][other][k]), v[k]);
                 closed = scan_mark(sh.word[buf][other][0]);
             }
         }
@@ -231,6 +241,12 @@ __device__ __forceinline__ int scan_groups(const ScanArgs& a, ScanShared<UNIT>& 
     for (int k = 0; k < UNIT; ++k) sh.word[buf][tid][k] = scan_word(v[k], closed);
     __syncthreads();
     return buf;
+}
+
+// The state a tile on.
+__device__ __forceinline__ double scan_over_tile(const ScanArgs& a, double handed, double own)
+{
+    return scan_state(scan_join(a.decay_chunk, (a.plain >> 8) & 1u, handed, own));
 }
 
 constexpr uint32_t kPartial = 1, kFinal = 2;
@@ -293,7 +309,7 @@ __device__ __forceinline__ bool scan_look_back(const ScanArgs& a, ScanShared<UNI
                 for (int j = found - 1; j >= 0; --j) {
 #pragma unroll
                     for (int k = 0; k < UNIT; ++k)
-                        handed[k] = scan_join(a.decay_chunk, handed[k], scan_value(sh.word[buf][j * a.row + q][k]));
+                        handed[k] = scan_over_tile(a, handed[k], scan_value(sh.word[buf][j * a.row + q][k]));
                 }
             }
             __syncthreads();
@@ -356,14 +372,14 @@ __device__ __forceinline__ void scan_carry_in(const ScanArgs& a, ScanShared<UNIT
     const bool front = s > 0 && s < a.subs;
     const bool front_closed = front && scan_mark(sh.word[buf][tid - a.row][0]) != 0;
 #pragma unroll
-    for (int k = 0; k < UNIT; ++k) h[k] = front ? scan_value(sh.word[buf][tid - a.row][k]) : 0.0;
+    for (int k = 0; k < UNIT; ++k) h[k] = front ? scan_state(scan_value(sh.word[buf][tid - a.row][k])) : 0.0;
     if (a.chunks == 1) return;
 
     const bool publishes = tile.c + 1 < a.chunks && active && s == 0;
     const bool tile_closed = scan_mark(sh.word[buf][last][0]) != 0;
     double total[UNIT], handed[UNIT];
 #pragma unroll
-    for (int k = 0; k < UNIT; ++k) total[k] = scan_value(sh.word[buf][last][k]);
+    for (int k = 0; k < UNIT; ++k) total[k] = scan_state(scan_value(sh.word[buf][last][k]));
     unsigned long long* words = a.words + (tile.unit * (int64_t)(a.chunks - 1) + tile.c) * a.feat_dim + feature;
     if (publishes && tile_closed) {
 #pragma unroll
@@ -386,19 +402,19 @@ __device__ __forceinline__ void scan_carry_in(const ScanArgs& a, ScanShared<UNIT
             const int at = scan_groups(a, sh, s, v, any);
 #pragma unroll
             for (int k = 0; k < UNIT; ++k) {
-                const double t = scan_value(sh.word[at][last][k]);
-                handed[k] = scan_mark(sh.word[at][last][k]) ? t : scan_join(a.decay_chunk, handed[k], t);
+                const double t = scan_state(scan_value(sh.word[at][last][k]));
+                handed[k] = scan_mark(sh.word[at][last][k]) ? t : scan_over_tile(a, handed[k], t);
             }
         }
     }
     if (publishes && !tile_closed) {
 #pragma unroll
-        for (int k = 0; k < UNIT; ++k) scan_publish(words + k, scan_join(a.decay_chunk, handed[k], total[k]), kFinal);
+        for (int k = 0; k < UNIT; ++k) scan_publish(words + k, scan_over_tile(a, handed[k], total[k]), kFinal);
     }
     if (!front_closed) {
         const double p = scan_power(a, s);
 #pragma unroll
-        for (int k = 0; k < UNIT; ++k) h[k] = scan_join(p, handed[k], h[k]);
+        for (int k = 0; k < UNIT; ++k) h[k] = scan_state(scan_join(p, false, handed[k], h[k]));
     }
 }
 
@@ -531,7 +547,7 @@ __device__ __forceinline__ uint32_t scan_flags16(const uint8_t* __restrict__ pla
 }
 
 // Smaller frames.  K is odd, so that lanes K frames apart in LDS spread over the banks.
-template <typename ElemT, int K>
+template <typename ElemT, int K, bool CACHED>
 __global__ __launch_bounds__(kThreads, 4) void scan_staged_kernel(ScanArgs a)
 {
     static_assert(K % 2 == 1 && K * kThreads <= kStagedElems && K < 34, "a lane's flags fit behind a 31-bit shift");
@@ -563,7 +579,8 @@ __global__ __launch_bounds__(kThreads, 4) void scan_staged_kernel(ScanArgs a)
         for (int k = 0; k < NV; ++k) {
             const int i = tid + k * kThreads;
             in[k] = vec16{0u, 0u, 0u, 0u};
-            if (i < vecs) in[k] = __builtin_nontemporal_load(reinterpret_cast<const vec16_any*>(from) + i);
+            const vec16_any* at = reinterpret_cast<const vec16_any*>(from) + i;
+            if (i < vecs) in[k] = CACHED ? *at : __builtin_nontemporal_load(at);
         }
         const int64_t total = a.num_blocks * (int64_t)a.t_blk;
         for (int i = tid; i < (a.chunk + 15) / 16 + 4; i += kThreads) {
@@ -638,6 +655,7 @@ __global__ __launch_bounds__(kThreads) void scan_clear_kernel(unsigned long long
 
 struct ScanPlan {
     bool staged;
+    bool cached;                       // staged: plain loads
     int32_t k;                         // slots per lane
     int32_t row, subs, slices, frame_units;
     int32_t chunk, chunks, blocks_per_tile;
@@ -646,22 +664,53 @@ struct ScanPlan {
     size_t bytes;                      // workspace: the published states
 };
 
+// The share of a tile's lanes that have slots, whether a tile holds whole blocks or a block is cut into tiles.
+static double scan_tile_use(int64_t tile, int32_t t_blk)
+{
+    if (t_blk <= tile) return (double)(tile / t_blk * t_blk) / (double)tile;
+    return (double)t_blk / (double)(ceil_div(t_blk, tile) * tile);
+}
+
+// Slots per lane of a staged tile: as many as leave the fewest lanes idle, unless it is a tenth or two that is
+// gained (624 shapes; 101 slots x 37 halfs in tiles of 198 slots 92 us, of 102 slots 77; 72 x 63 floats, 132 and 84: 25
+// and 22; 400 x 20 floats, two tiles of 396 and two of 204: 28.7 and 22; where all lengths fill alike they
+// differ by as much to either side).
+static int32_t scan_staged_slots(int32_t groups, int32_t t_blk)
+{
+    int32_t best = 0;
+    double most = 0.0;
+    for (int32_t k = kScanStagedLong; k >= kScanStagedHalf; k -= 4) {
+        const double worth = scan_tile_use((int64_t)groups * k, t_blk) * (1.0 - 0.0125 * (kScanStagedLong - k));
+        if (worth > most) { most = worth; best = k; }
+    }
+    return best;
+}
+
 static ScanPlan scan_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, size_t elem)
 {
     ScanPlan p{};
     p.staged = feat_dim < kScanSmallFrame;
+    // what was just written or read lies in the memory-side cache if it fits there, and plain loads fetch it
+    // sooner (0.1 GB of 252-byte frames: 62 us with streaming loads, 49 plain); of small tensors they do not
+    // (40 MB of 64-byte frames: 18 and 20)
+    const int64_t elems = num_blocks * t_blk * feat_dim;
+    p.cached = p.staged && elems > ((int64_t)16 << 20) && elems * (int64_t)elem <= ((int64_t)256 << 20);
     p.frame_units = (int32_t)(p.staged ? feat_dim : ceil_div(feat_dim, 4));
     // slices of equal width; a width of which the workgroup's 256 lanes hold a whole number
     p.slices = p.staged ? 1 : (int32_t)ceil_div(p.frame_units, kScanRow);
     p.row = (int32_t)ceil_div(p.frame_units, p.slices);
     int32_t most_subs = kThreads / p.row;
     // slots per lane: 64 registers of payload; fewer where that leaves the chip without enough tiles
-    p.k = p.staged ? kScanStagedLong : kScanLong;
+    p.k = p.staged ? scan_staged_slots(most_subs, t_blk) : kScanLong;
     const int32_t small_k = p.staged ? kScanStagedShort : kScanShort;
     // shorter tiles where the long ones are too few to fill the chip, but none that cut a block (a
     // chain of hand-overs costs more than idle CUs: 82 blocks of 109 slots x 874 bytes took 28 us in
     // four tiles per block, 20 us in one)
-    if (t_blk <= most_subs * small_k && num_blocks / (most_subs * p.k / t_blk) * p.slices < 512) p.k = small_k;
+    if (t_blk <= most_subs * small_k && num_blocks / (most_subs * p.k / t_blk) * p.slices < 512) {
+        // (staged: of two short lengths the one that fills; 30 slots x 37 halfs, 4 MB: 9 slots a lane 10.2 us, 17 7.4)
+        const bool half = p.staged && scan_tile_use((int64_t)most_subs * kScanStagedHalf, t_blk) >= scan_tile_use((int64_t)most_subs * small_k, t_blk);
+        p.k = half ? kScanStagedHalf : small_k;
+    }
     // the lanes' places in a tile are 32-bit byte offsets from its first slot
     if (!p.staged) most_subs = (int32_t)std::min<int64_t>(most_subs, std::max<int64_t>(1, ((int64_t)1 << 32) / (4 * p.k * feat_dim)));
     const int64_t most = (int64_t)most_subs * p.k;
@@ -692,6 +741,20 @@ static size_t scan_elem_bytes(bload_dtype dtype)
     return dtype == BLOAD_U8 ? 1 : (dtype == BLOAD_F16 ? 2 : 4);
 }
 
+template <typename ElemT, bool CACHED>
+static void scan_launch_staged(const ScanArgs& a, const ScanPlan& p, hipStream_t stream)
+{
+    const dim3 grid((uint32_t)p.grid), block(kThreads);
+    switch (p.k) {
+        case 33: hipLaunchKernelGGL((scan_staged_kernel<ElemT, 33, CACHED>), grid, block, 0, stream, a); break;
+        case 29: hipLaunchKernelGGL((scan_staged_kernel<ElemT, 29, CACHED>), grid, block, 0, stream, a); break;
+        case 25: hipLaunchKernelGGL((scan_staged_kernel<ElemT, 25, CACHED>), grid, block, 0, stream, a); break;
+        case 21: hipLaunchKernelGGL((scan_staged_kernel<ElemT, 21, CACHED>), grid, block, 0, stream, a); break;
+        case 17: hipLaunchKernelGGL((scan_staged_kernel<ElemT, 17, CACHED>), grid, block, 0, stream, a); break;
+        default: hipLaunchKernelGGL((scan_staged_kernel<ElemT, kScanStagedShort, false>), grid, block, 0, stream, a); break;
+    }
+}
+
 template <typename ElemT>
 static void scan_launch(const ScanArgs& a, const ScanPlan& p, hipStream_t stream)
 {
@@ -702,8 +765,8 @@ static void scan_launch(const ScanArgs& a, const ScanPlan& p, hipStream_t stream
         hipLaunchKernelGGL(scan_clear_kernel, dim3((uint32_t)(groups < 4096 ? groups : 4096)), block, 0, stream,
                            a.words, words);
     }
-    if (p.staged && p.k == kScanStagedLong) hipLaunchKernelGGL((scan_staged_kernel<ElemT, kScanStagedLong>), grid, block, 0, stream, a);
-    else if (p.staged) hipLaunchKernelGGL((scan_staged_kernel<ElemT, kScanStagedShort>), grid, block, 0, stream, a);
+    if (p.staged && p.cached) scan_launch_staged<ElemT, true>(a, p, stream);
+    else if (p.staged) scan_launch_staged<ElemT, false>(a, p, stream);
     else if (p.k == kScanLong) hipLaunchKernelGGL((scan_direct_kernel<ElemT, kScanLong>), grid, block, 0, stream, a);
     else hipLaunchKernelGGL((scan_direct_kernel<ElemT, kScanShort>), grid, block, 0, stream, a);
 }
@@ -762,8 +825,12 @@ extern "C" bload_status bload_segment_scan(const void* d_packed, const uint8_t* 
     a.polls = BLOAD_SCAN_POLLS;
     a.decay = decay;
     double power = pow((double)decay, (double)p.k);
-    for (int i = 0; i < 8; ++i, power *= power) a.decay_sub[i] = power;
+    for (int i = 0; i < 8; ++i, power *= power) {
+        a.decay_sub[i] = power;
+        if (std::isfinite(power) && power != 0.0) a.plain |= 1u << i;
+    }
     a.decay_chunk = pow((double)decay, (double)p.chunk);
+    if (std::isfinite(a.decay_chunk) && a.decay_chunk != 0.0) a.plain |= 1u << 8;
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (dtype == BLOAD_U8) scan_launch<uint8_t>(a, p, stream);

@@ -103,6 +103,12 @@ TILE_EDGES = [(3, 132, 63, "f16"), (3, 133, 63, "f32"), (2, 528, 64, "u8"), (2, 
               (257, 1100, 64, "u8"), (1, 2, 64, "u8"), (1, 15, 1, "f32"), (1, 17, 1, "f16")]
 
 
+# Smaller frames go with 9, 17, 21, 25, 29 or 33 slots a lane: blocks that fill a tile of six or of four groups of
+# lanes at each length and one slot more, one block a tile and several, and a tensor read with plain loads.
+TILE_EDGES += [(900 if T < 100 else 600, T, 37, "f16") for T in (54, 55, 102, 103, 126, 127, 150, 151, 174, 175, 198, 199, 340)]
+TILE_EDGES += [(7, 68, 63, "u8"), (800, 84, 63, "f32"), (3, 116, 57, "f32"), (2700, 100, 63, "f32")]
+
+
 @pytest.mark.parametrize("B,T,D,dtype", TILE_EDGES)
 def test_scan_tile_edges(B, T, D, dtype):
     """Flags with long runs that cross several tiles and flags without a start at all."""
