@@ -14,6 +14,8 @@ import glob
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -25,7 +27,7 @@ NOWAIT_LIB = os.path.join(PKG, "libbload_scan_nowait.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Wall", "-Wextra", "-Wno-unused-parameter",
     # keep the compiler from fusing float pairs into packed-fp32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -38,19 +40,28 @@ def sources():
 
 
 def build(verbose: bool = True) -> str:
-    cmd = [HIPCC] + FLAGS + ["-o", LIB] + sources()
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.check_call(cmd)
-    cmd = [HIPCC] + FLAGS + ["-o", YS_LIB, YS_SRC]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.check_call(cmd)
-    cmd = [HIPCC] + FLAGS + ["-DBLOAD_SCAN_POLLS=0", "-o", NOWAIT_LIB] + \
-        [os.path.join(CSRC, f) for f in ("bload_scan.hip", "bload_api.hip")]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.check_call(cmd)
+    """Every source file to an object, side by side, then the libraries from them."""
+    with tempfile.TemporaryDirectory() as tmp:
+        def compile_one(job):
+            src, out, extra = job
+            cmd = [HIPCC] + FLAGS + extra + ["-c", "-o", os.path.join(tmp, out), src]
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            subprocess.check_call(cmd)
+            return os.path.join(tmp, out)
+
+        api, scan = os.path.join(CSRC, "bload_api.hip"), os.path.join(CSRC, "bload_scan.hip")
+        jobs = [(scan, "nowait.o", ["-DBLOAD_SCAN_POLLS=0"])] + \
+            [(src, os.path.basename(src) + ".o", []) for src in sources()] + [(YS_SRC, "yardsticks.o", [])]
+        jobs.sort(key=lambda job: -os.path.getsize(job[0]))          # the longest first
+        with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as pool:
+            objects = dict(zip((job[1] for job in jobs), pool.map(compile_one, jobs)))
+        for lib, parts in ((LIB, [os.path.basename(src) + ".o" for src in sources()]), (YS_LIB, ["yardsticks.o"]),
+                           (NOWAIT_LIB, ["nowait.o", os.path.basename(api) + ".o"])):
+            cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib] + [objects[part] for part in parts]
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            subprocess.check_call(cmd)
     return LIB
 
 
