@@ -551,12 +551,12 @@ struct Assembled<vec16> {
 template <typename E, bool FUSED, bool PAYLOAD, bool TABLE>
 __device__ __forceinline__ void narrow_general_tile(const PackArgs& a, const Run* __restrict__ runs,
                                                     RunTable<kNarrowMaxRuns>& tab, int64_t g0, int64_t g1,
-                                                    int32_t first, int32_t last, int32_t part, int32_t parts,
-                                                    int32_t long_runs)
+                                                    int32_t first, int32_t last, int32_t part, int32_t parts)
 {
     const int tid = (int)threadIdx.x;
     const int nslot = (int)(g1 - g0);
     const int n = gather_runs(runs, a.n_seq, first, last, g0, g1, tab);
+    const bool long_runs = (int64_t)(n - 1) * 4096 <= nslot * a.frame_bytes;      // borders four waves of vectors apart
 
     // start table (and, FUSED, the payload): 4 consecutive slots per lane -> 16-byte / 4-byte stores
     for (int q = tid; (TABLE || FUSED) && part == 0 && 4 * q < nslot; q += kThreads) {
@@ -631,7 +631,8 @@ __device__ __forceinline__ void narrow_general_tile(const PackArgs& a, const Run
             // sequences 1.13 -> 0.79 ms for 1.4 GB, 62-byte frames of 75-slot sequences 1.67 -> 1.09 ms, 56
             // bytes 1.01 -> 0.97).  By the whole wave only, and only where runs are several waves long (the
             // host's rule): a wave with a vector across a border does both (60-byte frames of 27-slot
-            // sequences 70 -> 90 us, 20-byte frames of 75 slots 91 -> 104).  A plain load, as the elements':
+            // sequences 70 -> 90 us, 20-byte frames of 75 slots 91 -> 104).  By the tile's own runs: the call's
+            // sequences would tell too little of a worker's share, whose tables keep the numbers of all.  A plain load, as the elements':
             // a streaming one loses to them where the source is in the memory-side cache (60-byte frames,
             // 0.2 GB: 84 us by elements, 111 streaming, 86 plain).
             const int32_t t = cur.seek(slot);
@@ -684,7 +685,7 @@ __device__ __forceinline__ void narrow_general_tile(const PackArgs& a, const Run
 template <typename E, bool FUSED, bool PAYLOAD = true, bool TABLE = true, int GROUP = 1>
 __global__ __launch_bounds__(kThreads) void pack_narrow_kernel(PackArgs a, const Run* __restrict__ runs,
                                                                const int32_t* __restrict__ first_pos,
-                                                               uint32_t n_tiles, int32_t parts, int32_t long_runs)
+                                                               uint32_t n_tiles, int32_t parts)
 {
     static_assert(PAYLOAD || !FUSED, "the fused form is about the payload");
     static_assert(PAYLOAD || TABLE, "a pass writes something");
@@ -772,7 +773,7 @@ __global__ __launch_bounds__(kThreads) void pack_narrow_kernel(PackArgs a, const
         const int64_t g0 = (int64_t)(tile0 + (uint32_t)u) * kNarrowSlots;
         if (table_in_use) __syncthreads();           // the tile before is done with the gathered runs
         narrow_general_tile<E, FUSED, PAYLOAD, TABLE>(a, runs, tab, g0, min(g0 + kNarrowSlots, a.total_slots),
-                                                      entry[u], entry[u + 1], part, parts, long_runs);
+                                                      entry[u], entry[u + 1], part, parts);
         table_in_use = true;
     }
 }
@@ -967,7 +968,7 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
         if (l.table_tiles > 0)
             hipLaunchKernelGGL((pack_narrow_kernel<uint8_t, false, false, true, kPassGroup>),
                                dim3((uint32_t)ceil_div(l.table_tiles, kPassGroup)), block, 0, stream, a, runs,
-                               first_pos_table, (uint32_t)l.table_tiles, 1, 0);
+                               first_pos_table, (uint32_t)l.table_tiles, 1);
         return launch_status();
     }
     // slot tiles: one pass; 4-byte frames (whose payload and table share a loop, so that one kernel writes
@@ -983,26 +984,25 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
     const int64_t vectors = ceil_div(frame_bytes, 4);               // 1024 slots / 256 lanes / 16 bytes
     const int64_t wanted = ceil_div(frame_bytes < 64 ? 1024 : 4096, l.tiles);
     const int32_t parts = (int32_t)(frame_bytes == 4 && aligned_to(d_src, 4) ? 1 : wanted < vectors ? wanted : vectors);
-    const int32_t long_runs = a.total_slots * frame_bytes / n_seq >= 4096;        // four waves of vectors per run
     const dim3 grid((uint32_t)(l.tiles * parts));
     if (frame_bytes % 16 == 0 && aligned_to(d_src, 16)) {
-        hipLaunchKernelGGL((pack_narrow_kernel<vec16, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts, long_runs);
+        hipLaunchKernelGGL((pack_narrow_kernel<vec16, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
     } else if (frame_bytes == 4 && aligned_to(d_src, 4)) {
         if (a.total_slots >= kTablePassFromSlots) {
             const dim3 groups((uint32_t)ceil_div(l.tiles, kPassGroup));
             hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, true, true, false, kPassGroup>), groups, block, 0, stream,
-                               a, runs, first_pos, n_tiles, parts, long_runs);
+                               a, runs, first_pos, n_tiles, parts);
             hipLaunchKernelGGL((pack_narrow_kernel<uint8_t, false, false, true, kPassGroup>), groups, block, 0, stream,
-                               a, runs, first_pos, n_tiles, parts, long_runs);
+                               a, runs, first_pos, n_tiles, parts);
         } else {
-            hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, true>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts, long_runs);
+            hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, true>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
         }
     } else if (frame_bytes % 4 == 0 && aligned_to(d_src, 4)) {
-        hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts, long_runs);
+        hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
     } else if (frame_bytes % 2 == 0 && aligned_to(d_src, 2)) {
-        hipLaunchKernelGGL((pack_narrow_kernel<uint16_t, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts, long_runs);
+        hipLaunchKernelGGL((pack_narrow_kernel<uint16_t, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
     } else {
-        hipLaunchKernelGGL((pack_narrow_kernel<uint8_t, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts, long_runs);
+        hipLaunchKernelGGL((pack_narrow_kernel<uint8_t, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
     }
     return launch_status();
 }

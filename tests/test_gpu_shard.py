@@ -62,3 +62,29 @@ def test_shard_errors():
         with pytest.raises(bl.BloadError) as e:
             bl.bload_plan_shard(plan_dev, rank, world)
         assert e.value.status == bl.EINVAL
+
+
+@pytest.mark.parametrize("F,lo,hi", [(9, 400, 700), (62, 60, 700), (68, 1, 50)])
+def test_shard_pack_of_slot_tiles(F, lo, hi):
+    """Slot tiles load whole vectors where a tile's own runs are long, whatever the number of sequences that the
+    tables count: long runs, short ones and both in one tensor, every byte of each worker's share."""
+    bl = binding()
+    world, n, T = 8, 900, 700
+    L = np.random.default_rng(F).integers(lo, hi + 1, size=n).astype(np.int32)
+    L[::3] = 700 if F == 68 else L[::3]
+    so = workloads.src_offsets(L)
+    src = workloads.tagged_source(L, F)
+    ref_plan = oracle.plan(L, T, oracle.order(n, 5))
+    whole = oracle.pack(src, so, L, ref_plan, F)
+    plan_dev = gpu_plan(L, T, 5)
+    d_src, d_so, d_L = to_dev(np.ascontiguousarray(src).view(np.uint8).reshape(-1)), to_dev(so), to_dev(L)
+    for rank in range(world):
+        print(f"shard slot tiles F={F} rank {rank}/{world}", flush=True)
+        sh = bl.bload_plan_shard(plan_dev, rank, world)
+        out = bl.bload_pack(d_src, d_so, d_L, sh, F)
+        torch.cuda.synchronize()
+        rows = [j * world + rank for j in range(sh.num_blocks)]
+        want = []
+        for ref, pad in zip(whole, (0, -1, -1, 0, 0)):
+            want.append(np.stack([ref[b] if b < ref_plan.num_blocks else np.full_like(ref[0], pad) for b in rows]))
+        assert_packed_equal(out, want, f"F={F} rank {rank}/{world}: ")
