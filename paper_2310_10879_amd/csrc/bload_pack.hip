@@ -979,13 +979,21 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
     // A tile is 1024 frames, one workgroup's work: where that leaves compute units idle, several workgroups share
     // a tile, towards 1024 of them, or 4096 from 64 bytes on, where a tile is 64 KiB and more; never more than
     // one per vector of a lane.  Short sequences, before and after: 8 tiles of 62 bytes 37 -> 12 us, 59 tiles
-    // of 104 bytes 38 -> 12, 211 of 68 bytes 26 -> 15, 211 of 400 bytes 89 -> 35, 1055 of 128 bytes 50 -> 52.
-    // Towards 2048 under 64 bytes: 1055 tiles of 10 bytes 19 -> 21 us, of 48 bytes 25 -> 29.
+    // of 104 bytes 38 -> 12, 209 of 68 bytes 27 -> 14, 209 of 400 bytes 90 -> 30, 859 of 400 bytes 135 -> 101.
+    // Towards 2048 under 64 bytes: 1055 tiles of 10 bytes 19 -> 21 us, of 48 bytes 25 -> 29.  1024 to 2047 tiles
+    // of the large frames fill the card once by themselves, and a share each would be a second look at every tile's
+    // runs for nothing: whole and in shares, 1059 of 64 bytes 27.5 and 29.7 us, of 128 bytes 45.3 and 46.9, 1399
+    // of 400 bytes 220 and 234, 1199 of 68 bytes 36.0 and 38.5.  From 2048 on some tiles would run alone after the
+    // others: 2099 of 64 bytes 54 and 49, of 128 bytes 95 and 85, of 256 bytes 245 and 226 with two shares.
+    // Frames from 96 bytes on that are put together from elements, a load each, gain there too: 1556 tiles of
+    // 104 bytes 52 and 47 us, of 200 bytes 88 and 75.
     const int64_t vectors = ceil_div(frame_bytes, 4);               // 1024 slots / 256 lanes / 16 bytes
-    const int64_t wanted = ceil_div(frame_bytes < 64 ? 1024 : 4096, l.tiles);
+    const bool vectors_copied = frame_bytes % 16 == 0 && aligned_to(d_src, 16);
+    const bool once = l.tiles >= 1024 && l.tiles < 2048 && (vectors_copied || frame_bytes < 96);
+    const int64_t wanted = once ? 1 : ceil_div(frame_bytes < 64 ? 1024 : 4096, l.tiles);
     const int32_t parts = (int32_t)(frame_bytes == 4 && aligned_to(d_src, 4) ? 1 : wanted < vectors ? wanted : vectors);
     const dim3 grid((uint32_t)(l.tiles * parts));
-    if (frame_bytes % 16 == 0 && aligned_to(d_src, 16)) {
+    if (vectors_copied) {
         hipLaunchKernelGGL((pack_narrow_kernel<vec16, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
     } else if (frame_bytes == 4 && aligned_to(d_src, 4)) {
         if (a.total_slots >= kTablePassFromSlots) {

@@ -211,3 +211,24 @@ def test_pack_large_tensors_of_small_frames(n, T, F, kind, progress):
     torch.cuda.synchronize()
     assert_packed_equal_whole(out, src, so, L, ref_plan, F, max(1, (64 << 20) // (T * F)),
                               f"n={n} T={T} F={F} {kind}: ", say=progress)
+
+
+@pytest.mark.parametrize("F", [62, 64, 68, 100])
+@pytest.mark.parametrize("tiles", [1023, 1024, 2047, 2048])
+def test_pack_slot_tiles_in_shares(F, tiles):
+    """Slot tiles of frames from 64 bytes on are shared by several workgroups, but not from 1024 to 2047 of them where
+    tiles alone fill the card: the last and the first count of each, every block against the oracle."""
+    from gpu_util import assert_packed_equal_whole
+    bl = binding()
+    rng = np.random.default_rng(F + tiles)
+    T = 31
+    blocks = tiles * 1024 // T                   # the last tile is short
+    L = np.tile(np.array([20, 11], dtype=np.int32), blocks)[rng.permutation(2 * blocks)]     # a block is one of each
+    so = workloads.src_offsets(L)
+    src = rng.integers(0, 256, size=int(so[-1]) * F, dtype=np.uint8)
+    ref_plan = oracle.plan(L, T, np.argsort(L, kind="stable").reshape(2, -1).T.reshape(-1).astype(np.int32))
+    assert ref_plan.num_blocks == blocks and -(-blocks * T // 1024) == tiles
+    assert bl.bload_pack_tile_bytes(len(L), blocks, T, F, True) == 0
+    out = bl.bload_pack(to_dev(src), to_dev(so), to_dev(L), upload_plan(ref_plan, len(L)), F)
+    torch.cuda.synchronize()
+    assert_packed_equal_whole(out, src, so, L, ref_plan, F, max(1, (64 << 20) // (T * F)), f"F={F} tiles={tiles}: ")
