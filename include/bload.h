@@ -349,7 +349,12 @@ bload_status bload_segment_reduce(const void* d_packed, const int32_t* d_seq_id,
  *                 sequence the result differs from the exact one by at most (3k + 4) * 2^-24 * S,
  *                 S being the same recurrence run on |x| with |decay|.
  * d_workspace     device scratch of >= bload_segment_scan_workspace_bytes(...)
- *                 bytes, 16-byte aligned (may be NULL when that is 0).
+ *                 bytes, 16-byte aligned (may be NULL when that is 0).  With less, one
+ *                 workgroup takes a block from end to end, which is slower: accepted
+ *                 down to nothing where there are thousands of blocks or blocks are
+ *                 shorter than 128 slots, and in any case where 4 bytes per element and
+ *                 1 per slot of every 64th slot fit; else BLOAD_EWORKSPACE
+ *                 (BLOAD_EINVAL without a workspace).
  * Asynchronous on `hip_stream`; same inputs give bit-identical outputs.
  */
 size_t bload_segment_scan_workspace_bytes(int64_t num_blocks, int32_t t_blk, int64_t feat_dim,

@@ -64,6 +64,7 @@ constexpr int kScanRow = 64;           // units (quads or elements) of a frame s
 constexpr int kStagedElems = 8448;     // elements of a staged tile: 33 KiB of LDS, four workgroups per CU
 constexpr int kScanLong = 32, kScanShort = 8;                  // slots per lane, and where tiles are few
 constexpr int kScanStagedLong = 33, kScanStagedHalf = 17, kScanStagedShort = 9;      // odd, see scan_staged_kernel
+constexpr int kScanStagedWalk = 25;    // what a walking workgroup has the registers for
 constexpr int kScanGroup = 32;         // blocks whose tiles are taken side by side
 
 struct ScanArgs {
@@ -159,9 +160,11 @@ struct ScanTile {
     int32_t c, slice;
 };
 
+// (WALK: the first tile of a block)
+template <bool WALK>
 __device__ __forceinline__ ScanTile scan_tile(const ScanArgs& a)
 {
-    const uint32_t slices = (uint32_t)a.slices, per_unit = (uint32_t)a.chunks * slices;
+    const uint32_t slices = (uint32_t)a.slices, chunks = WALK ? 1u : (uint32_t)a.chunks, per_unit = chunks * slices;
     uint32_t y = blockIdx.x, first = 0, units = (uint32_t)a.n_units;
     if (a.by_xcd) {
         // workgroup b runs on XCD b mod 8: every XCD takes units of its own
@@ -175,7 +178,7 @@ __device__ __forceinline__ ScanTile scan_tile(const ScanArgs& a)
     if (g * G >= units) return ScanTile{a.n_units, 0, 0};
     const uint32_t here = min(G, units - g * G);                 // units of this group
     const uint32_t c = in_group / (here * slices), rest = in_group - c * (here * slices);
-    if (c >= (uint32_t)a.chunks) return ScanTile{a.n_units, 0, 0};
+    if (c >= chunks) return ScanTile{a.n_units, 0, 0};
     const uint32_t u = rest / slices;
     return ScanTile{(int64_t)(first + g * G + u), (int32_t)c, (int32_t)(rest - u * slices)};
 }
@@ -358,11 +361,12 @@ __device__ __forceinline__ uint32_t scan_slots_again(const ScanArgs& a, const Sc
 
 // The part both kernels share: from what the lane's slots make of a state of 0 (v), whether they
 // hold a boundary (closed) and whether the tile's first slot is one (starts_closed, the same in
-// all lanes), the state in front of the lane's first slot (h).
-template <typename ElemT, int UNIT, int K>
+// all lanes), the state in front of the lane's first slot (h).  WALK: the state in front of the tile is `carried`,
+// and the one behind it is left there.
+template <typename ElemT, int UNIT, int K, bool WALK>
 __device__ __forceinline__ void scan_carry_in(const ScanArgs& a, ScanShared<UNIT>& sh, const ScanTile& tile, int s,
                                               int q, int64_t feature, bool active, float (&v)[UNIT], uint32_t closed,
-                                              bool starts_closed, double (&h)[UNIT])
+                                              bool starts_closed, double (&h)[UNIT], double (&carried)[UNIT])
 {
     const int tid = (int)threadIdx.x;
     const int last = (a.subs - 1) * a.row + q;         // the lane that ends the tile at this place
@@ -380,6 +384,19 @@ __device__ __forceinline__ void scan_carry_in(const ScanArgs& a, ScanShared<UNIT
     double total[UNIT], handed[UNIT];
 #pragma unroll
     for (int k = 0; k < UNIT; ++k) total[k] = scan_state(scan_value(sh.word[buf][last][k]));
+    if constexpr (WALK) {
+#pragma unroll
+        for (int k = 0; k < UNIT; ++k) {
+            handed[k] = carried[k];
+            carried[k] = tile_closed ? total[k] : scan_over_tile(a, handed[k], total[k]);
+        }
+        if (open_front && !front_closed) {
+            const double p = scan_power(a, s);
+#pragma unroll
+            for (int k = 0; k < UNIT; ++k) h[k] = scan_state(scan_join(p, false, handed[k], h[k]));
+        }
+        return;
+    }
     unsigned long long* words = a.words + (tile.unit * (int64_t)(a.chunks - 1) + tile.c) * a.feat_dim + feature;
     if (publishes && tile_closed) {
 #pragma unroll
@@ -418,8 +435,10 @@ __device__ __forceinline__ void scan_carry_in(const ScanArgs& a, ScanShared<UNIT
     }
 }
 
-// Frames of 64 elements or more.
-template <typename ElemT, int K>
+// Frames of 64 elements or more.  WALK, where there is no room for published states: a workgroup takes all tiles of
+// its block, one after another with the state in registers: the same operations, the same bits.  (The loop's body is not indented;
+// as a function of its own, with what it needs in LDS by reference, it came out 5 to 15 % slower for halfs.)
+template <typename ElemT, int K, bool WALK>
 __global__ __launch_bounds__(kThreads, sizeof(ElemT) == 4 ? 2 : 3) void scan_direct_kernel(ScanArgs a)
 {
     constexpr int UNIT = 4;
@@ -429,7 +448,7 @@ __global__ __launch_bounds__(kThreads, sizeof(ElemT) == 4 ? 2 : 3) void scan_dir
     static_assert(64 % K == 0, "the flags of a lane lie in one 64-bit word");
     __shared__ ScanShared<UNIT> sh;
     __shared__ unsigned long long s_valid[kWords], s_bound[kWords];
-    const ScanTile tile = scan_tile(a);
+    ScanTile tile = scan_tile<WALK>(a);
     if (tile.unit >= a.n_units) return;
     const int tid = (int)threadIdx.x;
     const int s = (int)((uint32_t)tid / (uint32_t)a.row), q = tid - s * a.row;
@@ -441,6 +460,8 @@ __global__ __launch_bounds__(kThreads, sizeof(ElemT) == 4 ? 2 : 3) void scan_dir
     const int64_t D = a.feat_dim;
     const uint32_t lane_at = active ? (uint32_t)(s * K) * (uint32_t)a.feat_dim + (uint32_t)feature : 0u;
 
+    double carried[UNIT] = {};         // WALK: the state in front of the tile
+    do {
     ScanQuad<ElemT> x[K];
     uint32_t vm = 0, bm = 0;           // the lane's slots: valid, boundary
     const ScanSpan span = scan_span(a, tile.unit, tile.c);
@@ -495,8 +516,9 @@ __global__ __launch_bounds__(kThreads, sizeof(ElemT) == 4 ? 2 : 3) void scan_dir
                 v[k] = __builtin_fmaf(a.decay, starts ? 0.0f : v[k], ScanElem<ElemT>::get(x[u].e[k]));
         }
     }
-    scan_carry_in<ElemT, UNIT, K>(a, sh, tile, s, q, feature, active, v, bm != 0u ? 1u : 0u, (s_bound[0] & 1ull) != 0, in);
-    if (!active) return;
+    scan_carry_in<ElemT, UNIT, K, WALK>(a, sh, tile, s, q, feature, active, v, bm != 0u ? 1u : 0u, (s_bound[0] & 1ull) != 0, in,
+                                        carried);
+    if (!WALK && !active) return;
     // the payload stays packed until here: not the floats made of it above, four times as many registers
     if constexpr (sizeof(ElemT) < 4) {
 #pragma unroll
@@ -505,7 +527,7 @@ __global__ __launch_bounds__(kThreads, sizeof(ElemT) == 4 ? 2 : 3) void scan_dir
 
     uint8_t* to = reinterpret_cast<uint8_t*>(a.out + span.g0 * D);
     const uint32_t at = lane_at * 4u;
-    const int left = span.n - s * K;
+    const int left = active ? span.n - s * K : 0;
 #pragma unroll
     for (int u = 0; u < K; ++u) {
         const bool starts = (bm >> u) & 1u;
@@ -518,6 +540,8 @@ __global__ __launch_bounds__(kThreads, sizeof(ElemT) == 4 ? 2 : 3) void scan_dir
             __builtin_nontemporal_store(o, reinterpret_cast<float4v_any*>(to + u * D * 4 + at));
         }
     }
+    if constexpr (WALK) __syncthreads();
+    } while (WALK && ++tile.c < a.chunks);
 }
 
 // Bit j: byte j of the 16 flag bytes is non-zero.
@@ -547,7 +571,7 @@ __device__ __forceinline__ uint32_t scan_flags16(const uint8_t* __restrict__ pla
 }
 
 // Smaller frames.  K is odd, so that lanes K frames apart in LDS spread over the banks.
-template <typename ElemT, int K, bool CACHED>
+template <typename ElemT, int K, bool CACHED, bool WALK>
 __global__ __launch_bounds__(kThreads, 4) void scan_staged_kernel(ScanArgs a)
 {
     static_assert(K % 2 == 1 && K * kThreads <= kStagedElems && K < 34, "a lane's flags fit behind a 31-bit shift");
@@ -555,13 +579,15 @@ __global__ __launch_bounds__(kThreads, 4) void scan_staged_kernel(ScanArgs a)
     __shared__ ScanShared<1> sh;
     __shared__ alignas(16) float s_x[K * kThreads];
     __shared__ alignas(16) uint16_t s_valid[kGroups], s_reset[kGroups];
-    const ScanTile tile = scan_tile(a);
+    ScanTile tile = scan_tile<WALK>(a);
     if (tile.unit >= a.n_units) return;
     const int tid = (int)threadIdx.x;
     const int D = a.feat_dim;
     const int s = (int)((uint32_t)tid / (uint32_t)D), q = tid - s * D;
     const bool active = s < a.subs;
 
+    double carried[1] = {};            // WALK: the state in front of the tile
+    do {
     float x[K];
     uint64_t bm = 0;                   // the lane's slots: boundary
     const ScanSpan span = scan_span(a, tile.unit, tile.c);
@@ -629,7 +655,7 @@ __global__ __launch_bounds__(kThreads, 4) void scan_staged_kernel(ScanArgs a)
         v[0] = t;
         starts_closed = !before_tile || (s_reset[0] & 1u) || !(s_valid[0] & 1u);
     }
-    scan_carry_in<ElemT, 1, K>(a, sh, tile, s, q, q, active, v, bm != 0 ? 1u : 0u, starts_closed, in);
+    scan_carry_in<ElemT, 1, K, WALK>(a, sh, tile, s, q, q, active, v, bm != 0 ? 1u : 0u, starts_closed, in, carried);
 
     const int left = active ? span.n - s * K : 0;
 #pragma unroll
@@ -644,6 +670,8 @@ __global__ __launch_bounds__(kThreads, 4) void scan_staged_kernel(ScanArgs a)
     for (int i = tid; i < quads; i += kThreads)
         __builtin_nontemporal_store(*reinterpret_cast<const float4v*>(s_x + 4 * i), reinterpret_cast<float4v_any*>(to) + i);
     for (int i = quads * 4 + tid; i < elems; i += kThreads) __builtin_nontemporal_store(s_x[i], to + i);
+    if constexpr (WALK) __syncthreads();
+    } while (WALK && ++tile.c < a.chunks);
 }
 
 // No state is published yet.
@@ -662,6 +690,7 @@ struct ScanPlan {
     int64_t n_units, grid;
     bool by_xcd;
     size_t bytes;                      // workspace: the published states
+    bool walk;                         // no room for them: a workgroup per block
 };
 
 // The share of a tile's lanes that have slots, whether a tile holds whole blocks or a block is cut into tiles.
@@ -686,7 +715,8 @@ static int32_t scan_staged_slots(int32_t groups, int32_t t_blk)
     return best;
 }
 
-static ScanPlan scan_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, size_t elem)
+// `walk`: a block's tiles go to one workgroup, as long as there are.
+static ScanPlan scan_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, size_t elem, bool walk = false)
 {
     ScanPlan p{};
     p.staged = feat_dim < kScanSmallFrame;
@@ -694,19 +724,19 @@ static ScanPlan scan_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, s
     // sooner (0.1 GB of 252-byte frames: 62 us with streaming loads, 49 plain); of small tensors they do not
     // (40 MB of 64-byte frames: 18 and 20)
     const int64_t elems = num_blocks * t_blk * feat_dim;
-    p.cached = p.staged && elems > ((int64_t)16 << 20) && elems * (int64_t)elem <= ((int64_t)256 << 20);
+    p.cached = p.staged && !walk && elems > ((int64_t)16 << 20) && elems * (int64_t)elem <= ((int64_t)256 << 20);
     p.frame_units = (int32_t)(p.staged ? feat_dim : ceil_div(feat_dim, 4));
     // slices of equal width; a width of which the workgroup's 256 lanes hold a whole number
     p.slices = p.staged ? 1 : (int32_t)ceil_div(p.frame_units, kScanRow);
     p.row = (int32_t)ceil_div(p.frame_units, p.slices);
     int32_t most_subs = kThreads / p.row;
     // slots per lane: 64 registers of payload; fewer where that leaves the chip without enough tiles
-    p.k = p.staged ? scan_staged_slots(most_subs, t_blk) : kScanLong;
+    p.k = !p.staged ? kScanLong : walk ? kScanStagedWalk : scan_staged_slots(most_subs, t_blk);
     const int32_t small_k = p.staged ? kScanStagedShort : kScanShort;
     // shorter tiles where the long ones are too few to fill the chip, but none that cut a block (a
     // chain of hand-overs costs more than idle CUs: 82 blocks of 109 slots x 874 bytes took 28 us in
     // four tiles per block, 20 us in one)
-    if (t_blk <= most_subs * small_k && num_blocks / (most_subs * p.k / t_blk) * p.slices < 512) {
+    if (!walk && t_blk <= most_subs * small_k && num_blocks / (most_subs * p.k / t_blk) * p.slices < 512) {
         // (staged: of two short lengths the one that fills; 30 slots x 37 halfs, 4 MB: 9 slots a lane 10.2 us, 17 7.4)
         const bool half = p.staged && scan_tile_use((int64_t)most_subs * kScanStagedHalf, t_blk) >= scan_tile_use((int64_t)most_subs * small_k, t_blk);
         p.k = half ? kScanStagedHalf : small_k;
@@ -728,12 +758,28 @@ static ScanPlan scan_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, s
         p.blocks_per_tile = (int32_t)(most / t_blk);
         p.n_units = ceil_div(num_blocks, p.blocks_per_tile);
     }
-    const int64_t per_unit = (int64_t)p.chunks * p.slices;
+    p.walk = walk && p.chunks > 1;
+    const int64_t per_unit = p.walk ? p.slices : (int64_t)p.chunks * p.slices;
     // every XCD gets whole blocks where there are enough of them for equal shares
     p.by_xcd = p.n_units >= 256;
     p.grid = p.by_xcd ? ceil_div(p.n_units, kXcds) * kXcds * per_unit : p.n_units * per_unit;
-    p.bytes = round_up((size_t)num_blocks * (size_t)(p.chunks - 1) * (size_t)feat_dim * sizeof(unsigned long long), 16);
+    p.bytes = p.walk ? 0 : round_up((size_t)num_blocks * (size_t)(p.chunks - 1) * (size_t)feat_dim * sizeof(unsigned long long), 16);
     return p;
+}
+
+// The least workspace that a scan is given: a boundary mark and float32 states for stretches of 64 slots and more,
+// as many as fill the chip, and none where the blocks do that alone.
+static size_t scan_least_bytes(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, size_t elem)
+{
+    const bool vectors = feat_dim * (int64_t)elem % 16 == 0 && num_blocks * t_blk >= 8;
+    const int64_t units = vectors ? feat_dim / 4 : feat_dim, per_lane = vectors ? 4 / (int64_t)elem : 1;
+    int64_t lanes = 1;
+    while (lanes < kWave && lanes * per_lane < units) lanes *= 2;
+    const int64_t waves = 6144 * (kWave / lanes), rows = num_blocks * ceil_div(units, lanes * per_lane);
+    const int64_t parts = std::min<int64_t>(ceil_div(waves, rows), std::max<int32_t>(1, t_blk / 64));
+    const int64_t stretch = (int64_t)round_up((size_t)ceil_div(t_blk, parts), 8);
+    const size_t borders = (size_t)num_blocks * (size_t)(ceil_div(t_blk, stretch) - 1);
+    return round_up(borders * (size_t)feat_dim * sizeof(float), 16) + round_up(borders, 16);
 }
 
 static size_t scan_elem_bytes(bload_dtype dtype)
@@ -746,12 +792,12 @@ static void scan_launch_staged(const ScanArgs& a, const ScanPlan& p, hipStream_t
 {
     const dim3 grid((uint32_t)p.grid), block(kThreads);
     switch (p.k) {
-        case 33: hipLaunchKernelGGL((scan_staged_kernel<ElemT, 33, CACHED>), grid, block, 0, stream, a); break;
-        case 29: hipLaunchKernelGGL((scan_staged_kernel<ElemT, 29, CACHED>), grid, block, 0, stream, a); break;
-        case 25: hipLaunchKernelGGL((scan_staged_kernel<ElemT, 25, CACHED>), grid, block, 0, stream, a); break;
-        case 21: hipLaunchKernelGGL((scan_staged_kernel<ElemT, 21, CACHED>), grid, block, 0, stream, a); break;
-        case 17: hipLaunchKernelGGL((scan_staged_kernel<ElemT, 17, CACHED>), grid, block, 0, stream, a); break;
-        default: hipLaunchKernelGGL((scan_staged_kernel<ElemT, kScanStagedShort, false>), grid, block, 0, stream, a); break;
+        case 33: hipLaunchKernelGGL((scan_staged_kernel<ElemT, 33, CACHED, false>), grid, block, 0, stream, a); break;
+        case 29: hipLaunchKernelGGL((scan_staged_kernel<ElemT, 29, CACHED, false>), grid, block, 0, stream, a); break;
+        case 25: hipLaunchKernelGGL((scan_staged_kernel<ElemT, 25, CACHED, false>), grid, block, 0, stream, a); break;
+        case 21: hipLaunchKernelGGL((scan_staged_kernel<ElemT, 21, CACHED, false>), grid, block, 0, stream, a); break;
+        case 17: hipLaunchKernelGGL((scan_staged_kernel<ElemT, 17, CACHED, false>), grid, block, 0, stream, a); break;
+        default: hipLaunchKernelGGL((scan_staged_kernel<ElemT, kScanStagedShort, false, false>), grid, block, 0, stream, a); break;
     }
 }
 
@@ -759,16 +805,21 @@ template <typename ElemT>
 static void scan_launch(const ScanArgs& a, const ScanPlan& p, hipStream_t stream)
 {
     const dim3 grid((uint32_t)p.grid), block(kThreads);
-    if (p.chunks > 1) {
+    if (p.chunks > 1 && !p.walk) {
         const int64_t words = (int64_t)(p.bytes / sizeof(unsigned long long));
         const int64_t groups = ceil_div(words, kThreads);
         hipLaunchKernelGGL(scan_clear_kernel, dim3((uint32_t)(groups < 4096 ? groups : 4096)), block, 0, stream,
                            a.words, words);
     }
+    if (p.walk) {
+        if (p.staged) hipLaunchKernelGGL((scan_staged_kernel<ElemT, kScanStagedWalk, false, true>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((scan_direct_kernel<ElemT, kScanLong, true>), grid, block, 0, stream, a);
+        return;
+    }
     if (p.staged && p.cached) scan_launch_staged<ElemT, true>(a, p, stream);
     else if (p.staged) scan_launch_staged<ElemT, false>(a, p, stream);
-    else if (p.k == kScanLong) hipLaunchKernelGGL((scan_direct_kernel<ElemT, kScanLong>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((scan_direct_kernel<ElemT, kScanShort>), grid, block, 0, stream, a);
+    else if (p.k == kScanLong) hipLaunchKernelGGL((scan_direct_kernel<ElemT, kScanLong, false>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((scan_direct_kernel<ElemT, kScanShort, false>), grid, block, 0, stream, a);
 }
 
 }  // namespace bload
@@ -795,11 +846,15 @@ extern "C" bload_status bload_segment_scan(const void* d_packed, const uint8_t* 
     if (!d_packed || !d_reset || !d_valid || !d_out) return BLOAD_EINVAL;
     if (!aligned_to(d_packed, 16) || !aligned_to(d_out, 16)) return BLOAD_EALIGN;
     if (num_blocks * (int64_t)t_blk >= ((int64_t)1 << 40)) return BLOAD_EOVERFLOW;
-    const ScanPlan p = scan_plan(num_blocks, t_blk, feat_dim, scan_elem_bytes(dtype));
-    if (p.bytes > 0) {
-        if (!d_workspace) return BLOAD_EINVAL;
-        if (!aligned_to(d_workspace, 16)) return BLOAD_EALIGN;
-        if (workspace_bytes < p.bytes) return BLOAD_EWORKSPACE;
+    ScanPlan p = scan_plan(num_blocks, t_blk, feat_dim, scan_elem_bytes(dtype));
+    if (p.bytes > 0 && (!d_workspace || !aligned_to(d_workspace, 16) || workspace_bytes < p.bytes)) {
+        const size_t least = std::min(p.bytes, scan_least_bytes(num_blocks, t_blk, feat_dim, scan_elem_bytes(dtype)));
+        if (least > 0) {
+            if (!d_workspace) return BLOAD_EINVAL;
+            if (!aligned_to(d_workspace, 16)) return BLOAD_EALIGN;
+            if (workspace_bytes < least) return BLOAD_EWORKSPACE;
+        }
+        p = scan_plan(num_blocks, t_blk, feat_dim, scan_elem_bytes(dtype), true);
     }
     if (p.grid > 0x7fffffffLL) return BLOAD_EOVERFLOW;
 
@@ -821,7 +876,7 @@ extern "C" bload_status bload_segment_scan(const void* d_packed, const uint8_t* 
     a.slices = p.slices;
     a.frame_units = p.frame_units;
     a.by_xcd = p.by_xcd ? 1 : 0;
-    a.group = p.chunks > 1 ? (int32_t)std::min<int64_t>(kScanGroup, p.n_units) : 1;
+    a.group = p.chunks > 1 && !p.walk ? (int32_t)std::min<int64_t>(kScanGroup, p.n_units) : 1;
     a.polls = BLOAD_SCAN_POLLS;
     a.decay = decay;
     double power = pow((double)decay, (double)p.k);

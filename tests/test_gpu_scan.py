@@ -211,6 +211,39 @@ def test_scan_infinite_states(T, D):
         assert (got[0, :last] == 1).all() and np.isposinf(got[0, last]).all() and np.isnan(got[0, last + 1:]).all()
 
 
+# Less workspace than asked for, down to what is accepted (`room` bytes): a workgroup walks its block tile by tile.
+# Frames under and from 64 elements on, one slice and several, blocks of two tiles and of many, the last one short.
+@pytest.mark.parametrize("B,T,D,dtype,room", [(6144, 140, 63, "f32", 0), (12288, 270, 31, "u8", 0), (3072, 280, 130, "f32", 0),
+                                              (700, 300, 63, "f32", 531312), (40, 1000, 4100, "f16", 1312080),
+                                              (3, 4500, 1000, "f16", 744192), (6143, 140, 63, "f16", 1554192)])
+def test_scan_with_less_workspace_than_asked_for(B, T, D, dtype, room):
+    bl = binding()
+    asked = bl.bload_segment_scan_workspace_bytes(B, T, D, dtype)
+    assert room < asked
+    rng = np.random.default_rng(B + T + D)
+    for (p_valid, p_reset), decay in zip([(1.0, 0.0), (0.97, 0.01)], [0.999, -0.5]):
+        valid, reset, _, _ = random_flags(rng, B, T, p_valid, p_reset)
+        src = draw_source(rng, B * T, D, dtype)
+        ref, scale = oracle.segment_scan_packed(src, reset, valid, D, dtype, decay)
+        x, r, v = to_dev(src.view(np.uint8).reshape(-1)), to_dev(reset), to_dev(valid)
+        print(f"room {room} of {asked}: B={B} T={T} D={D} {dtype}", flush=True)
+        for take in (room, room - 1):
+            out = torch.full((B, T, D), float("nan"), dtype=torch.float32, device="cuda")
+            ws = torch.empty(max(room, 16), dtype=torch.uint8, device="cuda")
+            st = bl._lib.bload_segment_scan(x.data_ptr(), r.data_ptr(), v.data_ptr(), B, T, D, bl.DTYPES[dtype], decay,
+                                            out.data_ptr(), ws.data_ptr() if take > 0 else None, max(take, 0),
+                                            torch.cuda.current_stream().cuda_stream)
+            if take < room and room > 0:
+                assert st == bl.EWORKSPACE
+                continue
+            assert st == bl.OK
+            got = out.cpu().numpy()
+            assert not got[valid == 0].any()
+            assert_scan_close(got, ref, scale, f"{dtype} B={B} T={T} D={D}")
+            if D >= 64:                                    # the same stretches: the same bits
+                assert np.array_equal(got.view(np.int32), gpu_scan(src, reset, valid, D, dtype, decay).view(np.int32))
+
+
 def test_scan_closed_forms_and_determinism():
     bl = binding()
     B, T, D = 7, 200, 64
