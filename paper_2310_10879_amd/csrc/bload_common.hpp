@@ -31,7 +31,8 @@ inline bload_status launch_status()
 // until the process ends; null if it cannot be had.  An entry point whose caller waits for a few
 // numbers lets its last kernel write them there, so that only the wait for the stream follows
 // the launches (a copy back from device memory costs about 9 us more per call).  Only for plain
-// stores by one kernel: nothing that kernels read back or update atomically.
+// stores by the last kernels of a call, each word by one of them: nothing that kernels read back or update
+// atomically.
 inline void* host_result_buffer()
 {
     static thread_local void* mem = nullptr;
@@ -71,6 +72,19 @@ __device__ __forceinline__ vec16 load_stream(const vec16* p)
 __device__ __forceinline__ void store_stream(vec16* p, vec16 v)
 {
     __builtin_nontemporal_store(v, p);
+}
+
+// Bit j of the result: byte j of the 16 flag bytes is non-zero.
+__device__ __forceinline__ uint32_t nonzero_bytes16(vec16 w)
+{
+    // 0x80 in every non-zero byte; a dot product with byte weights 1, 2, 4, 8 (16 ... 128 for the
+    // next four bytes) then puts one bit per byte side by side, seven places up
+    uint32_t t[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) t[k] = (((w[k] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w[k]) & 0x80808080u;
+    const uint32_t lo = __builtin_amdgcn_udot4(t[1], 0x80402010u, __builtin_amdgcn_udot4(t[0], 0x08040201u, 0u, false), false);
+    const uint32_t hi = __builtin_amdgcn_udot4(t[3], 0x80402010u, __builtin_amdgcn_udot4(t[2], 0x08040201u, 0u, false), false);
+    return (lo >> 7) | ((hi >> 7) << 8);
 }
 
 // ---- moves between the lanes of a wavefront without LDS traffic (DPP) --------------

@@ -378,7 +378,7 @@ static RfLayout rf_layout(int64_t n_seq)
     l.seeded_len = take(n * 4);
     l.entry = take(n * 4);
     l.pick = take(n * sizeof(RfPick));
-    take(n * 8);              // unused: the size stays 28 bytes per sequence, which callers' buffers are made for
+    take(n * 8);              // not used: the answer stays at the 28 bytes per sequence that the layout always had
     l.first = take((size_t)kRfMaxT * 4);
     l.within = take((size_t)kRfGroups * kRfStride * 4);
     l.group_before = take((size_t)kRfGroups * 4);

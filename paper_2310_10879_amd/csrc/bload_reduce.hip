@@ -14,14 +14,15 @@
 // small kernel adds tail + following heads in time order.  Fixed chunking and
 // fixed order make the float32 result bit-reproducible.
 //
-// Two layouts of the work:
-//   wide   (a frame is >= 64 bytes): lanes across the features of a frame, 16 bytes each, each
-//          row of lanes (at most one wave) walks one chunk of time serially
-//          with several loads in flight, restarting its accumulators at every
-//          start flag.
-//   narrow (small frames, e.g. one token): lanes across time, 16 consecutive
-//          slots per lane, segmented scan over the workgroup with the segment
-//          breaks as heads and a carry between lanes and waves.
+// Three layouts of the work (reduce_plan draws the lines between them):
+//   wide    frames of 64 bytes or more: a row of lanes (at most one wave) lies across the features of a frame, 16
+//           bytes to a lane, or 4, or one element where frames are no whole vectors or workgroups too few;
+//           each row walks one chunk of time serially with several loads in flight, restarting its
+//           accumulators at every start flag.
+//   staged  frames of 2 to 63 elements that are smaller, or of which wide rows would be too few workgroups: a tile of
+//           slots goes through LDS as whole vectors, and each lane then sums 9 or 17 slots of one feature.
+//   narrow  frames of one element that are not wide: lanes across time, 16 consecutive slots per lane, segmented scan
+//           over the workgroup with the segment breaks as heads and a carry between lanes and waves.
 #include "bload_common.hpp"
 
 #include <hip/hip_fp16.h>
@@ -483,19 +484,6 @@ struct SegMove {
         return SegState<Acc>{dpp_move<CTRL, ROW_MASK>(s.sum, (Acc)0), dpp_move<CTRL, ROW_MASK>(s.any, 0u)};
     }
 };
-
-// Bit j of the result: byte j of the 16 flag bytes is non-zero.
-__device__ __forceinline__ uint32_t nonzero_bytes16(vec16 w)
-{
-    // 0x80 in every non-zero byte; a dot product with byte weights 1, 2, 4, 8 (16 ... 128 for the
-    // next four bytes) then puts one bit per byte side by side, seven places up
-    uint32_t t[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) t[k] = (((w[k] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w[k]) & 0x80808080u;
-    const uint32_t lo = __builtin_amdgcn_udot4(t[1], 0x80402010u, __builtin_amdgcn_udot4(t[0], 0x08040201u, 0u, false), false);
-    const uint32_t hi = __builtin_amdgcn_udot4(t[3], 0x80402010u, __builtin_amdgcn_udot4(t[2], 0x08040201u, 0u, false), false);
-    return (lo >> 7) | ((hi >> 7) << 8);
-}
 
 // The flag bytes of 16 consecutive slots, asked for with loads that stay inside the planes of
 // `total` slots wherever the slots lie (planes of fewer than 16 slots are read byte by byte).
@@ -1287,7 +1275,7 @@ struct ReducePlan {
     bool wide, staged;
     bool run;                // staged: a workgroup takes the tiles of a whole chunk one after another
     int32_t tile;            // of this many slots
-    int vec;                 // wide: elements per lane (16 / elem size)
+    int vec;                 // wide: elements per lane (16 bytes, 4 bytes or one element)
     int row_lanes_log2;
     int n_vec;
     int32_t chunk, n_chunks;

@@ -544,17 +544,6 @@ __global__ __launch_bounds__(kThreads, sizeof(ElemT) == 4 ? 2 : 3) void scan_dir
     } while (WALK && ++tile.c < a.chunks);
 }
 
-// Bit j: byte j of the 16 flag bytes is non-zero.
-__device__ __forceinline__ uint32_t scan_nonzero16(vec16 w)
-{
-    uint32_t t[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) t[k] = ((((w[k] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w[k]) >> 7) & 0x01010101u;
-    const uint32_t lo = __builtin_amdgcn_udot4(t[1], 0x80402010u, __builtin_amdgcn_udot4(t[0], 0x08040201u, 0u, false), false);
-    const uint32_t hi = __builtin_amdgcn_udot4(t[3], 0x80402010u, __builtin_amdgcn_udot4(t[2], 0x08040201u, 0u, false), false);
-    return lo | (hi << 8);
-}
-
 // The flags of the 16 slots from g on, of which `left` lie in the tile: one load that stays inside
 // the plane of `total` slots (a plane of fewer than 16 is read byte by byte).
 __device__ __forceinline__ uint32_t scan_flags16(const uint8_t* __restrict__ plane, int64_t g, int32_t left, int64_t total)
@@ -563,7 +552,7 @@ __device__ __forceinline__ uint32_t scan_flags16(const uint8_t* __restrict__ pla
     const uint32_t in_tile = left >= 16 ? 0xffffu : (1u << left) - 1u;
     if (total >= 16) {
         const int64_t from = min(g, total - 16);
-        return (scan_nonzero16(*reinterpret_cast<const vec16_any*>(plane + from)) >> (int)(g - from)) & in_tile;
+        return (nonzero_bytes16(*reinterpret_cast<const vec16_any*>(plane + from)) >> (int)(g - from)) & in_tile;
     }
     uint32_t m = 0;
     for (int j = 0; j < left && j < 16; ++j) m |= (uint32_t)(plane[g + j] != 0) << j;
