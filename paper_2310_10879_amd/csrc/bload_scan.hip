@@ -18,6 +18,8 @@
 //     decay^chunk * state + partial.  It publishes its own end state: partial while it waits, final then
 //   - the recurrence over the tile's own slots from that state, kept in registers meanwhile, is
 //     what leaves for the output
+// (The hand-over is the decoupled look-back of Merrill and Garland's single-pass scan, here with boundaries that make
+// most states final at once, and with an end to the wait.)
 // A state travels as a double whose last two mantissa bits are its mark (partial / final): one 8-byte
 // word, written and read by atomics of device scope, so no order between different words is needed.
 // Every state is cut to 50 mantissa bits when it is made, and the states are combined in the
@@ -26,8 +28,9 @@
 // 6.36e-8 instead of 6.17e-8 of the recurrence from end to end).
 // Tiles that wait hold their registers, so the order of the tiles is that of memory only in
 // the large: 32 blocks are taken side by side, chunk by chunk, and the tile in front has mostly
-// finished (6900 blocks of 3000 slots x 320 bytes: 3.75 ms block by block, 2.75 with 8 side by
-// side, 2.41 with 32 as with 128; without any hand-over, which is not the right result, 2.39).
+// finished (6900 blocks of 3000 slots x 320 bytes, one run on other pages than the figures below: 3.75 ms block by
+// block, 2.75 with 8 side by side, 2.41 with 32 as with 128; without any hand-over, which is not the
+// right result, 2.39).
 //
 // The wait ends.  A tile waits only for tiles in front of it in the same block, which publish
 // their partial state without waiting for anything and have lower workgroup numbers on the same
@@ -41,9 +44,9 @@
 //                       behind the other in time
 //   scan_staged_kernel  smaller frames, whose rows are too short to be read lane by lane: the
 //                       tile goes through LDS in both directions, whole 16-byte vectors to
-//                       and from memory
+//                       and from memory; a lane holds 9 to 33 slots, by what fills the tile
 // Measured against the form before (a row of lanes walking a stretch of time, behind a pass over
-// the open ends of the stretches): 6900 blocks of 3000 x 80 floats 3.05 -> 2.21 ms (5.3 TB/s),
+// the open ends of the stretches): 6900 blocks of 3000 x 80 floats 3.07 -> 2.32 ms (5.0 TB/s),
 // 79 blocks of 3000 x 2048 halfs 0.62 -> 0.49 ms, 300 videos of 37632 bytes a frame 1.34 -> 1.04 ms,
 // 1.5 * 10^8 slots of one float 6.9 -> 0.26 ms, 37 halfs a frame 0.74 -> 0.63 ms.
 #include "bload_common.hpp"
