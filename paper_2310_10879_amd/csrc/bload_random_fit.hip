@@ -168,47 +168,39 @@ __global__ __launch_bounds__(kRfOffsetThreads) void rf_offsets_kernel(
 }
 
 // Step 3, one workgroup per chunk: its sequences into their lists, in seeded order: tile by
-// tile of 256 positions, each thread ranking its sequence among the equal lengths before it
-// in the tile.
+// tile of 256 positions.  The lanes of a wave that hold the same length find each other by votes on its bits, and the
+// waves take their places in the lists one after another.  (Each thread ranking itself among the keys in front, read
+// from LDS, took 7 us a tile: 29 us at 10^4 sequences.)
 __global__ __launch_bounds__(kThreads) void rf_scatter_kernel(
     const int32_t* __restrict__ seeded, const int32_t* __restrict__ seeded_len, int32_t n_seq,
     int32_t t_blk, int32_t per_chunk, const int32_t* __restrict__ chunk_start, int32_t* __restrict__ entry)
 {
     __shared__ int32_t s_fill[kRfMaxT];         // next free place of every list, for this chunk
-    __shared__ alignas(16) int32_t s_key[kThreads];
-    const int tid = (int)threadIdx.x;
+    const int tid = (int)threadIdx.x, lane = lane_id(), wave = wave_id();
     const int lengths_kept = ((t_blk + kWave - 1) / kWave) * kWave;
+    const int bits = 32 - __clz(t_blk);
     for (int e = tid; e < lengths_kept; e += kThreads) s_fill[e] = chunk_start[(int64_t)blockIdx.x * kRfMaxT + e];
-    __syncthreads();
     const int64_t lo = (int64_t)blockIdx.x * per_chunk;
     const int64_t hi = min((int64_t)n_seq, lo + per_chunk);
     for (int64_t tile = lo; tile < hi; tile += kThreads) {
         const int64_t p = tile + tid;
         const int32_t len = p < hi ? seeded_len[p] : 0;
-        s_key[tid] = len;
-        __syncthreads();
-        int32_t rank = 0;
-        // four keys a look-up; only those of the waves up to this one can be in front
-        typedef int32_t int4v __attribute__((ext_vector_type(4)));
-        const int4v* key4 = reinterpret_cast<const int4v*>(s_key);
-        for (int w = 0; w <= wave_id(); ++w) {
-#pragma unroll
-            for (int t4 = 0; t4 < kWave / 4; ++t4) {
-                const int4v key = key4[w * (kWave / 4) + t4];
-                const int t = w * kWave + 4 * t4;
-                rank += (key[0] == len) & (t < tid);
-                rank += (key[1] == len) & (t + 1 < tid);
-                rank += (key[2] == len) & (t + 2 < tid);
-                rank += (key[3] == len) & (t + 3 < tid);
+        const int32_t sequence = p < hi ? seeded[p] : 0;
+        uint64_t same = ~0ull;                   // the lanes with this length
+        for (int b = 0; b < bits; ++b) {
+            const bool one = (len >> b) & 1;
+            const uint64_t vote = __ballot(one);
+            same &= one ? vote : ~vote;
+        }
+        const int rank = (int)__popcll(same & ((1ull << lane) - 1ull));
+        for (int w = 0; w < kThreads / kWave; ++w) {
+            __syncthreads();
+            if (wave == w && len) {
+                const int32_t at = s_fill[len - 1] + rank;
+                if ((same >> lane) == 1ull) s_fill[len - 1] = at + 1;        // the last of them
+                entry[at] = sequence;
             }
         }
-        const int32_t at = len ? s_fill[len - 1] + rank : 0;
-        __syncthreads();
-        if (len) {
-            entry[at] = seeded[p];
-            atomicAdd(&s_fill[len - 1], 1);
-        }
-        __syncthreads();
     }
 }
 
