@@ -3,8 +3,9 @@
 // among those no longer than the frames remaining in the open block).
 //
 // The draws are a chain: what fits, and how many of each length are left, depends on
-// every earlier draw.  So the chain itself runs on ONE wavefront and is kept as short
-// as the hardware allows, and everything around it is parallel:
+// every earlier draw.  So the draws are made by one workgroup that guesses many at a time and
+// goes over them until the guesses are right, or, where that does not pay, by ONE wavefront
+// whose chain is kept as short as the hardware allows, and everything around is parallel:
 //   rf_order_kernel    seeded position p -> sequence, its length, checks, frame total
 //   rf_count_kernel, rf_offsets_kernel, rf_scatter_kernel
 //                      L_dict: where each length's list starts, the lists themselves in
@@ -12,8 +13,9 @@
 //                      seeded positions are cut into chunks, one workgroup each, that
 //                      count their lengths, learn where their part of every list
 //                      begins, and fill it in order
-//   rf_draw_kernel     the chain: per placement only (length, rank in its list, block,
-//                      offset) - no global load on the chain
+//   rf_draw_batches_kernel, rf_draw_kernel
+//                      the draws: per placement only (length, free room, how many were left) - no
+//                      global load on the chain
 //   rf_assign_kernel   placement p -> sequence, and the per-sequence tables
 //
 // Counts per length live as two levels of running sums: inside groups of 64 lengths
@@ -38,6 +40,11 @@ struct RfPick {
     int32_t left;         // how many of that length were left: it takes the last of them
 };
 static_assert(kRfMaxT <= 1 << 15, "lengths and offsets, counted from 0, take 15 bits");
+
+// Where the chain of draws goes on behind those that were made in batches.
+struct RfState {
+    int32_t placed, blocks;   // draws made, blocks that they fill
+};
 
 __global__ void rf_clear_kernel(PlanResult* result)
 {
@@ -173,7 +180,8 @@ __global__ __launch_bounds__(kRfOffsetThreads) void rf_offsets_kernel(
 // from LDS, took 7 us a tile: 29 us at 10^4 sequences.)
 __global__ __launch_bounds__(kThreads) void rf_scatter_kernel(
     const int32_t* __restrict__ seeded, const int32_t* __restrict__ seeded_len, int32_t n_seq,
-    int32_t t_blk, int32_t per_chunk, const int32_t* __restrict__ chunk_start, int32_t* __restrict__ entry)
+    int32_t t_blk, int32_t per_chunk, const int32_t* __restrict__ chunk_start, int32_t* __restrict__ entry,
+    uint16_t* __restrict__ sorted_len)
 {
     __shared__ int32_t s_fill[kRfMaxT];         // next free place of every list, for this chunk
     const int tid = (int)threadIdx.x, lane = lane_id(), wave = wave_id();
@@ -199,10 +207,40 @@ __global__ __launch_bounds__(kThreads) void rf_scatter_kernel(
                 const int32_t at = s_fill[len - 1] + rank;
                 if ((same >> lane) == 1ull) s_fill[len - 1] = at + 1;        // the last of them
                 entry[at] = sequence;
+                sorted_len[at] = (uint16_t)len;
             }
         }
     }
 }
+
+// ---- the draws --------------------------------------------------------------------
+//
+// Two ways to make them, with the same result: many at a time by a workgroup as long as that pays,
+// and one after another by one wavefront.
+//
+// Many at a time.  The sequences left are kept as a list of their lengths in ascending order (`len`)
+// with, per length, how many are not longer (`upto`).  Draw i of a batch of 64 then is, with j over
+// the draws in front of it in the batch and ranks counted in the list as the batch finds it:
+//   fit_i  = upto[room_i] - #{j < i: rank_j < upto[room_i]}     (none fits: a new block, all left fit)
+//   k_i    = floor(u_i * fit_i / 2^64)
+//   rank_i = k_i + #{j < i: rank_j <= rank_i}                   (the k-th of those not yet taken)
+//   room_(i+1) = room_i - len[rank_i]
+// All 64 are guessed, the right sides computed from the guesses, and that again with what came out until
+// nothing changes.  A value that depends on right values in front of it alone is right, so after every
+// round the draws up to the first one that changed are exactly those of the chain: the rounds end, and
+// how many they are only depends on how far a wrong guess is carried on.  10^4 sequences of heavy-tailed
+// lengths take 5 rounds per 64 draws, lengths near the block's 3, lengths spread evenly over it 20 to 40, and 6 where
+// blocks are guessed ahead (below).
+// (rank_i is a fixed point of its own equation as well.  One on a rank already taken can be reached from
+// above only and has nothing but taken ranks down to the right one: it is then lowered by one.)
+// Bound by latency, like the chain: a round is 0.6 us of some 180 dependent instructions and three look-ups in LDS, on a
+// workgroup whose 8 waves share the counting (64 x 63 / 2 comparisons of two limits, 16 bits each); what follows the
+// rounds of a batch (taking the ranks out of the list and the counts) 2.6 us; 64 draws one after another 14 us.  Whole
+// call, before and after, 10^4 sequences in blocks of 3000: heavy-tailed lengths 2258 -> 915 us, nearly full blocks
+// 3540 -> 700, clips 3130 -> 1500; lengths spread evenly, which give up after the trial, 3060 -> 3025.
+//
+// One after another (rf_draw_kernel): what is left where batches cost more than they bring, and sequences beyond
+// kRfBatchMost.
 
 // The chain of draws, on one wavefront, everything wave-uniform except: the running sums of a
 // group's lengths (a row: lane j holds how many of the group's first j + 1 lengths are left),
@@ -219,13 +257,15 @@ __global__ __launch_bounds__(kThreads) void rf_scatter_kernel(
 // picked with an indexed register move, which saves the two waits for LDS of a draw (256 -> 233 ns);
 // more than 32 registers cannot be indexed as one, and choosing between two sets costs more
 // instructions than the waits (83 in all, 270 ns).  GROUPS_HI: more than 64 groups (t_blk > 4096).
+// With `state`, the draws behind it, which begin with a block of their own; the values that the loop begins with are
+// all there is to that (a flag in the loop, or the loop behind the batches in one kernel: 7 to 13 % slower).
 constexpr int kRfRegisterRows = 32;
 typedef int32_t rf_rows __attribute__((ext_vector_type(kRfRegisterRows)));
 
 template <bool REGISTERS, bool GROUPS_HI>
 __global__ __launch_bounds__(kWave) void rf_draw_kernel(
-    const int32_t* __restrict__ within, const int32_t* __restrict__ group_before, int32_t n_seq,
-    int32_t t_blk, uint64_t seed, RfPick* __restrict__ pick, int32_t* __restrict__ block_first,
+    const int32_t* __restrict__ within, const int32_t* __restrict__ group_before, const RfState* __restrict__ state,
+    int32_t n_seq, int32_t t_blk, uint64_t seed, RfPick* __restrict__ pick, int32_t* __restrict__ block_first,
     PlanResult* __restrict__ result, PlanResult* __restrict__ host_result)
 {
     __shared__ int32_t s_rows[REGISTERS ? 1 : (GROUPS_HI ? kRfGroups : kWave) * kWave];
@@ -247,13 +287,23 @@ __global__ __launch_bounds__(kWave) void rf_draw_kernel(
         if (lane == 0 && host_result) host_result->bad_length = bad;
         return;
     }
+    const RfState from = state ? *state : RfState{0, 0};
+    if (from.placed == n_seq) return;                    // the batches were all
 
     // Every block takes at least one sequence (all of them fit an empty block), every placement
     // uses up room, and at most n_seq blocks are begun: the loop ends whatever the sums hold.
-    int32_t placed = 0, blocks = 0;
+    int32_t placed = from.placed, blocks = from.blocks;
     int32_t last = -1;                                   // the longest length that fits, counted from 0; -1: none
     uint32_t u_lo = 0, u_hi = 0;
     int32_t kept_where = 0, kept_left = 0;               // placement (placed & ~63) + lane
+    if (placed > 0) {
+        const uint64_t u = splitmix64_at(seed, (uint64_t)(6 + (placed & ~(kWave - 1)) + lane));
+        u_lo = (uint32_t)u;
+        u_hi = (uint32_t)(u >> 32);
+        const RfPick k = pick[((placed - 1) & ~(kWave - 1)) + lane];     // (those behind `placed` mean nothing yet)
+        kept_where = k.where;
+        kept_left = k.left;
+    }
     while (placed < n_seq && blocks < n_seq && last >= -1) {
       if (lane == 0) block_first[blocks] = placed;
       blocks += 1;
@@ -326,6 +376,353 @@ __global__ __launch_bounds__(kWave) void rf_draw_kernel(
     }
 }
 
+constexpr int kRfBatch = kWave;                   // draws at a time, a lane each
+constexpr int kRfBatchWaves = 8;                  // two per SIMD hide each other's latencies
+constexpr int kRfBatchThreads = kRfBatchWaves * kWave;
+constexpr int kRfBatchMost = 24576;               // sequences: two lists of them fit the LDS
+constexpr int kRfBatchLeast = 768;                // a trial that brings nothing and the second launch cost 8 us
+// The first batch is a trial: it ends, with nothing drawn, if after so many rounds not so many of its draws are settled.
+// Of many sequences it is guessed ahead and lasts longer, which costs 10 us where it fails: 1 % of 4096 draws.
+constexpr int kRfTryRounds = 4, kRfTryDraws = 6, kRfTryLong = 8, kRfTryLongDraws = 16, kRfTryLongFrom = 4096;
+constexpr int kRfBatchRounds = 48;                // of a batch, before what is settled of it is taken
+constexpr int kRfGuessSteps = 16;                 // draws that a guess of a block's contents goes ahead
+constexpr int kRfPlainBatches = 16;               // batches without one after one that told of less than half the draws
+constexpr int kRfGuessFrom = 8;                   // rounds of a batch from which on the next are guessed so
+// What a batch costs and brings, in units of 1/64 us: a round, the rest of a batch (and a unit for so many entries of the
+// lists), a step of a guess; a draw of the chain.
+constexpr int kRfCostRound = 40, kRfCostBatch = 100, kRfCostEntries = 120, kRfCostGuess = 16, kRfCostDraw = 15;
+
+struct RfShared {
+    alignas(16) uint16_t len[2][kRfBatchMost + 8 * kWave];   // lengths that are left, ascending
+    alignas(16) uint16_t upto[kRfMaxT + 8];              // [7 + l]: sequences left of at most length l
+    unsigned long long gone[kRfBatchMost / 64 + 1];      // ranks that the batch takes, a bit each
+    uint2 taken[kRfBatchMost / 32 + 2];                  // the same, 32 ranks at a time: bits, and how many in front
+    uint32_t count[3][kRfBatch];                         // what the waves count, in turn; the next one is 0
+    unsigned long long random[kRfBatch];
+    uint16_t guess[kRfBatch][kRfGuessSteps];
+    uint16_t rank[kRfBatch];
+    unsigned long long opens;
+    int32_t known, steps;
+    uint16_t nowhere;                                    // where lengths that leave the list are stored
+};
+static_assert(sizeof(RfShared) <= 156 * 1024, "one workgroup's LDS");
+static_assert(kRfBatchWaves == 8 && kRfBatch == 64, "a wave counts eight draws");
+static_assert(kRfBatchMost < 1 << 15, "ranks and their limits are compared in 16 bits");
+
+struct RfMax { __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return max(a, b); } };
+struct RfMoveU {
+    template <int CTRL, int ROW_MASK>
+    __device__ __forceinline__ uint32_t at(uint32_t v) const { return dpp_move<CTRL, ROW_MASK>(v, 0u); }
+};
+
+typedef uint16_t rf_two __attribute__((ext_vector_type(2)));
+
+// One to each half of `sum` where the value in that half of `v` is below the one of `limits`.  (`one` is 1 in each
+// half, and not known to be: three packed instructions, not two comparisons and their bits put together.)
+__device__ __forceinline__ rf_two rf_add_below(rf_two sum, rf_two limits, uint32_t v, uint32_t one)
+{
+    return sum + __builtin_elementwise_min(__builtin_elementwise_sub_sat(limits, __builtin_bit_cast(rf_two, v)),
+                                           __builtin_bit_cast(rf_two, one));
+}
+
+// The wave's share of: how many of the draws in front of the lane's have a value below each of the two limits
+// (16 bits each, and so are the counts).  Wave w < 7 counts draws 8 w .. 8 w + 7 for the draws of later eights, the
+// last one the draws of the lane's own eight.
+__device__ __forceinline__ uint32_t rf_count_below(uint32_t value, uint32_t limits, int wave)
+{
+    const uint32_t both = value | value << 16;
+    uint32_t one = 0x10001u;
+    asm("" : "+v"(one));
+    rf_two sum = {0, 0};
+    if (wave < kRfBatchWaves - 1) {
+        const rf_two limit = __builtin_bit_cast(rf_two, lane_id() >= 8 * wave + 8 ? limits : 0u);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sum = rf_add_below(sum, limit, (uint32_t)__builtin_amdgcn_readlane((int)both, 8 * wave + j), one);
+    } else {
+        const rf_two limit = __builtin_bit_cast(rf_two, limits);
+        // (every lane moves, whatever becomes of it)
+        const uint32_t moved[7] = {dpp_move<kDppRowShr1>(both, ~0u), dpp_move<kDppRowShr1 + 1>(both, ~0u),
+                                   dpp_move<kDppRowShr1 + 2>(both, ~0u), dpp_move<kDppRowShr1 + 3>(both, ~0u),
+                                   dpp_move<kDppRowShr1 + 4>(both, ~0u), dpp_move<kDppRowShr1 + 5>(both, ~0u),
+                                   dpp_move<kDppRowShr1 + 6>(both, ~0u)};
+#pragma unroll
+        for (int j = 0; j < 7; ++j) sum = rf_add_below(sum, limit, (lane_id() & 7) > j ? moved[j] : ~0u, one);
+    }
+    return __builtin_bit_cast(uint32_t, sum);
+}
+
+// The sum of the waves' counts of the lane's draw; one barrier.  `turn` goes round over three sets, so that one is
+// cleared while another one is added to and the third may still be read.
+__device__ __forceinline__ uint32_t rf_all_counts(RfShared& sh, uint32_t mine, int wave, int& turn)
+{
+    const int lane = lane_id(), next = turn == 2 ? 0 : turn + 1;
+    atomicAdd(&sh.count[turn][lane], mine);
+    if (wave == kRfBatchWaves - 2) sh.count[next][lane] = 0;
+    __syncthreads();
+    const uint32_t all = sh.count[turn][lane];
+    turn = next;
+    return all;
+}
+
+// Every wave holds all 64 draws, a lane each, and does the same with them; a wave by itself only counts over its
+// eight draws, and moves its part of the list.
+__global__ __launch_bounds__(kRfBatchThreads) void rf_draw_batches_kernel(
+    const uint16_t* __restrict__ sorted_len, int32_t* __restrict__ within, int32_t* __restrict__ group_before,
+    RfState* __restrict__ state, int32_t n_seq, int32_t t_blk, uint64_t seed, RfPick* __restrict__ pick, int32_t* __restrict__ block_first,
+    PlanResult* __restrict__ result, PlanResult* __restrict__ host_result)
+{
+    __shared__ RfShared sh;
+    const int tid = (int)threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(wave_id());
+    const int32_t bad = result->bad_length;
+    if (bad) {
+        if (tid == 0 && host_result) host_result->bad_length = bad;
+        return;
+    }
+    const int groups = (t_blk + kWave - 1) / kWave, kept = groups * kWave;
+    const uint16_t* upto = sh.upto + 7;
+    for (int e = tid; e < kept; e += kRfBatchThreads)
+        sh.upto[8 + e] = (uint16_t)(group_before[e >> 6] + within[(e >> 6) * kRfStride + (e & 63) + 1]);
+    if (tid == 0) sh.upto[7] = 0;
+    for (int i = tid; i < (n_seq + 7) / 8; i += kRfBatchThreads)
+        reinterpret_cast<vec16*>(sh.len[0])[i] = reinterpret_cast<const vec16*>(sorted_len)[i];
+    for (int w = tid; w <= n_seq / 64; w += kRfBatchThreads) sh.gone[w] = 0;
+    if (tid < kRfBatch) {
+        sh.random[tid] = splitmix64_at(seed, (uint64_t)(6 + tid));
+        sh.count[0][tid] = 0;
+    }
+    __syncthreads();
+
+    int cur = 0, turn = 0;
+    int32_t placed = 0, blocks = 0;
+    int32_t room = 0;                                    // in the open block, in front of the batch (no block yet: 0)
+    int32_t left = n_seq;                                // sequences
+    int32_t credit = 2 * 64 + n_seq / 8;                 // batches may cost some 1 % of a chain of all draws
+    const int32_t most_credit = credit + 4 * 64;
+    const bool long_try = n_seq >= kRfTryLongFrom;
+    bool guesses = long_try;
+    int plain = 0;                                       // batches to come that are not guessed ahead
+    bool enough = false;                                 // the rest is drawn one after another
+    while (left > 0 && !enough) {
+        const uint16_t* len = sh.len[cur];
+        const int32_t w = min(kRfBatch, left);
+        const uint64_t in_batch = w == 64 ? ~0ull : (1ull << w) - 1ull;
+        // The first guess: all that is left fits, and of the draws in front the usual share lies below.
+        // Of the lane's draw: `rank`, `length`, and whether it `opens` a block.
+        const uint64_t u = sh.random[lane];
+        const uint32_t u_lo = (uint32_t)u, u_hi = (uint32_t)(u >> 32);
+        int32_t rank, length;
+        const bool opens_first = upto[room] == 0;
+        bool opens = lane == 0 && opens_first;
+        const float per_draw = __builtin_amdgcn_rcpf((float)left);
+        {
+            const int32_t k = (int32_t)__umulhi(u_hi, (uint32_t)max(left - lane, 1));
+            rank = min(k + (int32_t)((float)k * ((float)lane * per_draw)), left - 1);
+        }
+        const bool ahead = guesses && plain == 0;
+        if (ahead) {
+            // Every lane draws the contents of a block that begins with its draw (the first: that goes
+            // on with it), from counts that the batch does not lower.  The blocks that follow one
+            // another from the first draw on are then the guess.
+            if (wave == 0) {
+                int32_t free = lane == 0 && !opens_first ? room : t_blk, at = lane;
+                int step = 0;
+#pragma nounroll
+                for (; step < kRfGuessSteps; ++step) {
+                    const bool draws = at < w && free > 0 && at - lane == step;
+                    const int32_t all = draws ? (int32_t)upto[free] : 0;
+                    const float part = (float)at * per_draw;
+                    const int32_t fit = all - (int32_t)((float)all * part);
+                    if (__ballot(draws && fit > 0) == 0) break;
+                    if (draws && fit > 0) {
+                        const int32_t k = (int32_t)__umulhi((uint32_t)(sh.random[at] >> 32), (uint32_t)fit);
+                        const int32_t r = min(k + (int32_t)((float)k * part), left - 1);
+                        sh.guess[lane][step] = (uint16_t)r;
+                        free = max(free - (int32_t)len[r], 0);
+                        at += 1;
+                    }
+                }
+                uint64_t heads = 0;
+                int32_t head = 0, known = 0;             // first draw of a block, draws guessed so far
+                while (head < w) {
+                    heads |= 1ull << head;
+                    known = __builtin_amdgcn_readlane(at, head);
+                    if (known <= head || known - head >= kRfGuessSteps) break;
+                    head = known;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                const int mine = 63 - __builtin_clzll(heads & (~0ull >> (63 - lane)));       // (draw 0 is a head)
+                sh.rank[lane] = lane < known ? sh.guess[mine][lane - mine] : (uint16_t)rank;
+                if (lane == 0) {
+                    sh.opens = (heads & ~1ull) | (opens_first ? 1ull : 0ull);
+                    sh.known = known;
+                    sh.steps = step;
+                }
+            }
+            __syncthreads();
+            rank = sh.rank[lane];
+            opens = (sh.opens >> lane) & 1ull;
+            if (sh.known < kRfBatch / 2) plain = kRfPlainBatches;        // blocks of many sequences: not worth it
+        } else if (plain > 0) {
+            plain -= 1;
+        }
+        length = len[rank];
+
+        int32_t accepted = 0, room_at, same = 0;
+        int rounds = 0, until = placed == 0 && !long_try ? kRfTryRounds : kRfTryLong;
+        for (;;) {
+            // rooms, from the lengths in front in the block: a block that begins at draw j is full when the sum
+            // reaches t_blk + the sum in front of j
+            const int32_t own = lane < w ? length : 0;
+            const int32_t sum = wave_scan(own, RfSum(), RfMove()), front = sum - own;
+            const uint32_t full = opens ? (uint32_t)(t_blk + front) : 0u;
+            const uint32_t full_at = dpp_move<kDppWaveShr1>(wave_scan(full, RfMax(), RfMoveU()), 0u);
+            room_at = max(max((int32_t)full_at, room) - front, 0);
+            const uint32_t all = upto[room_at];
+            // what the right sides give
+            const uint32_t count = rf_all_counts(sh, rf_count_below((uint32_t)rank, all | (uint32_t)(rank + 1) << 16, wave), wave, turn);
+            rounds += 1;
+            int32_t fit = (int32_t)(all - (count & 0xffffu));
+            const bool opening = fit <= 0;
+            if (opening) fit = max(left - lane, 1);
+            // floor(u * fit / 2^64), fit < 2^16
+            const int32_t k = (int32_t)(((uint64_t)u_hi * (uint32_t)fit + __umulhi(u_lo, (uint32_t)fit)) >> 32);
+            const int32_t now = min(k + (int32_t)(count >> 16), left - 1);
+            const uint64_t changed = __ballot((now != rank) | (opening != opens)) & in_batch;
+            int32_t lowered = 0;
+            if (changed == 0 || --until == 0) {
+                until = 8;
+                const int32_t settled = changed ? __builtin_ctzll(changed) : w;
+                if (placed == 0 && changed != 0 && rounds <= kRfTryLong && settled < (long_try ? kRfTryLongDraws : kRfTryDraws)) break;
+                const bool ends = changed == 0 || rounds >= kRfBatchRounds || settled < 2 * rounds;
+                if (ends) {
+                    // settled, unless a draw has come to rest on a rank that one in front has taken
+                    const bool mine = lane < settled;
+                    if (wave == 0 && mine) atomicOr(&sh.gone[rank >> 6], 1ull << (rank & 63));
+                    const uint32_t of_length = rf_count_below((uint32_t)length, (uint32_t)length | (uint32_t)(length + 1) << 16, wave);
+                    const uint32_t of_rank = rf_count_below((uint32_t)rank, (uint32_t)rank, wave) & 0xffffu;
+                    const uint32_t more = rf_all_counts(sh, (of_length & 0xffffu) | (of_length >> 16) << 8 | of_rank << 16, wave, turn);
+                    same = (int32_t)((more >> 8) & 0xffu) - (int32_t)(more & 0xffu);
+                    const uint64_t twice = __ballot(mine && (count >> 16) != (more >> 16));
+                    if (twice == 0) { accepted = settled; break; }
+                    __syncthreads();                     // (no wave reads `gone` before this batch is accepted)
+                    if (wave == 0 && mine) atomicAnd(&sh.gone[rank >> 6], ~(1ull << (rank & 63)));
+                    if (changed != 0 || rounds >= kRfBatchRounds) {
+                        accepted = __builtin_ctzll(twice);
+                        if (wave == 0 && lane < accepted) atomicOr(&sh.gone[rank >> 6], 1ull << (rank & 63));
+                        __syncthreads();
+                        break;
+                    }
+                    lowered = (int32_t)((twice >> lane) & 1ull);
+                }
+            }
+            rank = max(now - lowered, 0);
+            opens = opening;
+            length = len[rank];
+        }
+
+        if (accepted == 0) break;                        // (of the first batch only)
+        // Goes on while batches bring more than they cost, within what has been gained or was given.  The last draw of
+        // all batches is the last of its block.
+        credit += kRfCostDraw * accepted - kRfCostRound * rounds - kRfCostBatch - (left + kept) / kRfCostEntries -
+                  (ahead ? kRfCostGuess * sh.steps : 0);
+        credit = min(credit, most_credit);
+        // (a long trial says nothing about rounds without a guess)
+        guesses = !(placed == 0 && long_try) && (guesses || rounds >= kRfGuessFrom);
+        if (credit < 0 && accepted < left) {
+            const uint64_t begins = __ballot(opens && lane < accepted && lane > 0);
+            if (begins) {
+                const int32_t all = accepted;
+                accepted = 63 - __builtin_clzll(begins);
+                enough = true;
+                if (wave == 0 && lane >= accepted && lane < all) atomicAnd(&sh.gone[rank >> 6], ~(1ull << (rank & 63)));
+                __syncthreads();
+            }
+        }
+
+        // The draws settled leave the list: every length moves down by the ranks taken in front of it.  Eight
+        // consecutive ranks per lane, eight lanes to a word of `gone`.
+        const int32_t in_block = opens ? t_blk : room_at;
+        const uint64_t opened = __ballot(opens && lane < accepted);
+        const int32_t rank_taken = lane < accepted ? rank : INT32_MAX;
+        uint16_t* to = sh.len[cur ^ 1];
+        for (int32_t r0 = (kRfBatchWaves - 1 - wave) * (8 * kWave); r0 <= left; r0 += kRfBatchWaves * 8 * kWave) {
+            int32_t in_front = 0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int32_t c = (int32_t)__popcll(__ballot(rank_taken < r0 + i * 64));
+                if ((lane >> 3) == i) in_front = c;
+            }
+            const int32_t r = r0 + 8 * lane;
+            if (r <= left) {
+                const unsigned long long word = sh.gone[r >> 6];
+                const vec16 l = *reinterpret_cast<const vec16*>(len + r);
+                const uint32_t half = (r & 32) ? (uint32_t)(word >> 32) : (uint32_t)word;
+                if (r & 32) in_front += (int32_t)__popc((uint32_t)word);
+                if ((lane & 3) == 0) sh.taken[r >> 5] = make_uint2(half, (uint32_t)in_front);
+                int32_t at = r - in_front - (int32_t)__popc(half & ((1u << (r & 31)) - 1u));
+                const uint32_t bits = half >> (r & 31);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    // (without a branch)
+                    const bool stays = (bits & (1u << i)) == 0;
+                    uint16_t* place = stays ? to + at : &sh.nowhere;
+                    *place = (uint16_t)((i & 1) ? l[i / 2] >> 16 : l[i / 2]);
+                    at += stays ? 1 : 0;
+                }
+            }
+        }
+        if (wave == 0) {
+            if (lane < accepted) {
+                // how many of its length are left: of those that the batch finds, less the draws in front
+                pick[placed + lane] = RfPick{(length - 1) << 16 | (in_block - 1), (int32_t)upto[length] - (int32_t)upto[length - 1] - same};
+                if (opens) block_first[blocks + (int32_t)__popcll(opened & ((1ull << lane) - 1ull))] = placed + lane;
+            }
+        }
+        if (wave == 1) sh.random[lane] = splitmix64_at(seed, (uint64_t)(6 + placed + accepted + lane));
+        __syncthreads();
+        for (int e = 8 * tid; e < kept; e += 8 * kRfBatchThreads) {
+            vec16 counts = *reinterpret_cast<const vec16*>(sh.upto + 8 + e);
+            uint2 taken[8];                              // (all look-ups before the first use)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) taken[i] = sh.taken[((i & 1) ? counts[i / 2] >> 16 : counts[i / 2] & 0xffffu) >> 5];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t lo = counts[i] & 0xffffu, hi = counts[i] >> 16;
+                const uint32_t lo_now = lo - taken[2 * i].y - (uint32_t)__popc(taken[2 * i].x & ((1u << (lo & 31)) - 1u));
+                const uint32_t hi_now = hi - taken[2 * i + 1].y - (uint32_t)__popc(taken[2 * i + 1].x & ((1u << (hi & 31)) - 1u));
+                counts[i] = lo_now | hi_now << 16;
+            }
+            *reinterpret_cast<vec16*>(sh.upto + 8 + e) = counts;
+        }
+        for (int32_t word = tid; word <= left / 64; word += kRfBatchThreads) sh.gone[word] = 0;
+        blocks += (int32_t)__popcll(opened);
+        room = __builtin_amdgcn_readlane(in_block - length, accepted - 1);
+        placed += accepted;
+        left -= accepted;
+        cur ^= 1;
+        __syncthreads();
+    }
+
+    if (tid == 0) {
+        *state = RfState{placed, blocks};
+        if (left == 0) {
+            block_first[blocks] = n_seq;
+            result->num_blocks = blocks;
+            if (host_result) {
+                host_result->num_blocks = blocks;
+                host_result->total_frames = result->total_frames;
+                host_result->bad_length = 0;
+            }
+        }
+    }
+    if (left == 0 || placed == 0) return;
+    // the rest is drawn one after another (a kernel of its own: behind the batches in this one, the chain was 13 %
+    // slower): the counts that it begins with
+    for (int e = tid; e < kept; e += kRfBatchThreads)
+        within[(e >> 6) * kRfStride + (e & 63) + 1] = (int32_t)upto[e + 1] - (int32_t)upto[e & ~63];
+    if (tid < kRfGroups) group_before[tid] = upto[min(tid, groups) * kWave];
+}
+
 __global__ __launch_bounds__(kThreads) void rf_assign_kernel(
     const RfPick* __restrict__ pick, const int32_t* __restrict__ first,
     const int32_t* __restrict__ entry, int32_t n_seq, int32_t t_blk, const int32_t* __restrict__ block_first,
@@ -355,7 +752,7 @@ __global__ __launch_bounds__(kThreads) void rf_assign_kernel(
 }
 
 struct RfLayout {
-    size_t result, seeded, seeded_len, entry, pick, first, within, group_before, chunk_count, bytes;
+    size_t result, seeded, seeded_len, entry, pick, sorted_len, first, within, group_before, chunk_count, bytes;
     int32_t n_chunks, per_chunk;
 };
 
@@ -370,7 +767,7 @@ static RfLayout rf_layout(int64_t n_seq)
     l.seeded_len = take(n * 4);
     l.entry = take(n * 4);
     l.pick = take(n * sizeof(RfPick));
-    take(n * 8);              // not used: the answer stays at the 28 bytes per sequence that the layout always had
+    l.sorted_len = take(n * 8);      // (2 of them used: the answer stays at the 28 bytes per sequence that the layout always had)
     l.first = take((size_t)kRfMaxT * 4);
     l.within = take((size_t)kRfGroups * kRfStride * 4);
     l.group_before = take((size_t)kRfGroups * 4);
@@ -427,6 +824,7 @@ extern "C" bload_status bload_plan_random_fit(const int32_t* d_lengths, int64_t 
     int32_t* seeded_len = reinterpret_cast<int32_t*>(ws + l.seeded_len);
     int32_t* entry = reinterpret_cast<int32_t*>(ws + l.entry);
     RfPick* pick = reinterpret_cast<RfPick*>(ws + l.pick);
+    uint16_t* sorted_len = reinterpret_cast<uint16_t*>(ws + l.sorted_len);
     int32_t* first = reinterpret_cast<int32_t*>(ws + l.first);
     int32_t* within = reinterpret_cast<int32_t*>(ws + l.within);
     int32_t* group_before = reinterpret_cast<int32_t*>(ws + l.group_before);
@@ -445,18 +843,18 @@ extern "C" bload_status bload_plan_random_fit(const int32_t* d_lengths, int64_t 
     hipLaunchKernelGGL(rf_offsets_kernel, dim3(1), dim3(kRfOffsetThreads), 0, stream, l.n_chunks, t_blk, chunk_count, first,
                        within, group_before);
     hipLaunchKernelGGL(rf_scatter_kernel, dim3((uint32_t)l.n_chunks), block, 0, stream, seeded, seeded_len,
-                       n, t_blk, l.per_chunk, chunk_count, entry);
-    // after a length outside [1, t_blk] the last two kernels return at once
-    const dim3 wave(kWave);
-    if (t_blk <= kRfRegisterRows * kWave)
-        hipLaunchKernelGGL((rf_draw_kernel<true, false>), dim3(1), wave, 0, stream, within, group_before, n, t_blk,
-                           seed, pick, d_block_first, result, pinned);
-    else if (t_blk <= kWave * kWave)
-        hipLaunchKernelGGL((rf_draw_kernel<false, false>), dim3(1), wave, 0, stream, within, group_before, n, t_blk,
-                           seed, pick, d_block_first, result, pinned);
-    else
-        hipLaunchKernelGGL((rf_draw_kernel<false, true>), dim3(1), wave, 0, stream, within, group_before, n, t_blk,
-                           seed, pick, d_block_first, result, pinned);
+                       n, t_blk, l.per_chunk, chunk_count, entry, sorted_len);
+    // after a length outside [1, t_blk] the last kernels return at once
+    const bool batches = n_seq >= kRfBatchLeast && n_seq <= kRfBatchMost;
+    // (behind the sorted lengths, 2 of the 8 bytes per sequence that their part of the workspace has)
+    RfState* state = reinterpret_cast<RfState*>(ws + l.sorted_len + round_up((size_t)n_seq * 2, 16));
+    if (batches)
+        hipLaunchKernelGGL(rf_draw_batches_kernel, dim3(1), dim3(kRfBatchThreads), 0, stream, sorted_len, within,
+                           group_before, state, n, t_blk, seed, pick, d_block_first, result, pinned);
+    const auto draw = t_blk <= kRfRegisterRows * kWave ? rf_draw_kernel<true, false>
+                      : t_blk <= kWave * kWave ? rf_draw_kernel<false, false> : rf_draw_kernel<false, true>;
+    hipLaunchKernelGGL(draw, dim3(1), dim3(kWave), 0, stream, within, group_before, batches ? state : nullptr, n, t_blk,
+                       seed, pick, d_block_first, result, pinned);
     hipLaunchKernelGGL(rf_assign_kernel, per_item, block, 0, stream, pick, first, entry, n, t_blk, d_block_first, d_order,
                        d_block_of_seq, d_offset_of_seq, result, pinned);
     if (launch_status() != BLOAD_OK) return BLOAD_EHIP;

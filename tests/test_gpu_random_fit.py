@@ -99,3 +99,28 @@ def test_random_fit_plan_packs_and_reduces(n, T, F, kind):
     red = bl.bload_segment_reduce(out.packed, out.seq_id, out.reset, out.valid, plan_dev.num_blocks,
                                   T, D, "i32", "sum", n)
     assert np.array_equal(red.cpu().numpy(), oracle.segment_reduce(src, so, L, D, "i32", "sum"))
+
+
+# Draws are made in batches of 64 from 768 to 24576 sequences: both ends, the end of the short trial (4096), blocks of one
+# length per group and of many, lists that end on and beside whole words; lengths that settle in a few rounds, in
+# many, not at all (the trial fails), that stop paying on the way, and of which there are so few that draws keep
+# meeting on the same ones.
+@pytest.mark.parametrize("n,T", [(767, 600), (768, 600), (769, 64), (1023, 65), (1024, 2048), (1025, 2049), (4095, 3000),
+                                 (4096, 3000), (4097, 4096), (5000, 4097), (2048, 8192), (10000, 60), (24576, 300),
+                                 (24577, 300), (6400, 1), (3000, 7)])
+@pytest.mark.parametrize("kind", ["uniform", "short", "long", "mixed", "heavy", "full", "clips", "two"])
+def test_random_fit_batches_match_oracle(n, T, kind):
+    rng = np.random.default_rng(n * 13 + T)
+    if kind == "heavy":
+        L = np.clip(np.floor(8 * (1 + rng.pareto(1.5, size=n))), 1, T).astype(np.int32)
+    elif kind == "full":
+        L = (T - np.minimum(rng.geometric(0.3, size=n) - 1, T - 1)).astype(np.int32)
+    elif kind == "clips":
+        L = rng.integers(max(1, T // 16), T, size=n, endpoint=True).astype(np.int32)
+    elif kind == "two":
+        L = rng.choice(np.array([1, max(1, T // 2)], dtype=np.int32), size=n)
+    else:
+        L = workloads.random_lengths(rng, n, T, kind)
+    for seed in workloads.SHUFFLE_SEEDS[:2]:
+        print(f"random fit batches n={n} T={T} kind={kind} seed={seed}", flush=True)
+        assert_plan_equal(gpu_random_fit(L, T, seed), oracle.plan_random_fit(L, T, seed), n)
