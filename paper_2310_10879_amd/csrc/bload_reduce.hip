@@ -63,6 +63,7 @@ struct ReduceArgs {
     void* out;               // [n_seq, feat_dim] float or int64
     // chunking
     int32_t chunk;           // slots per chunk
+    int32_t reach;           // wide: slots behind a chunk that a segment begun in front may end in and stay whole
     int32_t tile;            // staged, several tiles per workgroup: slots per tile
     int32_t n_chunks;        // wide: chunks per block
     int32_t row_lanes_log2;  // wide: lanes per row = 1 << this
@@ -176,6 +177,7 @@ __device__ __forceinline__ double finish<double>(double sum, int32_t cnt, int me
 // ------------------------------------------------------------------- wide
 
 constexpr int kWideUnroll = 8;
+constexpr int64_t kShortPieces = 32;       // slots per row of the result
 constexpr int kWideFlagBytes = 32768;      // LDS budget for the staged flags: also the longest chunk
 static_assert((int64_t)kWideFlagBytes * 255 < ((int64_t)1 << 24), "uint8 pieces must sum exactly in float");
 
@@ -275,7 +277,7 @@ __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
     typedef typename Elem<ElemT>::Acc Acc;
     extern __shared__ uint8_t s_flags[];   // rows x (chunk + 2): bit0 valid, bit1 reset
     const int tid = (int)threadIdx.x;
-    const int C = a.chunk, stride = C + 2;
+    const int C = a.chunk, stride = C + a.reach + 2;
     const int rows = kThreads >> a.row_lanes_log2;
     // consecutive workgroups take the lane-slices of one frame range, so that
     // workgroups running side by side read neighbouring memory
@@ -283,8 +285,8 @@ __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
     const int64_t q_base = (int64_t)(blockIdx.x / (uint32_t)a.feat_tiles) * rows;
     const int64_t T = a.t_blk;
 
-    // stage the flags of this workgroup's chunks, plus the slot before and the slot
-    // after each chunk (0 outside the block): row r holds slots t0-1 .. t0+len
+    // stage the flags of this workgroup's chunks, plus the slot before and the slots as far as a
+    // segment is followed behind each chunk (0 outside the block): row r holds slots t0-1 .. t0+len+reach
     for (int r = 0; r < rows; ++r) {
         const int64_t q = q_base + r;
         if (q >= a.total_chunks) break;
@@ -292,7 +294,7 @@ __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
         const int32_t t0 = (int32_t)(q - b * a.n_chunks) * C;
         const int32_t len = min(C, a.t_blk - t0);
         const int64_t g = b * T + t0;
-        for (int t = tid - 1; t <= len; t += kThreads) {
+        for (int t = tid - 1; t <= len + a.reach; t += kThreads) {
             uint8_t f = 0;
             if (t0 + t >= 0 && t0 + t < a.t_blk)
                 f = (uint8_t)((a.valid[g + t] ? 1 : 0) | (a.reset[g + t] ? 2 : 0));
@@ -313,9 +315,22 @@ __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
 
     const int64_t b = q / a.n_chunks;
     const int32_t t0 = (int32_t)(q - b * a.n_chunks) * C;
-    const int32_t len = min(C, a.t_blk - t0);
     const int64_t g = b * T + t0;
     const uint8_t* flags = s_flags + row * stride + 1;      // flags[-1] = the slot before the chunk
+    // A segment that runs over a border between two chunks and ends within `reach` slots behind it belongs whole to the
+    // chunk in front: both see the same flags and agree.  (`reach` is no longer than a chunk.)
+    int32_t len = min(C, a.t_blk - t0), begin = 0;
+    auto goes_on = [&](int32_t border) { return (flags[border] & 3) == 1 && (flags[border - 1] & 1); };
+    if (a.reach > 0) {
+        if (goes_on(0)) {
+            const int32_t end = next_slot<false, WAVE_ROW>(flags, 1, a.reach + 1, a.row_lanes_log2);
+            if (end <= a.reach) begin = end;
+        }
+        if (goes_on(len)) {
+            const int32_t end = next_slot<false, WAVE_ROW>(flags, len + 1, len + a.reach + 1, a.row_lanes_log2);
+            if (end <= len + a.reach) len = end;
+        }
+    }
     const int64_t frame_bytes = (int64_t)a.feat_dim * (int64_t)sizeof(ElemT);
     const uint8_t* chunk_src = a.packed + g * frame_bytes;                 // the chunk's first frame
     // a frame that is no whole number of vectors: its last vector lies over the end of the one before
@@ -358,7 +373,7 @@ __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
     // frames of a piece are added eight at a time as a balanced tree, and the
     // sums of the eights go into a compensated running sum: the float32 result
     // is within a few units in the last place of sum |x| at any piece length.
-    int32_t t = 0;
+    int32_t t = begin;
     for (;;) {
         t = next_slot<true, WAVE_ROW>(flags, t, len, a.row_lanes_log2);    // next valid slot
         if (t >= len) break;
@@ -1275,6 +1290,7 @@ struct ReducePlan {
     bool wide, staged;
     bool run;                // staged: a workgroup takes the tiles of a whole chunk one after another
     int32_t tile;            // of this many slots
+    int32_t reach;           // wide: see ReduceArgs
     int vec;                 // wide: elements per lane (16 bytes, 4 bytes or one element)
     int row_lanes_log2;
     int n_vec;
@@ -1341,6 +1357,7 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
     //     of 32 or 64 lanes in one wave keeps the vectors, half idle or not (260 bytes of floats: 266 us,
     //     342 with one a lane)
     // Whole vectors stay 16 bytes a lane whatever is idle (272 bytes, 2.5 GB: 484 us, one float a lane 722).
+    const bool whole = frame_bytes % 16 == 0;
     const int widths[3] = {16, 4, es};
     for (int w = 0; p.wide && w < 3; ++w) {
         p.vec = widths[w] / es;
@@ -1371,9 +1388,21 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
             if (want > most_long) want = most_long;
         }
         int64_t chunk = ceil_div(t_blk, want);
-        const int64_t lds_cap = kWideFlagBytes / rows - 2;
+        int64_t reach = 0;
+        // Rows of one wave and sequences of a few frames: the waves' chunks hold very different numbers of pieces, and
+        // all are at work at once, so that the call lasts as long as the slowest.  Twice as many shorter chunks
+        // even that out, and a segment that ends within 64 slots behind a border stays in one piece, so that they
+        // hardly make more partial sums (10000 sequences of 23 frames of 4096 bytes: 220 -> 203 us; 330 of them 21.4
+        // -> 18.1; 8900 of 3072 bytes 176 -> 157).  Longer pieces lose by it (500 of 280 frames: 128 -> 135 us).
+        if (!lean && whole && p.row_lanes_log2 == 6 && want > 1 && mean <= kShortPieces) {
+            want = std::min<int64_t>(ceil_div((int64_t)2048 * rows, num_blocks * feat_tiles), t_blk / 32);
+            chunk = ceil_div(t_blk, want);
+            reach = 64;
+        }
+        const int64_t lds_cap = (kWideFlagBytes / rows - 2) / (reach ? 2 : 1);
         if (chunk > lds_cap) chunk = lds_cap;
         p.chunk = (int32_t)chunk;
+        p.reach = (int32_t)std::min(reach, chunk);
         p.n_chunks = (int32_t)ceil_div(t_blk, chunk);
         p.total_chunks = num_blocks * p.n_chunks;
         p.partials = p.n_chunks > 1;
@@ -1384,7 +1413,6 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
         // 857 of 777 x 64: 70 us in wide rows of 16 or 4 bytes a lane 34, in tiles 16; 571 of 777 x 96: 51, 29, 24;
         // 428 of 777 x 192: 45, 23, 31; 2500 of 110 x 192: 32, 13, 20).
         if (w == 0 && feat_dim < kStagedFrame && (lean || groups * p.n_vec < (t_blk < 128 ? 760 : 1550))) p.wide = false;
-        const bool whole = frame_bytes % 16 == 0;
         const bool suits = w > 0 || whole ||
                            (frame_bytes > 256 && (feat_tiles == 1 || p.n_vec * 3 >= (feat_tiles << p.row_lanes_log2) * 2));
         if (groups >= (whole ? 512 : 1024) && suits && !one_element) break;
@@ -1446,7 +1474,7 @@ static void launch_wide(const ReducePlan& p, const ReduceArgs& a, hipStream_t st
     typedef typename Elem<ElemT>::Acc Acc;
     const int rows = kThreads >> p.row_lanes_log2;
     const dim3 grid((uint32_t)(ceil_div(p.total_chunks, rows) * a.feat_tiles));
-    size_t lds = (size_t)rows * (size_t)(p.chunk + 2);
+    size_t lds = (size_t)rows * (size_t)(p.chunk + p.reach + 2);
     if (VEC > 1 && p.row_lanes_log2 >= 6)     // + the per-wave scratch of the transposed stores
         lds = round_up(lds, 16) + (size_t)(kThreads / kWave) * kWave * kScratchStride<Acc, VEC>() * sizeof(Acc);
     if (p.row_lanes_log2 == 6)
@@ -1556,6 +1584,7 @@ extern "C" bload_status bload_segment_reduce(const void* d_packed, const int32_t
     a.out = d_out;
     a.chunk = p.chunk;
     a.tile = p.tile;
+    a.reach = p.wide ? p.reach : 0;
     a.n_chunks = p.n_chunks;
     a.row_lanes_log2 = p.row_lanes_log2;
     a.n_vec = p.n_vec;

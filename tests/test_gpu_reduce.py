@@ -423,3 +423,45 @@ def test_reduce_runs_of_tiles(B, T, D, dtype, op):
     scale, _ = oracle.segment_reduce_packed(absval, seq_id, reset, valid, D, "f32", op, n_seg)
     bound = REL_TOL * np.maximum(np.abs(want.astype(np.float64)), scale.astype(np.float64)) + 1e-30
     assert np.all(np.abs(got.astype(np.float64) - want.astype(np.float64)) <= bound)
+
+
+# Rows of one wave and many short sequences: blocks are cut into chunks of 32 slots and more (74 of 180 blocks of 3000), and
+# a segment that ends within the next chunk, and within 64 slots, belongs to the chunk it began in.  Segments that
+# begin and end at the chunks' borders, one slot beside them, as far behind them as they are followed and one slot farther,
+# some over several chunks, padding there as well.
+@pytest.mark.parametrize("B,T,dtype,op", [(12, 640, "f32", "mean"), (12, 640, "i32", "sum"), (12, 640, "u8", "mean"),
+                                          (12, 640, "f16", "sum"), (7, 133, "f16", "mean"), (1, 128, "f16", "mean"),
+                                          (180, 3000, "f16", "mean")])
+def test_reduce_short_pieces_over_chunk_borders(B, T, dtype, op):
+    bl = binding()
+    rng = np.random.default_rng(B + T)
+    D = 1024 // bl.ELEM_BYTES[dtype]
+    most = max(1, T // 32)
+    chunk = -(-T // min(most, -(-2048 * 4 // B)))
+    reach = min(64, chunk)
+    at = [c * chunk + k for c in range(1, T // chunk + 1) for k in (-1, 0, 1, reach - 1, reach, reach + 1)]
+    at = np.array([t for t in at if 0 < t < T])
+    valid, reset = np.ones((B, T), np.uint8), np.zeros((B, T), np.uint8)
+    for b in range(B):
+        reset[b, rng.choice(at, size=int(rng.integers(0, len(at) // 2 + 1)), replace=False)] = 1
+        if b % 3 == 2:
+            for t in rng.choice(at, size=3):
+                valid[b, t:t + int(rng.integers(1, 40))] = 0
+    reset &= valid
+    prev = np.concatenate([np.zeros((B, 1), np.uint8), valid[:, :-1]], axis=1)
+    starts = (valid == 1) & ((reset == 1) | (prev == 0))
+    seq_id = np.where(valid == 1, np.cumsum(starts.reshape(-1)).reshape(B, T) - 1, -1).astype(np.int32)
+    n_seg = int(starts.sum())
+    n = max(n_seg, B * T // 30)                             # rows enough to tell of short pieces
+    src = draw_source(rng, B * T, D, dtype)
+    want, _ = oracle.segment_reduce_packed(src.reshape(B, T, D), seq_id, reset, valid, D, dtype, op, n_seg)
+    print(f"chunk borders B={B} T={T} {dtype} chunk {chunk} segments {n_seg}", flush=True)
+    got = bl.bload_segment_reduce(to_dev(src), to_dev(seq_id), to_dev(reset), to_dev(valid), B, T, D, dtype, op, n).cpu().numpy()
+    assert not got[n_seg:].any()
+    if dtype == "i32":
+        assert np.array_equal(got[:n_seg], want)
+        return
+    absval = np.abs(src.astype(np.float32)).reshape(B, T, D)
+    scale, _ = oracle.segment_reduce_packed(absval, seq_id, reset, valid, D, "f32", op, n_seg)
+    bound = REL_TOL * np.maximum(np.abs(want.astype(np.float64)), scale.astype(np.float64)) + 1e-30
+    assert np.all(np.abs(got[:n_seg].astype(np.float64) - want.astype(np.float64)) <= bound)
