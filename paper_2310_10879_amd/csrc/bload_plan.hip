@@ -11,18 +11,19 @@
 //            (round k: every marked p marks jump[p], then jump = jump o jump)
 //   block    inclusive count of heads up to p, minus one
 //   offset   P[p] - P[head of p's block]
-// Up to 2048 sequences one workgroup does all of it in LDS, in one launch.
+// Up to 256 sequences one workgroup does all of it in LDS, in one launch; up to 12288, one of 16 waves does, between a
+// launch that finds the order, which is work for the whole chip, and one that writes the tables (plan_mid_kernel).
 // Beyond that the scans work on tiles of 2048 positions (many small workgroups)
 // and the orbit is found on tiles of 8192 in three steps that need no launch per
 // jumping round: every tile jumps inside its own LDS until each of its positions
 // has left the tile (exit[p]); the orbit's entry into each tile is found by following
 // exit[] from position 0 (one hop per tile; from 40 tiles on over groups of 8 tiles, whose
 // exits a small kernel composes first; beyond 1024 tiles one thread finds all entries); every
-// tile then marks its heads from its entry by jumping in LDS again.  Five launches up to 8192
-// sequences, where the one tile is entered at position 0, six up to 40 tiles, seven beyond.
-// Bound by launches and latencies: 10^4 sequences 66 -> 59 us per call with one position per
-// thread in the order kernel (10 -> 4.3 us), 10^6 sequences 154 -> 129 us with that (17 -> 11)
-// and the groups of tiles (marking kernel 46 -> 24 us, their own 4).
+// tile then marks its heads from its entry by jumping in LDS again.  Six launches up to 40 tiles,
+// seven beyond.  (Blocks so long that prefix sums of 12288 sequences leave 32 bits: one workgroup of four waves up to 2048
+// sequences, the tiles from there on, five launches up to 8192, where the one tile is entered at position 0.)
+// Bound by launches and latencies: 10^6 sequences 154 -> 129 us per call with one position per thread in the order
+// kernel (17 -> 11) and the groups of tiles (marking kernel 46 -> 24 us, their own 4).
 #include "bload_common.hpp"
 #include "bload_order.hpp"
 
@@ -34,6 +35,8 @@ constexpr int kJumpThreads = 512;                 // workgroup size where a work
                                                   // LDS look-ups of one wave hide behind the others')
 constexpr int kJumpItems = 16;                    // positions per thread there
 constexpr int kJumpTile = kJumpThreads * kJumpItems;   // 8192
+constexpr int kSmallMost = 256;                   // up to this many sequences a launch and four waves do (300: 29.3 us, 28.1
+                                                  // in three launches; 2048 at 130 to a block 76 and 47, one to a block 62 and 45)
 constexpr int kWalkTiles = 1024;                  // up to this many jump tiles, each finds its own entry (see plan_mark_kernel),
 constexpr int kGroupFrom = 40;                    // and from this many on with the exits of groups of tiles: their launch
                                                   // costs 5 us, a hop of the walk 0.24
@@ -594,6 +597,268 @@ __global__ __launch_bounds__(kThreads) void plan_small_kernel(
     }
 }
 
+// The plan of up to kMidMost sequences behind plan_order_kernel: the steps of the tiled path in one workgroup of 16
+// waves, with everything in LDS and a barrier where that has a kernel boundary.  Positions are kept in 16 bits and
+// prefix sums in 32 (the host sees to it that they fit).  Thread t takes `per` consecutive positions, so that a
+// wave's positions are a jump tile of its own, whose rounds need no barrier:
+//   next      by binary search, a thread's first position in the whole window, the others between that one and
+//             the next thread's (next[] never falls)
+//   exits     each wave jumps inside its positions until every pointer has left them (in place: a wave's look-ups of a
+//             round are all made before its stores)
+//   entries   one thread follows the exits, a hop per wave
+//   heads     each wave from its entry, as plan_mark_kernel does
+// What the sequences get is left in the order of the positions; plan_scatter_kernel brings it to them, which one
+// compute unit would take longer for than the launch does.
+// Bound by the latency of LDS.  Whole call, before and after: 10^4 sequences of heavy-tailed length in blocks of 3000, six launches -> three,
+// 57 -> 44 us, nearly full blocks 74 -> 63; 3001 sequences, one to six to a block, 52 -> 34.
+constexpr int kMidThreads = 1024;
+constexpr int kMidWaves = kMidThreads / kWave;
+constexpr int kMidPer = 13;                       // an odd number, so that the threads' places in LDS spread over the banks
+constexpr int kMidMost = 12 * kMidThreads;        // beyond, the tiled path is as fast (13400 of nearly full blocks: 73 us, 76 here)
+
+struct MidShared {
+    alignas(16) int32_t prefix[kMidThreads * kMidPer + 4];     // lengths, then their prefix sums, in the end the offsets
+    alignas(16) uint16_t next[kMidThreads * kMidPer];        // in the end, with `jump`, the blocks
+    uint16_t jump[kMidThreads * kMidPer];
+    uint32_t mark[kMidThreads * kMidPer / 32];
+    uint16_t first[kMidThreads + 1];              // next[] of every thread's first position
+    uint16_t entry[kMidWaves];
+    int32_t wave_sum[kMidWaves];
+    HeadPair wave_heads[kMidWaves];
+};
+static_assert(kMidMost < 1 << 16 && sizeof(MidShared) <= 150 * 1024, "positions in 16 bits, one workgroup's LDS");
+
+struct SumI32 { __device__ int32_t operator()(int32_t a, int32_t b) const { return a + b; } };
+struct LaneMoveI32 {
+    template <int CTRL, int ROW_MASK>
+    __device__ __forceinline__ int32_t at(int32_t v) const { return dpp_move<CTRL, ROW_MASK>(v, 0); }
+};
+
+// PER: positions per thread.
+template <int PER>
+__global__ __launch_bounds__(kMidThreads) void plan_mid_kernel(
+    const int32_t* __restrict__ shuffled_len, int32_t n_seq, int32_t t_blk, const int32_t* __restrict__ bads,
+    int32_t n_bads, int32_t* __restrict__ block_at, int32_t* __restrict__ offset_at, int32_t* __restrict__ block_first,
+    PlanResult* __restrict__ result)
+{
+    __shared__ MidShared sh;
+    const int tid = (int)threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(wave_id());
+    constexpr int per = PER;
+    const int base = tid * per, mine = max(min(per, n_seq - base), 0);
+    const int wave_lo = min(wave * kWave * per, n_seq), wave_hi = min((wave + 1) * kWave * per, n_seq);
+
+    int bad = 0;
+    for (int k = tid; k < n_bads; k += kMidThreads) bad |= bads[k];
+    for (int p = tid; p < n_seq; p += kMidThreads) sh.prefix[p] = shuffled_len[p];
+    for (int w = tid; w < kMidThreads * kMidPer / 32; w += kMidThreads) sh.mark[w] = 0;
+    bad = __syncthreads_or(bad);
+
+    // prefix sums, in place
+    int32_t x[PER];
+    int32_t sum = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        x[j] = j < mine ? sh.prefix[base + j] : 0;
+        sum += x[j];
+    }
+    const int32_t upto = wave_scan(sum, SumI32(), LaneMoveI32());
+    if (lane == kWave - 1) sh.wave_sum[wave] = upto;
+    __syncthreads();
+    int32_t run = upto - sum, total = 0;
+#pragma unroll
+    for (int w = 0; w < kMidWaves; ++w) {
+        const int32_t t = sh.wave_sum[w];
+        run += w < wave ? t : 0;
+        total += t;
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        if (j < mine) sh.prefix[base + j] = run;
+        run += x[j];
+    }
+    if (tid == 0) sh.prefix[n_seq] = total;
+    __syncthreads();
+
+    // next[]: the smallest q behind p with P[q + 1] - P[p] > t_blk, n_seq if there is none.  (Every length is 1 or more.)
+    {
+        int lo = base + 1, hi = (int)min((int64_t)n_seq, (int64_t)base + t_blk);
+        const int32_t limit = mine > 0 ? sh.prefix[base] + t_blk : 0;
+        while (mine > 0 && lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (sh.prefix[mid + 1] > limit) hi = mid; else lo = mid + 1;
+        }
+        sh.first[tid] = (uint16_t)(mine > 0 ? lo : n_seq);
+        if (tid == 0) sh.first[kMidThreads] = (uint16_t)n_seq;
+    }
+    __syncthreads();
+    int32_t next[PER];
+    {
+        const int from = sh.first[tid], to = sh.first[tid + 1];
+        int32_t high[PER], limit[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            next[j] = j < mine ? max(from, base + j + 1) : n_seq;
+            high[j] = j < mine && j > 0 ? max(to, next[j]) : next[j];
+            limit[j] = j < mine ? sh.prefix[base + j] + t_blk : 0;
+        }
+        for (;;) {
+            bool more = false;
+#pragma unroll
+            for (int j = 1; j < PER; ++j) {
+                const int mid = (next[j] + high[j]) >> 1;
+                const bool open = next[j] < high[j];
+                const bool beyond = sh.prefix[open ? mid + 1 : 0] > limit[j];
+                high[j] = open && beyond ? mid : high[j];
+                next[j] = open && !beyond ? mid + 1 : next[j];
+                more |= next[j] < high[j];
+            }
+            if (__ballot(more) == 0) break;
+        }
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            if (j < mine) sh.next[base + j] = sh.jump[base + j] = (uint16_t)next[j];
+        }
+    }
+
+    // one round of jumping over the wave's positions: x = the lane's pointers, what they are after it
+    auto jump_round = [&]() {
+        int32_t then[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            then[j] = x[j] < wave_hi ? (int32_t)sh.jump[x[j]] : x[j];
+        bool inside = false;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            x[j] = then[j];
+            inside |= x[j] < wave_hi;
+            if (j < mine) sh.jump[base + j] = (uint16_t)x[j];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        return __ballot(inside) != 0;
+    };
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int j = 0; j < PER; ++j) x[j] = next[j];
+    // (pointers rise, so 2^10 hops leave the wave's 1024 positions)
+    for (int r = 0; r < 10 && jump_round(); ++r) {}
+    __syncthreads();
+    if (tid == 0) {
+        int e = 0;
+        for (int w = 0; w < kMidWaves; ++w) {
+            const bool in = e < min((w + 1) * kWave * per, n_seq);
+            sh.entry[w] = (uint16_t)(in ? e : kMidMost);
+            if (in) e = sh.jump[e];
+        }
+    }
+    __syncthreads();
+
+    // the wave's heads: the list so far, and twice as many with every round
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        x[j] = next[j];
+        if (j < mine) sh.jump[base + j] = (uint16_t)x[j];
+    }
+    const int entry = __builtin_amdgcn_readfirstlane((int)sh.entry[wave]);
+    uint16_t* heads = sh.next + wave_lo;                 // (next[] is in registers now)
+    int n_heads = entry < kMidMost ? 1 : 0;
+    if (n_heads > 0) {
+        if (lane == 0) {
+            heads[0] = (uint16_t)entry;
+            atomicOr(&sh.mark[entry >> 5], 1u << (entry & 31));
+        }
+        for (int r = 0; r < 11; ++r) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            int found = 0;
+            for (int i0 = 0; i0 < n_heads; i0 += kWave) {
+                const int i = i0 + lane;
+                const int to = i < n_heads ? (int)sh.jump[heads[i]] : wave_hi;
+                const bool inside = to < wave_hi;
+                if (inside) {
+                    heads[n_heads + i] = (uint16_t)to;
+                    atomicOr(&sh.mark[to >> 5], 1u << (to & 31));
+                }
+                found += (int)__popcll(__ballot(inside));        // (the first so many of the list: an orbit leaves in order)
+            }
+            if (found == 0) break;
+            n_heads += found;
+            jump_round();
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+
+    // blocks and offsets
+    uint32_t marks = 0;
+    if (mine > 0) {
+        const int word = base >> 5, more = min(word + 1, kMidThreads * kMidPer / 32 - 1);
+        marks = (uint32_t)(((uint64_t)sh.mark[more] << 32 | sh.mark[word]) >> (base & 31)) & ((1u << mine) - 1u);
+    }
+    HeadPair own{(int32_t)__popc(marks), marks ? base + 31 - __clz((int)marks) : -1};
+    const HeadPair heads_upto = wave_scan(own, HeadOp(), LaneMove());
+    HeadPair at = LaneMove().template at<kDppWaveShr1, 0xF>(heads_upto);
+    if (lane == 0) at = HeadPair{0, -1};
+    if (lane == kWave - 1) sh.wave_heads[wave] = heads_upto;
+    __syncthreads();
+    HeadPair all{0, -1}, before{0, -1};
+#pragma unroll
+    for (int w = 0; w < kMidWaves; ++w) {
+        if (w == wave) before = all;
+        all = HeadOp()(all, sh.wave_heads[w]);
+    }
+    at = HeadOp()(before, at);
+    int32_t offset[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        if (j < mine) {
+            if ((marks >> j) & 1u) {
+                at.cnt += 1;
+                at.head = base + j;
+                block_first[at.cnt - 1] = base + j;
+            }
+            x[j] = at.cnt - 1;
+            offset[j] = sh.prefix[base + j] - sh.prefix[at.head];
+        }
+    }
+    __syncthreads();                                     // the prefix sums and pointers have been read
+    int32_t* blocks = reinterpret_cast<int32_t*>(sh.next);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        if (j < mine) {
+            blocks[base + j] = x[j];
+            sh.prefix[base + j] = offset[j];
+        }
+    }
+    __syncthreads();
+    for (int p = tid; p < n_seq; p += kMidThreads) {
+        block_at[p] = blocks[p];
+        offset_at[p] = sh.prefix[p];
+    }
+    if (tid == 0) {
+        block_first[all.cnt] = n_seq;
+        result->num_blocks = all.cnt;
+        result->total_frames = total;
+        result->bad_length = bad;
+        result->pad_ = 0;
+    }
+}
+
+// What is known per position, to the sequences.
+__global__ __launch_bounds__(kThreads) void plan_scatter_kernel(
+    const int32_t* __restrict__ order, const int32_t* __restrict__ block_at, const int32_t* __restrict__ offset_at,
+    int32_t n_seq, int32_t* __restrict__ block_of_seq, int32_t* __restrict__ offset_of_seq)
+{
+    const int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (p >= n_seq) return;
+    const int32_t i = order[p];
+    block_of_seq[i] = block_at[p];
+    offset_of_seq[i] = offset_at[p];
+}
+
 // Workspace layout (every part 16-byte aligned).
 struct PlanLayout {
     size_t result, shuffled_len, prefix, next, exit_of, mark, tile_cnt, tile_head, tile_entry, tile_bad, bytes;
@@ -686,12 +951,28 @@ extern "C" bload_status bload_plan(const int32_t* d_lengths, int64_t n_seq, int3
     const dim3 block(kThreads);
     const dim3 tiles((uint32_t)l.n_tiles), jump_tiles((uint32_t)l.n_jump_tiles);
 
-    if (n_seq <= kTile) {
+    // (the workgroup of 16 waves keeps its prefix sums in 32 bits)
+    const bool mid_fits = n_seq <= kMidMost && n_seq * (int64_t)t_blk <= INT32_MAX - t_blk;
+    if (n_seq <= kSmallMost || (n_seq <= kTile && !mid_fits)) {
         // 2^rounds >= n_seq >= number of heads
         int rounds = 0;
         while (((int64_t)1 << rounds) < n_seq) ++rounds;
         hipLaunchKernelGGL(plan_small_kernel, dim3(1), block, 0, stream, d_lengths, n, t_blk, key,
                            rounds, d_order, d_block_of_seq, d_offset_of_seq, d_block_first, result);
+    } else if (mid_fits) {
+        const dim3 sums((uint32_t)l.n_sums), per_item((uint32_t)ceil_div(n_seq, kThreads));
+        int32_t* block_at = next;
+        int32_t* offset_at = reinterpret_cast<int32_t*>(prefix);
+        hipLaunchKernelGGL(plan_order_kernel<1>, sums, block, 0, stream, d_lengths, n, t_blk, key, d_order,
+                           shuffled_len, sum_of, bad_of);
+        const int per = (int)ceil_div(n_seq, kMidThreads) | 1;
+        const auto mid = per == 1 ? plan_mid_kernel<1> : per == 3 ? plan_mid_kernel<3> : per == 5 ? plan_mid_kernel<5> : per == 7 ? plan_mid_kernel<7>
+                         : per == 9 ? plan_mid_kernel<9> : per == 11 ? plan_mid_kernel<11> : plan_mid_kernel<13>;
+        static_assert(kMidPer == 13 && kMidMost <= kMidThreads * kMidPer, "1 to 13 positions per thread");
+        hipLaunchKernelGGL(mid, dim3(1), dim3(kMidThreads), 0, stream, shuffled_len, n, t_blk, bad_of, l.n_sums, block_at,
+                           offset_at, d_block_first, result);
+        hipLaunchKernelGGL(plan_scatter_kernel, per_item, block, 0, stream, d_order, block_at, offset_at, n, d_block_of_seq,
+                           d_offset_of_seq);
     } else {
         const dim3 sums((uint32_t)l.n_sums);
         if (l.sums_per_tile == 1)

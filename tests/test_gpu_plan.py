@@ -111,3 +111,27 @@ def test_plan_is_deterministic():
     b = gpu_plan(L, 3000, 11)
     assert torch.equal(a.order, b.order) and torch.equal(a.offset_of_seq, b.offset_of_seq)
     assert torch.equal(a.block_of_seq, b.block_of_seq)
+
+
+# One workgroup of 16 waves, 1 to 13 positions per thread: both ends of each, both ends of its range, a last wave
+# with one position, blocks of one sequence, of two, of nearly all, of all, and over several waves; and where prefix
+# sums just fit 32 bits and just do not, which the other kernels then take.
+@pytest.mark.parametrize("n", [256, 257, 1023, 1024, 1025, 2048, 3072, 3073, 5120, 5121, 7169, 9216, 9217, 11265, 12288, 12289])
+def test_plan_one_workgroup_of_sixteen_waves(n):
+    rng = np.random.default_rng(n)
+    cases = [(np.ones(n), 1), (np.ones(n), 2), (np.full(n, 5), 14), (np.ones(n), n), (np.ones(n), n - 1), (np.ones(n), 700),
+             (rng.integers(1, 4, size=n), 3000), (rng.integers(1, 3001, size=n), 3000),
+             (np.clip(8 * (1 + rng.pareto(1.5, size=n)), 1, 3000), 3000), (np.where(rng.random(n) < 0.01, 900, 1), 900)]
+    last = (2 ** 31 - 1) // (n + 1)
+    cases += [(rng.integers(max(1, last // 3), last, size=n, endpoint=True), last), (np.full(n, last + 1), last + 1)]
+    for k, (L, T) in enumerate(cases):
+        L = np.asarray(L).astype(np.int32)
+        print(f"plan n={n} T={T} case {k}", flush=True)
+        assert_plan_equal(gpu_plan(L, T, 5 + k), oracle.plan(L, T, oracle.order(n, 5 + k)), n)
+    bl = binding()
+    for bad in (0, 301, -2 ** 31):
+        L = rng.integers(1, 301, size=n).astype(np.int32)
+        L[n // 2] = bad
+        with pytest.raises(bl.BloadError) as e:
+            gpu_plan(L, 300, 1)
+        assert e.value.status == bl.ELENGTH
