@@ -68,6 +68,20 @@ __device__ __forceinline__ uint32_t feistel(uint32_t x, const OrderKey& k)
     return (left << k.half_bits) | right;
 }
 
+// The permutation backwards.
+__device__ __forceinline__ uint32_t feistel_back(uint32_t x, const OrderKey& k)
+{
+    const uint32_t mask = (1u << k.half_bits) - 1u;
+    uint32_t left = x >> k.half_bits, right = x & mask;
+#pragma unroll
+    for (int r = kFeistelRounds - 1; r >= 0; --r) {
+        const uint32_t t = right ^ (fmix32(left + k.key[r]) & mask);
+        right = left;
+        left = t;
+    }
+    return (left << k.half_bits) | right;
+}
+
 // Sequence at shuffled position p: walk the Feistel permutation of the
 // enclosing power-of-four domain until it lands inside [0, n_seq).
 __device__ __forceinline__ int32_t order_at(uint32_t p, uint32_t n_seq, const OrderKey& k)
@@ -76,6 +90,15 @@ __device__ __forceinline__ int32_t order_at(uint32_t p, uint32_t n_seq, const Or
     uint32_t y = feistel(p, k);
     while (y >= n_seq) y = feistel(y, k);
     return (int32_t)y;
+}
+
+// Shuffled position of sequence i: the same walk backwards.
+__device__ __forceinline__ int32_t position_of(uint32_t i, uint32_t n_seq, const OrderKey& k)
+{
+    if (k.half_bits == 0) return (int32_t)i;
+    uint32_t x = feistel_back(i, k);
+    while (x >= n_seq) x = feistel_back(x, k);
+    return (int32_t)x;
 }
 
 }  // namespace bload

@@ -14,37 +14,43 @@
 // Up to 256 sequences one workgroup does all of it in LDS, in one launch; up to 12288, one of 16 waves does, between a
 // launch that finds the order, which is work for the whole chip, and one that writes the tables (plan_mid_kernel).
 // Beyond that the scans work on tiles of 2048 positions (many small workgroups)
-// and the orbit is found on tiles of 8192 in three steps that need no launch per
+// and the orbit is found on tiles of 2048 to 8192 in three steps that need no launch per
 // jumping round: every tile jumps inside its own LDS until each of its positions
 // has left the tile (exit[p]); the orbit's entry into each tile is found by following
-// exit[] from position 0 (one hop per tile; from 40 tiles on over groups of 8 tiles, whose
+// exit[] from position 0 (one hop per tile; from 40 tiles on over groups of 8 or 16 tiles, whose
 // exits a small kernel composes first; beyond 1024 tiles one thread finds all entries); every
 // tile then marks its heads from its entry by jumping in LDS again.  Six launches up to 40 tiles,
-// seven beyond.  (Blocks so long that prefix sums of 12288 sequences leave 32 bits: one workgroup of four waves up to 2048
-// sequences, the tiles from there on, five launches up to 8192, where the one tile is entered at position 0.)
-// Bound by launches and latencies: 10^6 sequences 154 -> 129 us per call with one position per thread in the order
-// kernel (17 -> 11) and the groups of tiles (marking kernel 46 -> 24 us, their own 4).
+// seven beyond, one more where the sequences fetch what they get (plan_gather_kernel).  (Blocks so long that prefix sums
+// of 12288 sequences leave 32 bits: one workgroup of four waves up to 2048 sequences, the tiles from there on, five
+// launches where the one tile is entered at position 0.)
+// Bound by launches and latencies: 10^6 documents 125 -> 111 us per call with smaller jump tiles (exit kernel 17 -> 13 us;
+// the marking kernel's shorter rounds pay for its longer walk: 23 -> 25), tables fetched instead of scattered (32 -> 11 +
+// 12) and next[] searched in LDS (16 -> 10).
 #include "bload_common.hpp"
 #include "bload_order.hpp"
+
+#include <type_traits>
 
 namespace bload {
 
 constexpr int kItems = 8;                         // consecutive positions per thread in the scans
 constexpr int kTile = kThreads * kItems;          // positions per workgroup in the scans: 2048
-constexpr int kJumpThreads = 512;                 // workgroup size where a workgroup jumps in LDS (8 waves:
-                                                  // LDS look-ups of one wave hide behind the others')
-constexpr int kJumpItems = 16;                    // positions per thread there
-constexpr int kJumpTile = kJumpThreads * kJumpItems;   // 8192
+constexpr int kJumpItems = 16;                    // positions per thread where a workgroup jumps in LDS
+// Such a workgroup takes a jump tile of 16 positions for each of its NT threads: 2048, 4096 or 8192 of them.  Small ones
+// spread over more compute units and their rounds are shorter, but the walk over them is longer: 20000
+// sequences 74 us in tiles of 8192, 69 in tiles of 4096, 66 of 2048; 10^6 114.8, 111.2, 113; 2 * 10^6 213, 216, 219.
+constexpr int kJumpTile = 8192;                   // the largest
+template <int NT> __host__ __device__ constexpr int jump_tile() { return NT * kJumpItems; }
+constexpr int64_t kSmallTilesUpTo = 160000, kMidTilesUpTo = (int64_t)1 << 20;
 constexpr int kSmallMost = 256;                   // up to this many sequences a launch and four waves do (300: 29.3 us, 28.1
                                                   // in three launches; 2048 at 130 to a block 76 and 47, one to a block 62 and 45)
 constexpr int kWalkTiles = 1024;                  // up to this many jump tiles, each finds its own entry (see plan_mark_kernel),
 constexpr int kGroupFrom = 40;                    // and from this many on with the exits of groups of tiles: their launch
                                                   // costs 5 us, a hop of the walk 0.24
+constexpr int64_t kGatherFrom = (int64_t)1 << 19;      // see plan_gather_kernel
 constexpr int64_t kSingleItems = (int64_t)1 << 20;     // up to this many sequences the order kernel takes one per thread
 constexpr int kJumpRounds = 13;                   // 2^13 = kJumpTile: rounds that cross a whole tile
-constexpr int kScanPerJump = kJumpTile / kTile;   // scan tiles in a jump tile
 constexpr int kWavesPerScanTile = kTile / (kWave * kJumpItems);     // waves of the marking kernel per scan tile
-static_assert(kScanPerJump * kWavesPerScanTile == kJumpThreads / kWave, "waves of the marking kernel tile the scan tiles");
 
 // ---- workgroup scans --------------------------------------------------------
 
@@ -153,20 +159,20 @@ __device__ __forceinline__ bool jump_round(const int32_t* __restrict__ from, int
     return inside_any;
 }
 
-// The same round (without marks) over a whole jump tile of kJumpTile positions, four neighbouring
+// The same round (without marks) over a whole jump tile, four neighbouring
 // positions per thread and step: their pointers come and go as one 16-byte LDS access, only the
 // look-ups behind them are single words (24 LDS instructions per thread and round instead of
 // 48).  Positions from `count` on must hold pointers that point behind the tile.
+template <int NT>
 __device__ __forceinline__ bool jump_round_tile(const int32_t* __restrict__ from, int32_t* __restrict__ to,
                                                 int32_t lo, int32_t count)
 {
     typedef int32_t int4v __attribute__((ext_vector_type(4)));
-    constexpr int kQuads = kJumpTile / 4 / kJumpThreads;      // quads of positions per thread
-    static_assert(kQuads * 4 * kJumpThreads == kJumpTile, "the threads' quads tile the jump tile");
+    constexpr int kQuads = kJumpItems / 4;        // quads of positions per thread
     int4v at[kQuads], then[kQuads];
 #pragma unroll
     for (int u = 0; u < kQuads; ++u)
-        at[u] = *reinterpret_cast<const int4v*>(from + 4 * ((int)threadIdx.x + u * kJumpThreads));
+        at[u] = *reinterpret_cast<const int4v*>(from + 4 * ((int)threadIdx.x + u * NT));
     bool inside_any = false;
 #pragma unroll
     for (int u = 0; u < kQuads; ++u) {
@@ -179,14 +185,15 @@ __device__ __forceinline__ bool jump_round_tile(const int32_t* __restrict__ from
     }
 #pragma unroll
     for (int u = 0; u < kQuads; ++u)
-        *reinterpret_cast<int4v*>(to + 4 * ((int)threadIdx.x + u * kJumpThreads)) = then[u];
+        *reinterpret_cast<int4v*>(to + 4 * ((int)threadIdx.x + u * NT)) = then[u];
     return inside_any;
 }
 
 // Pointers behind the tile for the positions of a jump tile that lie behind the last sequence.
+template <int NT>
 __device__ __forceinline__ void pad_tile(int32_t* tile, int32_t lo, int32_t count)
 {
-    for (int32_t k = count + (int32_t)threadIdx.x; k < kJumpTile; k += kJumpThreads) tile[k] = lo + count;
+    for (int32_t k = count + (int32_t)threadIdx.x; k < jump_tile<NT>(); k += NT) tile[k] = lo + count;
 }
 
 // ---- kernels ------------------------------------------------------------------
@@ -238,7 +245,14 @@ __global__ __launch_bounds__(kThreads) void plan_prefix_kernel(
         if (lane_id() == 0) tile_bad[blockIdx.x] = bad != 0;
     }
     int64_t mine = 0;
-    for (int32_t t = (int32_t)threadIdx.x; t < first_sum; t += kThreads) mine += sums[t];
+    constexpr int kBatch = 8;          // in flight together
+    for (int32_t t0 = (int32_t)threadIdx.x; t0 < first_sum; t0 += kBatch * kThreads) {
+        int64_t v[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) v[u] = sums[min(t0 + u * kThreads, first_sum - 1)];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) mine += t0 + u * kThreads < first_sum ? v[u] : 0;
+    }
     int64_t before;
     block_exclusive_scan<int64_t>(mine, 0, SumI64(), &before);
 
@@ -262,13 +276,33 @@ __global__ __launch_bounds__(kThreads) void plan_prefix_kernel(
     }
 }
 
-// next[p] for every position: one thread each (a chain of dependent look-ups in P).
+// next[p] for every position, one thread each: a chain of dependent look-ups in P, of which the next kNextWindow
+// positions lie in LDS and hold the answer where blocks are of fewer sequences.
+constexpr int kNextWindow = 1024;
+
 __global__ __launch_bounds__(kThreads) void plan_next_kernel(const int64_t* __restrict__ prefix,
                                                              int32_t n_seq, int32_t t_blk,
                                                              int32_t* __restrict__ next)
 {
-    const int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (p < n_seq) next[p] = next_head([&](int32_t q) { return prefix[q]; }, (int32_t)p, n_seq, t_blk);
+    __shared__ int64_t s_prefix[kNextWindow + kThreads];
+    const int64_t first = (int64_t)blockIdx.x * kThreads;
+    const int32_t held = (int32_t)min((int64_t)(kNextWindow + kThreads), (int64_t)n_seq + 1 - first);    // from `first` on
+    for (int32_t k = (int32_t)threadIdx.x; k < held; k += kThreads) s_prefix[k] = prefix[first + k];
+    __syncthreads();
+    const int64_t p = first + threadIdx.x;
+    if (p >= n_seq) return;
+    const int64_t limit = s_prefix[threadIdx.x] + t_blk;
+    // the first entry above the limit is next[p] + 1; P[p + 1] never is
+    if (s_prefix[held - 1] > limit) {
+        int32_t lo = (int32_t)threadIdx.x + 2, hi = held - 1;
+        while (lo < hi) {
+            const int32_t mid = (lo + hi) >> 1;
+            if (s_prefix[mid] > limit) hi = mid; else lo = mid + 1;
+        }
+        next[p] = (int32_t)(first + lo - 1);
+    } else {
+        next[p] = next_head([&](int32_t q) { return prefix[q]; }, (int32_t)p, n_seq, t_blk);
+    }
 }
 
 // Copy `count` ints between global memory and LDS, thread t taking elements t, t + NT, ...,
@@ -290,43 +324,45 @@ __device__ __forceinline__ void copy_tile(const int32_t* __restrict__ from, int3
 
 // For each position of a jump tile, where the orbit that passes through it leaves the tile:
 // exit[p] = the first position at or behind the tile's end reached from p under next[].
-__global__ __launch_bounds__(kJumpThreads) void plan_exit_kernel(const int32_t* __restrict__ next,
+template <int NT>
+__global__ __launch_bounds__(NT) void plan_exit_kernel(const int32_t* __restrict__ next,
                                                                  int32_t n_seq,
                                                                  int32_t* __restrict__ exit_of)
 {
-    __shared__ __attribute__((aligned(16))) int32_t s_jump[2][kJumpTile];
-    const int32_t lo = (int32_t)blockIdx.x * kJumpTile;
-    const int32_t count = min(kJumpTile, n_seq - lo);
-    copy_tile<kJumpThreads>(next + lo, s_jump[0], count);
-    pad_tile(s_jump[0], lo, count);
+    __shared__ __attribute__((aligned(16))) int32_t s_jump[2][jump_tile<NT>()];
+    const int32_t lo = (int32_t)blockIdx.x * jump_tile<NT>();
+    const int32_t count = min(jump_tile<NT>(), n_seq - lo);
+    copy_tile<NT>(next + lo, s_jump[0], count);
+    pad_tile<NT>(s_jump[0], lo, count);
     int cur = 0;
     for (int r = 0; r < kJumpRounds; ++r) {
         __syncthreads();
-        const bool more = jump_round_tile(s_jump[cur], s_jump[cur ^ 1], lo, count);
+        const bool more = jump_round_tile<NT>(s_jump[cur], s_jump[cur ^ 1], lo, count);
         cur ^= 1;
         if (!__syncthreads_or(more ? 1 : 0)) break;       // every pointer has left the tile
     }
     __syncthreads();
-    copy_tile<kJumpThreads>(s_jump[cur], exit_of + lo, count);
+    copy_tile<NT>(s_jump[cur], exit_of + lo, count);
 }
 
-// The same over kGroupTiles jump tiles at a time, for the positions where an orbit can enter such a
+// The same over 8 jump tiles at a time (16 of the smallest), for the positions where an orbit can enter such a
 // group (next[] never falls, so those are at most next[the position in front of the group]; the
 // first group is entered at 0).  A tile that looks for its entry then takes a hop per group and a
 // few per tile instead of one per tile.
-constexpr int kGroupTiles = 8;
+template <int NT> constexpr int kGroupTiles = NT == 128 ? 16 : 8;
 constexpr int kGroupSpread = 16;                  // workgroups side by side over a group's entries
 
+template <int NT>
 __global__ __launch_bounds__(kThreads) void plan_group_exit_kernel(const int32_t* __restrict__ next,
                                                                    const int32_t* __restrict__ exit_of, int32_t n_seq,
                                                                    int32_t* __restrict__ group_exit)
 {
-    const int32_t lo = (int32_t)blockIdx.x * (kGroupTiles * kJumpTile);
-    const int32_t end = min((int64_t)lo + kGroupTiles * kJumpTile, (int64_t)n_seq);
+    const int32_t lo = (int32_t)blockIdx.x * (kGroupTiles<NT> * jump_tile<NT>());
+    const int32_t end = min((int64_t)lo + kGroupTiles<NT> * jump_tile<NT>(), (int64_t)n_seq);
     const int32_t most = min(lo == 0 ? 0 : next[lo - 1], end - 1);
     for (int64_t p = (int64_t)lo + blockIdx.y * kThreads + threadIdx.x; p <= most; p += kGroupSpread * kThreads) {
         int32_t e = (int32_t)p;
-        while (e < end) e = exit_of[e];           // exit[e] lies in a later tile than e: at most kGroupTiles hops
+        while (e < end) e = exit_of[e];           // exit[e] lies in a later tile than e: at most a hop per tile
         group_exit[p] = e;
     }
 }
@@ -334,7 +370,7 @@ __global__ __launch_bounds__(kThreads) void plan_group_exit_kernel(const int32_t
 // Where the orbit of position 0 enters each jump tile (-1: it passes over the tile): one hop
 // per tile along exit[].  One workgroup; thread 0 walks.
 __global__ __launch_bounds__(kThreads) void plan_chain_kernel(const int32_t* __restrict__ exit_of,
-                                                              int32_t n_seq, int32_t n_jump_tiles,
+                                                              int32_t n_seq, int32_t n_jump_tiles, int32_t tile,
                                                               int32_t* __restrict__ tile_entry)
 {
     for (int32_t t = (int32_t)threadIdx.x; t < n_jump_tiles; t += kThreads) tile_entry[t] = -1;
@@ -342,7 +378,7 @@ __global__ __launch_bounds__(kThreads) void plan_chain_kernel(const int32_t* __r
     if (threadIdx.x == 0) {
         int32_t e = 0;
         while (e < n_seq) {               // exit[e] lies in a later tile: at most n_jump_tiles hops
-            tile_entry[e / kJumpTile] = e;
+            tile_entry[e / tile] = e;
             e = exit_of[e];
         }
     }
@@ -359,29 +395,32 @@ __global__ __launch_bounds__(kThreads) void plan_chain_kernel(const int32_t* __r
 // moves forward, so they leave the tile in order and the list has no holes).  A round that
 // adds no head ends the search.  Also, for each of its scan tiles (one per wave), the number of heads
 // and the last head.
-__global__ __launch_bounds__(kJumpThreads) void plan_mark_kernel(
+template <int NT>
+__global__ __launch_bounds__(NT) void plan_mark_kernel(
     const int32_t* __restrict__ next, const int32_t* __restrict__ tile_entry,
     const int32_t* __restrict__ exit_of, const int32_t* __restrict__ group_exit, int32_t n_seq,
     uint8_t* __restrict__ mark, int32_t* __restrict__ tile_cnt, int32_t* __restrict__ tile_head)
 {
-    __shared__ __attribute__((aligned(16))) int32_t s_jump[2][kJumpTile];
-    __shared__ __attribute__((aligned(16))) uint8_t s_mark[kJumpTile];
-    __shared__ uint16_t s_heads[kJumpTile];           // positions inside the tile, relative to its first
+    __shared__ __attribute__((aligned(16))) int32_t s_jump[2][jump_tile<NT>()];
+    __shared__ __attribute__((aligned(16))) uint8_t s_mark[jump_tile<NT>()];
+    __shared__ uint16_t s_heads[jump_tile<NT>()];           // positions inside the tile, relative to its first
     __shared__ int32_t s_n_heads;
-    __shared__ HeadPair s_wave[kJumpThreads / kWave];
+    __shared__ HeadPair s_wave[NT / kWave];
+    constexpr int kScans = jump_tile<NT>() / kTile;    // scan tiles in the jump tile
+    static_assert(kScans * kWavesPerScanTile == NT / kWave, "the waves tile the scan tiles");
     static_assert(kJumpTile <= 65536, "a head's place inside the tile is kept in 16 bits");
-    const int32_t lo = (int32_t)blockIdx.x * kJumpTile;
-    const int32_t count = min(kJumpTile, n_seq - lo);
+    const int32_t lo = (int32_t)blockIdx.x * jump_tile<NT>();
+    const int32_t count = min(jump_tile<NT>(), n_seq - lo);
     __shared__ int32_t s_entry;
-    copy_tile<kJumpThreads>(next + lo, s_jump[0], count);
-    pad_tile(s_jump[0], lo, count);
+    copy_tile<NT>(next + lo, s_jump[0], count);
+    pad_tile<NT>(s_jump[0], lo, count);
     if (threadIdx.x == 0) {
         int32_t e = 0;
         if (tile_entry) {
             e = tile_entry[blockIdx.x];
         } else if (exit_of) {
             // group by group up to this tile's group, then tile by tile: every hop leads into a later one
-            const int32_t group_lo = group_exit ? lo - lo % (kGroupTiles * kJumpTile) : 0;
+            const int32_t group_lo = group_exit ? lo - lo % (kGroupTiles<NT> * jump_tile<NT>()) : 0;
             while (e < group_lo) e = group_exit[e];
             while (e < lo) e = exit_of[e];
             if (e >= lo + count) e = -1;              // the orbit passes over this tile
@@ -390,7 +429,7 @@ __global__ __launch_bounds__(kJumpThreads) void plan_mark_kernel(
     }
     __syncthreads();
     const int32_t entry = s_entry;
-    for (int32_t k = (int32_t)threadIdx.x; k < count; k += kJumpThreads) s_mark[k] = (uint8_t)(lo + k == entry);
+    for (int32_t k = (int32_t)threadIdx.x; k < count; k += NT) s_mark[k] = (uint8_t)(lo + k == entry);
     if (threadIdx.x == 0) {
         s_heads[0] = (uint16_t)max(entry - lo, 0);
         s_n_heads = entry >= 0 ? 1 : 0;
@@ -401,7 +440,7 @@ __global__ __launch_bounds__(kJumpThreads) void plan_mark_kernel(
         int cur = 0;
         for (int r = 0; r < kJumpRounds; ++r) {
             const int32_t* jump = s_jump[cur];
-            for (int32_t i0 = (int32_t)threadIdx.x - lane_id(); i0 < n_heads; i0 += kJumpThreads) {   // wave-uniform
+            for (int32_t i0 = (int32_t)threadIdx.x - lane_id(); i0 < n_heads; i0 += NT) {   // wave-uniform
                 const int32_t i = i0 + lane_id();
                 const int32_t to = i < n_heads ? jump[s_heads[i]] - lo : count;
                 const bool inside = to < count;
@@ -414,7 +453,7 @@ __global__ __launch_bounds__(kJumpThreads) void plan_mark_kernel(
                 const unsigned long long found = __ballot(inside);
                 if (found != 0ull && lane_id() == 63 - __builtin_clzll(found)) atomicMax(&s_n_heads, n_heads + i + 1);
             }
-            const bool more = jump_round_tile(s_jump[cur], s_jump[cur ^ 1], lo, count);
+            const bool more = jump_round_tile<NT>(s_jump[cur], s_jump[cur ^ 1], lo, count);
             cur ^= 1;
             const bool any_inside = __syncthreads_or(more ? 1 : 0) != 0;
             const int32_t now = s_n_heads;
@@ -447,8 +486,8 @@ __global__ __launch_bounds__(kJumpThreads) void plan_mark_kernel(
     const HeadPair upto = wave_scan(v, HeadOp(), LaneMove());
     if (lane_id() == kWave - 1) s_wave[wave_id()] = upto;
     __syncthreads();
-    if (threadIdx.x < kScanPerJump) {
-        const int32_t scan_tile = (int32_t)blockIdx.x * kScanPerJump + (int32_t)threadIdx.x;
+    if (threadIdx.x < kScans) {
+        const int32_t scan_tile = (int32_t)blockIdx.x * kScans + (int32_t)threadIdx.x;
         if ((int64_t)scan_tile * kTile < n_seq) {
             HeadPair sum{0, -1};
             for (int w = 0; w < kWavesPerScanTile; ++w)
@@ -460,12 +499,13 @@ __global__ __launch_bounds__(kJumpThreads) void plan_mark_kernel(
 }
 
 // Block and offset of every sequence, first position of every block, totals.  Every tile
-// adds up the head counts of the tiles before it by itself.
+// adds up the head counts of the tiles before it by itself.  With `at_position`, what the sequences get is left there, in
+// the order of the positions, for plan_gather_kernel.
 __global__ __launch_bounds__(kThreads) void plan_assign_kernel(
     const uint8_t* __restrict__ mark, const int32_t* __restrict__ order,
     const int64_t* __restrict__ prefix, int32_t n_seq, const int32_t* __restrict__ tile_cnt,
     const int32_t* __restrict__ tile_head, const int32_t* __restrict__ tile_bad,
-    int32_t* __restrict__ block_of_seq, int32_t* __restrict__ offset_of_seq,
+    int32_t* __restrict__ block_of_seq, int32_t* __restrict__ offset_of_seq, int2* __restrict__ at_position,
     int32_t* __restrict__ block_first, PlanResult* __restrict__ result)
 {
     // heads in front of this tile and the last of them; the last tile also collects the
@@ -501,9 +541,14 @@ __global__ __launch_bounds__(kThreads) void plan_assign_kernel(
                 run.head = (int32_t)p;
                 block_first[run.cnt - 1] = (int32_t)p;
             }
-            const int32_t i = order[p];
-            block_of_seq[i] = run.cnt - 1;
-            offset_of_seq[i] = (int32_t)(prefix[p] - prefix[run.head]);
+            const int32_t offset = (int32_t)(prefix[p] - prefix[run.head]);
+            if (at_position) {
+                at_position[p] = make_int2(run.cnt - 1, offset);
+            } else {
+                const int32_t i = order[p];
+                block_of_seq[i] = run.cnt - 1;
+                offset_of_seq[i] = offset;
+            }
             if (p == (int64_t)n_seq - 1) {
                 block_first[run.cnt] = n_seq;
                 result->num_blocks = run.cnt;
@@ -513,6 +558,22 @@ __global__ __launch_bounds__(kThreads) void plan_assign_kernel(
             }
         }
     }
+}
+
+// From the positions to the sequences: every sequence finds its position (the order is a permutation that runs backwards
+// as well) and fetches what lies there.  Two tables written in order and one look-up of 8 bytes, instead of two
+// stores of 4 bytes at random places, of which every compute die keeps lines of its own to write back: 10^6 sequences
+// 32 us, 11 + 12 like this.  Where the permutation's domain is more than 2.25 times the sequences the walks get too long
+// (300000: 97 us the call, 105 like this), and below 2^19 the launch costs what it saves.
+__global__ __launch_bounds__(kThreads) void plan_gather_kernel(const int2* __restrict__ at_position, int32_t n_seq, OrderKey key,
+                                                               int32_t* __restrict__ block_of_seq,
+                                                               int32_t* __restrict__ offset_of_seq)
+{
+    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (i >= n_seq) return;
+    const int2 v = at_position[position_of((uint32_t)i, (uint32_t)n_seq, key)];
+    block_of_seq[i] = v.x;
+    offset_of_seq[i] = v.y;
 }
 
 // The whole plan of at most kTile sequences in one workgroup: the same steps as the
@@ -866,7 +927,7 @@ struct PlanLayout {
     int32_t n_tiles;           // scan tiles
     int32_t sums_per_tile;     // workgroups of the order kernel to a scan tile
     int32_t n_sums;
-    int32_t n_jump_tiles;
+    int32_t n_jump_tiles, jump_threads;
 };
 
 static PlanLayout plan_layout(int64_t n_seq)
@@ -874,7 +935,8 @@ static PlanLayout plan_layout(int64_t n_seq)
     PlanLayout l{};
     const size_t n = (size_t)(n_seq > 0 ? n_seq : 0);
     l.n_tiles = (int32_t)ceil_div((int64_t)n, kTile);
-    l.n_jump_tiles = (int32_t)ceil_div((int64_t)n, kJumpTile);
+    l.jump_threads = (int64_t)n <= kSmallTilesUpTo ? 128 : (int64_t)n <= kMidTilesUpTo ? 256 : 512;
+    l.n_jump_tiles = (int32_t)ceil_div((int64_t)n, l.jump_threads * kJumpItems);
     l.sums_per_tile = (int64_t)n <= kSingleItems ? kItems : 1;
     l.n_sums = (int32_t)ceil_div((int64_t)n, kTile / l.sums_per_tile);
     size_t off = 0;
@@ -883,11 +945,11 @@ static PlanLayout plan_layout(int64_t n_seq)
     l.shuffled_len = take(n * 4);
     l.prefix = take((n + 1) * 8);
     l.next = take(n * 4);
-    l.exit_of = take(n * 4);
+    l.exit_of = take(n * 4);           // (right behind `next`: the two are one table of 8 bytes per position in the end)
     l.mark = take(n);
     l.tile_cnt = take((size_t)l.n_tiles * 4);
     l.tile_head = take((size_t)l.n_tiles * 4);
-    l.tile_entry = take((size_t)l.n_jump_tiles * 4);
+    l.tile_entry = take((size_t)ceil_div((int64_t)n, kJumpTile) * 4);      // (only the largest tiles are so many that it is used)
     l.tile_bad = take((size_t)l.n_tiles * 4);
     l.bytes = off;
     // (12 bytes per 256 positions and a rest, beyond 2048 positions of 4 bytes: they fit)
@@ -988,23 +1050,33 @@ extern "C" bload_status bload_plan(const int32_t* d_lengths, int64_t n_seq, int3
         // where the orbit of position 0 enters each jump tile: a single tile it enters at 0; up to
         // kWalkTiles tiles every tile finds its own entry; beyond, one thread finds them all
         const bool one_jump_tile = l.n_jump_tiles == 1, tiles_walk = l.n_jump_tiles <= kWalkTiles;
-        if (!one_jump_tile)
-            hipLaunchKernelGGL(plan_exit_kernel, jump_tiles, dim3(kJumpThreads), 0, stream, next, n, exit_of);
         const bool grouped = tiles_walk && l.n_jump_tiles >= kGroupFrom;
         int32_t* group_exit = shuffled_len;       // (the shuffled lengths are not needed any more)
-        if (grouped)
-            hipLaunchKernelGGL(plan_group_exit_kernel, dim3((uint32_t)ceil_div(l.n_jump_tiles, kGroupTiles), kGroupSpread),
-                               block, 0, stream, next, exit_of, n, group_exit);
-        if (!tiles_walk)
-            hipLaunchKernelGGL(plan_chain_kernel, dim3(1), block, 0, stream, exit_of, n, l.n_jump_tiles,
-                               tile_entry);
-        hipLaunchKernelGGL(plan_mark_kernel, jump_tiles, dim3(kJumpThreads), 0, stream, next,
-                           tiles_walk ? nullptr : tile_entry, one_jump_tile ? nullptr : exit_of,
-                           grouped ? group_exit : nullptr, n, mark,
-                           tile_cnt, tile_head);
+        auto jump = [&](auto threads) {
+            constexpr int NT = decltype(threads)::value;
+            if (!one_jump_tile)
+                hipLaunchKernelGGL(plan_exit_kernel<NT>, jump_tiles, dim3(NT), 0, stream, next, n, exit_of);
+            if (grouped)
+                hipLaunchKernelGGL(plan_group_exit_kernel<NT>, dim3((uint32_t)ceil_div(l.n_jump_tiles, kGroupTiles<NT>), kGroupSpread),
+                                   block, 0, stream, next, exit_of, n, group_exit);
+            if (!tiles_walk)
+                hipLaunchKernelGGL(plan_chain_kernel, dim3(1), block, 0, stream, exit_of, n, l.n_jump_tiles, jump_tile<NT>(),
+                                   tile_entry);
+            hipLaunchKernelGGL(plan_mark_kernel<NT>, jump_tiles, dim3(NT), 0, stream, next, tiles_walk ? nullptr : tile_entry,
+                               one_jump_tile ? nullptr : exit_of, grouped ? group_exit : nullptr, n, mark, tile_cnt, tile_head);
+        };
+        if (l.jump_threads == 128) jump(std::integral_constant<int, 128>());
+        else if (l.jump_threads == 256) jump(std::integral_constant<int, 256>());
+        else jump(std::integral_constant<int, 512>());
+        // (`next` and `exit_of` behind it, 8 bytes per position, are not needed any more)
+        const bool gathers = n_seq >= kGatherFrom && ((int64_t)1 << (2 * key.half_bits)) * 4 <= n_seq * 9;
+        int2* at_position = gathers ? reinterpret_cast<int2*>(next) : nullptr;
         hipLaunchKernelGGL(plan_assign_kernel, tiles, block, 0, stream, mark, d_order, prefix, n,
-                           tile_cnt, tile_head, tile_bad, d_block_of_seq, d_offset_of_seq,
+                           tile_cnt, tile_head, tile_bad, d_block_of_seq, d_offset_of_seq, at_position,
                            d_block_first, result);
+        if (at_position)
+            hipLaunchKernelGGL(plan_gather_kernel, dim3((uint32_t)ceil_div(n_seq, kThreads)), block, 0, stream, at_position, n,
+                               key, d_block_of_seq, d_offset_of_seq);
     }
     if (launch_status() != BLOAD_OK) return BLOAD_EHIP;
 

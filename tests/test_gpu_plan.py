@@ -135,3 +135,21 @@ def test_plan_one_workgroup_of_sixteen_waves(n):
         with pytest.raises(bl.BloadError) as e:
             gpu_plan(L, 300, 1)
         assert e.value.status == bl.ELENGTH
+
+
+# Jump tiles of 2048, 4096 and 8192 positions (up to 160000 sequences, 2^20, beyond): one position in the last tile, in the
+# last group of 16 or 8 of them, both sides of the line from which on groups are used; the sequences fetch what
+# they get from 2^19 on (unless the order's domain is much larger); blocks that pass over tiles and groups.
+@pytest.mark.parametrize("n", [12289, 7 * 2048, 7 * 2048 + 1, 39 * 2048, 40 * 2048 - 1, 40 * 2048 + 1, 48 * 2048 + 1, 160000, 160001,
+                               48 * 4096 + 1, (1 << 19) - 1, 1 << 19, 600001, (1 << 20) - 1, (1 << 20) + 1, 1200000])
+@pytest.mark.parametrize("T,kind", [(1, "uniform"), (40, "short"), (3000, "uniform"), (4096, "heavy"), (100000, "short"), (300, "two")])
+def test_plan_sizes_of_jump_tiles(n, T, kind):
+    rng = np.random.default_rng(n + T)
+    if kind == "heavy":
+        L = np.clip(rng.zipf(1.2, size=n), 1, T).astype(np.int32)
+    elif kind == "two":
+        L = np.full(n, T // 2, dtype=np.int32)
+    else:
+        L = workloads.random_lengths(rng, n, T, kind)
+    print(f"plan n={n} T={T} kind={kind}", flush=True)
+    assert_plan_equal(gpu_plan(L, T, 7), oracle.plan(L, T, oracle.order(n, 7)), n)
