@@ -710,12 +710,16 @@ __global__ __launch_bounds__(kMidThreads) void plan_mid_kernel(
 
     int bad = 0;
     for (int k = tid; k < n_bads; k += kMidThreads) bad |= bads[k];
-    for (int p = tid; p < n_seq; p += kMidThreads) sh.prefix[p] = shuffled_len[p];
+    int32_t x[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) x[j] = shuffled_len[min(tid + j * kMidThreads, n_seq - 1)];      // all asked for at once
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if (tid + j * kMidThreads < n_seq) sh.prefix[tid + j * kMidThreads] = x[j];
     for (int w = tid; w < kMidThreads * kMidPer / 32; w += kMidThreads) sh.mark[w] = 0;
     bad = __syncthreads_or(bad);
 
     // prefix sums, in place
-    int32_t x[PER];
     int32_t sum = 0;
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
