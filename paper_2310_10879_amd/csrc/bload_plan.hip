@@ -671,7 +671,7 @@ __global__ __launch_bounds__(kThreads) void plan_small_kernel(
 // What the sequences get is left in the order of the positions; plan_scatter_kernel brings it to them, which one
 // compute unit would take longer for than the launch does.
 // Bound by the latency of LDS.  Whole call, before and after: 10^4 sequences of heavy-tailed length in blocks of 3000, six launches -> three,
-// 57 -> 44 us, nearly full blocks 74 -> 63; 3001 sequences, one to six to a block, 52 -> 34.
+// 56 -> 40 us, nearly full blocks 74 -> 61; 3001 sequences, one to six to a block, 52 -> 34.
 constexpr int kMidThreads = 1024;
 constexpr int kMidWaves = kMidThreads / kWave;
 constexpr int kMidPer = 13;                       // an odd number, so that the threads' places in LDS spread over the banks

@@ -300,7 +300,7 @@ __global__ __launch_bounds__(kWave) void rf_draw_kernel(
         const uint64_t u = splitmix64_at(seed, (uint64_t)(6 + (placed & ~(kWave - 1)) + lane));
         u_lo = (uint32_t)u;
         u_hi = (uint32_t)(u >> 32);
-        const RfPick k = pick[((placed - 1) & ~(kWave - 1)) + lane];     // (those behind `placed` mean nothing yet)
+        const RfPick k = pick[min(((placed - 1) & ~(kWave - 1)) + lane, placed - 1)];      // (lanes behind are set before they are stored)
         kept_where = k.where;
         kept_left = k.left;
     }

@@ -1392,8 +1392,8 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
         // Rows of one wave and sequences of a few frames: the waves' chunks hold very different numbers of pieces, and
         // all are at work at once, so that the call lasts as long as the slowest.  Twice as many shorter chunks
         // even that out, and a segment that ends within 64 slots behind a border stays in one piece, so that they
-        // hardly make more partial sums (10000 sequences of 23 frames of 4096 bytes: 220 -> 203 us; 330 of them 21.4
-        // -> 18.1; 8900 of 3072 bytes 176 -> 157).  Longer pieces lose by it (500 of 280 frames: 128 -> 135 us).
+        // hardly make more partial sums (10000 sequences of 23 frames of 4096 bytes: 220 -> 203 us, another draw of
+        // them 219 both; 330 of them 21.4 -> 18.1; 8900 of 3072 bytes 176 -> 157).  Longer pieces lose by it (500 of 280 frames: 128 -> 135 us).
         if (!lean && whole && p.row_lanes_log2 == 6 && want > 1 && mean <= kShortPieces) {
             want = std::min<int64_t>(ceil_div((int64_t)2048 * rows, num_blocks * feat_tiles), t_blk / 32);
             chunk = ceil_div(t_blk, want);
