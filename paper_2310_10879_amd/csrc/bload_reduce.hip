@@ -1394,7 +1394,8 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
         // even that out, and a segment that ends within 64 slots behind a border stays in one piece, so that they
         // hardly make more partial sums (10000 sequences of 23 frames of 4096 bytes: 220 -> 203 us, another draw of
         // them 219 both; 330 of them 21.4 -> 18.1; 8900 of 3072 bytes 176 -> 157).  Longer pieces lose by it (500 of 280 frames: 128 -> 135 us).
-        if (!lean && whole && p.row_lanes_log2 == 6 && want > 1 && mean <= kShortPieces) {
+        // (Not where the chunks above are cut for more workgroups than are at work at once: those are the more.)
+        if (!lean && whole && p.row_lanes_log2 == 6 && want > 1 && whole_block_groups < 2048 && mean <= kShortPieces) {
             want = std::min<int64_t>(ceil_div((int64_t)2048 * rows, num_blocks * feat_tiles), t_blk / 32);
             chunk = ceil_div(t_blk, want);
             reach = 64;

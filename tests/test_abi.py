@@ -104,6 +104,19 @@ def test_reduce_reads_whole_vectors_whatever_lanes_idle(lib, D, dtype):
     assert reduce_query(lib)(3000, 3000, D, dtype) == chunks * 16 + 2 * chunks * D * acc
 
 
+@pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="a call that is not refused would be launched on these addresses")
+@pytest.mark.parametrize("B,T,D", [(9000, 3000, 512), (9000, 4096, 512), (12000, 1024, 1024), (2300, 8192, 2048)])
+def test_reduce_cuts_many_blocks_as_finely_for_short_pieces(lib, B, T, D):
+    """Whole blocks that make 2048 to 12288 workgroups are cut into more of them, whatever the length of the pieces: 16
+    bytes less than that cut needs are refused, with pieces of 20 frames and of 500."""
+    p, need, f = ctypes.c_void_p(0x10000), reduce_query(lib)(B, T, D, 1), lib.bload_segment_reduce
+    assert need >= 2 * B * (16 + 2 * D * 4)
+    f.restype = ctypes.c_int
+    for frames in (20, 500):
+        assert f(p, p, p, p, ctypes.c_int64(B), ctypes.c_int32(T), ctypes.c_int64(D), 1, 1,
+                 ctypes.c_int64(B * T // frames), p, p, ctypes.c_size_t(need - 16), None) == 3
+
+
 def test_argument_checks_need_no_gpu(lib):
     # every call below must be refused on the host, before any HIP call
     vp, i64, i32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32
