@@ -63,7 +63,7 @@ struct ReduceArgs {
     void* out;               // [n_seq, feat_dim] float or int64
     // chunking
     int32_t chunk;           // slots per chunk
-    int32_t reach;           // wide: slots behind a chunk that a segment begun in front may end in and stay whole
+    int32_t split;           // wide, rows of one wave: 1 if two waves share a chunk
     int32_t tile;            // staged, several tiles per workgroup: slots per tile
     int32_t n_chunks;        // wide: chunks per block
     int32_t row_lanes_log2;  // wide: lanes per row = 1 << this
@@ -275,26 +275,27 @@ template <typename ElemT, int VEC, bool WAVE_ROW, bool STREAM>
 __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
 {
     typedef typename Elem<ElemT>::Acc Acc;
-    extern __shared__ uint8_t s_flags[];   // rows x (chunk + 2): bit0 valid, bit1 reset
+    extern __shared__ uint8_t s_flags[];   // chunks x (chunk + 2): bit0 valid, bit1 reset
     const int tid = (int)threadIdx.x;
-    const int C = a.chunk, stride = C + a.reach + 2;
-    const int rows = kThreads >> a.row_lanes_log2;
+    const int C = a.chunk, stride = C + 2;
+    const int split = WAVE_ROW ? a.split : 0;
+    const int chunks = (kThreads >> a.row_lanes_log2) >> split;       // of the workgroup
     // consecutive workgroups take the lane-slices of one frame range, so that
     // workgroups running side by side read neighbouring memory
     const int feat_tile = (int)(blockIdx.x % (uint32_t)a.feat_tiles);
-    const int64_t q_base = (int64_t)(blockIdx.x / (uint32_t)a.feat_tiles) * rows;
+    const int64_t q_base = (int64_t)(blockIdx.x / (uint32_t)a.feat_tiles) * chunks;
     const int64_t T = a.t_blk;
 
-    // stage the flags of this workgroup's chunks, plus the slot before and the slots as far as a
-    // segment is followed behind each chunk (0 outside the block): row r holds slots t0-1 .. t0+len+reach
-    for (int r = 0; r < rows; ++r) {
+    // stage the flags of this workgroup's chunks, plus the slot before and the slot
+    // after each chunk (0 outside the block): row r holds slots t0-1 .. t0+len
+    for (int r = 0; r < chunks; ++r) {
         const int64_t q = q_base + r;
         if (q >= a.total_chunks) break;
         const int64_t b = q / a.n_chunks;
         const int32_t t0 = (int32_t)(q - b * a.n_chunks) * C;
         const int32_t len = min(C, a.t_blk - t0);
         const int64_t g = b * T + t0;
-        for (int t = tid - 1; t <= len + a.reach; t += kThreads) {
+        for (int t = tid - 1; t <= len; t += kThreads) {
             uint8_t f = 0;
             if (t0 + t >= 0 && t0 + t < a.t_blk)
                 f = (uint8_t)((a.valid[g + t] ? 1 : 0) | (a.reset[g + t] ? 2 : 0));
@@ -305,7 +306,7 @@ __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
 
     const int row = WAVE_ROW ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> a.row_lanes_log2;
     const int col = WAVE_ROW ? lane_id() : tid & ((1 << a.row_lanes_log2) - 1);
-    const int64_t q = q_base + row;
+    const int64_t q = q_base + (row >> split);
     if (q >= a.total_chunks) return;
     // which lane-slice of the frame; the surplus lanes of a row stay alive (they
     // take part in the votes of next_slot), read what the last lane reads, and store nothing
@@ -316,20 +317,17 @@ __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
     const int64_t b = q / a.n_chunks;
     const int32_t t0 = (int32_t)(q - b * a.n_chunks) * C;
     const int64_t g = b * T + t0;
-    const uint8_t* flags = s_flags + row * stride + 1;      // flags[-1] = the slot before the chunk
-    // A segment that runs over a border between two chunks and ends within `reach` slots behind it belongs whole to the
-    // chunk in front: both see the same flags and agree.  (`reach` is no longer than a chunk.)
-    int32_t len = min(C, a.t_blk - t0), begin = 0;
-    auto goes_on = [&](int32_t border) { return (flags[border] & 3) == 1 && (flags[border - 1] & 1); };
-    if (a.reach > 0) {
-        if (goes_on(0)) {
-            const int32_t end = next_slot<false, WAVE_ROW>(flags, 1, a.reach + 1, a.row_lanes_log2);
-            if (end <= a.reach) begin = end;
-        }
-        if (goes_on(len)) {
-            const int32_t end = next_slot<false, WAVE_ROW>(flags, len + 1, len + a.reach + 1, a.row_lanes_log2);
-            if (end <= len + a.reach) len = end;
-        }
+    const uint8_t* flags = s_flags + (row >> split) * stride + 1;      // flags[-1] = the slot before the chunk
+    // Two waves to a chunk: the first one takes the segments that begin in front of the middle (and the one that comes
+    // in), to their end or the chunk's, the second one those behind.  Neither cuts one.
+    const int32_t chunk_len = min(C, a.t_blk - t0);
+    int32_t len = chunk_len, begin = 0;
+    if (split) {
+        int32_t cut = (chunk_len + 1) >> 1;
+        if (cut < chunk_len && (flags[cut] & 3) == 1 && (flags[cut - 1] & 1))
+            cut = next_slot<false, WAVE_ROW>(flags, cut + 1, chunk_len, a.row_lanes_log2);
+        if (row & 1) begin = cut;
+        else len = cut;
     }
     const int64_t frame_bytes = (int64_t)a.feat_dim * (int64_t)sizeof(ElemT);
     const uint8_t* chunk_src = a.packed + g * frame_bytes;                 // the chunk's first frame
@@ -348,7 +346,7 @@ __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
     Acc* scratch = nullptr;
     const int64_t wave_feat0 = (int64_t)(fv_raw - lane_id()) * VEC;   // first feature of the wave
     if (VEC > 1 && WAVE_ROW) {
-        const size_t flag_bytes = ((size_t)rows * stride + 15) & ~(size_t)15;
+        const size_t flag_bytes = ((size_t)chunks * stride + 15) & ~(size_t)15;
         scratch = reinterpret_cast<Acc*>(s_flags + flag_bytes) + (size_t)wave_id() * kWave * kScratchStride<Acc, VEC>();
     }
 
@@ -442,7 +440,20 @@ __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
         }
         t = e;
     }
-    if (writes_desc) a.desc[q] = desc;
+    if (!writes_desc) return;
+    if (!split) {
+        a.desc[q] = desc;
+        return;
+    }
+    // what comes in is the first wave's, what goes out that one's whose slots are the chunk's last
+    if ((row & 1) == 0) {
+        a.desc[q].head_state = desc.head_state;
+        a.desc[q].cnt_head = desc.cnt_head;
+    }
+    if ((row & 1) == 0 ? len == chunk_len : begin < chunk_len) {
+        a.desc[q].cnt_tail = desc.cnt_tail;
+        a.desc[q].seq_tail = desc.seq_tail;
+    }
 }
 
 // ----------------------------------------------------------------- narrow
@@ -1290,7 +1301,7 @@ struct ReducePlan {
     bool wide, staged;
     bool run;                // staged: a workgroup takes the tiles of a whole chunk one after another
     int32_t tile;            // of this many slots
-    int32_t reach;           // wide: see ReduceArgs
+    bool split;              // wide: two waves to a chunk
     int vec;                 // wide: elements per lane (16 bytes, 4 bytes or one element)
     int row_lanes_log2;
     int n_vec;
@@ -1388,26 +1399,22 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
             if (want > most_long) want = most_long;
         }
         int64_t chunk = ceil_div(t_blk, want);
-        int64_t reach = 0;
         // Rows of one wave and sequences of a few frames: the waves' chunks hold very different numbers of pieces, and
-        // all are at work at once, so that the call lasts as long as the slowest.  Twice as many shorter chunks
-        // even that out, and a segment that ends within 64 slots behind a border stays in one piece, so that they
-        // hardly make more partial sums (10000 sequences of 23 frames of 4096 bytes: 220 -> 203 us, another draw of
-        // them 219 both; 330 of them 21.4 -> 18.1; 8900 of 3072 bytes 176 -> 157).  Longer pieces lose by it (500 of 280 frames: 128 -> 135 us).
-        // (Not where the chunks above are cut for more workgroups than are at work at once: those are the more.)
-        if (!lean && whole && p.row_lanes_log2 == 6 && want > 1 && whole_block_groups < 2048 && mean <= kShortPieces) {
-            want = std::min<int64_t>(ceil_div((int64_t)2048 * rows, num_blocks * feat_tiles), t_blk / 32);
-            chunk = ceil_div(t_blk, want);
-            reach = 64;
-        }
-        const int64_t lds_cap = (kWideFlagBytes / rows - 2) / (reach ? 2 : 1);
+        // all are at work at once, so that the call lasts as long as the slowest.  Two waves to a chunk even that out, and
+        // as neither cuts a segment they make no partial sums beyond those of the chunk (10000 sequences of 23 frames of 4096
+        // bytes: 221 -> 203 us; 330 of them 21.0 -> 17.5; 8900 of 3072 bytes 156 -> 142).  Chunks half as long would do
+        // that too, but where pieces are long, as they may be in a worker's share whatever `mean` says, those cost partial
+        // sums (an eighth of the rows, 128 frames of 1024 bytes in blocks of 300: 99 us, 136 in half chunks, 101 like
+        // this; 250 of 4096 bytes 65, 77, 68).  (Not where the chunks above are cut for more workgroups than are at work
+        // at once.)
+        p.split = !lean && whole && p.row_lanes_log2 == 6 && want > 1 && whole_block_groups < 2048 && mean <= kShortPieces;
+        const int64_t lds_cap = kWideFlagBytes / rows - 2;
         if (chunk > lds_cap) chunk = lds_cap;
         p.chunk = (int32_t)chunk;
-        p.reach = (int32_t)std::min(reach, chunk);
         p.n_chunks = (int32_t)ceil_div(t_blk, chunk);
         p.total_chunks = num_blocks * p.n_chunks;
         p.partials = p.n_chunks > 1;
-        const int64_t groups = ceil_div(p.total_chunks, rows) * feat_tiles;
+        const int64_t groups = ceil_div(p.total_chunks << p.split, rows) * feat_tiles;
         // Small frames in rows of a few lanes: a workgroup walks many chunks, and where that leaves too
         // few workgroups the staged tiles are the more.  The line lies at some 24 KiB of lanes' vectors at a time,
         // at half of that for blocks of less than two chunks (13 blocks of 1580 slots x 128 bytes: 33 -> 15 us;
@@ -1473,9 +1480,9 @@ template <typename ElemT, int VEC, bool STREAM>
 static void launch_wide(const ReducePlan& p, const ReduceArgs& a, hipStream_t stream)
 {
     typedef typename Elem<ElemT>::Acc Acc;
-    const int rows = kThreads >> p.row_lanes_log2;
-    const dim3 grid((uint32_t)(ceil_div(p.total_chunks, rows) * a.feat_tiles));
-    size_t lds = (size_t)rows * (size_t)(p.chunk + p.reach + 2);
+    const int chunks = (kThreads >> p.row_lanes_log2) >> p.split;      // of a workgroup
+    const dim3 grid((uint32_t)(ceil_div(p.total_chunks, chunks) * a.feat_tiles));
+    size_t lds = (size_t)chunks * (size_t)(p.chunk + 2);
     if (VEC > 1 && p.row_lanes_log2 >= 6)     // + the per-wave scratch of the transposed stores
         lds = round_up(lds, 16) + (size_t)(kThreads / kWave) * kWave * kScratchStride<Acc, VEC>() * sizeof(Acc);
     if (p.row_lanes_log2 == 6)
@@ -1559,7 +1566,7 @@ extern "C" bload_status bload_segment_reduce(const void* d_packed, const int32_t
         if (lean.bytes <= room) p = lean;
     }
     if (p.total_chunks * ceil_div(feat_dim, kThreads) > INT32_MAX) return BLOAD_EOVERFLOW;
-    if (p.wide && ceil_div(p.total_chunks, kThreads >> p.row_lanes_log2) *
+    if (p.wide && ceil_div(p.total_chunks, (kThreads >> p.row_lanes_log2) >> p.split) *
                       ceil_div(p.n_vec, 1 << p.row_lanes_log2) > INT32_MAX)
         return BLOAD_EOVERFLOW;
     if (p.partials) {
@@ -1585,7 +1592,7 @@ extern "C" bload_status bload_segment_reduce(const void* d_packed, const int32_t
     a.out = d_out;
     a.chunk = p.chunk;
     a.tile = p.tile;
-    a.reach = p.wide ? p.reach : 0;
+    a.split = p.wide && p.split ? 1 : 0;
     a.n_chunks = p.n_chunks;
     a.row_lanes_log2 = p.row_lanes_log2;
     a.n_vec = p.n_vec;

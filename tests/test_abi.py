@@ -104,6 +104,14 @@ def test_reduce_reads_whole_vectors_whatever_lanes_idle(lib, D, dtype):
     assert reduce_query(lib)(3000, 3000, D, dtype) == chunks * 16 + 2 * chunks * D * acc
 
 
+def test_reduce_chunks_do_not_hang_on_the_pieces(lib):
+    """Rows of one wave: for sequences of a few frames two waves share a chunk, but no block is cut in more of them (a
+    worker's share has the rows of all workers, and its pieces may be long ones)."""
+    f = reduce_query(lib)
+    for B, T, D, dtype, chunks in ((79, 3000, 2048, 1, 13), (977, 300, 1024, 0, 4), (12, 640, 256, 2, 10)):
+        assert f(B, T, D, dtype) == B * chunks * (16 + 2 * D * 4)
+
+
 @pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="a call that is not refused would be launched on these addresses")
 @pytest.mark.parametrize("B,T,D", [(9000, 3000, 512), (9000, 4096, 512), (12000, 1024, 1024), (2300, 8192, 2048)])
 def test_reduce_cuts_many_blocks_as_finely_for_short_pieces(lib, B, T, D):

@@ -425,10 +425,9 @@ def test_reduce_runs_of_tiles(B, T, D, dtype, op):
     assert np.all(np.abs(got.astype(np.float64) - want.astype(np.float64)) <= bound)
 
 
-# Rows of one wave and many short sequences: blocks are cut into chunks of 32 slots and more (74 of 180 blocks of 3000), and
-# a segment that ends within the next chunk, and within 64 slots, belongs to the chunk it began in.  Segments that
-# begin and end at the chunks' borders, one slot beside them, as far behind them as they are followed and one slot farther,
-# some over several chunks, padding there as well.
+# Rows of one wave and many short sequences: two waves share a chunk (64 slots; 67 and 66; 131 of 180 blocks of 3000), the first
+# takes the segments that begin in front of its middle.  Segments that begin and end at the chunks' borders and middles and
+# one slot beside them, some over several chunks, some from a middle to a border, padding there as well.
 @pytest.mark.parametrize("B,T,dtype,op", [(12, 640, "f32", "mean"), (12, 640, "i32", "sum"), (12, 640, "u8", "mean"),
                                           (12, 640, "f16", "sum"), (7, 133, "f16", "mean"), (1, 128, "f16", "mean"),
                                           (180, 3000, "f16", "mean")])
@@ -436,10 +435,11 @@ def test_reduce_short_pieces_over_chunk_borders(B, T, dtype, op):
     bl = binding()
     rng = np.random.default_rng(B + T)
     D = 1024 // bl.ELEM_BYTES[dtype]
-    most = max(1, T // 32)
-    chunk = -(-T // min(most, -(-2048 * 4 // B)))
-    reach = min(64, chunk)
-    at = [c * chunk + k for c in range(1, T // chunk + 1) for k in (-1, 0, 1, reach - 1, reach, reach + 1)]
+    chunk = -(-T // min(T // 64, -(-1024 * 4 // B)))
+    chunks = B * -(-T // chunk)
+    # (the query tells how many chunks there are)
+    assert bl.bload_segment_reduce_workspace_bytes(B, T, D, dtype) == chunks * (16 + 2 * D * (8 if dtype == "i32" else 4))
+    at = [t0 + m + k for t0 in range(0, T, chunk) for m in (0, (min(chunk, T - t0) + 1) // 2) for k in (-1, 0, 1)]
     at = np.array([t for t in at if 0 < t < T])
     valid, reset = np.ones((B, T), np.uint8), np.zeros((B, T), np.uint8)
     for b in range(B):
