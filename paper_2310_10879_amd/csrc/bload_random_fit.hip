@@ -43,7 +43,9 @@ static_assert(kRfMaxT <= 1 << 15, "lengths and offsets, counted from 0, take 15 
 
 // Where the chain of draws goes on behind those that were made in batches.
 struct RfState {
-    int32_t placed, blocks;   // draws made, blocks that they fill
+    int32_t placed, blocks;   // draws made, blocks begun
+    int32_t room;             // what is free in the last of them
+    int32_t pad_;
 };
 
 __global__ void rf_clear_kernel(PlanResult* result)
@@ -229,15 +231,17 @@ __global__ __launch_bounds__(kThreads) void rf_scatter_kernel(
 // nothing changes.  A value that depends on right values in front of it alone is right, so after every
 // round the draws up to the first one that changed are exactly those of the chain: the rounds end, and
 // how many they are only depends on how far a wrong guess is carried on.  10^4 sequences of heavy-tailed
-// lengths take 5 rounds per 64 draws, lengths near the block's 3, lengths spread evenly over it 20 to 40, and 6 where
-// blocks are guessed ahead (below).
+// lengths take 5 rounds per 64 draws, lengths near the block's 3, clips of a sixteenth of it and more 26, and 6 where
+// blocks are guessed ahead (below); lengths spread evenly over it 20 to 40, guessed ahead or not.
 // (rank_i is a fixed point of its own equation as well.  One on a rank already taken can be reached from
 // above only and has nothing but taken ranks down to the right one: it is then lowered by one.)
 // Bound by latency, like the chain: a round is 0.6 us of some 180 dependent instructions and three look-ups in LDS, on a
 // workgroup whose 8 waves share the counting (64 x 63 / 2 comparisons of two limits, 16 bits each); what follows the
 // rounds of a batch (taking the ranks out of the list and the counts) 2.6 us; 64 draws one after another 14 us.  Whole
-// call, before and after, 10^4 sequences in blocks of 3000: heavy-tailed lengths 2258 -> 915 us, nearly full blocks
-// 3540 -> 700, clips 3130 -> 1500; lengths spread evenly, which give up after the trial, 3060 -> 3025.
+// call, before and after, 10^4 sequences in blocks of 3000: heavy-tailed lengths 2250 -> 930 us, nearly full blocks
+// 3540 -> 705, clips 3110 -> 1505; lengths spread evenly, which give up after the trial, 3055 -> 2985.
+// Where they stop paying, batches end at once and the chain goes on within the block.  (Ones and halves of a block of 8192: 3060
+// us by the chain alone, 3030 like this, 5300 where batches went on until a block began in the middle of one.)
 //
 // One after another (rf_draw_kernel): what is left where batches cost more than they bring, and sequences beyond
 // kRfBatchMost.
@@ -257,8 +261,8 @@ __global__ __launch_bounds__(kThreads) void rf_scatter_kernel(
 // picked with an indexed register move, which saves the two waits for LDS of a draw (256 -> 233 ns);
 // more than 32 registers cannot be indexed as one, and choosing between two sets costs more
 // instructions than the waits (83 in all, 270 ns).  GROUPS_HI: more than 64 groups (t_blk > 4096).
-// With `state`, the draws behind it, which begin with a block of their own; the values that the loop begins with are
-// all there is to that (a flag in the loop, or the loop behind the batches in one kernel: 7 to 13 % slower).
+// With `state`, the draws behind it, in the block that is open there: the loop is entered in the middle of a block and
+// needs to know nothing else (a flag in it, or the loop behind the batches in one kernel: 7 to 13 % slower).
 constexpr int kRfRegisterRows = 32;
 typedef int32_t rf_rows __attribute__((ext_vector_type(kRfRegisterRows)));
 
@@ -287,13 +291,14 @@ __global__ __launch_bounds__(kWave) void rf_draw_kernel(
         if (lane == 0 && host_result) host_result->bad_length = bad;
         return;
     }
-    const RfState from = state ? *state : RfState{0, 0};
+    const RfState from = state ? *state : RfState{0, 0, 0, 0};
     if (from.placed == n_seq) return;                    // the batches were all
 
     // Every block takes at least one sequence (all of them fit an empty block), every placement
     // uses up room, and at most n_seq blocks are begun: the loop ends whatever the sums hold.
     int32_t placed = from.placed, blocks = from.blocks;
-    int32_t last = -1;                                   // the longest length that fits, counted from 0; -1: none
+    int32_t last = from.room - 1;                        // the longest length that fits, counted from 0; -1: none
+    int32_t least = -1;                                  // of these at the blocks' ends: below -1 only if the sums were wrong
     uint32_t u_lo = 0, u_hi = 0;
     int32_t kept_where = 0, kept_left = 0;               // placement (placed & ~63) + lane
     if (placed > 0) {
@@ -304,10 +309,8 @@ __global__ __launch_bounds__(kWave) void rf_draw_kernel(
         kept_where = k.where;
         kept_left = k.left;
     }
-    while (placed < n_seq && blocks < n_seq && last >= -1) {
-      if (lane == 0) block_first[blocks] = placed;
-      blocks += 1;
-      last = t_blk - 1;
+    __builtin_amdgcn_s_waitcnt(0);                       // (or every draw waits for what is loaded above)
+    for (;;) {
       while (last >= 0) {
         const int g_room = last >> 6;
         int32_t fit = REGISTERS ? __builtin_amdgcn_readlane(rows[g_room & (kRfRegisterRows - 1)], last & 63)
@@ -355,14 +358,19 @@ __global__ __launch_bounds__(kWave) void rf_draw_kernel(
         const int32_t where = drawn << 16 | last;
         kept_where = lane == turn ? where : kept_where;
         kept_left = lane == turn ? left : kept_left;
-        last -= drawn + 1;                               // (below -1 only if the sums were wrong)
+        last -= drawn + 1;
         placed += 1;
       }
+      least = min(least, last);
+      if (max(placed, blocks) >= n_seq) break;           // (one test a block: three cost 3 % where blocks hold a sequence or two)
+      if (lane == 0) block_first[blocks] = placed;
+      blocks += 1;
+      last = t_blk - 1;
     }
     const int32_t rest = (placed - 1) & (kWave - 1);     // the last set of placements
     if (placed > 0 && lane <= rest) pick[placed - 1 - rest + lane] = RfPick{kept_where, kept_left};
     if (lane == 0) {
-        if (last >= -1 && placed == n_seq) {
+        if (least == -1 && placed == n_seq) {
             block_first[blocks] = n_seq;
             result->num_blocks = blocks;
         } else {
@@ -371,7 +379,7 @@ __global__ __launch_bounds__(kWave) void rf_draw_kernel(
         if (host_result) {
             host_result->num_blocks = blocks;
             host_result->total_frames = result->total_frames;
-            host_result->bad_length = last >= -1 && placed == n_seq ? 0 : 2;
+            host_result->bad_length = least == -1 && placed == n_seq ? 0 : 2;
         }
     }
 }
@@ -379,8 +387,11 @@ __global__ __launch_bounds__(kWave) void rf_draw_kernel(
 constexpr int kRfBatch = kWave;                   // draws at a time, a lane each
 constexpr int kRfBatchWaves = 8;                  // two per SIMD hide each other's latencies
 constexpr int kRfBatchThreads = kRfBatchWaves * kWave;
-constexpr int kRfBatchMost = 24576;               // sequences: two lists of them fit the LDS
-constexpr int kRfBatchLeast = 768;                // a trial that brings nothing and the second launch cost 8 us
+constexpr int kRfBatchMost = 24576;               // sequences: what is kept of them in LDS, 35 bits each, is 129 KiB with the rest
+// From so many sequences on.  A trial that brings nothing and the second launch cost 8 us, 3 % of a call here, and batches that
+// pay until few sequences are left up to 20 (lengths of some tenth of a block of 40: 218 -> 235 us); lengths near the
+// block's gain half (304 -> 136), heavy-tailed ones in blocks of 3000 40 % (226 -> 138).
+constexpr int kRfBatchLeast = 768;
 // The first batch is a trial: it ends, with nothing drawn, if after so many rounds not so many of its draws are settled.
 // Of many sequences it is guessed ahead and lasts longer, which costs 10 us where it fails: 1 % of 4096 draws.
 constexpr int kRfTryRounds = 4, kRfTryDraws = 6, kRfTryLong = 8, kRfTryLongDraws = 16, kRfTryLongFrom = 4096;
@@ -389,8 +400,8 @@ constexpr int kRfGuessSteps = 16;                 // draws that a guess of a blo
 constexpr int kRfPlainBatches = 16;               // batches without one after one that told of less than half the draws
 constexpr int kRfGuessFrom = 8;                   // rounds of a batch from which on the next are guessed so
 // What a batch costs and brings, in units of 1/64 us: a round, the rest of a batch (and a unit for so many entries of the
-// lists), a step of a guess; a draw of the chain.
-constexpr int kRfCostRound = 40, kRfCostBatch = 100, kRfCostEntries = 120, kRfCostGuess = 16, kRfCostDraw = 15;
+// lists), a step of a guess; a draw of the chain in blocks of up to 2048 (longer ones 18).
+constexpr int kRfCostRound = 40, kRfCostBatch = 100, kRfCostEntries = 120, kRfCostGuess = 16, kRfCostDraw = 14;
 
 struct RfShared {
     alignas(16) uint16_t len[2][kRfBatchMost + 8 * kWave];   // lengths that are left, ascending
@@ -496,13 +507,12 @@ __global__ __launch_bounds__(kRfBatchThreads) void rf_draw_batches_kernel(
     int32_t placed = 0, blocks = 0;
     int32_t room = 0;                                    // in the open block, in front of the batch (no block yet: 0)
     int32_t left = n_seq;                                // sequences
-    int32_t credit = 2 * 64 + n_seq / 8;                 // batches may cost some 1 % of a chain of all draws
+    int32_t credit = 4 * 64 + n_seq / 8;                 // batches may cost 4 us and some 1 % of a chain of all draws
     const int32_t most_credit = credit + 4 * 64;
     const bool long_try = n_seq >= kRfTryLongFrom;
     bool guesses = long_try;
     int plain = 0;                                       // batches to come that are not guessed ahead
-    bool enough = false;                                 // the rest is drawn one after another
-    while (left > 0 && !enough) {
+    while (left > 0 && credit >= 0) {
         const uint16_t* len = sh.len[cur];
         const int32_t w = min(kRfBatch, left);
         const uint64_t in_batch = w == 64 ? ~0ull : (1ull << w) - 1ull;
@@ -593,7 +603,8 @@ __global__ __launch_bounds__(kRfBatchThreads) void rf_draw_batches_kernel(
                 until = 8;
                 const int32_t settled = changed ? __builtin_ctzll(changed) : w;
                 if (placed == 0 && changed != 0 && rounds <= kRfTryLong && settled < (long_try ? kRfTryLongDraws : kRfTryDraws)) break;
-                const bool ends = changed == 0 || rounds >= kRfBatchRounds || settled < 2 * rounds;
+                const bool ends = changed == 0 || rounds >= kRfBatchRounds || settled < 2 * rounds ||
+                                  credit + kRfCostDraw * settled < kRfCostRound * rounds + kRfCostBatch;
                 if (ends) {
                     // settled, unless a draw has come to rest on a rank that one in front has taken
                     const bool mine = lane < settled;
@@ -621,23 +632,12 @@ __global__ __launch_bounds__(kRfBatchThreads) void rf_draw_batches_kernel(
         }
 
         if (accepted == 0) break;                        // (of the first batch only)
-        // Goes on while batches bring more than they cost, within what has been gained or was given.  The last draw of
-        // all batches is the last of its block.
+        // Goes on while batches bring more than they cost, within what has been gained or was given.
         credit += kRfCostDraw * accepted - kRfCostRound * rounds - kRfCostBatch - (left + kept) / kRfCostEntries -
                   (ahead ? kRfCostGuess * sh.steps : 0);
         credit = min(credit, most_credit);
         // (a long trial says nothing about rounds without a guess)
         guesses = !(placed == 0 && long_try) && (guesses || rounds >= kRfGuessFrom);
-        if (credit < 0 && accepted < left) {
-            const uint64_t begins = __ballot(opens && lane < accepted && lane > 0);
-            if (begins) {
-                const int32_t all = accepted;
-                accepted = 63 - __builtin_clzll(begins);
-                enough = true;
-                if (wave == 0 && lane >= accepted && lane < all) atomicAnd(&sh.gone[rank >> 6], ~(1ull << (rank & 63)));
-                __syncthreads();
-            }
-        }
 
         // The draws settled leave the list: every length moves down by the ranks taken in front of it.  Eight
         // consecutive ranks per lane, eight lanes to a word of `gone`.
@@ -704,7 +704,7 @@ __global__ __launch_bounds__(kRfBatchThreads) void rf_draw_batches_kernel(
     }
 
     if (tid == 0) {
-        *state = RfState{placed, blocks};
+        *state = RfState{placed, blocks, room, 0};
         if (left == 0) {
             block_first[blocks] = n_seq;
             result->num_blocks = blocks;

@@ -124,3 +124,29 @@ def test_random_fit_batches_match_oracle(n, T, kind):
     for seed in workloads.SHUFFLE_SEEDS[:2]:
         print(f"random fit batches n={n} T={T} kind={kind} seed={seed}", flush=True)
         assert_plan_equal(gpu_random_fit(L, T, seed), oracle.plan_random_fit(L, T, seed), n)
+
+
+# Batches end where they stop paying, which is within a block wherever that is long or settles slowly, and the chain goes on
+# in it: with a hundred draws made in the block and with one, with room for many more and for hardly any, at a whole number of
+# 64 draws (640 and 896 of the first two's) and beside it; and far into the call, after batches that paid.
+@pytest.mark.parametrize("n,T,kind", [(768, 40, "tenth"), (1024, 40, "quarters"), (1500, 3000, "tenth"), (6000, 2048, "two"),
+                                      (4096, 2049, "two"), (4096, 8192, "zipf"), (5000, 4097, "two"), (10000, 8192, "two"),
+                                      (10000, 8192, "long and short"), (24576, 300, "heavy"), (24576, 8192, "two")])
+def test_random_fit_batches_end_within_a_block(n, T, kind):
+    rng = np.random.default_rng(n + T)
+    if kind == "tenth":
+        L = np.rint(T / 10 * (1 + 0.5 * rng.standard_normal(n)))
+    elif kind == "quarters":
+        L = rng.choice([T // 4, T // 4 + 1, T // 5, T // 7], size=n)
+    elif kind == "two":
+        L = rng.choice([1, T // 2], size=n)
+    elif kind == "zipf":
+        L = rng.zipf(1.2, size=n)
+    elif kind == "heavy":
+        L = np.floor(8 * (1 + rng.pareto(1.5, size=n)))
+    else:
+        L = np.where(rng.random(n) < 0.9, rng.integers(1, T // 100, size=n), rng.integers(T * 9 // 10, T, size=n))
+    L = np.clip(L, 1, T).astype(np.int32)
+    for seed in workloads.SHUFFLE_SEEDS[:2]:
+        print(f"random fit, batches end n={n} T={T} kind={kind} seed={seed}", flush=True)
+        assert_plan_equal(gpu_random_fit(L, T, seed), oracle.plan_random_fit(L, T, seed), n)
