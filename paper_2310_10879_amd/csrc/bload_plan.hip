@@ -39,6 +39,8 @@ constexpr int kJumpItems = 16;                    // positions per thread where 
 // Such a workgroup takes a jump tile of 16 positions for each of its NT threads: 2048, 4096 or 8192 of them.  Small ones
 // spread over more compute units and their rounds are shorter, but the walk over them is longer: 20000
 // sequences 74 us in tiles of 8192, 69 in tiles of 4096, 66 of 2048; 10^6 114.8, 111.2, 113; 2 * 10^6 213, 216, 219.
+// Up to 8192 sequences one tile needs no exits (those of which the sums leave 32 bits come here: 2049 and 8192 in blocks of
+// 2^24 slots 51 and 58 us, 64 and 67 in tiles of 2048).
 constexpr int kJumpTile = 8192;                   // the largest
 template <int NT> __host__ __device__ constexpr int jump_tile() { return NT * kJumpItems; }
 constexpr int64_t kSmallTilesUpTo = 160000, kMidTilesUpTo = (int64_t)1 << 20;
@@ -939,7 +941,7 @@ static PlanLayout plan_layout(int64_t n_seq)
     PlanLayout l{};
     const size_t n = (size_t)(n_seq > 0 ? n_seq : 0);
     l.n_tiles = (int32_t)ceil_div((int64_t)n, kTile);
-    l.jump_threads = (int64_t)n <= kSmallTilesUpTo ? 128 : (int64_t)n <= kMidTilesUpTo ? 256 : 512;
+    l.jump_threads = (int64_t)n <= kJumpTile ? 512 : (int64_t)n <= kSmallTilesUpTo ? 128 : (int64_t)n <= kMidTilesUpTo ? 256 : 512;
     l.n_jump_tiles = (int32_t)ceil_div((int64_t)n, l.jump_threads * kJumpItems);
     l.sums_per_tile = (int64_t)n <= kSingleItems ? kItems : 1;
     l.n_sums = (int32_t)ceil_div((int64_t)n, kTile / l.sums_per_tile);

@@ -153,3 +153,15 @@ def test_plan_sizes_of_jump_tiles(n, T, kind):
         L = workloads.random_lengths(rng, n, T, kind)
     print(f"plan n={n} T={T} kind={kind}", flush=True)
     assert_plan_equal(gpu_plan(L, T, 7), oracle.plan(L, T, oracle.order(n, 7)), n)
+
+
+# Sums that leave 32 bits keep up to 8192 sequences off the workgroup of 16 waves: they are one jump tile, entered at position 0;
+# from 8193 on several.  Blocks of one sequence, of some, of nearly all and of all of them.
+@pytest.mark.parametrize("n", [2049, 4097, 8191, 8192, 8193])
+@pytest.mark.parametrize("T,lo,hi", [(1 << 24, 1, 1 << 24), (1 << 24, (1 << 23) + 1, 1 << 24), (1 << 24, 1, 1 << 14), (1 << 20, 100, 160),
+                                     (2000000000, 1, 2000000000), (2000000000, 1, 3)])
+def test_plan_one_jump_tile(n, T, lo, hi):
+    rng = np.random.default_rng(n + hi)
+    L = rng.integers(lo, hi, size=n, endpoint=True).astype(np.int32)
+    print(f"plan n={n} T={T} lengths {lo} to {hi}", flush=True)
+    assert_plan_equal(gpu_plan(L, T, 3), oracle.plan(L, T, oracle.order(n, 3)), n)
