@@ -279,24 +279,32 @@ __global__ __launch_bounds__(kThreads) void plan_prefix_kernel(
 }
 
 // next[p] for every position, one thread each: a chain of dependent look-ups in P, of which the next kNextWindow
-// positions lie in LDS and hold the answer where blocks are of fewer sequences.
+// positions (or t_blk of them, beyond which no block reaches) lie in LDS and hold the answer where blocks are of fewer
+// sequences.  Where the first position's block is of more, so are the others', and P is searched where it lies.  (10^6
+// documents 16 us without the window, 10 with it.  5 * 10^6 sequences: documents 58 and 44, 64 to a block at most 32 and 20;
+// blocks of 50000, which it does not hold, 75 and 79, with the window fetched all the same 89; blocks of one 14, 15 and 40.)
 constexpr int kNextWindow = 1024;
+constexpr int kNextLeast = 16;                    // shorter blocks: four look-ups at most
 
 __global__ __launch_bounds__(kThreads) void plan_next_kernel(const int64_t* __restrict__ prefix,
                                                              int32_t n_seq, int32_t t_blk,
                                                              int32_t* __restrict__ next)
 {
-    __shared__ int64_t s_prefix[kNextWindow + kThreads];
-    const int64_t first = (int64_t)blockIdx.x * kThreads;
-    const int32_t held = (int32_t)min((int64_t)(kNextWindow + kThreads), (int64_t)n_seq + 1 - first);    // from `first` on
-    for (int32_t k = (int32_t)threadIdx.x; k < held; k += kThreads) s_prefix[k] = prefix[first + k];
-    __syncthreads();
-    const int64_t p = first + threadIdx.x;
+    __shared__ int64_t s_prefix[kNextWindow + kThreads + 1];
+    const int64_t first = (int64_t)blockIdx.x * kThreads, p = first + threadIdx.x;
+    const int32_t held = (int32_t)min((int64_t)(min(kNextWindow, t_blk) + kThreads + 1), (int64_t)n_seq + 1 - first);    // from `first` on
+    const int64_t own = prefix[min(p, (int64_t)n_seq)], limit = own + t_blk;
+    // is an answer among them (next[] never falls), and worth bringing them here
+    const bool within = t_blk >= kNextLeast && prefix[first + held - 1] - prefix[first] > t_blk;
+    if (within) {
+        s_prefix[threadIdx.x] = own;
+        for (int32_t k = (int32_t)threadIdx.x + kThreads; k < held; k += kThreads) s_prefix[k] = prefix[first + k];
+        __syncthreads();
+    }
     if (p >= n_seq) return;
-    const int64_t limit = s_prefix[threadIdx.x] + t_blk;
     // the first entry above the limit is next[p] + 1; P[p + 1] never is
-    if (s_prefix[held - 1] > limit) {
-        int32_t lo = (int32_t)threadIdx.x + 2, hi = held - 1;
+    if (within && s_prefix[held - 1] > limit) {
+        int32_t lo = (int32_t)threadIdx.x + 2, hi = (int32_t)min((int64_t)held - 1, (int64_t)threadIdx.x + 1 + t_blk);
         while (lo < hi) {
             const int32_t mid = (lo + hi) >> 1;
             if (s_prefix[mid] > limit) hi = mid; else lo = mid + 1;
