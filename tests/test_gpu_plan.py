@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n,T", [(1, 1), (1, 9), (2, 2), (3, 5), (64, 32), (255, 7), (257, 600),
                                  (1000, 600), (2047, 33), (2048, 1), (2049, 4096), (5000, 3),
                                  (70001, 100),
-                                 # around the tiles of the scans (2048) and of the jumping (8192)
+                                 # around the tiles of the scans (2048), and up to and beyond the workgroup of 16 waves (12288)
                                  (4096, 17), (4097, 900), (8191, 2), (8192, 50), (8193, 7),
                                  (16384, 64), (16385, 300), (24577, 5)])
 def test_plan_matches_oracle(kind, n, T):
@@ -28,7 +28,8 @@ def test_plan_matches_oracle(kind, n, T):
 
 @pytest.mark.parametrize("case", range(16))
 def test_plan_random_sizes_of_several_jump_tiles(case):
-    # 2 .. 37 tiles of 8192 positions: every tile finds where the orbit of position 0 enters it
+    # tiles of 2048 and 4096 positions, up to 79 of them, with groups from 40 on: every tile finds where the orbit of
+    # position 0 enters it
     rng = np.random.default_rng(9000 + case)
     n = int(rng.integers(8193, 300000))
     T = int(rng.choice([1, 3, 64, 600, 4096, 100000]))
@@ -39,8 +40,8 @@ def test_plan_random_sizes_of_several_jump_tiles(case):
     assert_plan_equal(gpu_plan(L, T, seed), oracle.plan(L, T, oracle.order(n, seed)), n)
 
 
-# From 40 jump tiles of 8192 on a tile reaches its entry over the exits of groups of
-# 8 tiles: both sides of that line, a last group of one position, blocks that pass over whole tiles and
+# From 40 jump tiles on a tile reaches its entry over the exits of groups of tiles (here 8 of 4096 positions, beyond 2^20
+# of 8192): a last group of one position, blocks that pass over whole tiles and
 # whole groups, blocks of one sequence, and both sides of 2^20, where the order kernel changes.
 @pytest.mark.parametrize("n,T,kind", [(39 * 8192, 64, "mixed"), (39 * 8192 + 1, 64, "mixed"), (40 * 8192 + 1, 600, "short"),
                                       (48 * 8192 + 1, 20000, "short"), (600000, 200000, "short"), (600000, 70000, "short"),
@@ -74,7 +75,7 @@ def test_plan_workloads_full_size(wid):
         assert_plan_equal(gpu_plan(L, w.t_blk, seed), ref, w.n_seq)
 
 
-@pytest.mark.parametrize("n", [4100, 8192, 20000])        # one jump tile, a full one, three
+@pytest.mark.parametrize("n", [4100, 8192, 20000])        # one workgroup of 16 waves, ten jump tiles
 def test_plan_closed_forms(n):
     # every position a block head; one block head in 12; every position; every second one
     T = 12
@@ -165,3 +166,28 @@ def test_plan_one_jump_tile(n, T, lo, hi):
     L = rng.integers(lo, hi, size=n, endpoint=True).astype(np.int32)
     print(f"plan n={n} T={T} lengths {lo} to {hi}", flush=True)
     assert_plan_equal(gpu_plan(L, T, 3), oracle.plan(L, T, oracle.order(n, 3)), n)
+
+
+# Beyond 1024 jump tiles (of 8192) one thread finds where every tile is entered: both sides of that line, blocks of a few
+# sequences, of one, and such that pass over whole tiles.
+@pytest.mark.parametrize("n", [1024 * 8192, 1024 * 8192 + 1, 1027 * 8192 + 5000])
+@pytest.mark.parametrize("T,kind", [(4096, "mixed"), (1, "uniform"), (100000, "short")])
+def test_plan_entries_found_by_one_thread(n, T, kind):
+    rng = np.random.default_rng(n + T)
+    L = workloads.random_lengths(rng, n, T, kind)
+    print(f"plan n={n} T={T} kind={kind}", flush=True)
+    assert_plan_equal(gpu_plan(L, T, 9), oracle.plan(L, T, oracle.order(n, 9)), n)
+
+
+# next[] is searched for in a window of 1024 positions (of t_blk, in shorter blocks) held in LDS, from blocks of 16 slots on, unless
+# the first position's block passes over it: blocks of as many sequences as the window, one fewer and one more, of a few, of
+# several windows; and blocks that differ so much that some positions of a workgroup find theirs in it and some behind it.
+@pytest.mark.parametrize("n", [12289, 20000])
+@pytest.mark.parametrize("T", [1, 2, 15, 16, 17, 1022, 1023, 1024, 1025, 1279, 1280, 1281, 5000])
+def test_plan_window_of_next(n, T):
+    rng = np.random.default_rng(n + T)
+    rare = np.where(rng.random(n) < 0.002, T, 1)
+    for k, L in enumerate((np.ones(n), np.minimum(rng.integers(1, 3, size=n), T), rare)):
+        L = L.astype(np.int32)
+        print(f"plan n={n} T={T} case {k}", flush=True)
+        assert_plan_equal(gpu_plan(L, T, 5), oracle.plan(L, T, oracle.order(n, 5)), n)
