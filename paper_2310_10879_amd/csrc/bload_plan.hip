@@ -688,12 +688,18 @@ __global__ __launch_bounds__(kThreads) void plan_small_kernel(
 constexpr int kMidThreads = 1024;
 constexpr int kMidWaves = kMidThreads / kWave;
 constexpr int kMidPer = 13;                       // an odd number, so that the threads' places in LDS spread over the banks
-constexpr int kMidMost = 12 * kMidThreads;        // beyond, the tiled path is as fast (13400 of nearly full blocks: 73 us, 76 here)
+constexpr int kMidMost = 12 * kMidThreads;        // about there the tiled path is as fast (nearly full blocks: 12288 sequences 68.2 us,
+                                                  // 12289 by tiles 67.7; documents 57 and 62; 13312 is what the threads hold)
 
 struct MidShared {
     alignas(16) int32_t prefix[kMidThreads * kMidPer + 4];     // lengths, then their prefix sums, in the end the offsets
-    alignas(16) uint16_t next[kMidThreads * kMidPer];        // in the end, with `jump`, the blocks
-    uint16_t jump[kMidThreads * kMidPer];
+    union {
+        struct {
+            uint16_t heads[kMidThreads * kMidPer];       // every wave's, in its positions' part
+            uint16_t jump[kMidThreads * kMidPer];
+        };
+        int32_t blocks[kMidThreads * kMidPer];           // in the end
+    };
     uint32_t mark[kMidThreads * kMidPer / 32];
     uint16_t first[kMidThreads + 1];              // next[] of every thread's first position
     uint16_t entry[kMidWaves];
@@ -794,7 +800,7 @@ __global__ __launch_bounds__(kMidThreads) void plan_mid_kernel(
         }
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
-            if (j < mine) sh.next[base + j] = sh.jump[base + j] = (uint16_t)next[j];
+            if (j < mine) sh.jump[base + j] = (uint16_t)next[j];
         }
     }
 
@@ -841,7 +847,7 @@ __global__ __launch_bounds__(kMidThreads) void plan_mid_kernel(
         if (j < mine) sh.jump[base + j] = (uint16_t)x[j];
     }
     const int entry = __builtin_amdgcn_readfirstlane((int)sh.entry[wave]);
-    uint16_t* heads = sh.next + wave_lo;                 // (next[] is in registers now)
+    uint16_t* heads = sh.heads + wave_lo;
     int n_heads = entry < kMidMost ? 1 : 0;
     if (n_heads > 0) {
         if (lane == 0) {
@@ -903,17 +909,16 @@ __global__ __launch_bounds__(kMidThreads) void plan_mid_kernel(
         }
     }
     __syncthreads();                                     // the prefix sums and pointers have been read
-    int32_t* blocks = reinterpret_cast<int32_t*>(sh.next);
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
         if (j < mine) {
-            blocks[base + j] = x[j];
+            sh.blocks[base + j] = x[j];
             sh.prefix[base + j] = offset[j];
         }
     }
     __syncthreads();
     for (int p = tid; p < n_seq; p += kMidThreads) {
-        block_at[p] = blocks[p];
+        block_at[p] = sh.blocks[p];
         offset_at[p] = sh.prefix[p];
     }
     if (tid == 0) {
