@@ -64,6 +64,7 @@ struct ReduceArgs {
     // chunking
     int32_t chunk;           // slots per chunk
     int32_t split;           // wide, rows of one wave: 1 if two waves share a chunk
+    int32_t reach;           // then: slots behind a chunk that a segment begun in it may end in and stay whole
     int32_t tile;            // staged, several tiles per workgroup: slots per tile
     int32_t n_chunks;        // wide: chunks per block
     int32_t row_lanes_log2;  // wide: lanes per row = 1 << this
@@ -178,6 +179,7 @@ __device__ __forceinline__ double finish<double>(double sum, int32_t cnt, int me
 
 constexpr int kWideUnroll = 8;
 constexpr int64_t kShortPieces = 32;       // slots per row of the result
+constexpr int32_t kReach = 32;             // longer ones gain no more, and leave waves with more slots than others
 constexpr int kWideFlagBytes = 32768;      // LDS budget for the staged flags: also the longest chunk
 static_assert((int64_t)kWideFlagBytes * 255 < ((int64_t)1 << 24), "uint8 pieces must sum exactly in float");
 
@@ -275,10 +277,10 @@ template <typename ElemT, int VEC, bool WAVE_ROW, bool STREAM>
 __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
 {
     typedef typename Elem<ElemT>::Acc Acc;
-    extern __shared__ uint8_t s_flags[];   // chunks x (chunk + 2): bit0 valid, bit1 reset
+    extern __shared__ uint8_t s_flags[];   // chunks x (chunk + reach + 2): bit0 valid, bit1 reset
     const int tid = (int)threadIdx.x;
-    const int C = a.chunk, stride = C + 2;
-    const int split = WAVE_ROW ? a.split : 0;
+    const int split = WAVE_ROW ? a.split : 0, reach = WAVE_ROW ? a.reach : 0;
+    const int C = a.chunk, stride = C + reach + 2;
     const int chunks = (kThreads >> a.row_lanes_log2) >> split;       // of the workgroup
     // consecutive workgroups take the lane-slices of one frame range, so that
     // workgroups running side by side read neighbouring memory
@@ -286,8 +288,8 @@ __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
     const int64_t q_base = (int64_t)(blockIdx.x / (uint32_t)a.feat_tiles) * chunks;
     const int64_t T = a.t_blk;
 
-    // stage the flags of this workgroup's chunks, plus the slot before and the slot
-    // after each chunk (0 outside the block): row r holds slots t0-1 .. t0+len
+    // stage the flags of this workgroup's chunks, plus the slot before and the slots as far as a segment
+    // is followed behind each chunk (0 outside the block): row r holds slots t0-1 .. t0+len+reach
     for (int r = 0; r < chunks; ++r) {
         const int64_t q = q_base + r;
         if (q >= a.total_chunks) break;
@@ -295,7 +297,7 @@ __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
         const int32_t t0 = (int32_t)(q - b * a.n_chunks) * C;
         const int32_t len = min(C, a.t_blk - t0);
         const int64_t g = b * T + t0;
-        for (int t = tid - 1; t <= len; t += kThreads) {
+        for (int t = tid - 1; t <= len + reach; t += kThreads) {
             uint8_t f = 0;
             if (t0 + t >= 0 && t0 + t < a.t_blk)
                 f = (uint8_t)((a.valid[g + t] ? 1 : 0) | (a.reset[g + t] ? 2 : 0));
@@ -318,16 +320,42 @@ __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
     const int32_t t0 = (int32_t)(q - b * a.n_chunks) * C;
     const int64_t g = b * T + t0;
     const uint8_t* flags = s_flags + (row >> split) * stride + 1;      // flags[-1] = the slot before the chunk
-    // Two waves to a chunk: the first one takes the segments that begin in front of the middle (and the one that comes
-    // in), to their end or the chunk's, the second one those behind.  Neither cuts one.
+    // Two waves to a chunk: they part where a segment begins or ends next to the middle, at the chunk's end if none does.  A
+    // segment that runs out of the chunk and ends within `reach` slots stays whole as well; the next chunk sees the same
+    // flags and leaves it out.  (`reach` is no longer than a chunk.)
     const int32_t chunk_len = min(C, a.t_blk - t0);
     int32_t len = chunk_len, begin = 0;
+    bool has_end = true;                   // does this wave take the chunk's last slot
     if (split) {
+        auto goes_on = [&](int32_t at) { return (flags[at] & 3) == 1 && (flags[at - 1] & 1); };
         int32_t cut = (chunk_len + 1) >> 1;
-        if (cut < chunk_len && (flags[cut] & 3) == 1 && (flags[cut - 1] & 1))
-            cut = next_slot<false, WAVE_ROW>(flags, cut + 1, chunk_len, a.row_lanes_log2);
-        if (row & 1) begin = cut;
-        else len = cut;
+        if (cut < chunk_len && goes_on(cut)) {
+            const int32_t end = next_slot<false, WAVE_ROW>(flags, cut + 1, chunk_len, a.row_lanes_log2);
+            // the last slot in front of the middle that is padding or a start, if it is the nearer
+            const int32_t least = max(2 * cut - end, 0);
+            int32_t start = -1;
+            for (int32_t hi = cut - 1; hi > least && start < 0; hi -= kWave) {
+                const int32_t t = hi - lane_id();
+                const uint64_t vote = __ballot(t > least && (flags[max(t, 0)] & 3) != 1);
+                if (vote) start = hi - __builtin_ctzll(vote);
+            }
+            cut = start < 0 ? end : (flags[start] & 1) ? start : start + 1;
+        }
+        if (row & 1) {
+            begin = cut;
+            has_end = cut < chunk_len;
+        } else {
+            len = cut;
+            has_end = cut == chunk_len;
+            if (goes_on(0)) {
+                const int32_t end = next_slot<false, WAVE_ROW>(flags, 1, reach + 1, a.row_lanes_log2);
+                if (end <= reach) begin = end;
+            }
+        }
+        if (has_end && goes_on(chunk_len)) {
+            const int32_t end = next_slot<false, WAVE_ROW>(flags, chunk_len + 1, chunk_len + reach + 1, a.row_lanes_log2);
+            if (end <= chunk_len + reach) len = end;
+        }
     }
     const int64_t frame_bytes = (int64_t)a.feat_dim * (int64_t)sizeof(ElemT);
     const uint8_t* chunk_src = a.packed + g * frame_bytes;                 // the chunk's first frame
@@ -445,12 +473,12 @@ __global__ __launch_bounds__(kThreads) void reduce_wide_kernel(ReduceArgs a)
         a.desc[q] = desc;
         return;
     }
-    // what comes in is the first wave's, what goes out that one's whose slots are the chunk's last
+    // what comes in is the first wave's
     if ((row & 1) == 0) {
         a.desc[q].head_state = desc.head_state;
         a.desc[q].cnt_head = desc.cnt_head;
     }
-    if ((row & 1) == 0 ? len == chunk_len : begin < chunk_len) {
+    if (has_end) {
         a.desc[q].cnt_tail = desc.cnt_tail;
         a.desc[q].seq_tail = desc.seq_tail;
     }
@@ -1301,7 +1329,8 @@ struct ReducePlan {
     bool wide, staged;
     bool run;                // staged: a workgroup takes the tiles of a whole chunk one after another
     int32_t tile;            // of this many slots
-    bool split;              // wide: two waves to a chunk
+    bool split;              // wide: two waves to a chunk, and see ReduceArgs
+    int32_t reach;
     int vec;                 // wide: elements per lane (16 bytes, 4 bytes or one element)
     int row_lanes_log2;
     int n_vec;
@@ -1400,17 +1429,18 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
         }
         int64_t chunk = ceil_div(t_blk, want);
         // Rows of one wave and sequences of a few frames: the waves' chunks hold very different numbers of pieces, and
-        // all are at work at once, so that the call lasts as long as the slowest.  Two waves to a chunk even that out, and
-        // as neither cuts a segment they make no partial sums beyond those of the chunk (10000 sequences of 23 frames of 4096
-        // bytes: 221 -> 203 us; 330 of them 21.0 -> 17.5; 8900 of 3072 bytes 156 -> 142).  Chunks half as long would do
-        // that too, but where pieces are long, as they may be in a worker's share whatever `mean` says, those cost partial
-        // sums (an eighth of the rows, 128 frames of 1024 bytes in blocks of 300: 99 us, 136 in half chunks, 101 like
-        // this; 250 of 4096 bytes 65, 77, 68).  (Not where the chunks above are cut for more workgroups than are at work
-        // at once.)
+        // all are at work at once, so that the call lasts as long as the slowest.  Two waves to a chunk even that out.  Neither
+        // cuts a segment, and one that ends within 32 slots behind the chunk stays whole, so that hardly any partial sums
+        // are left (10000 sequences of 23 frames of 4096 bytes: 220 -> 197 us, 203 where the chunks' borders cut; 330 of them
+        // 21.0 -> 15.9; 8900 of 3072 bytes 156 -> 136).  Chunks half as long would even out as much, but where pieces are
+        // long, as they may be in a worker's share whatever `mean` says, those cost partial sums (an eighth of the rows, 128
+        // frames of 1024 bytes in blocks of 300: 99 us, 136 in half chunks, 82 like this; 250 of 4096 bytes 64, 77, 67).
+        // (Not where the chunks above are cut for more workgroups than are at work at once.)
         p.split = !lean && whole && p.row_lanes_log2 == 6 && want > 1 && whole_block_groups < 2048 && mean <= kShortPieces;
         const int64_t lds_cap = kWideFlagBytes / rows - 2;
         if (chunk > lds_cap) chunk = lds_cap;
         p.chunk = (int32_t)chunk;
+        p.reach = p.split ? std::min(kReach, p.chunk) : 0;
         p.n_chunks = (int32_t)ceil_div(t_blk, chunk);
         p.total_chunks = num_blocks * p.n_chunks;
         p.partials = p.n_chunks > 1;
@@ -1482,7 +1512,7 @@ static void launch_wide(const ReducePlan& p, const ReduceArgs& a, hipStream_t st
     typedef typename Elem<ElemT>::Acc Acc;
     const int chunks = (kThreads >> p.row_lanes_log2) >> p.split;      // of a workgroup
     const dim3 grid((uint32_t)(ceil_div(p.total_chunks, chunks) * a.feat_tiles));
-    size_t lds = (size_t)chunks * (size_t)(p.chunk + 2);
+    size_t lds = (size_t)chunks * (size_t)(p.chunk + p.reach + 2);
     if (VEC > 1 && p.row_lanes_log2 >= 6)     // + the per-wave scratch of the transposed stores
         lds = round_up(lds, 16) + (size_t)(kThreads / kWave) * kWave * kScratchStride<Acc, VEC>() * sizeof(Acc);
     if (p.row_lanes_log2 == 6)
@@ -1593,6 +1623,7 @@ extern "C" bload_status bload_segment_reduce(const void* d_packed, const int32_t
     a.chunk = p.chunk;
     a.tile = p.tile;
     a.split = p.wide && p.split ? 1 : 0;
+    a.reach = a.split ? p.reach : 0;
     a.n_chunks = p.n_chunks;
     a.row_lanes_log2 = p.row_lanes_log2;
     a.n_vec = p.n_vec;

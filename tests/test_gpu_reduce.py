@@ -425,12 +425,13 @@ def test_reduce_runs_of_tiles(B, T, D, dtype, op):
     assert np.all(np.abs(got.astype(np.float64) - want.astype(np.float64)) <= bound)
 
 
-# Rows of one wave and many short sequences: two waves share a chunk (64 slots; 67 and 66; 131 of 180 blocks of 3000), the first
-# takes the segments that begin in front of its middle.  Segments that begin and end at the chunks' borders and middles and
-# one slot beside them, some over several chunks, some from a middle to a border, padding there as well.
+# Rows of one wave and many short sequences: two waves share a chunk (64 slots; 67 and 66; 131 of 180 blocks of 3000; 65 and a
+# last one of 3), part where a segment begins or ends next to its middle, and leave one whole that ends within 32 slots behind
+# it.  Segments that begin and end at the chunks' borders and middles, as far behind the borders as they are followed, beside
+# all of these and some slots off, some over several chunks, some from a middle to a border, padding there as well.
 @pytest.mark.parametrize("B,T,dtype,op", [(12, 640, "f32", "mean"), (12, 640, "i32", "sum"), (12, 640, "u8", "mean"),
                                           (12, 640, "f16", "sum"), (7, 133, "f16", "mean"), (1, 128, "f16", "mean"),
-                                          (180, 3000, "f16", "mean")])
+                                          (180, 3000, "f16", "mean"), (3, 4033, "f32", "mean")])
 def test_reduce_short_pieces_over_chunk_borders(B, T, dtype, op):
     bl = binding()
     rng = np.random.default_rng(B + T)
@@ -439,7 +440,8 @@ def test_reduce_short_pieces_over_chunk_borders(B, T, dtype, op):
     chunks = B * -(-T // chunk)
     # (the query tells how many chunks there are)
     assert bl.bload_segment_reduce_workspace_bytes(B, T, D, dtype) == chunks * (16 + 2 * D * (8 if dtype == "i32" else 4))
-    at = [t0 + m + k for t0 in range(0, T, chunk) for m in (0, (min(chunk, T - t0) + 1) // 2) for k in (-1, 0, 1)]
+    at = [t0 + m + k for t0 in range(0, T, chunk) for m in (0, (min(chunk, T - t0) + 1) // 2, 32)
+          for k in (-9, -1, 0, 1, 5)]
     at = np.array([t for t in at if 0 < t < T])
     valid, reset = np.ones((B, T), np.uint8), np.zeros((B, T), np.uint8)
     for b in range(B):
