@@ -17,7 +17,7 @@
 // Three layouts of the work (reduce_plan draws the lines between them):
 //   wide    frames of 64 bytes or more: a row of lanes (at most one wave) lies across the features of a frame, 16
 //           bytes to a lane, or 4, or one element where frames are no whole vectors or workgroups too few;
-//           each row walks one chunk of time serially with several loads in flight, restarting its
+//           each row walks one chunk of time (or two waves share it) serially with several loads in flight, restarting its
 //           accumulators at every start flag.
 //   staged  frames of 2 to 63 elements that are smaller, or of which wide rows would be too few workgroups: a tile of
 //           slots goes through LDS as whole vectors, and each lane then sums 9 or 17 slots of one feature.
@@ -1403,7 +1403,7 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
         p.vec = widths[w] / es;
         p.n_vec = (int)ceil_div(feat_dim, p.vec);
         // a row is at most one wave wide: the last lane-slice of a frame then idles at most 63
-        // lanes, and the four waves of a workgroup walk four different chunks
+        // lanes, and the four waves of a workgroup walk four different chunks, or two
         p.row_lanes_log2 = 0;
         while ((1 << p.row_lanes_log2) < p.n_vec && p.row_lanes_log2 < 6) ++p.row_lanes_log2;
         const int rows = kThreads >> p.row_lanes_log2;
