@@ -14,13 +14,15 @@
 // small kernel adds tail + following heads in time order.  Fixed chunking and
 // fixed order make the float32 result bit-reproducible.
 //
-// Three layouts of the work (reduce_plan draws the lines between them):
+// Four layouts of the work (reduce_plan and takes_flat draw the lines between them):
 //   wide    frames of 64 bytes or more: a row of lanes (at most one wave) lies across the features of a frame, 16
 //           bytes to a lane, or 4, or one element where frames are no whole vectors or workgroups too few;
 //           each row walks one chunk of time (or two waves share it) serially with several loads in flight, restarting its
 //           accumulators at every start flag.
 //   staged  frames of 2 to 63 elements that are smaller, or of which wide rows would be too few workgroups: a tile of
 //           slots goes through LDS as whole vectors, and each lane then sums 9 or 17 slots of one feature.
+//   flat    frames of up to 512 bytes, whole multiples of which are at most a wave's 64 vectors, in pieces of some KB: a wave
+//           takes the bytes of a piece as one stream, 16 to a lane, and adds the lanes' sums up by feature at its end.
 //   narrow  frames of one element that are not wide: lanes across time, 16 consecutive slots per lane, segmented scan
 //           over the workgroup with the segment breaks as heads and a carry between lanes and waves.
 #include "bload_common.hpp"
@@ -70,6 +72,9 @@ struct ReduceArgs {
     int32_t row_lanes_log2;  // wide: lanes per row = 1 << this
     int32_t n_vec;           // wide: lanes needed to cover one frame
     int32_t feat_tiles;      // wide: workgroups side by side over one frame
+    int32_t step_vec;        // flat: vectors that a wave takes in one step, a whole number of frames
+    int32_t step_frames;     // and how many frames those are
+    uint32_t step_magic;     // floor(2^32 / step_frames) + 1: divides counts of up to 2^16 frames
     // partial buffers (null when no chunk border can cut a segment)
     ChunkDesc* desc;         // [total_chunks]
     void* head_part;         // [total_chunks, feat_dim] accumulators; [total_chunks, 2, feat_dim] floats and
@@ -1246,6 +1251,346 @@ __global__ __launch_bounds__(kThreads) void reduce_staged_kernel(ReduceArgs a)
     if (tid == 0 && a.desc) a.desc[q] = s_desc;
 }
 
+// ------------------------------------------------------------------- flat
+//
+// Frames of few bytes in pieces that are long beside them: a wave takes the bytes of a piece as one flat stream, 16 to a
+// lane, whatever a frame is.  The least common multiple of a frame and a vector is `P` vectors (of 74 bytes: 37, eight
+// frames), and a step is as many whole multiples of that as the wave's lanes hold, once or twice over (NV), so that a lane
+// finds the same features of the same frames in every step and adds them up in registers.  Only where a piece ends are
+// the lanes' sums brought together by feature, through LDS.
+// A workgroup takes a piece of one block, or several whole ones, and each of its four waves a quarter of the slots, wherever
+// that cuts a segment: what the waves leave open is put together in LDS, so that only borders between workgroups inside a
+// block cost partial sums.
+
+constexpr int kFlatSlots = 8000;           // of a workgroup, at most: a wave's quarter and its neighbours' flags are 64 words
+constexpr int kFlatGroups = 512;           // of 16 slots' flags
+constexpr int kFlatLoads = 4;              // steps asked for at a time (8 take registers from half the waves: 5 to 40 % slower)
+constexpr int kWaves = kThreads / kWave;
+static_assert(kFlatSlots / kWaves + 1 + 32 <= kWave * 32, "a wave's slots: a word of flags per lane");
+static_assert((kFlatSlots / kWaves * (kWaves - 1)) / 32 + kWave <= kFlatGroups / 2, "the words that the last wave reads");
+
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+template <typename ElemT>
+constexpr int kFlatScratch = kWave * (16 / (int)sizeof(ElemT));      // sums of a wave's lanes
+
+// What a lane adds up of a piece: element k of its vector in every step.  Trees of the steps taken at a time, and those
+// in 64 bits.
+template <typename ElemT>
+struct FlatSums {
+    typedef typename Elem<ElemT>::Acc Acc;
+    typedef typename TileSum<ElemT>::T Part;
+    static constexpr int EPV = 16 / (int)sizeof(ElemT);
+    Part sum[EPV];
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int k = 0; k < EPV; ++k) sum[k] = 0;
+    }
+    template <int C>
+    __device__ __forceinline__ void add(const vec16 (&x)[C])
+    {
+#pragma unroll
+        for (int k = 0; k < EPV; ++k) {
+            Acc s[C];
+#pragma unroll
+            for (int u = 0; u < C; ++u) {
+                union { vec16 v; ElemT e[EPV]; } w;
+                w.v = x[u];
+                s[u] = Elem<ElemT>::get(w.e[k]);
+            }
+#pragma unroll
+            for (int w = 1; w < C; w *= 2)
+#pragma unroll
+                for (int u = 0; u + w < C; u += 2 * w) s[u] += s[u + w];
+            sum[k] += (Part)s[0];
+        }
+    }
+    __device__ __forceinline__ Part get(int k) const { return sum[k]; }
+};
+// Bytes: whole numbers, two to a word, the even and the odd ones of each.
+template <>
+struct FlatSums<uint8_t> {
+    uint32_t even[4], odd[4];
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) even[j] = odd[j] = 0;
+    }
+    template <int C>
+    __device__ __forceinline__ void add(const vec16 (&x)[C])
+    {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int u = 0; u < C; ++u) {
+                even[j] += x[u][j] & 0x00ff00ffu;
+                odd[j] += (x[u][j] >> 8) & 0x00ff00ffu;
+            }
+    }
+    __device__ __forceinline__ float get(int k) const
+    {
+        const uint32_t w = (k & 1) ? odd[k / 4] : even[k / 4];
+        return (float)((k & 2) ? w >> 16 : w & 0xffffu);
+    }
+};
+constexpr int kFlatByteFrames = 8;         // of bytes, a step holds so many frames or more:
+static_assert((kFlatSlots / kWaves + 1 + kFlatByteFrames - 1) / kFlatByteFrames * 255 < 1 << 16, "a piece's bytes add up in 16 bits");
+
+template <typename ElemT, bool STREAM>
+__global__ __launch_bounds__(kThreads, 8) void reduce_flat_kernel(ReduceArgs a)
+{
+    typedef typename Elem<ElemT>::Acc Acc;
+    typedef typename TileSum<ElemT>::T Part;
+    typedef typename OutOf<Acc>::T Out;
+    constexpr int EPV = 16 / (int)sizeof(ElemT);
+    constexpr int N = kFlatLoads;
+    extern __shared__ vec16 s_flat[];          // sums of the waves' lanes, then heads and tails of the waves
+    __shared__ alignas(16) uint16_t s_valid[kFlatGroups], s_break[kFlatGroups];
+    __shared__ ChunkDesc s_piece[kWaves];
+    const int tid = (int)threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(wave_id());
+    const int32_t D = a.feat_dim;
+    Part* const scratch = reinterpret_cast<Part*>(s_flat) + wave * kFlatScratch<ElemT>;
+    Part* const s_head = reinterpret_cast<Part*>(s_flat) + kWaves * kFlatScratch<ElemT>;       // [kWaves][D]
+    Part* const s_tail = s_head + kWaves * D;
+
+    const int64_t q = blockIdx.x;
+    int64_t g0;
+    int32_t n, rem0;
+    if (a.n_chunks > 1) {
+        const int64_t b = (int64_t)((uint32_t)q / (uint32_t)a.n_chunks);
+        rem0 = (int32_t)(q - b * a.n_chunks) * a.chunk;
+        g0 = b * (int64_t)a.t_blk + rem0;
+        n = min(a.chunk, a.t_blk - rem0);
+    } else {
+        const int64_t b0 = q * a.blocks_per_tile;
+        rem0 = 0;
+        g0 = b0 * (int64_t)a.t_blk;
+        n = (int32_t)min((int64_t)a.blocks_per_tile, a.num_blocks - b0) * a.t_blk;
+    }
+    // flags, 16 slots to a lane: which slots are valid, and which cannot continue the segment of the slot in front (padding, a
+    // start flag, a block's first slot, a slot behind padding); breaks behind the tile but for the slot next to it
+    {
+        const uint32_t T = (uint32_t)a.t_blk;
+        constexpr int kRounds = kFlatGroups / kThreads;
+        FlagBytes fb[kRounds];
+        const bool more_behind = a.n_chunks > 1 && rem0 + n < a.t_blk;
+        const int64_t behind = min(g0 + n, a.total_slots - 1);
+        const uint8_t behind_valid = a.valid[behind], behind_reset = a.reset[behind];
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) fb[r].load(a, g0 + 16 * (tid + r * kThreads), n - 16 * (tid + r * kThreads));
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            const int i = tid + r * kThreads;
+            uint32_t vm16 = 0, brk = 0xffffu;
+            const int32_t left16 = n - 16 * i;
+            if (left16 >= 0) {
+                const uint32_t pos = (uint32_t)(rem0 + 16 * i) % T;
+                const uint32_t before = pos != 0 && fb[r].before != 0 ? 1u : 0u;
+                vm16 = fb[r].mask(fb[r].valid, a.valid, left16, a.total_slots);
+                const uint32_t rm16 = fb[r].mask(fb[r].reset, a.reset, left16, a.total_slots);
+                uint32_t first = 0;
+                for (uint32_t k = pos == 0 ? 0 : T - pos; k < 16; k += T) first |= 1u << k;
+                brk = (~vm16 | rm16 | first | ~(vm16 << 1 | before)) & 0xffffu;
+                if (left16 < 16) {
+                    const bool goes_on = more_behind && behind_valid != 0 && behind_reset == 0 &&
+                                         ((left16 == 0 ? before : vm16 >> (left16 - 1)) & 1u);
+                    brk = goes_on ? brk & ~(1u << left16) : brk | 1u << left16;
+                }
+            }
+            s_valid[i] = (uint16_t)vm16;
+            s_break[i] = (uint16_t)brk;
+        }
+    }
+    __syncthreads();
+
+    // the wave's slots [lo, hi); a lane holds the flags of 32 of them
+    const int32_t lo = n * wave / kWaves, hi = n * (wave + 1) / kWaves;
+    const int32_t base = lo & ~31, mine = base + 32 * lane;
+    auto below = [&](int32_t slot) { const int32_t k = slot - mine; return k <= 0 ? 0u : k >= 32 ? ~0u : (1u << k) - 1u; };
+    const uint32_t brk = reinterpret_cast<const uint32_t*>(s_break)[(base >> 5) + lane] | ~below(hi + 1);
+    const uint32_t val = reinterpret_cast<const uint32_t*>(s_valid)[(base >> 5) + lane] & below(hi);
+    // the first slot from `t` on whose bit is set, INT32_MAX if there is none
+    auto find = [&](uint32_t bits, int32_t t) {
+        const uint32_t m = bits & ~below(t);
+        const uint64_t vote = __ballot(m != 0);
+        if (vote == 0) return INT32_MAX;
+        const int l = __builtin_ctzll(vote);
+        return base + 32 * l + (int32_t)__builtin_ctz((uint32_t)__builtin_amdgcn_readlane((int)m, l));
+    };
+
+    const int64_t frame_bytes = (int64_t)D * (int64_t)sizeof(ElemT);
+    const uint8_t* const end_of_all = a.packed + a.total_slots * frame_bytes;
+    const uint32_t step_bytes = (uint32_t)a.step_vec * 16u;
+    const uint32_t lane_off = 16u * (uint32_t)min(lane, a.step_vec - 1);      // (what idle lanes add up is not looked at)
+    ChunkDesc piece{kHeadNone, 0, 0, -1};
+    FlatSums<ElemT> run;
+    auto load = [](const uint8_t* at) {
+        const vec16_any* from = reinterpret_cast<const vec16_any*>(at);
+        return STREAM ? __builtin_nontemporal_load(from) : *from;
+    };
+
+    for (int32_t t = lo; t < hi;) {
+        t = find(val, t);
+        if (t >= hi) break;
+        const int32_t stop = find(brk, t + 1), e = min(stop, hi);
+        const bool closed = stop <= hi;
+        const bool head_open = t == lo && find(brk, t) != t;
+        const int32_t seq = head_open ? -1 : a.seq_id[g0 + t];
+        const int32_t frames = e - t;
+        // whole steps, and frames of one more
+        const int32_t steps = (int32_t)__umulhi((uint32_t)frames, a.step_magic), rest = frames - steps * a.step_frames;
+        const uint8_t* p = a.packed + (g0 + t) * frame_bytes;
+        run.clear();
+        int32_t at = 0;
+        for (; at + N <= steps; at += N) {
+            vec16 x[N];
+#pragma unroll
+            for (int u = 0; u < N; ++u) x[u] = load(p + (uint32_t)u * step_bytes + lane_off);
+            run.add(x);
+            p += (int64_t)N * step_bytes;
+        }
+        const int32_t left = steps - at + (rest ? 1 : 0);          // the last ones, `rest` frames in the very last
+        auto last_steps = [&](auto count) {
+            constexpr int C = decltype(count)::value;
+            // in the very last step: how many of a lane's bytes count, and vectors up to the last that holds one
+            const int32_t bytes = rest ? rest * (int32_t)frame_bytes : (int32_t)step_bytes;
+            const uint32_t last_vec = (uint32_t)(bytes + 15) / 16u - 1u;
+            const bool careful = p + (int64_t)(left - 1) * step_bytes + 16 * ((int64_t)last_vec + 1) > end_of_all;
+            vec16 x[C];
+#pragma unroll
+            for (int u = 0; u < C; ++u) {
+                const uint32_t off = u < left - 1 ? lane_off : min(lane_off, 16u * last_vec);
+                const uint8_t* from = p + (int64_t)min(u, left - 1) * step_bytes + off;
+                // (the tensor's last vector, where it is no whole one, is put together below)
+                x[u] = load(careful && from > end_of_all - 16 ? end_of_all - 16 : from);
+            }
+            const int32_t counts = bytes - 16 * lane;
+            vec16 keep;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int32_t bits = 8 * counts - 32 * j;
+                keep[j] = bits >= 32 ? ~0u : (1u << max(bits, 0)) - 1u;
+            }
+            if (careful && lane == (int)last_vec) {
+                const uint8_t* from = p + (int64_t)(left - 1) * step_bytes + 16u * last_vec;
+                union { vec16 v; ElemT e[EPV]; } own;
+                own.v = vec16{0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int k = 0; k < EPV; ++k)
+                    if (k * (int)sizeof(ElemT) < counts) own.e[k] = reinterpret_cast<const ElemT*>(from)[k];
+#pragma unroll
+                for (int u = 0; u < C; ++u)
+                    if (u == left - 1) x[u] = own.v;
+            }
+#pragma unroll
+            for (int u = 0; u < C; ++u) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[u][j] &= u < left - 1 ? ~0u : u == left - 1 ? keep[j] : 0u;
+            }
+            run.add(x);
+        };
+        if (left > N / 2) last_steps(std::integral_constant<int, N>());
+        else if (left > 0) last_steps(std::integral_constant<int, N / 2>());
+
+        // the lanes' sums by feature: element i of a step is feature i % D
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < EPV; ++k) scratch[lane * EPV + k] = run.get(k);
+        wave_sync();
+        const int32_t side = D <= kWave / 2 ? kWave / D : 1;          // lanes that share a feature
+        for (int32_t d0 = 0; d0 < D; d0 += kWave) {
+            const int32_t j0 = side > 1 ? lane / D : 0;
+            const int32_t d = side > 1 ? lane - j0 * D : d0 + lane;
+            Part sum = 0;
+            if (j0 < side && d < D) {
+                for (int32_t j = j0; j < a.step_frames; j += 4 * side) {      // (four look-ups at a time)
+                    Part part[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) part[i] = scratch[min(j + i * side, a.step_frames - 1) * D + d];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) sum += j + i * side < a.step_frames ? part[i] : (Part)0;
+                }
+            }
+            if (side > 1) {
+                wave_sync();
+                scratch[lane] = sum;
+                wave_sync();
+                if (lane < D) {
+                    sum = 0;
+                    for (int32_t j = 0; j < side; j += 4) {
+                        Part part[4];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) part[i] = scratch[min(j + i, side - 1) * D + lane];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) sum += j + i < side ? part[i] : (Part)0;
+                    }
+                }
+            }
+            if (j0 != 0 || d >= D) continue;
+            if (head_open) s_head[wave * D + d] = sum;
+            else if (!closed) s_tail[wave * D + d] = sum;
+            else if ((uint32_t)seq < (uint32_t)a.n_seq)
+                static_cast<Out*>(a.out)[(int64_t)seq * D + d] = (Out)finish<Part>(sum, frames, a.mean);
+        }
+        if (head_open) {
+            piece.head_state = closed ? kHeadClosed : kHeadThrough;
+            piece.cnt_head = frames;
+        } else if (!closed) {
+            piece.cnt_tail = frames;
+            piece.seq_tail = seq;
+        }
+        t = e;
+    }
+    if (lane == 0) s_piece[wave] = piece;
+    __syncthreads();
+
+    // what the waves left open, in time order
+    ChunkDesc desc{kHeadNone, 0, 0, -1};
+    for (int32_t d = tid; d == tid || d < D; d += kThreads) {
+        Part sum = 0;
+        int32_t cnt = 0, seq = -1;
+        bool live = false, started = false;
+        for (int w = 0; w < kWaves; ++w) {
+            const ChunkDesc part = s_piece[w];
+            if (part.head_state != kHeadNone) {
+                if (!live) { sum = 0; cnt = 0; started = false; }     // it comes from the tile in front
+                live = part.head_state == kHeadThrough;
+                cnt += part.cnt_head;
+                if (d < D) sum += s_head[w * D + d];
+                if (!live && started) {
+                    if (d < D && (uint32_t)seq < (uint32_t)a.n_seq)
+                        static_cast<Out*>(a.out)[(int64_t)seq * D + d] = (Out)finish<Part>(sum, cnt, a.mean);
+                } else if (!live) {
+                    if (d < D && a.head_part) put_part<Part>(a.head_part, q, d, D, sum);
+                    desc.head_state = kHeadClosed;
+                    desc.cnt_head = cnt;
+                }
+            }
+            if (part.cnt_tail > 0) {
+                live = started = true;
+                cnt = part.cnt_tail;
+                seq = part.seq_tail;
+                if (d < D) sum = s_tail[w * D + d];
+            }
+        }
+        if (live && started) {
+            if (d < D && a.tail_part) put_part<Part>(a.tail_part, q, d, D, sum);
+            desc.cnt_tail = cnt;
+            desc.seq_tail = seq;
+        } else if (live) {
+            if (d < D && a.head_part) put_part<Part>(a.head_part, q, d, D, sum);
+            desc.head_state = kHeadThrough;
+            desc.cnt_head = cnt;
+        }
+    }
+    if (tid == 0 && a.desc) a.desc[q] = desc;
+}
+
 // ----------------------------------------------------------------- stitch
 
 // Segments cut by chunk borders: tail piece + the head pieces of the following
@@ -1329,6 +1674,8 @@ struct ReducePlan {
     bool wide, staged;
     bool run;                // staged: a workgroup takes the tiles of a whole chunk one after another
     int32_t tile;            // of this many slots
+    bool flat;
+    int step_vec, step_frames;   // flat: see ReduceArgs
     bool split;              // wide: two waves to a chunk, and see ReduceArgs
     int32_t reach;
     int vec;                 // wide: elements per lane (16 bytes, 4 bytes or one element)
@@ -1371,6 +1718,83 @@ static bool takes_one_element(int32_t t_blk, int64_t feat_dim, int es, int64_t m
 static bool takes_run(int64_t tiles, bool few, int64_t feat_dim, int es, int64_t mean)
 {
     return feat_dim <= 5 && mean >= 64 && (few ? tiles <= 2 : es == 4 && tiles <= 3);
+}
+
+// The flat cut, if the frames allow it: a step holds two frames or more, and of bytes eight.
+constexpr int64_t kFlatLeast = (int64_t)12 << 20, kFlatMiddle = (int64_t)50 << 20, kFlatLarge = (int64_t)200 << 20;
+static bool flat_cut(ReducePlan& p, int64_t num_blocks, int32_t t_blk, int64_t feat_dim, int es)
+{
+    const int64_t frame_bytes = feat_dim * es;
+    if (feat_dim < 2 || frame_bytes > kWave * 16 / 2 || num_blocks * t_blk * frame_bytes < kFlatLeast) return false;
+    int64_t common = 16;                   // of a frame and a vector
+    while (frame_bytes % common) common /= 2;
+    const int64_t period = frame_bytes / common;
+    if (period > kWave) return false;
+    p.step_vec = (int)(kWave / period * period);
+    p.step_frames = (int)(p.step_vec * 16 / frame_bytes);
+    if (es == 1 && p.step_frames < kFlatByteFrames) return false;
+    p.flat = true;
+    // A thousand workgroups are enough (four times as many: 7 to 25 % slower where that cuts blocks), none smaller than 16
+    // KiB, and several short blocks to one up to 128 KiB (600 MB of 384 bytes, blocks of 60 slots, pieces of 40: 182 us with
+    // 32 KiB, 123 like this).
+    int64_t cuts = std::min<int64_t>(ceil_div((int64_t)1024, num_blocks), t_blk * frame_bytes >> 14);
+    cuts = std::max<int64_t>(std::max<int64_t>(cuts, 1), ceil_div(t_blk, kFlatSlots));
+    p.chunk = (int32_t)ceil_div(t_blk, cuts);
+    p.n_chunks = (int32_t)ceil_div(t_blk, p.chunk);
+    p.blocks_per_tile = 1;
+    p.total_chunks = num_blocks * p.n_chunks;
+    if (p.n_chunks == 1) {
+        const int64_t blocks = std::min(std::min<int64_t>(kFlatSlots / t_blk, ((int64_t)128 << 10) / (t_blk * frame_bytes)), num_blocks / 1024);
+        p.blocks_per_tile = (int32_t)std::max<int64_t>(1, blocks);
+        p.total_chunks = ceil_div(num_blocks, p.blocks_per_tile);
+    }
+    p.partials = p.n_chunks > 1;
+    return true;
+}
+
+// Whether pieces are long enough for it.  A piece costs a wave some 5 us whatever it holds, with 8192 waves at work, so
+// that its bytes have to make up for that against
+//   - staged tiles, which take their time by elements: 250 MB, 58 bytes in pieces of 80 frames 173 -> 69 us, 14 bytes x 80 211
+//     -> 147, 16 bytes x 80 even, 17 bytes x 20 0.4 times as fast; 28 halfs x 130 189 -> 77; 8 bytes of floats x 400 107 -> 76, x 80 123 and 266
+//     (frames of few floats end in many lanes); 16 to 60 MB, less in flight: 22 bytes of halfs x 40 20 and 30; 16 MB of
+//     80-byte frames in blocks of 3000, which both cut, x 160 12 and 14
+//   - wide rows of 4-byte lanes or single elements: 600 MB, 86 bytes of halfs x 40 197 -> 148; 100 bytes of int32 x 80 153 ->
+//     127; but 140 bytes of floats, half the lanes idle here, x 60 43 and 52
+//   - wide rows of whole vectors, whose rows wait for each other: 600 MB, 64 bytes x 80 184 -> 117, 208 x 10 176 -> 152, 480 x 20 159 ->
+//     135; 60 MB, 336 bytes x 40 24.5 -> 18, 144 x 20 23 and 30; 16 MB, 384 x 400 12 and 14.
+static bool takes_flat(const ReducePlan& flat, const ReducePlan& other, int64_t total_bytes, int64_t frame_bytes, int es, int64_t mean)
+{
+    const int64_t piece = mean * frame_bytes;
+    if (!other.wide) {
+        if (total_bytes < kFlatMiddle && flat.n_chunks > 1 && frame_bytes >= 32) return false;
+        const int64_t least = es == 1 ? 1100 : es == 2 ? 2000 : frame_bytes < 20 ? 3200 : 1600;
+        return piece >= (total_bytes >= kFlatLarge ? least : least * 8 / 5);
+    }
+    if (frame_bytes % 16 == 0)
+        return total_bytes >= kFlatLarge ? piece >= 2000 : total_bytes >= kFlatMiddle && flat.n_chunks == 1 && piece >= 12000;
+    if (es == 4) return frame_bytes <= 128 && piece >= 5000;
+    return piece >= 3000 && (total_bytes >= kFlatMiddle || frame_bytes <= 128);
+}
+
+// Where the workspace holds what borders cut.
+static void add_partials(ReducePlan& p, int64_t feat_dim, bload_dtype dtype, bool lean)
+{
+    const int es = elem_size(dtype);
+    if (!p.partials) return;
+    {
+        // Rows of whole vectors keep their partial sums of halfs and floats in 32 bits.  Tiles, and narrower lanes
+        // of frames that are no whole vectors, make more of them, and rounding each would cost accuracy (sequences
+        // of 388 frames of 66 halfs in chunks of 70 slots: root mean square error against 64 bits 2.7e-8, 2.3e-8 in
+        // half as many chunks)
+        p.pair_parts = (dtype == BLOAD_F16 || dtype == BLOAD_F32) &&
+                       (p.staged || p.flat || (p.wide && p.vec * es < 16 && feat_dim * es % 16 != 0 && !lean));
+        const size_t acc = dtype == BLOAD_I32 || p.pair_parts ? 8 : 4;
+        size_t off = 0;
+        p.desc_off = off; off += round_up((size_t)p.total_chunks * sizeof(ChunkDesc), 16);
+        p.head_off = off; off += round_up((size_t)p.total_chunks * (size_t)feat_dim * acc, 16);
+        p.tail_off = off; off += round_up((size_t)p.total_chunks * (size_t)feat_dim * acc, 16);
+        p.bytes = off;
+    }
 }
 
 // `lean`: a cut that makes do with little workspace, or none, at the price of workgroups: tiles of a whole chunk
@@ -1489,20 +1913,14 @@ static ReducePlan reduce_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_di
         // only a block cut into several tiles can have a segment across a tile border
         p.partials = p.n_chunks > 1;
     }
-    if (p.partials) {
-        // Rows of whole vectors keep their partial sums of halfs and floats in 32 bits.  Tiles, and narrower lanes
-        // of frames that are no whole vectors, make more of them, and rounding each would cost accuracy (sequences
-        // of 388 frames of 66 halfs in chunks of 70 slots: root mean square error against 64 bits 2.7e-8, 2.3e-8 in
-        // half as many chunks)
-        p.pair_parts = (dtype == BLOAD_F16 || dtype == BLOAD_F32) &&
-                       (p.staged || (p.wide && p.vec * es < 16 && frame_bytes % 16 != 0 && !lean));
-        const size_t acc = dtype == BLOAD_I32 || p.pair_parts ? 8 : 4;
-        size_t off = 0;
-        p.desc_off = off; off += round_up((size_t)p.total_chunks * sizeof(ChunkDesc), 16);
-        p.head_off = off; off += round_up((size_t)p.total_chunks * (size_t)feat_dim * acc, 16);
-        p.tail_off = off; off += round_up((size_t)p.total_chunks * (size_t)feat_dim * acc, 16);
-        p.bytes = off;
-    }
+    add_partials(p, feat_dim, dtype, lean);
+    return p;
+}
+
+static ReducePlan flat_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, bload_dtype dtype)
+{
+    ReducePlan p{};
+    if (flat_cut(p, num_blocks, t_blk, feat_dim, elem_size(dtype))) add_partials(p, feat_dim, dtype, false);
     return p;
 }
 
@@ -1521,13 +1939,23 @@ static void launch_wide(const ReducePlan& p, const ReduceArgs& a, hipStream_t st
         hipLaunchKernelGGL((reduce_wide_kernel<ElemT, VEC, false, STREAM>), grid, dim3(kThreads), lds, stream, a);
 }
 
+template <typename ElemT, bool STREAM>
+static void launch_flat(const ReducePlan& p, const ReduceArgs& a, hipStream_t stream)
+{
+    const size_t lds = (size_t)kWaves * (size_t)(kFlatScratch<ElemT> + 2 * a.feat_dim) * sizeof(typename TileSum<ElemT>::T);
+    hipLaunchKernelGGL((reduce_flat_kernel<ElemT, STREAM>), dim3((uint32_t)p.total_chunks), dim3(kThreads), lds, stream, a);
+}
+
 template <typename ElemT>
 static void launch_reduce(const ReducePlan& p, const ReduceArgs& a, hipStream_t stream)
 {
     typedef typename Elem<ElemT>::Acc Acc;
-    if (p.wide) {
+    const bool fits_cache = a.total_slots * a.feat_dim * (int64_t)sizeof(ElemT) <= kMemorySideCache;
+    if (p.flat) {
+        if (fits_cache) launch_flat<ElemT, false>(p, a, stream);
+        else launch_flat<ElemT, true>(p, a, stream);
+    } else if (p.wide) {
         constexpr int kVec = 16 / (int)sizeof(ElemT), kSmallVec = 4 / (int)sizeof(ElemT);
-        const bool fits_cache = a.total_slots * a.feat_dim * (int64_t)sizeof(ElemT) <= kMemorySideCache;
         if (p.vec == kVec && fits_cache) launch_wide<ElemT, kVec, false>(p, a, stream);
         else if (p.vec == kVec) launch_wide<ElemT, kVec, true>(p, a, stream);
         else if (p.vec == kSmallVec) launch_wide<ElemT, kSmallVec, false>(p, a, stream);
@@ -1564,9 +1992,10 @@ extern "C" size_t bload_segment_reduce_workspace_bytes(int64_t num_blocks, int32
                                                        int64_t feat_dim, bload_dtype dtype)
 {
     if (num_blocks <= 0 || t_blk < 1 || feat_dim < 1 || (int)dtype < 0 || (int)dtype > 3) return 0;
-    // either end of the guess at the pieces' length
-    return std::max(reduce_plan(num_blocks, t_blk, feat_dim, dtype, 0).bytes,
-                    reduce_plan(num_blocks, t_blk, feat_dim, dtype, (int64_t)1 << 40).bytes);
+    // either end of the guess at the pieces' length, and the flat cut
+    return std::max(flat_plan(num_blocks, t_blk, feat_dim, dtype).bytes,
+                    std::max(reduce_plan(num_blocks, t_blk, feat_dim, dtype, 0).bytes,
+                             reduce_plan(num_blocks, t_blk, feat_dim, dtype, (int64_t)1 << 40).bytes));
 }
 
 extern "C" bload_status bload_segment_reduce(const void* d_packed, const int32_t* d_seq_id,
@@ -1589,8 +2018,12 @@ extern "C" bload_status bload_segment_reduce(const void* d_packed, const int32_t
         return BLOAD_EALIGN;
 
     ReducePlan p = reduce_plan(num_blocks, t_blk, feat_dim, dtype, total_slots / n_seq);
-    // a workspace that is smaller than the query's answer but holds what the leanest cut needs
+    // a workspace that is smaller than the query's answer but holds what another cut needs, in the end the leanest
     const size_t room = d_workspace ? workspace_bytes : 0;
+    const ReducePlan flat = flat_plan(num_blocks, t_blk, feat_dim, dtype);
+    if (flat.flat && flat.bytes <= room &&
+        takes_flat(flat, p, total_slots * feat_dim * elem_size(dtype), feat_dim * elem_size(dtype), elem_size(dtype), total_slots / n_seq))
+        p = flat;
     if (room < p.bytes) {
         const ReducePlan lean = reduce_plan(num_blocks, t_blk, feat_dim, dtype, total_slots / n_seq, true);
         if (lean.bytes <= room) p = lean;
@@ -1627,6 +2060,9 @@ extern "C" bload_status bload_segment_reduce(const void* d_packed, const int32_t
     a.n_chunks = p.n_chunks;
     a.row_lanes_log2 = p.row_lanes_log2;
     a.n_vec = p.n_vec;
+    a.step_vec = p.step_vec;
+    a.step_frames = p.step_frames;
+    a.step_magic = p.flat ? (uint32_t)(((uint64_t)1 << 32) / (uint64_t)p.step_frames + 1) : 0u;
     a.feat_tiles = p.wide ? (int32_t)ceil_div(p.n_vec, 1 << p.row_lanes_log2) : 1;
     if (p.partials) {
         uint8_t* ws = static_cast<uint8_t*>(d_workspace);

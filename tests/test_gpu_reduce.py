@@ -467,3 +467,41 @@ def test_reduce_short_pieces_over_chunk_borders(B, T, dtype, op):
     scale, _ = oracle.segment_reduce_packed(absval, seq_id, reset, valid, D, "f32", op, n_seg)
     bound = REL_TOL * np.maximum(np.abs(want.astype(np.float64)), scale.astype(np.float64)) + 1e-30
     assert np.all(np.abs(got[:n_seg].astype(np.float64) - want.astype(np.float64)) <= bound)
+
+
+# Frames whose whole multiples are at most 64 vectors, in long pieces: a wave takes a piece's bytes as one stream.  Blocks cut
+# into several workgroups' shares and several blocks to a workgroup, segments that begin and end around the quarters that
+# the waves take, padding there as well, pieces of fewer frames than a step and of whole steps, the tensor's last bytes (no
+# whole vector).  The lanes' trees of four lose 2 units of roundoff of sum |x|, the result's rounding one, as does the oracle's.
+@pytest.mark.parametrize("dtype,op", [("f32", "mean"), ("i32", "sum"), ("u8", "mean"), ("f16", "sum")])
+@pytest.mark.parametrize("B,T,frame_bytes", [(40, 8001, 44), (3, 60000, 76), (1, 70001, 188), (6000, 33, 124), (1100, 300, 48),
+                                             (300, 7000, 8), (1030, 160, 128), (150, 3000, 128), (1025, 777, 64)])
+def test_reduce_flat_streams(B, T, frame_bytes, dtype, op):
+    bl = binding()
+    rng = np.random.default_rng(B + T + frame_bytes)
+    D = frame_bytes // bl.ELEM_BYTES[dtype]
+    valid, reset = np.ones((B, T), np.uint8), np.zeros((B, T), np.uint8)
+    at = np.unique(np.clip([T * w // 4 + k for w in range(5) for k in (-17, -1, 0, 1, 2, 16)], 1, T - 1))
+    for b in range(B):
+        reset[b, rng.choice(at, size=int(rng.integers(0, 4)))] = 1 if b * frame_bytes % 3 else 0
+        if b % 5 == 1:
+            valid[b, int(rng.choice(at)):][:int(rng.integers(1, 12))] = 0
+    reset &= valid
+    prev = np.concatenate([np.zeros((B, 1), np.uint8), valid[:, :-1]], axis=1)
+    starts = (valid == 1) & ((reset == 1) | (prev == 0))
+    seq_id = np.where(valid == 1, np.cumsum(starts.reshape(-1)).reshape(B, T) - 1, -1).astype(np.int32)
+    n_seg = int(starts.sum())
+    src = draw_source(rng, B * T, D, dtype)
+    want, _ = oracle.segment_reduce_packed(src.reshape(B, T, D), seq_id, reset, valid, D, dtype, op, n_seg)
+    absval = np.abs(src.astype(np.float32)).reshape(B, T, D)
+    scale, _ = oracle.segment_reduce_packed(absval, seq_id, reset, valid, D, "f32", op, n_seg)
+
+    ws = bl.bload_segment_reduce_workspace_bytes(B, T, D, dtype)
+    print(f"flat B={B} T={T} {frame_bytes} bytes {dtype} segments {n_seg} workspace {ws}", flush=True)
+    got = bl.bload_segment_reduce(to_dev(src), to_dev(seq_id), to_dev(reset), to_dev(valid), B, T, D, dtype, op, n_seg).cpu().numpy()
+    if dtype == "i32":
+        assert np.array_equal(got, want)
+        return
+    bound = 2.01 * U * scale.astype(np.float64) + 2 * U * np.abs(want.astype(np.float64))
+    err = np.abs(got.astype(np.float64) - want.astype(np.float64))
+    assert np.all(err <= bound), f"{np.max(err / (U * scale))} units"
