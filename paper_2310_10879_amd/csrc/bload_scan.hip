@@ -69,6 +69,7 @@ constexpr int kScanLong = 32, kScanShort = 8;                  // slots per lane
 constexpr int kScanStagedLong = 33, kScanStagedHalf = 17, kScanStagedShort = 9;      // odd, see scan_staged_kernel
 constexpr int kScanStagedWalk = 25;    // what a walking workgroup has the registers for
 constexpr int kScanGroup = 32;         // blocks whose tiles are taken side by side
+constexpr int kScanLine = 32;          // floats of a cache line
 
 struct ScanArgs {
     const uint8_t* packed;
@@ -707,8 +708,8 @@ static int32_t scan_staged_slots(int32_t groups, int32_t t_blk)
     return best;
 }
 
-// `walk`: a block's tiles go to one workgroup, as long as there are.
-static ScanPlan scan_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, size_t elem, bool walk = false)
+// `walk`: a block's tiles go to one workgroup, as long as there are.  `lines`: slices of whole cache lines.
+static ScanPlan scan_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, size_t elem, bool walk = false, bool lines = true)
 {
     ScanPlan p{};
     p.staged = feat_dim < kScanSmallFrame;
@@ -721,6 +722,9 @@ static ScanPlan scan_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, s
     // slices of equal width; a width of which the workgroup's 256 lanes hold a whole number
     p.slices = p.staged ? 1 : (int32_t)ceil_div(p.frame_units, kScanRow);
     p.row = (int32_t)ceil_div(p.frame_units, p.slices);
+    // and of whole cache lines where frames are, or two workgroups would write the lines between them (1056 bytes, five
+    // slices of 848 bytes of output: 289 -> 224 us, 800 floats 448 -> 383, 960 halfs 69 -> 64)
+    if (lines && p.slices > 1 && feat_dim % kScanLine == 0) p.row = (int32_t)round_up((size_t)p.row, kScanLine / 4);
     int32_t most_subs = kThreads / p.row;
     // slots per lane: 64 registers of payload; fewer where that leaves the chip without enough tiles
     p.k = !p.staged ? kScanLong : walk ? kScanStagedWalk : scan_staged_slots(most_subs, t_blk);
@@ -839,7 +843,9 @@ extern "C" bload_status bload_segment_scan(const void* d_packed, const uint8_t* 
     if (!aligned_to(d_packed, 16) || !aligned_to(d_out, 16)) return BLOAD_EALIGN;
     if (num_blocks * (int64_t)t_blk >= ((int64_t)1 << 40)) return BLOAD_EOVERFLOW;
     ScanPlan p = scan_plan(num_blocks, t_blk, feat_dim, scan_elem_bytes(dtype));
-    if (p.bytes > 0 && (!d_workspace || !aligned_to(d_workspace, 16) || workspace_bytes < p.bytes)) {
+    const size_t room = d_workspace && aligned_to(d_workspace, 16) ? workspace_bytes : 0;
+    if (room < p.bytes) p = scan_plan(num_blocks, t_blk, feat_dim, scan_elem_bytes(dtype), false, false);
+    if (room < p.bytes) {
         const size_t least = std::min(p.bytes, scan_least_bytes(num_blocks, t_blk, feat_dim, scan_elem_bytes(dtype)));
         if (least > 0) {
             if (!d_workspace) return BLOAD_EINVAL;

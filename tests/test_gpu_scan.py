@@ -276,3 +276,34 @@ def test_scan_errors():
         bl.bload_segment_scan(z[1:], z, z, 1, 4, 4, "f32", 0.5)
     assert e.value.status == bl.EALIGN
     assert bl.bload_segment_scan(z, z, z, 0, 4, 4, "f32", 0.5).numel() == 0
+
+
+# Frames of several slices whose output is whole cache lines: slices of 10 and 8, 16 and 14, 22, 22 and 22 groups of eight
+# features, beside one feature more or less, whose tiles pass the cache by another way; then with the workspace that slices
+# of equal width need (a state per feature, 8 bytes, behind each but the last of a block's tiles of 32 slots a lane), if it is less.
+@pytest.mark.parametrize("dtype", ["u8", "f16", "f32"])
+@pytest.mark.parametrize("B,T,D", [(400, 300, 288), (40, 700, 480), (40, 700, 479), (700, 129, 704), (300, 260, 270), (1200, 90, 100)])
+def test_scan_slices_of_whole_lines(B, T, D, dtype):
+    bl = binding()
+    asked = bl.bload_segment_scan_workspace_bytes(B, T, D, dtype)
+    units = -(-D // 4)
+    groups = 256 // -(-units // -(-units // 64))
+    tiles = -(-T // (32 * groups))
+    tiles = -(-T // (32 * -(-(-(-T // tiles)) // 32)))
+    equal = (B * (tiles - 1) * D * 8 + 15) // 16 * 16
+    assert equal <= asked
+    rng = np.random.default_rng(B + T + D)
+    valid, reset, _, _ = random_flags(rng, B, T, 0.97, 0.01)
+    src = draw_source(rng, B * T, D, dtype)
+    ref, scale = oracle.segment_scan_packed(src, reset, valid, D, dtype, 0.95)
+    x, r, v = to_dev(src.view(np.uint8).reshape(-1)), to_dev(reset), to_dev(valid)
+    for room in sorted({asked, equal}):
+        out = torch.full((B, T, D), float("nan"), dtype=torch.float32, device="cuda")
+        ws = torch.empty(max(room, 16), dtype=torch.uint8, device="cuda")
+        print(f"scan B={B} T={T} D={D} {dtype} workspace {room} of {asked}", flush=True)
+        st = bl._lib.bload_segment_scan(x.data_ptr(), r.data_ptr(), v.data_ptr(), B, T, D, bl.DTYPES[dtype], 0.95, out.data_ptr(),
+                                        ws.data_ptr(), room, torch.cuda.current_stream().cuda_stream)
+        assert st == bl.OK
+        got = out.cpu().numpy()
+        assert not got[valid == 0].any()
+        assert_scan_close(got, ref, scale, f"{dtype} B={B} T={T} D={D}")
