@@ -71,6 +71,9 @@ constexpr int kScanStagedWalk = 25;    // what a walking workgroup has the regis
 constexpr int kScanGroup = 32;         // blocks whose tiles are taken side by side
 constexpr int kScanLine = 32;          // floats of a cache line
 
+// Direct tiles, how they pass the caches (scan_traffic).
+enum ScanTraffic : int { kScanStream = 0, kScanCached = 1, kScanPlain = 2 };
+
 struct ScanArgs {
     const uint8_t* packed;
     const uint8_t* reset;
@@ -442,7 +445,7 @@ __device__ __forceinline__ void scan_carry_in(const ScanArgs& a, ScanShared<UNIT
 // Frames of 64 elements or more.  WALK, where there is no room for published states: a workgroup takes all tiles of
 // its block, one after another with the state in registers: the same operations, the same bits.  (The loop's body is not indented;
 // as a function of its own, with what it needs in LDS by reference, it came out 5 to 15 % slower for halfs.)
-template <typename ElemT, int K, bool WALK>
+template <typename ElemT, int K, bool WALK, int TRAFFIC>
 __global__ __launch_bounds__(kThreads, sizeof(ElemT) == 4 ? 2 : 3) void scan_direct_kernel(ScanArgs a)
 {
     constexpr int UNIT = 4;
@@ -498,16 +501,20 @@ __global__ __launch_bounds__(kThreads, sizeof(ElemT) == 4 ? 2 : 3) void scan_dir
         const uint32_t at = lane_at * (uint32_t)sizeof(ElemT);
         typedef typename ScanBits<sizeof(ElemT) * 4>::T Bits;
         typedef typename ScanBits<sizeof(ElemT) * 4>::Any BitsAny;
+        auto load = [](const uint8_t* place) -> Bits {
+            const BitsAny* p = reinterpret_cast<const BitsAny*>(place);
+            return TRAFFIC == kScanStream ? __builtin_nontemporal_load(p) : *p;
+        };
         if (vm == ALL) {
 #pragma unroll
             for (int u = 0; u < K; ++u)
-                x[u].bits = __builtin_nontemporal_load(reinterpret_cast<const BitsAny*>(from + u * frame_bytes + at));
+                x[u].bits = load(from + u * frame_bytes + at);
         } else {
 #pragma unroll
             for (int u = 0; u < K; ++u) {
                 x[u].bits = Bits{};
                 if ((vm >> u) & 1u)
-                    x[u].bits = __builtin_nontemporal_load(reinterpret_cast<const BitsAny*>(from + u * frame_bytes + at));
+                    x[u].bits = load(from + u * frame_bytes + at);
             }
         }
 #pragma unroll
@@ -541,7 +548,9 @@ __global__ __launch_bounds__(kThreads, sizeof(ElemT) == 4 ? 2 : 3) void scan_dir
                           : __builtin_fmaf(a.decay, starts ? 0.0f : h[k], ScanElem<ElemT>::get(x[u].e[k]));
         if (u < left) {
             const float4v o = {h[0], h[1], h[2], h[3]};
-            __builtin_nontemporal_store(o, reinterpret_cast<float4v_any*>(to + u * D * 4 + at));
+            float4v_any* place = reinterpret_cast<float4v_any*>(to + u * D * 4 + at);
+            if (TRAFFIC == kScanPlain) *place = o;
+            else __builtin_nontemporal_store(o, place);
         }
     }
     if constexpr (WALK) __syncthreads();
@@ -677,6 +686,7 @@ __global__ __launch_bounds__(kThreads) void scan_clear_kernel(unsigned long long
 struct ScanPlan {
     bool staged;
     bool cached;                       // staged: plain loads
+    ScanTraffic traffic;               // direct
     int32_t k;                         // slots per lane
     int32_t row, subs, slices, frame_units;
     int32_t chunk, chunks, blocks_per_tile;
@@ -708,6 +718,23 @@ static int32_t scan_staged_slots(int32_t groups, int32_t t_blk)
     return best;
 }
 
+// How direct tiles of 32 slots a lane read and write.
+//   - Input that fits the memory-side cache is read with plain loads, from there where it was just written or read: 200 MB,
+//     3104 halfs 122 -> 91 us, 208 bytes 134 -> 100, 320 floats 83 -> 69; up to 30 MB even.
+//   - Where output lines are written by two workgroups (frames of several slices) or twice by one (frames that are no whole
+//     half lines), in parts, streaming stores send both parts to memory; plain ones meet in the cache.  270 halfs, 1.2
+//     GB: 1034 -> 820 us, 2415 of them 1710 -> 1504, 72 bytes 868 -> 736, 100 floats 504 -> 454; whole lines lose as much by it (256 floats 372
+//     -> 418), and single slices from 192 elements on gain nothing (250 halfs 764 and 780).  Input and output of 300 MB in all stay in
+//     the cache (944 bytes of 50 MB 68 -> 46); more than that would push input out that fits (250 floats, 216 MB: 93 us with
+//     plain loads alone, 117).
+static ScanTraffic scan_traffic(int64_t elems, size_t elem, int64_t feat_dim, bool one_slice)
+{
+    const bool cached = elems * (int64_t)elem <= ((int64_t)256 << 20);
+    const bool parts = one_slice ? feat_dim % (kScanLine / 2) != 0 && feat_dim < 192 : feat_dim % kScanLine != 0;
+    if (parts && (!cached || elems * (int64_t)(elem + 4) <= ((int64_t)300 << 20))) return kScanPlain;
+    return cached ? kScanCached : kScanStream;
+}
+
 // `walk`: a block's tiles go to one workgroup, as long as there are.  `lines`: slices of whole cache lines.
 static ScanPlan scan_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, size_t elem, bool walk = false, bool lines = true)
 {
@@ -725,6 +752,7 @@ static ScanPlan scan_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, s
     // and of whole cache lines where frames are, or two workgroups would write the lines between them (1056 bytes, five
     // slices of 848 bytes of output: 289 -> 224 us, 800 floats 448 -> 383, 960 halfs 69 -> 64)
     if (lines && p.slices > 1 && feat_dim % kScanLine == 0) p.row = (int32_t)round_up((size_t)p.row, kScanLine / 4);
+    p.traffic = scan_traffic(elems, elem, feat_dim, p.slices == 1);
     int32_t most_subs = kThreads / p.row;
     // slots per lane: 64 registers of payload; fewer where that leaves the chip without enough tiles
     p.k = !p.staged ? kScanLong : walk ? kScanStagedWalk : scan_staged_slots(most_subs, t_blk);
@@ -809,13 +837,15 @@ static void scan_launch(const ScanArgs& a, const ScanPlan& p, hipStream_t stream
     }
     if (p.walk) {
         if (p.staged) hipLaunchKernelGGL((scan_staged_kernel<ElemT, kScanStagedWalk, false, true>), grid, block, 0, stream, a);
-        else hipLaunchKernelGGL((scan_direct_kernel<ElemT, kScanLong, true>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((scan_direct_kernel<ElemT, kScanLong, true, kScanStream>), grid, block, 0, stream, a);
         return;
     }
     if (p.staged && p.cached) scan_launch_staged<ElemT, true>(a, p, stream);
     else if (p.staged) scan_launch_staged<ElemT, false>(a, p, stream);
-    else if (p.k == kScanLong) hipLaunchKernelGGL((scan_direct_kernel<ElemT, kScanLong, false>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((scan_direct_kernel<ElemT, kScanShort, false>), grid, block, 0, stream, a);
+    else if (p.k != kScanLong) hipLaunchKernelGGL((scan_direct_kernel<ElemT, kScanShort, false, kScanStream>), grid, block, 0, stream, a);
+    else if (p.traffic == kScanStream) hipLaunchKernelGGL((scan_direct_kernel<ElemT, kScanLong, false, kScanStream>), grid, block, 0, stream, a);
+    else if (p.traffic == kScanCached) hipLaunchKernelGGL((scan_direct_kernel<ElemT, kScanLong, false, kScanCached>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((scan_direct_kernel<ElemT, kScanLong, false, kScanPlain>), grid, block, 0, stream, a);
 }
 
 }  // namespace bload
