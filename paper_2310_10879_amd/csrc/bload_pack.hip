@@ -26,7 +26,7 @@
 //          sequences.  Without its payload part the same kernel writes the start
 //          table of large tensors of wide frames, whose 4 KiB tiles then only
 //          copy.
-// All large outputs leave through streaming stores (see store_slot).
+// Large outputs leave through streaming stores (see store_slot), small ones stay in the memory-side cache (pack_traffic).
 #include "bload_common.hpp"
 
 #include <limits.h>
@@ -146,6 +146,22 @@ static_assert(kWideTile / kWideMinFrame + 2 <= kWideRuns, "a tile's runs must fi
 
 typedef vec16 __attribute__((aligned(1))) vec16_unaligned;
 
+// How the payload passes the caches (pack_traffic).
+enum PackTraffic : int { kPackStream = 0, kPackCached = 1, kPackPlain = 2 };
+
+template <int TRAFFIC>
+__device__ __forceinline__ vec16 load_source(const uint8_t* p)
+{
+    const vec16_unaligned* v = reinterpret_cast<const vec16_unaligned*>(p);
+    return TRAFFIC == kPackStream ? __builtin_nontemporal_load(v) : *v;
+}
+template <int TRAFFIC>
+__device__ __forceinline__ void store_packed(vec16* p, vec16 v)
+{
+    if (TRAFFIC == kPackPlain) *p = v;
+    else store_stream(p, v);
+}
+
 // floor(x / d) for 0 <= x < 2^52, d >= 1, with inv_d = 1.0 / d: the double
 // quotient is within one of the answer, fixed up exactly in integers.
 __device__ __forceinline__ int64_t floor_div(int64_t x, int64_t d, double inv_d)
@@ -159,7 +175,7 @@ __device__ __forceinline__ int64_t floor_div(int64_t x, int64_t d, double inv_d)
 // Write packed bytes [lo, hi): copies of src[0 ..) (any alignment) or zeros.
 // Destination vectors are 16-byte aligned; the ragged ends of the range are
 // written byte by byte.  Called by all threads of the workgroup.
-template <bool ZERO>
+template <bool ZERO, int TRAFFIC>
 __device__ __forceinline__ void write_range(uint8_t* packed, int64_t lo, int64_t hi,
                                             const uint8_t* src)
 {
@@ -180,27 +196,19 @@ __device__ __forceinline__ void write_range(uint8_t* packed, int64_t lo, int64_t
     int v = tid;
     if (ZERO) {
         const vec16 z = {0u, 0u, 0u, 0u};
-        for (; v < nv; v += kThreads) store_stream(d + v, z);
+        for (; v < nv; v += kThreads) store_packed<TRAFFIC>(d + v, z);
     } else {
         for (; v + 3 * kThreads < nv; v += 4 * kThreads) {
-            const vec16 x0 = __builtin_nontemporal_load(
-                reinterpret_cast<const vec16_unaligned*>(s + 16 * (int64_t)v));
-            const vec16 x1 = __builtin_nontemporal_load(
-                reinterpret_cast<const vec16_unaligned*>(s + 16 * (int64_t)(v + kThreads)));
-            const vec16 x2 = __builtin_nontemporal_load(
-                reinterpret_cast<const vec16_unaligned*>(s + 16 * (int64_t)(v + 2 * kThreads)));
-            const vec16 x3 = __builtin_nontemporal_load(
-                reinterpret_cast<const vec16_unaligned*>(s + 16 * (int64_t)(v + 3 * kThreads)));
-            store_stream(d + v, x0);
-            store_stream(d + v + kThreads, x1);
-            store_stream(d + v + 2 * kThreads, x2);
-            store_stream(d + v + 3 * kThreads, x3);
+            const vec16 x0 = load_source<TRAFFIC>(s + 16 * (int64_t)v);
+            const vec16 x1 = load_source<TRAFFIC>(s + 16 * (int64_t)(v + kThreads));
+            const vec16 x2 = load_source<TRAFFIC>(s + 16 * (int64_t)(v + 2 * kThreads));
+            const vec16 x3 = load_source<TRAFFIC>(s + 16 * (int64_t)(v + 3 * kThreads));
+            store_packed<TRAFFIC>(d + v, x0);
+            store_packed<TRAFFIC>(d + v + kThreads, x1);
+            store_packed<TRAFFIC>(d + v + 2 * kThreads, x2);
+            store_packed<TRAFFIC>(d + v + 3 * kThreads, x3);
         }
-        for (; v < nv; v += kThreads) {
-            const vec16 x = __builtin_nontemporal_load(
-                reinterpret_cast<const vec16_unaligned*>(s + 16 * (int64_t)v));
-            store_stream(d + v, x);
-        }
+        for (; v < nv; v += kThreads) store_packed<TRAFFIC>(d + v, load_source<TRAFFIC>(s + 16 * (int64_t)v));
     }
 }
 
@@ -209,8 +217,16 @@ __device__ __forceinline__ void write_range(uint8_t* packed, int64_t lo, int64_t
 // cache, and a consumer that streams the packed tensor right afterwards then reads about a tenth
 // slower (measured: the reduction of 3000 x 320-byte blocks takes 3.98 ms alone and 4.45 ms
 // behind a pack that wrote them with plain stores).
+template <int TRAFFIC = kPackStream>
 __device__ __forceinline__ void store_slot(const PackArgs& a, int64_t slot, int32_t seq, int32_t fid)
 {
+    if (TRAFFIC == kPackPlain) {
+        a.seq_id[slot] = seq;
+        a.frame_idx[slot] = fid;
+        a.reset[slot] = (uint8_t)(fid == 0);
+        a.valid[slot] = (uint8_t)(fid >= 0);
+        return;
+    }
     __builtin_nontemporal_store(seq, a.seq_id + slot);
     __builtin_nontemporal_store(fid, a.frame_idx + slot);
     __builtin_nontemporal_store((uint8_t)(fid == 0), a.reset + slot);
@@ -219,13 +235,14 @@ __device__ __forceinline__ void store_slot(const PackArgs& a, int64_t slot, int3
 
 // Start-table entries of global slots [lo, hi): lane k of the calling wave writes the slots
 // lo + k, lo + k + 64, ...  frame0 = frame index of slot lo, or -1 for padding.
+template <int TRAFFIC>
 __device__ __forceinline__ void write_slots(const PackArgs& a, int64_t lo, int64_t hi, int32_t seq,
                                             int64_t frame0)
 {
     for (int64_t k = lane_id(); lo + k < hi; k += kWave) {
         const int64_t g = lo + k;
         const int32_t fid = frame0 < 0 ? -1 : (int32_t)(frame0 + k);
-        store_slot(a, g, frame0 < 0 ? -1 : seq, fid);
+        store_slot<TRAFFIC>(a, g, frame0 < 0 ? -1 : seq, fid);
     }
 }
 
@@ -282,6 +299,7 @@ __global__ __launch_bounds__(kThreads) void pack_prepare_kernel(
 // Pass 2: the copy.  The run table and the tiles' entries come as separate
 // __restrict__ pointers so that the compiler knows nothing this kernel stores
 // can alias them and keeps their loads on the scalar unit.
+template <int TRAFFIC>
 __global__ __launch_bounds__(kThreads) void pack_wide_kernel(
     PackArgs a, const Run* __restrict__ runs, const int32_t* __restrict__ first_pos,
     int32_t tile_bytes, double inv_frame_bytes, int32_t writes_table)
@@ -307,13 +325,12 @@ __global__ __launch_bounds__(kThreads) void pack_wide_kernel(
             const int64_t run_lo = g * F;
             if (run_lo <= D0 && run_lo + len * F >= D0 + tile_bytes && D0 + tile_bytes <= total_bytes) {
                 const uint8_t* s = a.src + r.src * F + (D0 - run_lo) + 16 * (int64_t)threadIdx.x;
-                const vec16 x = __builtin_nontemporal_load(reinterpret_cast<const vec16_unaligned*>(s));
-                store_stream(reinterpret_cast<vec16*>(a.packed + D0) + threadIdx.x, x);
+                store_packed<TRAFFIC>(reinterpret_cast<vec16*>(a.packed + D0) + threadIdx.x, load_source<TRAFFIC>(s));
                 if (table_wave) {
                     // frames t of this run with D0 <= run_lo + t * F < D1
                     for (int64_t t = floor_div(D0 - run_lo + F - 1, F, inv_frame_bytes) + lane_id();
                          run_lo + t * F < D1 && t < len; t += kWave) {
-                        store_slot(a, g + t, r.seq, (int32_t)t);
+                        store_slot<TRAFFIC>(a, g + t, r.seq, (int32_t)t);
                     }
                 }
                 return;
@@ -321,11 +338,11 @@ __global__ __launch_bounds__(kThreads) void pack_wide_kernel(
             // next most common: the tile lies in the zero tail of the run's block
             if (run_lo + len * F <= D0 && ((int64_t)r.block + 1) * T * F >= D0 + tile_bytes) {
                 const vec16 z = {0u, 0u, 0u, 0u};
-                store_stream(reinterpret_cast<vec16*>(a.packed + D0) + threadIdx.x, z);
+                store_packed<TRAFFIC>(reinterpret_cast<vec16*>(a.packed + D0) + threadIdx.x, z);
                 if (table_wave) {
                     for (int64_t slot = floor_div(D0 + F - 1, F, inv_frame_bytes) + lane_id(); slot * F < D1;
                          slot += kWave) {
-                        store_slot(a, slot, -1, -1);
+                        store_slot<TRAFFIC>(a, slot, -1, -1);
                     }
                 }
                 return;
@@ -357,18 +374,18 @@ __global__ __launch_bounds__(kThreads) void pack_wide_kernel(
             const int64_t lo = max(max(run_lo, D0), cursor);
             const int64_t hi = min(run_lo + len * F, D1);
             if (hi > lo) {
-                if (lo > cursor) write_range<true>(a.packed, cursor, lo, nullptr);
-                write_range<false>(a.packed, lo, hi, a.src + r.src * F + (lo - run_lo));
+                if (lo > cursor) write_range<true, TRAFFIC>(a.packed, cursor, lo, nullptr);
+                write_range<false, TRAFFIC>(a.packed, lo, hi, a.src + r.src * F + (lo - run_lo));
                 cursor = hi;
             }
             if (table_wave) {
                 const int64_t s_lo = max(g, mcursor), s_hi = min(g + len, m_hi);
-                if (s_lo > mcursor) write_slots(a, mcursor, s_lo, -1, -1);
-                if (s_hi > s_lo) { write_slots(a, s_lo, s_hi, r.seq, s_lo - g); mcursor = s_hi; }
+                if (s_lo > mcursor) write_slots<TRAFFIC>(a, mcursor, s_lo, -1, -1);
+                if (s_hi > s_lo) { write_slots<TRAFFIC>(a, s_lo, s_hi, r.seq, s_lo - g); mcursor = s_hi; }
             }
         }
-        if (cursor < D1) write_range<true>(a.packed, cursor, D1, nullptr);
-        if (table_wave && mcursor < m_hi) write_slots(a, mcursor, m_hi, -1, -1);
+        if (cursor < D1) write_range<true, TRAFFIC>(a.packed, cursor, D1, nullptr);
+        if (table_wave && mcursor < m_hi) write_slots<TRAFFIC>(a, mcursor, m_hi, -1, -1);
         return;
     }
 
@@ -421,10 +438,10 @@ __global__ __launch_bounds__(kThreads) void pack_wide_kernel(
         vec16* dst = reinterpret_cast<vec16*>(a.packed + x0);
         if (x0 + 16 <= D1 && x0 + 16 <= hi) {                           // inside one run
             const uint8_t* from = a.src + s_run_src[k] + (x0 - lo);
-            store_stream(dst, __builtin_nontemporal_load(reinterpret_cast<const vec16_unaligned*>(from)));
+            store_packed<TRAFFIC>(dst, load_source<TRAFFIC>(from));
         } else if (x0 + 16 <= D1 && x0 >= hi && x0 + 16 <= next_lo) {   // inside a block's zero tail
             const vec16 z = {0u, 0u, 0u, 0u};
-            store_stream(dst, z);
+            store_packed<TRAFFIC>(dst, z);
         } else {                                                        // a border inside: byte by byte
             for (int j = 0; j < 16 && x0 + j < D1; ++j) {
                 const int64_t x = x0 + j;
@@ -444,7 +461,7 @@ __global__ __launch_bounds__(kThreads) void pack_wide_kernel(
                 seq = s_run_seq[k];
                 fid = (int32_t)(slot - floor_div(s_run_lo[k], F, inv_frame_bytes));
             }
-            store_slot(a, slot, seq, fid);
+            store_slot<TRAFFIC>(a, slot, seq, fid);
         }
     }
 }
@@ -507,6 +524,7 @@ __device__ __forceinline__ void narrow_uniform_table(const PackArgs& a, int64_t 
 }
 
 // The payload of such a tile: per step one 16-byte vector per lane.
+template <int TRAFFIC>
 __device__ __forceinline__ void narrow_uniform_payload(const PackArgs& a, int64_t g0, const Run* r,
                                                        int32_t part, int32_t parts)
 {
@@ -517,7 +535,7 @@ __device__ __forceinline__ void narrow_uniform_payload(const PackArgs& a, int64_
     if (r) {
         const uint8_t* from = a.src + (r->src + (g0 - r->dst)) * F;
         for (int32_t v = first; v < nvec; v += step)
-            store_stream(dst + v, __builtin_nontemporal_load(reinterpret_cast<const vec16_unaligned*>(from) + v));
+            store_stream(dst + v, load_source<TRAFFIC>(from + 16 * (int64_t)v));
     } else {
         const vec16 z = {0u, 0u, 0u, 0u};
         for (int32_t v = first; v < nvec; v += step) store_stream(dst + v, z);
@@ -548,7 +566,7 @@ struct Assembled<vec16> {
 // One tile of kNarrowSlots slots (or the shorter last one) that needs its runs looked up: the
 // candidates `first` .. `last` of the run table are gathered into `tab` first.  Called by the
 // whole workgroup.
-template <typename E, bool FUSED, bool PAYLOAD, bool TABLE>
+template <typename E, bool FUSED, bool PAYLOAD, bool TABLE, int TRAFFIC>
 __device__ __forceinline__ void narrow_general_tile(const PackArgs& a, const Run* __restrict__ runs,
                                                     RunTable<kNarrowMaxRuns>& tab, int64_t g0, int64_t g1,
                                                     int32_t first, int32_t last, int32_t part, int32_t parts)
@@ -575,8 +593,7 @@ __device__ __forceinline__ void narrow_general_tile(const PackArgs& a, const Run
             vec16 pv;
             if (fid[0] >= 0 && sid[3] == sid[0] && fid[3] == fid[0] + 3) {
                 // one run: 16 contiguous source bytes (4-byte aligned)
-                typedef vec16 __attribute__((aligned(4))) vec16_a4;
-                pv = __builtin_nontemporal_load(reinterpret_cast<const vec16_a4*>(src32 + from[0]));
+                pv = load_source<TRAFFIC>(reinterpret_cast<const uint8_t*>(src32 + from[0]));
             } else {
                 uint32_t e0 = 0u, e1 = 0u, e2 = 0u, e3 = 0u;
                 if (fid[0] >= 0) e0 = src32[from[0]];
@@ -682,7 +699,7 @@ __device__ __forceinline__ void narrow_general_tile(const PackArgs& a, const Run
 // several tiles per workgroup the look-ups of a stage are asked for together, and so is the
 // payload of all tiles that lie inside one run, so that a wave has GROUP times the bytes in
 // flight per wait.  Tiles that need their runs gathered follow one by one.
-template <typename E, bool FUSED, bool PAYLOAD = true, bool TABLE = true, int GROUP = 1>
+template <typename E, bool FUSED, int TRAFFIC, bool PAYLOAD = true, bool TABLE = true, int GROUP = 1>
 __global__ __launch_bounds__(kThreads) void pack_narrow_kernel(PackArgs a, const Run* __restrict__ runs,
                                                                const int32_t* __restrict__ first_pos,
                                                                uint32_t n_tiles, int32_t parts)
@@ -739,7 +756,7 @@ __global__ __launch_bounds__(kThreads) void pack_narrow_kernel(PackArgs a, const
             if (kind[u] == kTileOneRun) {
                 const int64_t g0 = (int64_t)(tile0 + (uint32_t)u) * kNarrowSlots;
                 const uint8_t* from = a.src + (r[u].src + (g0 - r[u].dst)) * 4;
-                pv[u] = __builtin_nontemporal_load(reinterpret_cast<const vec16_unaligned*>(from) + tid);
+                pv[u] = load_source<TRAFFIC>(from + 16 * tid);
             }
         }
 #pragma unroll
@@ -753,8 +770,8 @@ __global__ __launch_bounds__(kThreads) void pack_narrow_kernel(PackArgs a, const
 #pragma unroll
         for (int u = 0; u < GROUP; ++u) {
             const int64_t g0 = (int64_t)(tile0 + (uint32_t)u) * kNarrowSlots;
-            if (kind[u] == kTileOneRun) narrow_uniform_payload(a, g0, &r[u], part, parts);
-            else if (kind[u] == kTilePadding) narrow_uniform_payload(a, g0, nullptr, part, parts);
+            if (kind[u] == kTileOneRun) narrow_uniform_payload<TRAFFIC>(a, g0, &r[u], part, parts);
+            else if (kind[u] == kTilePadding) narrow_uniform_payload<TRAFFIC>(a, g0, nullptr, part, parts);
         }
     }
     if (TABLE && part == 0) {
@@ -772,7 +789,7 @@ __global__ __launch_bounds__(kThreads) void pack_narrow_kernel(PackArgs a, const
         if (kind[u] != kTileGeneral) continue;
         const int64_t g0 = (int64_t)(tile0 + (uint32_t)u) * kNarrowSlots;
         if (table_in_use) __syncthreads();           // the tile before is done with the gathered runs
-        narrow_general_tile<E, FUSED, PAYLOAD, TABLE>(a, runs, tab, g0, min(g0 + kNarrowSlots, a.total_slots),
+        narrow_general_tile<E, FUSED, PAYLOAD, TABLE, TRAFFIC>(a, runs, tab, g0, min(g0 + kNarrowSlots, a.total_slots),
                                                       entry[u], entry[u + 1], part, parts);
         table_in_use = true;
     }
@@ -925,6 +942,48 @@ bload_status pack_check_args(const void* d_src, const int64_t* d_src_offsets, co
     return BLOAD_OK;
 }
 
+// How a call reads its source and writes its payload.
+//   - Packed tensor, source and table of 256 MB in all (the source taken as long as the packed tensor: what the host knows),
+//     4 KiB tiles: plain loads and stores.  Source and payload stay in the memory-side cache, where a consumer finds them.  Pack
+//     and reduction of 3001 sequences of 37 halfs, 86 MB, in turn 89 -> 68 us, 75 where each pack has another source; of 250
+//     sequences of 80 floats, 118 MB, 97 -> 85 and 86; 60 of them 41 -> 37 and 39; with the scan 127 -> 109 and 108.  Packs alone, the same
+//     source again and again: 50 -> 39, 52 -> 49, 11 and 13 us; another source each time 3 to 5 % slower.
+//   - Up to 300 MB: plain loads.  100 floats, 200 MB 82 -> 65 us, 37 halfs, 220 MB 111 -> 88, tokens, 220 MB 238 -> 210;
+//     sources from elsewhere 1 to 4 % slower.  Plain stores as well: 88, 127 and 266 us.
+//   - Larger ones pass by: 1.5 GB of 320-byte frames 595 us, 630 with plain loads, 660 with plain stores as well.
+// Slot tiles never store plainly: five streams of parts of lines (20-byte frames 47 us, 60).
+static PackTraffic pack_traffic(int64_t total_slots, int64_t total_bytes, bool wide)
+{
+    if (wide && 2 * total_bytes + 10 * total_slots <= ((int64_t)256 << 20)) return kPackPlain;
+    return total_bytes <= ((int64_t)300 << 20) ? kPackCached : kPackStream;
+}
+
+template <int TRAFFIC>
+static void pack_launch_wide(const PackArgs& a, const Run* runs, const int32_t* first_pos, uint32_t n_tiles, double inv_frame,
+                             int32_t writes_table, hipStream_t stream)
+{
+    hipLaunchKernelGGL(pack_wide_kernel<TRAFFIC>, dim3(n_tiles), dim3(kThreads), 0, stream, a, runs, first_pos, kWideTile, inv_frame,
+                       writes_table);
+}
+
+// One pass over slot tiles.
+template <int TRAFFIC>
+static void pack_launch_slots(const PackArgs& a, const Run* runs, const int32_t* first_pos, uint32_t n_tiles, int32_t parts,
+                              bool vectors_copied, hipStream_t stream)
+{
+    const dim3 grid(n_tiles * (uint32_t)parts), block(kThreads);
+    if (vectors_copied)
+        hipLaunchKernelGGL((pack_narrow_kernel<vec16, false, TRAFFIC>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
+    else if (a.frame_bytes == 4 && aligned_to(a.src, 4))
+        hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, true, TRAFFIC>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
+    else if (a.frame_bytes % 4 == 0 && aligned_to(a.src, 4))
+        hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, false, TRAFFIC>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
+    else if (a.frame_bytes % 2 == 0 && aligned_to(a.src, 2))
+        hipLaunchKernelGGL((pack_narrow_kernel<uint16_t, false, TRAFFIC>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
+    else
+        hipLaunchKernelGGL((pack_narrow_kernel<uint8_t, false, TRAFFIC>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
+}
+
 // Enqueue the two passes.  `ws` holds l.bytes bytes, 32-byte aligned or better.
 bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t* d_src_offsets,
                           const int32_t* d_lengths, const int32_t* d_order, const int32_t* d_block_of_seq,
@@ -962,11 +1021,13 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
                        l.tiles, tile_units, inv_unit, inv_t, runs, first_pos, l.table_tiles, first_pos_table);
     const dim3 block(kThreads);
     const uint32_t n_tiles = (uint32_t)l.tiles;
+    const PackTraffic traffic = pack_traffic(a.total_slots, a.total_slots * frame_bytes, l.wide);
     if (l.wide) {
-        hipLaunchKernelGGL(pack_wide_kernel, dim3(n_tiles), block, 0, stream, a, runs, first_pos, kWideTile, inv_unit,
-                           l.table_tiles == 0 ? 1 : 0);
+        const auto launch = traffic == kPackPlain ? pack_launch_wide<kPackPlain> : traffic == kPackCached ? pack_launch_wide<kPackCached>
+                                                                                                       : pack_launch_wide<kPackStream>;
+        launch(a, runs, first_pos, n_tiles, inv_unit, l.table_tiles == 0 ? 1 : 0, stream);
         if (l.table_tiles > 0)
-            hipLaunchKernelGGL((pack_narrow_kernel<uint8_t, false, false, true, kPassGroup>),
+            hipLaunchKernelGGL((pack_narrow_kernel<uint8_t, false, kPackStream, false, true, kPassGroup>),
                                dim3((uint32_t)ceil_div(l.table_tiles, kPassGroup)), block, 0, stream, a, runs,
                                first_pos_table, (uint32_t)l.table_tiles, 1);
         return launch_status();
@@ -992,25 +1053,20 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
     const bool once = l.tiles >= 1024 && l.tiles < 2048 && (vectors_copied || frame_bytes < 96);
     const int64_t wanted = once ? 1 : ceil_div(frame_bytes < 64 ? 1024 : 4096, l.tiles);
     const int32_t parts = (int32_t)(frame_bytes == 4 && aligned_to(d_src, 4) ? 1 : wanted < vectors ? wanted : vectors);
-    const dim3 grid((uint32_t)(l.tiles * parts));
-    if (vectors_copied) {
-        hipLaunchKernelGGL((pack_narrow_kernel<vec16, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
-    } else if (frame_bytes == 4 && aligned_to(d_src, 4)) {
-        if (a.total_slots >= kTablePassFromSlots) {
-            const dim3 groups((uint32_t)ceil_div(l.tiles, kPassGroup));
-            hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, true, true, false, kPassGroup>), groups, block, 0, stream,
-                               a, runs, first_pos, n_tiles, parts);
-            hipLaunchKernelGGL((pack_narrow_kernel<uint8_t, false, false, true, kPassGroup>), groups, block, 0, stream,
-                               a, runs, first_pos, n_tiles, parts);
-        } else {
-            hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, true>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
-        }
-    } else if (frame_bytes % 4 == 0 && aligned_to(d_src, 4)) {
-        hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
-    } else if (frame_bytes % 2 == 0 && aligned_to(d_src, 2)) {
-        hipLaunchKernelGGL((pack_narrow_kernel<uint16_t, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
+    if (frame_bytes == 4 && aligned_to(d_src, 4) && a.total_slots >= kTablePassFromSlots) {
+        const dim3 groups((uint32_t)ceil_div(l.tiles, kPassGroup));
+        if (traffic == kPackCached)
+            hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, true, kPackCached, true, false, kPassGroup>), groups, block, 0, stream, a,
+                               runs, first_pos, n_tiles, parts);
+        else
+            hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, true, kPackStream, true, false, kPassGroup>), groups, block, 0, stream, a,
+                               runs, first_pos, n_tiles, parts);
+        hipLaunchKernelGGL((pack_narrow_kernel<uint8_t, false, kPackStream, false, true, kPassGroup>), groups, block, 0, stream, a,
+                           runs, first_pos, n_tiles, parts);
+    } else if (traffic == kPackCached) {
+        pack_launch_slots<kPackCached>(a, runs, first_pos, n_tiles, parts, vectors_copied, stream);
     } else {
-        hipLaunchKernelGGL((pack_narrow_kernel<uint8_t, false>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
+        pack_launch_slots<kPackStream>(a, runs, first_pos, n_tiles, parts, vectors_copied, stream);
     }
     return launch_status();
 }
