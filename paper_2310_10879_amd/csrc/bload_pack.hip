@@ -64,6 +64,34 @@ struct PackArgs {
     uint8_t* valid;
 };
 
+// The plan as the entry points get it.
+struct PlanTables {
+    const int64_t* src_offsets;
+    const int32_t* lengths;
+    const int32_t* order;
+    const int32_t* block_of_seq;
+    const int32_t* offset_of_seq;
+    const int32_t* block_first;
+};
+
+// The run of shuffled position p, from the plan's tables.
+__device__ __forceinline__ Run run_at_position(const PlanTables& t, int64_t p, int32_t n_seq, int64_t num_blocks, int64_t t_blk)
+{
+    Run r{kNoRun, 0, 0, -1, -1, 0};
+    const uint32_t i = (uint32_t)t.order[p];
+    if (i < (uint32_t)n_seq) {
+        const int64_t b = t.block_of_seq[i];
+        if (b >= 0 && b < num_blocks) {
+            r.dst = b * t_blk + t.offset_of_seq[i];
+            r.src = t.src_offsets[i];
+            r.len = t.lengths[i];
+            r.seq = (int32_t)i;
+            r.block = (int32_t)b;
+        }
+    }
+    return r;
+}
+
 // The sequences ("runs") that overlap one tile, in shuffled order.  Slots are
 // numbered globally (block * T_blk + slot in block); dst is relative to the
 // tile's first slot and is negative for a run that starts before the tile.
@@ -255,45 +283,103 @@ constexpr int kTableSlots = 1024;                   // slots per workgroup of th
 // starts at slot 0, so there is one); it searches the plan's own tables, so the two
 // halves do not depend on each other.
 __global__ __launch_bounds__(kThreads) void pack_prepare_kernel(
-    const int64_t* __restrict__ src_offsets, const int32_t* __restrict__ lengths,
-    const int32_t* __restrict__ order, const int32_t* __restrict__ block_of_seq,
-    const int32_t* __restrict__ offset_of_seq, const int32_t* __restrict__ block_first,
-    int32_t n_seq, int64_t num_blocks, int64_t t_blk, int64_t frame_bytes, int64_t n_tiles,
+    PlanTables t, int32_t n_seq, int64_t num_blocks, int64_t t_blk, int64_t frame_bytes, int64_t n_tiles,
     int32_t tile_bytes, double inv_frame_bytes, double inv_t_blk, Run* __restrict__ runs,
     int32_t* __restrict__ first_pos, int64_t n_table_tiles, int32_t* __restrict__ first_pos_table)
 {
     const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (idx < n_seq) {
-        Run r{kNoRun, 0, 0, -1, -1, 0};
-        const uint32_t i = (uint32_t)order[idx];
-        if (i < (uint32_t)n_seq) {
-            const int64_t b = block_of_seq[i];
-            if (b >= 0 && b < num_blocks) {
-                r.dst = b * t_blk + offset_of_seq[i];
-                r.src = src_offsets[i];
-                r.len = lengths[i];
-                r.seq = (int32_t)i;
-                r.block = (int32_t)b;
-            }
-        }
-        runs[idx] = r;
-    }
+    if (idx < n_seq) runs[idx] = run_at_position(t, idx, n_seq, num_blocks, t_blk);
     // the last shuffled position of slot gs_lo's block whose sequence starts at or before gs_lo
     auto entry_of = [&](int64_t gs_lo) {
         const int64_t b0 = floor_div(gs_lo, t_blk, inv_t_blk);
         const int32_t rel = (int32_t)(gs_lo - b0 * t_blk);
-        int32_t p = min(max(block_first[b0], 0), n_seq);
-        int32_t above = min(max(block_first[b0 + 1], p), n_seq);
+        int32_t p = min(max(t.block_first[b0], 0), n_seq);
+        int32_t above = min(max(t.block_first[b0 + 1], p), n_seq);
         while (above - p > 1) {
             const int32_t mid = p + ((above - p) >> 1);
-            const uint32_t i = (uint32_t)order[mid];
-            if (i < (uint32_t)n_seq && offset_of_seq[i] <= rel) p = mid; else above = mid;
+            const uint32_t i = (uint32_t)t.order[mid];
+            if (i < (uint32_t)n_seq && t.offset_of_seq[i] <= rel) p = mid; else above = mid;
         }
         return p;
     };
     if (idx < n_tiles) first_pos[idx] = entry_of(floor_div(idx * tile_bytes, frame_bytes, inv_frame_bytes));
     // tiles of kTableSlots slots, for the pass that writes the start table of wide frames
     if (idx < n_table_tiles) first_pos_table[idx] = entry_of(idx * kTableSlots);
+}
+
+// The runs of a 4 KiB tile, looked up side by side.
+struct WideRuns {
+    int64_t lo[kWideRuns + 1];     // first packed byte of the run; INT64_MAX: no run
+    int64_t hi[kWideRuns];         // one past its last packed byte
+    int64_t src[kWideRuns];        // source byte that goes to `lo`
+    int32_t seq[kWideRuns];
+};
+
+// Packed bytes [D0, D1) of a tile whose runs, `n` at most and in destination order, are known, and the start-table entries of
+// slots [m_lo, m_hi) if `table_wave`.  Every thread finds the run of its own 16 bytes.
+template <int TRAFFIC>
+__device__ __forceinline__ void write_wide_tile(const PackArgs& a, const WideRuns& r, int32_t n, int64_t D0, int64_t D1,
+                                                int64_t m_lo, int64_t m_hi, bool table_wave, double inv_frame_bytes)
+{
+    const int64_t F = a.frame_bytes;
+    const int tid = (int)threadIdx.x;
+    // last gathered run that starts at or before packed byte x, -1 if none
+    // (a binary search over the first `span` entries, span = a power of two that covers them)
+    int span = 1;
+    while (span < min(n, kWideRuns)) span <<= 1;
+    auto run_at = [&](int64_t x) {
+        int k = -1;
+        for (int step = span >> 1; step >= 1; step >>= 1)
+            if (r.lo[k + step] <= x) k += step;
+        if (r.lo[k + 1] <= x) ++k;
+        return k;
+    };
+
+    for (int64_t x0 = D0 + 16 * (int64_t)tid; x0 < D1; x0 += 16 * (int64_t)kThreads) {
+        int k = run_at(x0);
+        const int64_t next_lo = r.lo[k + 1];
+        const int64_t lo = k >= 0 ? r.lo[k] : 0, hi = k >= 0 ? r.hi[k] : 0;
+        vec16* dst = reinterpret_cast<vec16*>(a.packed + x0);
+        if (x0 + 16 <= D1 && x0 + 16 <= hi) {                           // inside one run
+            const uint8_t* from = a.src + r.src[k] + (x0 - lo);
+            store_packed<TRAFFIC>(dst, load_source<TRAFFIC>(from));
+        } else if (x0 + 16 <= D1 && x0 >= hi && x0 + 16 <= next_lo) {   // inside a block's zero tail
+            const vec16 z = {0u, 0u, 0u, 0u};
+            store_packed<TRAFFIC>(dst, z);
+        } else {
+            // a border inside: byte by byte, all of them asked for before the first is stored
+            uint32_t bytes[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const int64_t x = x0 + j;
+                while (r.lo[k + 1] <= x) ++k;
+                bytes[j] = 0;
+                if (k >= 0 && x < r.hi[k] && x < D1) bytes[j] = a.src[r.src[k] + (x - r.lo[k])];
+            }
+            if (x0 + 16 <= D1) {
+                vec16 v;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) v[w] = bytes[4 * w] | bytes[4 * w + 1] << 8 | bytes[4 * w + 2] << 16 | bytes[4 * w + 3] << 24;
+                store_packed<TRAFFIC>(dst, v);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 16; ++j)
+                    if (x0 + j < D1) a.packed[x0 + j] = (uint8_t)bytes[j];
+            }
+        }
+    }
+    if (table_wave) {
+        for (int64_t slot = m_lo + lane_id(); slot < m_hi; slot += kWave) {
+            const int64_t x = slot * F;
+            const int k = run_at(x);
+            int32_t seq = -1, fid = -1;
+            if (k >= 0 && x < r.hi[k]) {
+                seq = r.seq[k];
+                fid = (int32_t)(slot - floor_div(r.lo[k], F, inv_frame_bytes));
+            }
+            store_slot<TRAFFIC>(a, slot, seq, fid);
+        }
+    }
 }
 
 // Pass 2: the copy.  The run table and the tiles' entries come as separate
@@ -393,10 +479,7 @@ __global__ __launch_bounds__(kThreads) void pack_wide_kernel(
     // k-th shuffled position from p on), so that the cost does not grow with their number, and
     // every thread then finds the run of its own 16 bytes.  A frame of kWideMinFrame bytes or
     // more puts at most kWideTile / kWideMinFrame + 2 runs into a tile.
-    __shared__ int64_t s_run_lo[kWideRuns + 1];     // first packed byte of the run; INT64_MAX: no run
-    __shared__ int64_t s_run_hi[kWideRuns];         // one past its last packed byte
-    __shared__ int64_t s_run_src[kWideRuns];        // source byte that goes to s_run_lo
-    __shared__ int32_t s_run_seq[kWideRuns];
+    __shared__ WideRuns runs_here;
     const int tid = (int)threadIdx.x;
     if (tid <= kWideRuns) {
         int64_t lo = INT64_MAX, hi = 0, from = 0;
@@ -411,61 +494,71 @@ __global__ __launch_bounds__(kThreads) void pack_wide_kernel(
                 seq = r.seq;
             }
         }
-        s_run_lo[tid] = lo;
+        runs_here.lo[tid] = lo;
         if (tid < kWideRuns) {
-            s_run_hi[tid] = hi;
-            s_run_src[tid] = from;
-            s_run_seq[tid] = seq;
+            runs_here.hi[tid] = hi;
+            runs_here.src[tid] = from;
+            runs_here.seq[tid] = seq;
         }
     }
     __syncthreads();
-    // last gathered run that starts at or before packed byte x, -1 if none
-    // (a binary search over the first `span` entries, span = a power of two that covers them)
-    int span = 1;
-    while (span < min(p_next - p + 2, kWideRuns)) span <<= 1;
-    auto run_at = [&](int64_t x) {
-        int k = -1;
-        for (int step = span >> 1; step >= 1; step >>= 1)
-            if (s_run_lo[k + step] <= x) k += step;
-        if (s_run_lo[k + 1] <= x) ++k;
-        return k;
-    };
-
-    for (int64_t x0 = D0 + 16 * (int64_t)tid; x0 < D1; x0 += 16 * (int64_t)kThreads) {
-        int k = run_at(x0);
-        const int64_t next_lo = s_run_lo[k + 1];
-        const int64_t lo = k >= 0 ? s_run_lo[k] : 0, hi = k >= 0 ? s_run_hi[k] : 0;
-        vec16* dst = reinterpret_cast<vec16*>(a.packed + x0);
-        if (x0 + 16 <= D1 && x0 + 16 <= hi) {                           // inside one run
-            const uint8_t* from = a.src + s_run_src[k] + (x0 - lo);
-            store_packed<TRAFFIC>(dst, load_source<TRAFFIC>(from));
-        } else if (x0 + 16 <= D1 && x0 >= hi && x0 + 16 <= next_lo) {   // inside a block's zero tail
-            const vec16 z = {0u, 0u, 0u, 0u};
-            store_packed<TRAFFIC>(dst, z);
-        } else {                                                        // a border inside: byte by byte
-            for (int j = 0; j < 16 && x0 + j < D1; ++j) {
-                const int64_t x = x0 + j;
-                while (s_run_lo[k + 1] <= x) ++k;
-                uint8_t v = 0;
-                if (k >= 0 && x < s_run_hi[k]) v = a.src[s_run_src[k] + (x - s_run_lo[k])];
-                a.packed[x] = v;
-            }
-        }
-    }
-    if (table_wave) {
-        for (int64_t slot = m_lo + lane_id(); slot < m_hi; slot += kWave) {
-            const int64_t x = slot * F;
-            const int k = run_at(x);
-            int32_t seq = -1, fid = -1;
-            if (k >= 0 && x < s_run_hi[k]) {
-                seq = s_run_seq[k];
-                fid = (int32_t)(slot - floor_div(s_run_lo[k], F, inv_frame_bytes));
-            }
-            store_slot<TRAFFIC>(a, slot, seq, fid);
-        }
-    }
+    write_wide_tile<TRAFFIC>(a, runs_here, p_next - p + 2, D0, D1, m_lo, m_hi, table_wave, inv_frame_bytes);
 }
 
+// The same in one launch, for calls of few tiles: every workgroup looks up the runs of its tile in the plan's tables by itself, a
+// thread to a shuffled position of the blocks that it touches.  Bound by latency: four look-ups one after the other here, against
+// three and a launch there.
+template <int TRAFFIC>
+__global__ __launch_bounds__(kThreads) void pack_direct_kernel(PackArgs a, PlanTables t, int64_t num_blocks, double inv_frame_bytes,
+                                                               double inv_t_blk)
+{
+    const int64_t F = a.frame_bytes, T = a.t_blk, total_bytes = a.total_slots * F;
+    const uint32_t tile = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int64_t D0 = (int64_t)tile * kWideTile, D1 = min(D0 + kWideTile, total_bytes);
+    const int64_t gs_lo = floor_div(D0, F, inv_frame_bytes);              // first slot touched
+    const int64_t gs_hi = floor_div(D1 + F - 1, F, inv_frame_bytes);      // one past the last
+    const int64_t m_lo = gs_lo + ((gs_lo * F < D0) ? 1 : 0), m_hi = min(gs_hi, a.total_slots);
+    const int64_t b0 = floor_div(gs_lo, T, inv_t_blk), b1 = floor_div(m_hi - 1, T, inv_t_blk);
+    int32_t first = min(max(t.block_first[b0], 0), a.n_seq);
+    const int32_t last = min(max(t.block_first[b1 + 1], first), a.n_seq);
+
+    __shared__ WideRuns runs_here;
+    __shared__ int32_t s_found[kThreads / kWave];
+    const int tid = (int)threadIdx.x;
+    if (tid <= kWideRuns) runs_here.lo[tid] = INT64_MAX;
+    // of many positions, the last of 256 evenly spaced ones that starts at or before the tile
+    if (last - first > kThreads) {
+        const int32_t step = (last - first + kThreads - 1) / kThreads;
+        const int32_t p = first + tid * step;
+        const int before = __syncthreads_count(p < last && run_at_position(t, p, a.n_seq, num_blocks, T).dst <= gs_lo);
+        first += max(before - 1, 0) * step;
+    }
+    int32_t n = 0;
+    for (int32_t p0 = first; p0 < last; p0 += kThreads) {
+        Run r{kNoRun, 0, 0, -1, -1, 0};
+        if (p0 + tid < last) r = run_at_position(t, p0 + tid, a.n_seq, num_blocks, T);
+        const bool here = r.dst < gs_hi && r.dst + r.len > gs_lo;
+        const uint64_t vote = __ballot(here);
+        const int behind = __syncthreads_or(r.dst >= gs_hi);       // (a barrier behind the marks, and the counts of the round before)
+        if (lane_id() == 0) s_found[wave_id()] = (int32_t)__popcll(vote);
+        __syncthreads();
+        int32_t at = n + (int32_t)__popcll(vote & ((1ull << lane_id()) - 1ull));
+#pragma unroll
+        for (int w = 0; w < kThreads / kWave; ++w) {
+            at += w < wave_id() ? s_found[w] : 0;
+            n += s_found[w];
+        }
+        if (here && at < kWideRuns) {
+            runs_here.lo[at] = r.dst * F;
+            runs_here.hi[at] = (r.dst + r.len) * F;
+            runs_here.src[at] = r.src * F;
+            runs_here.seq[at] = r.seq;
+        }
+        if (behind) break;
+    }
+    __syncthreads();
+    write_wide_tile<TRAFFIC>(a, runs_here, n + 1, D0, D1, m_lo, m_hi, wave_id() == 0, inv_frame_bytes);
+}
 // ----------------------------------------------------------------- narrow
 
 constexpr int kNarrowSlots = kTableSlots;            // slots per workgroup
@@ -893,6 +986,9 @@ constexpr int64_t kTablePassFromSlots = (int64_t)1 << 21;
 // 0.8-1.3 * 10^9 token slots of four length mixes: two tiles 1-3.5 % faster than one, four between 3 %
 // slower and 2 % faster, eight 40 % slower.
 constexpr int kPassGroup = 2;
+// Up to so many workgroups, every one looks up its tile's runs itself, in one launch (pack_direct_kernel): 64 clips of 3 KB frames 11.4 -> 8.2
+// us, 3000 sequences of two 700-byte frames 13.4 -> 9.2, 18 MB of 320-byte frames 23.5 -> 21; 8192 tiles: 19.4 -> 20.4.
+constexpr int64_t kDirectTiles = 4096;
 
 // Sizes the caller cannot know in advance (which tile shape the lengths will choose) are
 // taken at their larger value when `for_query`.
@@ -1009,6 +1105,12 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
     a.reset = d_reset;
     a.valid = d_valid;
 
+    const PlanTables t{d_src_offsets, d_lengths, d_order, d_block_of_seq, d_offset_of_seq, d_block_first};
+    if (l.wide && l.tiles <= kDirectTiles) {
+        hipLaunchKernelGGL(pack_direct_kernel<kPackPlain>, dim3((uint32_t)l.tiles), dim3(kThreads), 0, stream, a, t, num_blocks,
+                           1.0 / (double)frame_bytes, 1.0 / (double)t_blk);
+        return launch_status();
+    }
     // pass 1 (both tile shapes): the run table, and where each tile starts in it.  The
     // narrow tiles are 1024 slots, which the kernel takes as "1024 bytes of 1-byte frames".
     const int64_t unit_bytes = l.wide ? frame_bytes : 1;
@@ -1016,8 +1118,7 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
     const double inv_unit = 1.0 / (double)unit_bytes, inv_t = 1.0 / (double)t_blk;
     const int64_t prepare_threads = l.tiles > n_seq ? l.tiles : n_seq;       // table_tiles <= tiles
     hipLaunchKernelGGL(pack_prepare_kernel, dim3((uint32_t)ceil_div(prepare_threads, kThreads)),
-                       dim3(kThreads), 0, stream, d_src_offsets, d_lengths, d_order, d_block_of_seq,
-                       d_offset_of_seq, d_block_first, (int32_t)n_seq, num_blocks, (int64_t)t_blk, unit_bytes,
+                       dim3(kThreads), 0, stream, t, (int32_t)n_seq, num_blocks, (int64_t)t_blk, unit_bytes,
                        l.tiles, tile_units, inv_unit, inv_t, runs, first_pos, l.table_tiles, first_pos_table);
     const dim3 block(kThreads);
     const uint32_t n_tiles = (uint32_t)l.tiles;
