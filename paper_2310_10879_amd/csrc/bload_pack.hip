@@ -12,6 +12,8 @@
 // read per sequence instead of a chain of look-ups through five tables -- and
 // finds, for every tile, where in that table its runs begin.
 //
+// Calls of few tiles do without that pass: their workgroups look the runs up by themselves (pack_direct_kernel).
+//
 // Two tile shapes (takes_wide_tiles chooses, from the frame size and the bytes
 // per sequence):
 //   wide   a tile is 4 KiB of the packed tensor, one 16-byte vector per thread;
@@ -32,6 +34,7 @@
 #include <limits.h>
 
 #include <mutex>
+#include <type_traits>
 
 namespace bload {
 
@@ -505,28 +508,20 @@ __global__ __launch_bounds__(kThreads) void pack_wide_kernel(
     write_wide_tile<TRAFFIC>(a, runs_here, p_next - p + 2, D0, D1, m_lo, m_hi, table_wave, inv_frame_bytes);
 }
 
-// The same in one launch, for calls of few tiles: every workgroup looks up the runs of its tile in the plan's tables by itself, a
-// thread to a shuffled position of the blocks that it touches.  Bound by latency: four look-ups one after the other here, against
-// three and a launch there.
-template <int TRAFFIC>
-__global__ __launch_bounds__(kThreads) void pack_direct_kernel(PackArgs a, PlanTables t, int64_t num_blocks, double inv_frame_bytes,
-                                                               double inv_t_blk)
+// The runs that overlap slots [gs_lo, gs_hi), the last of which that there is lies at or before `slot_hi` - 1, from the plan's tables, a
+// thread to a shuffled position of the blocks that the slots touch: put(index, run), in destination order.  Returns how many there
+// are.  Called by the whole workgroup; what it put is there for all behind a barrier.
+template <typename Put>
+__device__ __forceinline__ int32_t find_runs(const PackArgs& a, const PlanTables& t, int64_t num_blocks, double inv_t_blk, int64_t gs_lo,
+                                             int64_t slot_hi, int64_t gs_hi, Put put)
 {
-    const int64_t F = a.frame_bytes, T = a.t_blk, total_bytes = a.total_slots * F;
-    const uint32_t tile = xcd_contiguous(blockIdx.x, gridDim.x);
-    const int64_t D0 = (int64_t)tile * kWideTile, D1 = min(D0 + kWideTile, total_bytes);
-    const int64_t gs_lo = floor_div(D0, F, inv_frame_bytes);              // first slot touched
-    const int64_t gs_hi = floor_div(D1 + F - 1, F, inv_frame_bytes);      // one past the last
-    const int64_t m_lo = gs_lo + ((gs_lo * F < D0) ? 1 : 0), m_hi = min(gs_hi, a.total_slots);
-    const int64_t b0 = floor_div(gs_lo, T, inv_t_blk), b1 = floor_div(m_hi - 1, T, inv_t_blk);
+    __shared__ int32_t s_found[kThreads / kWave];
+    const int64_t T = a.t_blk;
+    const int tid = (int)threadIdx.x;
+    const int64_t b0 = floor_div(gs_lo, T, inv_t_blk), b1 = floor_div(slot_hi - 1, T, inv_t_blk);
     int32_t first = min(max(t.block_first[b0], 0), a.n_seq);
     const int32_t last = min(max(t.block_first[b1 + 1], first), a.n_seq);
-
-    __shared__ WideRuns runs_here;
-    __shared__ int32_t s_found[kThreads / kWave];
-    const int tid = (int)threadIdx.x;
-    if (tid <= kWideRuns) runs_here.lo[tid] = INT64_MAX;
-    // of many positions, the last of 256 evenly spaced ones that starts at or before the tile
+    // of many positions, the last of 256 evenly spaced ones that starts at or before the slots
     if (last - first > kThreads) {
         const int32_t step = (last - first + kThreads - 1) / kThreads;
         const int32_t p = first + tid * step;
@@ -539,7 +534,7 @@ __global__ __launch_bounds__(kThreads) void pack_direct_kernel(PackArgs a, PlanT
         if (p0 + tid < last) r = run_at_position(t, p0 + tid, a.n_seq, num_blocks, T);
         const bool here = r.dst < gs_hi && r.dst + r.len > gs_lo;
         const uint64_t vote = __ballot(here);
-        const int behind = __syncthreads_or(r.dst >= gs_hi);       // (a barrier behind the marks, and the counts of the round before)
+        const int behind = __syncthreads_or(r.dst >= gs_hi);       // (also a barrier behind the counts of the round before)
         if (lane_id() == 0) s_found[wave_id()] = (int32_t)__popcll(vote);
         __syncthreads();
         int32_t at = n + (int32_t)__popcll(vote & ((1ull << lane_id()) - 1ull));
@@ -548,14 +543,36 @@ __global__ __launch_bounds__(kThreads) void pack_direct_kernel(PackArgs a, PlanT
             at += w < wave_id() ? s_found[w] : 0;
             n += s_found[w];
         }
-        if (here && at < kWideRuns) {
+        if (here) put(at, r);
+        if (behind) break;
+    }
+    return n;
+}
+
+// The same in one launch, for calls of few tiles: every workgroup looks up the runs of its tile in the plan's tables by itself, a
+// thread to a shuffled position of the blocks that it touches.  Bound by latency: four look-ups one after the other here, against
+// three and a launch there.
+template <int TRAFFIC>
+__global__ __launch_bounds__(kThreads) void pack_direct_kernel(PackArgs a, PlanTables t, int64_t num_blocks, double inv_frame_bytes,
+                                                               double inv_t_blk)
+{
+    const int64_t F = a.frame_bytes, total_bytes = a.total_slots * F;
+    const uint32_t tile = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int64_t D0 = (int64_t)tile * kWideTile, D1 = min(D0 + kWideTile, total_bytes);
+    const int64_t gs_lo = floor_div(D0, F, inv_frame_bytes);              // first slot touched
+    const int64_t gs_hi = floor_div(D1 + F - 1, F, inv_frame_bytes);      // one past the last
+    const int64_t m_lo = gs_lo + ((gs_lo * F < D0) ? 1 : 0), m_hi = min(gs_hi, a.total_slots);
+    __shared__ WideRuns runs_here;
+    const int tid = (int)threadIdx.x;
+    if (tid <= kWideRuns) runs_here.lo[tid] = INT64_MAX;
+    const int32_t n = find_runs(a, t, num_blocks, inv_t_blk, gs_lo, m_hi, gs_hi, [&](int32_t at, const Run& r) {
+        if (at < kWideRuns) {
             runs_here.lo[at] = r.dst * F;
             runs_here.hi[at] = (r.dst + r.len) * F;
             runs_here.src[at] = r.src * F;
             runs_here.seq[at] = r.seq;
         }
-        if (behind) break;
-    }
+    });
     __syncthreads();
     write_wide_tile<TRAFFIC>(a, runs_here, n + 1, D0, D1, m_lo, m_hi, wave_id() == 0, inv_frame_bytes);
 }
@@ -656,19 +673,14 @@ struct Assembled<vec16> {
     __device__ __forceinline__ vec16 get(int) const { return vec; }
 };
 
-// One tile of kNarrowSlots slots (or the shorter last one) that needs its runs looked up: the
-// candidates `first` .. `last` of the run table are gathered into `tab` first.  Called by the
-// whole workgroup.
+// One tile of kNarrowSlots slots (or the shorter last one) whose `n` runs are in `tab`.  Called by the whole workgroup.
 template <typename E, bool FUSED, bool PAYLOAD, bool TABLE, int TRAFFIC>
-__device__ __forceinline__ void narrow_general_tile(const PackArgs& a, const Run* __restrict__ runs,
-                                                    RunTable<kNarrowMaxRuns>& tab, int64_t g0, int64_t g1,
-                                                    int32_t first, int32_t last, int32_t part, int32_t parts)
+__device__ __forceinline__ void narrow_write_tile(const PackArgs& a, const RunTable<kNarrowMaxRuns>& tab, int n, int64_t g0, int64_t g1,
+                                                  int32_t part, int32_t parts)
 {
     const int tid = (int)threadIdx.x;
     const int nslot = (int)(g1 - g0);
-    const int n = gather_runs(runs, a.n_seq, first, last, g0, g1, tab);
     const bool long_runs = (int64_t)(n - 1) * 4096 <= nslot * a.frame_bytes;      // borders four waves of vectors apart
-
     // start table (and, FUSED, the payload): 4 consecutive slots per lane -> 16-byte / 4-byte stores
     for (int q = tid; (TABLE || FUSED) && part == 0 && 4 * q < nslot; q += kThreads) {
         const int32_t s0 = 4 * q;
@@ -882,10 +894,33 @@ __global__ __launch_bounds__(kThreads) void pack_narrow_kernel(PackArgs a, const
         if (kind[u] != kTileGeneral) continue;
         const int64_t g0 = (int64_t)(tile0 + (uint32_t)u) * kNarrowSlots;
         if (table_in_use) __syncthreads();           // the tile before is done with the gathered runs
-        narrow_general_tile<E, FUSED, PAYLOAD, TABLE, TRAFFIC>(a, runs, tab, g0, min(g0 + kNarrowSlots, a.total_slots),
-                                                      entry[u], entry[u + 1], part, parts);
+        const int64_t g1 = min(g0 + kNarrowSlots, a.total_slots);
+        const int n = gather_runs(runs, a.n_seq, entry[u], entry[u + 1], g0, g1, tab);
+        narrow_write_tile<E, FUSED, PAYLOAD, TABLE, TRAFFIC>(a, tab, n, g0, g1, part, parts);
         table_in_use = true;
     }
+}
+
+// Slot tiles in one launch, like pack_direct_kernel.
+template <typename E, bool FUSED>
+__global__ __launch_bounds__(kThreads) void pack_narrow_direct_kernel(PackArgs a, PlanTables t, int64_t num_blocks, double inv_t_blk,
+                                                                      int32_t parts)
+{
+    __shared__ RunTable<kNarrowMaxRuns> tab;
+    const uint32_t unit = xcd_contiguous(blockIdx.x, gridDim.x), tile = unit / (uint32_t)parts;
+    const int64_t g0 = (int64_t)tile * kNarrowSlots, g1 = min(g0 + kNarrowSlots, a.total_slots);
+    const int32_t n = find_runs(a, t, num_blocks, inv_t_blk, g0, g1, g1, [&](int32_t at, const Run& r) {
+        if (at < kNarrowMaxRuns) {
+            tab.src[at] = r.src;
+            tab.dst[at] = (int32_t)(r.dst - g0);
+            tab.end[at] = (int16_t)min(max(r.dst - g0 + r.len, (int64_t)0), (int64_t)kNarrowMaxRuns);
+            tab.seq[at] = r.seq;
+        }
+    });
+    const int kept = min(n, kNarrowMaxRuns);
+    if (threadIdx.x == 0) tab.dst[kept] = INT_MAX;
+    __syncthreads();
+    narrow_write_tile<E, FUSED, true, true, kPackCached>(a, tab, kept, g0, g1, (int32_t)(unit - tile * (uint32_t)parts), parts);
 }
 
 // ------------------------------------------------------------------ check
@@ -987,7 +1022,10 @@ constexpr int64_t kTablePassFromSlots = (int64_t)1 << 21;
 // slower and 2 % faster, eight 40 % slower.
 constexpr int kPassGroup = 2;
 // Up to so many workgroups, every one looks up its tile's runs itself, in one launch (pack_direct_kernel): 64 clips of 3 KB frames 11.4 -> 8.2
-// us, 3000 sequences of two 700-byte frames 13.4 -> 9.2, 18 MB of 320-byte frames 23.5 -> 21; 8192 tiles: 19.4 -> 20.4.
+// us, 3000 sequences of two 700-byte frames 13.4 -> 9.2, 18 MB of 320-byte frames 23.5 -> 21; 8192 tiles: 19.4 -> 20.4.  Slot tiles:
+// 300 sequences of tokens 10.7 -> 8.0, 400 of 63-byte frames 22.5 -> 16.2, 4 MB of 40-byte frames 14.8 -> 11.9, 3000 full ones of 60
+// bytes 64 -> 62; but not tiles of more than 256 sequences that several workgroups share, each of which would look them all up
+// (20000 sequences of three 64-byte frames in blocks of 6000: 12.3 us, 15.3).
 constexpr int64_t kDirectTiles = 4096;
 
 // Sizes the caller cannot know in advance (which tile shape the lengths will choose) are
@@ -1062,22 +1100,26 @@ static void pack_launch_wide(const PackArgs& a, const Run* runs, const int32_t* 
                        writes_table);
 }
 
+// The widest elements that divide the frame and that the source is aligned to: f(element, whether payload and table share a loop).
+template <typename F>
+static void with_element(const PackArgs& a, F f)
+{
+    if (a.frame_bytes % 16 == 0 && aligned_to(a.src, 16)) f(vec16{}, std::false_type());
+    else if (a.frame_bytes == 4 && aligned_to(a.src, 4)) f(uint32_t{}, std::true_type());
+    else if (a.frame_bytes % 4 == 0 && aligned_to(a.src, 4)) f(uint32_t{}, std::false_type());
+    else if (a.frame_bytes % 2 == 0 && aligned_to(a.src, 2)) f(uint16_t{}, std::false_type());
+    else f(uint8_t{}, std::false_type());
+}
+
 // One pass over slot tiles.
 template <int TRAFFIC>
 static void pack_launch_slots(const PackArgs& a, const Run* runs, const int32_t* first_pos, uint32_t n_tiles, int32_t parts,
-                              bool vectors_copied, hipStream_t stream)
+                              hipStream_t stream)
 {
-    const dim3 grid(n_tiles * (uint32_t)parts), block(kThreads);
-    if (vectors_copied)
-        hipLaunchKernelGGL((pack_narrow_kernel<vec16, false, TRAFFIC>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
-    else if (a.frame_bytes == 4 && aligned_to(a.src, 4))
-        hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, true, TRAFFIC>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
-    else if (a.frame_bytes % 4 == 0 && aligned_to(a.src, 4))
-        hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, false, TRAFFIC>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
-    else if (a.frame_bytes % 2 == 0 && aligned_to(a.src, 2))
-        hipLaunchKernelGGL((pack_narrow_kernel<uint16_t, false, TRAFFIC>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
-    else
-        hipLaunchKernelGGL((pack_narrow_kernel<uint8_t, false, TRAFFIC>), grid, block, 0, stream, a, runs, first_pos, n_tiles, parts);
+    with_element(a, [&](auto element, auto fused) {
+        hipLaunchKernelGGL((pack_narrow_kernel<decltype(element), decltype(fused)::value, TRAFFIC>), dim3(n_tiles * (uint32_t)parts),
+                           dim3(kThreads), 0, stream, a, runs, first_pos, n_tiles, parts);
+    });
 }
 
 // Enqueue the two passes.  `ws` holds l.bytes bytes, 32-byte aligned or better.
@@ -1105,10 +1147,35 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
     a.reset = d_reset;
     a.valid = d_valid;
 
+    // A tile is 1024 frames, one workgroup's work: where that leaves compute units idle, several workgroups share
+    // a tile, towards 1024 of them, or 4096 from 64 bytes on, where a tile is 64 KiB and more; never more than
+    // one per vector of a lane.  Short sequences, before and after: 8 tiles of 62 bytes 37 -> 12 us, 59 tiles
+    // of 104 bytes 38 -> 12, 209 of 68 bytes 27 -> 14, 209 of 400 bytes 90 -> 30, 859 of 400 bytes 135 -> 101.
+    // Towards 2048 under 64 bytes: 1055 tiles of 10 bytes 19 -> 21 us, of 48 bytes 25 -> 29.  1024 to 2047 tiles
+    // of the large frames fill the card once by themselves, and a share each would be a second look at every tile's
+    // runs for nothing: whole and in shares, 1059 of 64 bytes 27.5 and 29.7 us, of 128 bytes 45.3 and 46.9, 1399
+    // of 400 bytes 220 and 234, 1199 of 68 bytes 36.0 and 38.5.  From 2048 on some tiles would run alone after the
+    // others: 2099 of 64 bytes 54 and 49, of 128 bytes 95 and 85, of 256 bytes 245 and 226 with two shares.
+    // Frames from 96 bytes on that are put together from elements, a load each, gain there too: 1556 tiles of
+    // 104 bytes 52 and 47 us, of 200 bytes 88 and 75.
+    const int64_t vectors = ceil_div(frame_bytes, 4);               // 1024 slots / 256 lanes / 16 bytes
+    const bool vectors_copied = frame_bytes % 16 == 0 && aligned_to(d_src, 16);
+    const bool once = l.tiles >= 1024 && l.tiles < 2048 && (vectors_copied || frame_bytes < 96);
+    const int64_t wanted = once ? 1 : ceil_div(frame_bytes < 64 ? 1024 : 4096, l.tiles);
+    const int32_t parts = (int32_t)(frame_bytes == 4 && aligned_to(d_src, 4) ? 1 : wanted < vectors ? wanted : vectors);
+    const bool two_passes = frame_bytes == 4 && aligned_to(d_src, 4) && a.total_slots >= kTablePassFromSlots;
+
     const PlanTables t{d_src_offsets, d_lengths, d_order, d_block_of_seq, d_offset_of_seq, d_block_first};
     if (l.wide && l.tiles <= kDirectTiles) {
         hipLaunchKernelGGL(pack_direct_kernel<kPackPlain>, dim3((uint32_t)l.tiles), dim3(kThreads), 0, stream, a, t, num_blocks,
                            1.0 / (double)frame_bytes, 1.0 / (double)t_blk);
+        return launch_status();
+    }
+    if (!l.wide && !two_passes && l.tiles * parts <= kDirectTiles && (parts == 1 || n_seq * 4 <= a.total_slots)) {
+        with_element(a, [&](auto element, auto fused) {
+            hipLaunchKernelGGL((pack_narrow_direct_kernel<decltype(element), decltype(fused)::value>), dim3((uint32_t)(l.tiles * parts)),
+                               dim3(kThreads), 0, stream, a, t, num_blocks, 1.0 / (double)t_blk, parts);
+        });
         return launch_status();
     }
     // pass 1 (both tile shapes): the run table, and where each tile starts in it.  The
@@ -1138,23 +1205,7 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
     // each over the same tiles.  Measured on 1.3 * 10^9 token slots: 3.98 -> 3.72 ms; frames of 6 and 8
     // bytes, whose one pass already writes the table first and the payload after it, lose 5-7 % to the
     // second pass's look-ups and keep the one pass.
-    // A tile is 1024 frames, one workgroup's work: where that leaves compute units idle, several workgroups share
-    // a tile, towards 1024 of them, or 4096 from 64 bytes on, where a tile is 64 KiB and more; never more than
-    // one per vector of a lane.  Short sequences, before and after: 8 tiles of 62 bytes 37 -> 12 us, 59 tiles
-    // of 104 bytes 38 -> 12, 209 of 68 bytes 27 -> 14, 209 of 400 bytes 90 -> 30, 859 of 400 bytes 135 -> 101.
-    // Towards 2048 under 64 bytes: 1055 tiles of 10 bytes 19 -> 21 us, of 48 bytes 25 -> 29.  1024 to 2047 tiles
-    // of the large frames fill the card once by themselves, and a share each would be a second look at every tile's
-    // runs for nothing: whole and in shares, 1059 of 64 bytes 27.5 and 29.7 us, of 128 bytes 45.3 and 46.9, 1399
-    // of 400 bytes 220 and 234, 1199 of 68 bytes 36.0 and 38.5.  From 2048 on some tiles would run alone after the
-    // others: 2099 of 64 bytes 54 and 49, of 128 bytes 95 and 85, of 256 bytes 245 and 226 with two shares.
-    // Frames from 96 bytes on that are put together from elements, a load each, gain there too: 1556 tiles of
-    // 104 bytes 52 and 47 us, of 200 bytes 88 and 75.
-    const int64_t vectors = ceil_div(frame_bytes, 4);               // 1024 slots / 256 lanes / 16 bytes
-    const bool vectors_copied = frame_bytes % 16 == 0 && aligned_to(d_src, 16);
-    const bool once = l.tiles >= 1024 && l.tiles < 2048 && (vectors_copied || frame_bytes < 96);
-    const int64_t wanted = once ? 1 : ceil_div(frame_bytes < 64 ? 1024 : 4096, l.tiles);
-    const int32_t parts = (int32_t)(frame_bytes == 4 && aligned_to(d_src, 4) ? 1 : wanted < vectors ? wanted : vectors);
-    if (frame_bytes == 4 && aligned_to(d_src, 4) && a.total_slots >= kTablePassFromSlots) {
+    if (two_passes) {
         const dim3 groups((uint32_t)ceil_div(l.tiles, kPassGroup));
         if (traffic == kPackCached)
             hipLaunchKernelGGL((pack_narrow_kernel<uint32_t, true, kPackCached, true, false, kPassGroup>), groups, block, 0, stream, a,
@@ -1165,9 +1216,9 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
         hipLaunchKernelGGL((pack_narrow_kernel<uint8_t, false, kPackStream, false, true, kPassGroup>), groups, block, 0, stream, a,
                            runs, first_pos, n_tiles, parts);
     } else if (traffic == kPackCached) {
-        pack_launch_slots<kPackCached>(a, runs, first_pos, n_tiles, parts, vectors_copied, stream);
+        pack_launch_slots<kPackCached>(a, runs, first_pos, n_tiles, parts, stream);
     } else {
-        pack_launch_slots<kPackStream>(a, runs, first_pos, n_tiles, parts, vectors_copied, stream);
+        pack_launch_slots<kPackStream>(a, runs, first_pos, n_tiles, parts, stream);
     }
     return launch_status();
 }

@@ -232,3 +232,30 @@ def test_pack_slot_tiles_in_shares(F, tiles):
     out = bl.bload_pack(to_dev(src), to_dev(so), to_dev(L), upload_plan(ref_plan, len(L)), F)
     torch.cuda.synchronize()
     assert_packed_equal_whole(out, src, so, L, ref_plan, F, max(1, (64 << 20) // (T * F)), f"F={F} tiles={tiles}: ")
+
+
+@pytest.mark.parametrize("F", [1, 4, 7, 62, 64, 100, 600])
+def test_pack_looks_runs_up_in_the_plan(F):
+    """Calls of few tiles find their runs in the plan's tables: blocks of as many sequences as a workgroup looks at at once,
+    one fewer and one more, of thousands (which it narrows down first), dozens of blocks to a tile, short sequences beside
+    long ones; bytes must be equal."""
+    rng = np.random.default_rng(F)
+    some = np.where(rng.random(4000) < 0.97, 1, rng.integers(500, 3000, size=4000))
+    for T, L in [(300, np.ones(255)), (300, np.ones(256)), (300, np.ones(257)), (600, np.ones(513)), (6000, np.ones(13001)),
+                 (7000, rng.integers(1, 4, size=9000)), (1, np.ones(3000)), (3, rng.integers(1, 4, size=3000)), (7000, some)]:
+        L = L.astype(np.int32)
+        if int(L.sum()) * F > 40_000_000:
+            L = L[:max(1, 40_000_000 * len(L) // (int(L.sum()) * F))]
+        so = workloads.src_offsets(L)
+        src = workloads.tagged_source(L, F)
+        ref_plan = oracle.plan(L, T, oracle.order(len(L), 4))
+        ref = oracle.pack(src, so, L, ref_plan, F)
+        print(f"pack direct F={F} n={len(L)} T={T}", flush=True)
+        out = gpu_pack_guarded(src, so, L, upload_plan(ref_plan, len(L)), F)
+        assert_packed_equal(out, ref, f"F={F} n={len(L)} T={T}: ")
+
+
+@pytest.mark.parametrize("F,n", [(4096, 4096), (4096, 4097), (9, 4096 * 1024), (9, 4096 * 1024 + 1), (64, 1023 * 1024)])
+def test_pack_with_and_without_a_run_table(F, n):
+    """The last number of tiles that find their runs themselves and the first that are given them."""
+    run_case(n, 1, F, "uniform", seed=1)
