@@ -11,8 +11,9 @@
 //            (round k: every marked p marks jump[p], then jump = jump o jump)
 //   block    inclusive count of heads up to p, minus one
 //   offset   P[p] - P[head of p's block]
-// Up to 256 sequences one workgroup does all of it in LDS, in one launch; up to 12288, one of 16 waves does, between a
-// launch that finds the order, which is work for the whole chip, and one that writes the tables (plan_mid_kernel).
+// Up to 2048 sequences one workgroup does all of it in one launch, a position to a lane (plan_wave_kernel and
+// plan_waves_kernel); up to 12288, one of 16 waves does, between a launch that finds the order, which is work for the
+// whole chip, and one that writes the tables (plan_mid_kernel).
 // Beyond that the scans work on tiles of 2048 positions (many small workgroups)
 // and the orbit is found on tiles of 2048 to 8192 in three steps that need no launch per
 // jumping round: every tile jumps inside its own LDS until each of its positions
@@ -21,14 +22,15 @@
 // exits a small kernel composes first; beyond 1024 tiles one thread finds all entries); every
 // tile then marks its heads from its entry by jumping in LDS again.  Six launches up to 40 tiles,
 // seven beyond, one more where the sequences fetch what they get (plan_gather_kernel).  (Blocks so long that prefix sums
-// of 12288 sequences leave 32 bits: one workgroup of four waves up to 2048 sequences, the tiles from there on, five
-// launches where the one tile is entered at position 0.)
+// of 12288 sequences leave 32 bits: the tiles from 2049 sequences on, five launches where the one tile is entered at
+// position 0.)
 // Bound by launches and latencies: 10^6 documents 125 -> 111 us per call with smaller jump tiles (exit kernel 17 -> 13 us;
 // the marking kernel's shorter rounds pay for its longer walk: 23 -> 25), tables fetched instead of scattered (32 -> 11 +
 // 12) and next[] searched in LDS (16 -> 10).
 #include "bload_common.hpp"
 #include "bload_order.hpp"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace bload {
@@ -44,8 +46,9 @@ constexpr int kJumpItems = 16;                    // positions per thread where 
 constexpr int kJumpTile = 8192;                   // the largest
 template <int NT> __host__ __device__ constexpr int jump_tile() { return NT * kJumpItems; }
 constexpr int64_t kSmallTilesUpTo = 160000, kMidTilesUpTo = (int64_t)1 << 20;
-constexpr int kSmallMost = 256;                   // up to this many sequences a launch and four waves do (300: 29.3 us, 28.1
-                                                  // in three launches; 2048 at 130 to a block 76 and 47, one to a block 62 and 45)
+constexpr int kPlanWaves = 16;                    // one launch and up to this many waves do for 64 to kWavesMost sequences (256: 23.4
+constexpr int kWavesMost = 2 * kPlanWaves * kWave;     // -> 18.5 us a call; 300: 28.1 -> 20.3; 2048, 125 and 1 to a block: 29.3 -> 26.3,
+                                                  // 33.5 -> 26.1.  At 4096 three launches are faster: 31.8 and 39.0, 33.8 and 33.0 in one)
 constexpr int kWalkTiles = 1024;                  // up to this many jump tiles, each finds its own entry (see plan_mark_kernel),
 constexpr int kGroupFrom = 40;                    // and from this many on with the exits of groups of tiles: their launch
                                                   // costs 5 us, a hop of the walk 0.24
@@ -104,7 +107,7 @@ __device__ __forceinline__ T block_exclusive_scan(T x, T ident, Op op, T* total)
     return op(before, excl);
 }
 
-// ---- steps shared by the one-workgroup plan and the tiled one --------------------------
+// ---- steps shared by the plans of one workgroup and the tiled one --------------------------
 
 // next[p]: smallest q > p with P[q+1] - P[p] > t_blk, n_seq if there is none; P is read
 // through `prefix_at`.  Every length is >= 1, so q - p <= t_blk bounds the search window.
@@ -121,50 +124,14 @@ __device__ __forceinline__ int32_t next_head(PrefixAt prefix_at, int32_t p, int3
     return (lo <= n_seq) ? (int32_t)(lo - 1) : n_seq;
 }
 
-// One round of pointer jumping over the `count` positions [lo, lo + count) held in LDS: a
-// pointer that points behind them stays; with MARK a marked position marks where it points.
-// Thread t works on positions t, t + NT, ...: neighbours in LDS.  Eight positions at a time,
-// all first look-ups, then all second ones, then the stores, so that the look-ups of a batch
-// are in flight together (`from`, `to` and `mark` are different arrays).  Returns whether a
-// pointer of the calling thread still pointed into the tile (when none of the workgroup does,
-// further rounds change nothing).  The caller puts a barrier between rounds.
-template <bool MARK, int NT>
-__device__ __forceinline__ bool jump_round(const int32_t* __restrict__ from, int32_t* __restrict__ to,
-                                           uint8_t* mark, int32_t lo, int32_t count)
-{
-    constexpr int kBatch = 8;
-    bool inside_any = false;           // did a pointer of this thread still point into the tile
-    for (int32_t k0 = (int32_t)threadIdx.x; k0 < count; k0 += kBatch * NT) {
-        int32_t at[kBatch], then[kBatch];
-        uint8_t marked[kBatch];
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const int32_t k = k0 + u * NT;
-            at[u] = k < count ? from[k] : lo + count;
-            marked[u] = (MARK && k < count) ? mark[k] : (uint8_t)0;
-        }
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const bool inside = at[u] - lo < count;
-            inside_any |= inside;
-            then[u] = inside ? from[at[u] - lo] : at[u];
-        }
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const int32_t k = k0 + u * NT;
-            if (k < count) {
-                to[k] = then[u];
-                if (MARK && marked[u] && at[u] - lo < count) mark[at[u] - lo] = 1;
-            }
-        }
-    }
-    return inside_any;
-}
-
-// The same round (without marks) over a whole jump tile, four neighbouring
+// One round of pointer jumping over the `count` positions from lo on that a jump tile holds in LDS (`from` and `to` are
+// different arrays): a pointer that points behind them stays.  Four neighbouring
 // positions per thread and step: their pointers come and go as one 16-byte LDS access, only the
 // look-ups behind them are single words (24 LDS instructions per thread and round instead of
-// 48).  Positions from `count` on must hold pointers that point behind the tile.
+// 48), and all first accesses are made before the second ones, so that they are in flight together.  Positions from
+// `count` on must hold pointers that point behind the tile.  Returns whether a pointer of the calling thread still
+// pointed into the tile (when none of the workgroup does, further rounds change nothing).  The caller puts a barrier
+// between rounds.
 template <int NT>
 __device__ __forceinline__ bool jump_round_tile(const int32_t* __restrict__ from, int32_t* __restrict__ to,
                                                 int32_t lo, int32_t count)
@@ -589,82 +556,187 @@ __global__ __launch_bounds__(kThreads) void plan_gather_kernel(const int2* __res
     offset_of_seq[i] = v.y;
 }
 
-// The whole plan of at most kTile sequences in one workgroup: the same steps as the
-// kernels above with the prefix sums, jump tables and head marks in LDS and a barrier where
-// the tiled path has a kernel boundary.  A thread scans ceil(n_seq / 256) consecutive
-// positions, so that small inputs still spread over all threads.
-__global__ __launch_bounds__(kThreads) void plan_small_kernel(
+// The whole plan of at most 64 sequences in one wave, a position to a lane: prefix sums by DPP, next[] searched in the other
+// lanes' sums, and the orbit as masks of 64 positions (round k: the positions that 2^k steps from a lane reach), of which
+// lane 0 ends with the heads; block and offset are then a count and the highest bit below the lane.  No barrier and no LDS
+// array: what bounds it is the chain of look-ups in other lanes, seven for next[] and two a round for the masks.  (In four
+// waves with the pointers in LDS, as up to 256 sequences were planned before, a round costs a barrier and three trips
+// there: 64 sequences 21.7 -> 17.0 us the call, of which the launch and the wait for it are 16.)
+__global__ __launch_bounds__(kWave) void plan_wave_kernel(
     const int32_t* __restrict__ lengths, int32_t n_seq, int32_t t_blk, OrderKey key, int rounds,
     int32_t* __restrict__ order, int32_t* __restrict__ block_of_seq,
     int32_t* __restrict__ offset_of_seq, int32_t* __restrict__ block_first,
     PlanResult* __restrict__ result)
 {
-    __shared__ int64_t s_prefix[kTile + 1];
-    __shared__ int32_t s_jump[2][kTile];          // [0] holds the shuffled lengths first
-    __shared__ uint8_t s_mark[kTile];
-    const int per_thread = (n_seq + kThreads - 1) / kThreads;
-    const int base = (int)threadIdx.x * per_thread;
-    const int end = min(base + per_thread, n_seq);
-
-    int bad = 0;
-    for (int p = (int)threadIdx.x; p < n_seq; p += kThreads) {
-        const int32_t i = order_at((uint32_t)p, (uint32_t)n_seq, key);
-        const int32_t len = lengths[i];
-        order[p] = i;
-        s_jump[0][p] = len;
-        bad |= (len < 1) | (len > t_blk);
-    }
-    bad = __syncthreads_or(bad);
-    int64_t sum = 0;
-    for (int p = base; p < end; ++p) sum += s_jump[0][p];
-    int64_t total;
-    int64_t run = block_exclusive_scan<int64_t>(sum, 0, SumI64(), &total);
-    for (int p = base; p < end; ++p) {
-        s_prefix[p] = run;
-        run += s_jump[0][p];
-    }
-    if (threadIdx.x == 0) s_prefix[n_seq] = total;
-    __syncthreads();
-
-    // next[p]: the position that opens the next block if p opens one
-    for (int p = (int)threadIdx.x; p < n_seq; p += kThreads) {
-        s_jump[0][p] = next_head([&](int32_t q) { return s_prefix[q]; }, p, n_seq, t_blk);
-        s_mark[p] = (uint8_t)(p == 0);
-    }
-    // pointer jumping: 2^rounds >= n_seq
-    int cur = 0;
-    for (int r = 0; r < rounds; ++r) {
-        __syncthreads();
-        jump_round<true, kThreads>(s_jump[cur], s_jump[cur ^ 1], s_mark, 0, n_seq);
-        cur ^= 1;
-    }
-    __syncthreads();
-
-    // blocks, offsets, first positions: block and head of every position into the (now free)
-    // jump tables, then every thread finishes the positions it ordered itself
-    HeadPair v{0, -1};
-    for (int p = base; p < end; ++p)
-        if (s_mark[p]) { v.cnt += 1; v.head = p; }
-    HeadPair all;
-    HeadPair at = block_exclusive_scan<HeadPair>(v, HeadPair{0, -1}, HeadOp(), &all);
-    for (int p = base; p < end; ++p) {
-        if (s_mark[p]) {
-            at.cnt += 1;
-            at.head = p;
-            block_first[at.cnt - 1] = p;
+    const int p = (int)threadIdx.x;
+    const bool mine = p < n_seq;
+    int32_t i = 0, len = 0;
+    if (key.half_bits > 0) {                          // (a domain of at most 64: every lane has one step of the walks)
+        const int step = (int)(feistel((uint32_t)p & ((1u << 2 * key.half_bits) - 1u), key));
+        i = step;
+        while (__any(mine && i >= n_seq)) {
+            const int on = __shfl(step, i, kWave);
+            if (i >= n_seq) i = on;
         }
-        s_jump[0][p] = at.cnt - 1;
-        s_jump[1][p] = at.head;
+    }
+    if (mine) {
+        len = lengths[i];
+        order[p] = i;
+    }
+    const bool bad = __any(mine && (len < 1 || len > t_blk));
+    const int64_t upto = wave_scan((int64_t)len, SumI64(), LaneMove());
+    const int64_t front = upto - len, limit = front + t_blk;
+
+    // next[p]: the number of positions whose sum the limit covers (lanes behind the last one repeat the total)
+    int next = 0;
+#pragma unroll
+    for (int step = kWave / 2; step > 0; step >>= 1)
+        if (__shfl((long long)upto, next + step - 1, kWave) <= limit) next += step;
+    if (__shfl((long long)upto, next, kWave) <= limit) ++next;
+    next = min(max(next, p + 1), n_seq);              // (lengths that are refused: the sums need not rise)
+
+    unsigned long long reach = mine ? 1ull << p : 0ull;
+    for (int r = 0; r < rounds; ++r) {                // 2^rounds >= n_seq
+        const int at = min(next, kWave - 1);
+        const unsigned long long there = __shfl(reach, at, kWave);
+        const int beyond = __shfl(next, at, kWave);
+        if (next < n_seq) {
+            reach |= there;
+            next = beyond;
+        }
+    }
+    const unsigned long long heads = __shfl(reach, 0, kWave);
+    const unsigned long long own = heads & (~0ull >> (kWave - 1 - p));       // heads up to this position: bit 0 at least
+    const int head = kWave - 1 - __clzll((long long)own), block = __popcll(own) - 1, blocks = __popcll(heads);
+    const int64_t head_front = __shfl((long long)front, head, kWave);
+    if (mine) {
+        if (head == p) block_first[block] = p;
+        block_of_seq[i] = block;
+        offset_of_seq[i] = (int32_t)(front - head_front);
+    }
+    if (p == kWave - 1) {
+        block_first[blocks] = n_seq;
+        result->num_blocks = blocks;
+        result->total_frames = upto;
+        result->bad_length = bad;
+        result->pad_ = 0;
+    }
+}
+
+// The same with several waves, J chunks of 64 positions to each, for at most 1024 * J sequences: the walks of the order are
+// look-ups in a table of the permutation's whole domain, a chunk's masks stop at its end, every wave then follows the
+// orbit of position 0 from chunk to chunk (a look-up each), and lane c holds the heads of chunk c.
+template <int J>
+__global__ __launch_bounds__(kPlanWaves * kWave) void plan_waves_kernel(
+    const int32_t* __restrict__ lengths, int32_t n_seq, int32_t t_blk, OrderKey key,
+    int32_t* __restrict__ order, int32_t* __restrict__ block_of_seq,
+    int32_t* __restrict__ offset_of_seq, int32_t* __restrict__ block_first,
+    PlanResult* __restrict__ result)
+{
+    constexpr int kMost = J * kPlanWaves * kWave;
+    __shared__ int64_t s_front[kMost + 1];
+    __shared__ unsigned long long s_reach[kMost];
+    __shared__ uint16_t s_exit[kMost];
+    __shared__ uint16_t s_step[J == 1 ? 1024 : 4096];        // the smallest power of four that holds kMost
+    __shared__ int64_t s_sums[kPlanWaves];
+    const int lane = lane_id(), wave = wave_id(), threads = (int)blockDim.x;
+    const int domain = 1 << 2 * key.half_bits;
+    for (int x = (int)threadIdx.x; x < domain; x += threads) s_step[x] = (uint16_t)feistel((uint32_t)x, key);
+    __syncthreads();
+
+    int32_t i[J], len[J];
+    int64_t front[J], sum = 0;
+    int bad = 0;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int p = (wave * J + j) * kWave + lane;
+        i[j] = len[j] = 0;
+        if (p < n_seq) {
+            i[j] = s_step[p];
+            while (i[j] >= n_seq) i[j] = s_step[i[j]];
+            len[j] = lengths[i[j]];
+            order[p] = i[j];
+            bad |= (len[j] < 1) | (len[j] > t_blk);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int64_t upto = wave_scan((int64_t)len[j], SumI64(), LaneMove());
+        front[j] = sum + upto - len[j];
+        sum += __shfl((long long)upto, kWave - 1, kWave);
+    }
+    if (lane == 0) s_sums[wave] = sum;
+    bad = __syncthreads_or(bad);
+    int64_t before = 0, total = 0;
+    for (int w = 0; w < threads / kWave; ++w) {
+        const int64_t t = s_sums[w];
+        if (w < wave) before += t;
+        total += t;
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int p = (wave * J + j) * kWave + lane;
+        front[j] += before;
+        if (p < n_seq) s_front[p] = front[j];
+    }
+    if (threadIdx.x == 0) s_front[n_seq] = total;
+    __syncthreads();
+
+    int next[J];
+    unsigned long long reach[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int p = (wave * J + j) * kWave + lane;
+        next[j] = n_seq;
+        if (p < n_seq) next[j] = next_head([&](int32_t q) { return s_front[q]; }, p, n_seq, t_blk);
+        reach[j] = 1ull << lane;
+    }
+    for (int r = 0; r < 6; ++r) {                     // 2^6 positions in a chunk
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int stop = min((wave * J + j + 1) * kWave, n_seq), at = next[j] & (kWave - 1);
+            const unsigned long long there = __shfl(reach[j], at, kWave);
+            const int beyond = __shfl(next[j], at, kWave);
+            if (next[j] < stop) {
+                reach[j] |= there;
+                next[j] = beyond;
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int p = (wave * J + j) * kWave + lane;
+        if (p < n_seq) {
+            s_exit[p] = (uint16_t)next[j];
+            s_reach[p] = reach[j];
+        }
     }
     __syncthreads();
-    for (int p = (int)threadIdx.x; p < n_seq; p += kThreads) {
-        const int32_t i = order[p];               // this thread's own store above
-        block_of_seq[i] = s_jump[0][p];
-        offset_of_seq[i] = (int32_t)(s_prefix[p] - s_prefix[s_jump[1][p]]);
+
+    int entry = -1;
+    for (int e = 0; e < n_seq; e = s_exit[e])
+        if (e >> 6 == lane) entry = e;
+    const unsigned long long heads = entry >= 0 ? s_reach[entry] : 0ull;
+    const HeadPair here{(int32_t)__popcll(heads),
+                        entry >= 0 ? lane * kWave + kWave - 1 - (int32_t)__clzll((long long)heads) : -1};
+    const HeadPair upto = wave_scan(here, HeadOp(), LaneMove());
+    const HeadPair front_of = LaneMove().template at<kDppWaveShr1, 0xF>(upto);
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int chunk = wave * J + j, p = chunk * kWave + lane;
+        const unsigned long long own = __shfl(heads, chunk, kWave) & (~0ull >> (kWave - 1 - lane));
+        const int earlier = __shfl(front_of.cnt, chunk, kWave), last = __shfl(front_of.head, chunk, kWave);
+        if (p < n_seq) {
+            const int block = earlier + __popcll(own) - 1;
+            const int head = own ? chunk * kWave + kWave - 1 - __clzll((long long)own) : last;
+            if (head == p) block_first[block] = p;
+            block_of_seq[i[j]] = block;
+            offset_of_seq[i[j]] = (int32_t)(front[j] - s_front[head]);
+        }
     }
-    if (threadIdx.x == 0) {
-        block_first[all.cnt] = n_seq;
-        result->num_blocks = all.cnt;
+    if (threadIdx.x == kWave - 1) {
+        block_first[upto.cnt] = n_seq;
+        result->num_blocks = upto.cnt;
         result->total_frames = total;
         result->bad_length = bad;
         result->pad_ = 0;
@@ -673,7 +745,7 @@ __global__ __launch_bounds__(kThreads) void plan_small_kernel(
 
 // The plan of up to kMidMost sequences behind plan_order_kernel: the steps of the tiled path in one workgroup of 16
 // waves, with everything in LDS and a barrier where that has a kernel boundary.  Positions are kept in 16 bits and
-// prefix sums in 32 (the host sees to it that they fit).  Thread t takes `per` consecutive positions, so that a
+// prefix sums in 32 (the host sees to it that they fit).  Thread t takes `per` (3 to 13) consecutive positions, so that a
 // wave's positions are a jump tile of its own, whose rounds need no barrier:
 //   next      by binary search, a thread's first position in the whole window, the others between that one and
 //             the next thread's (next[] never falls)
@@ -1037,12 +1109,17 @@ extern "C" bload_status bload_plan(const int32_t* d_lengths, int64_t n_seq, int3
 
     // (the workgroup of 16 waves keeps its prefix sums in 32 bits)
     const bool mid_fits = n_seq <= kMidMost && n_seq * (int64_t)t_blk <= INT32_MAX - t_blk;
-    if (n_seq <= kSmallMost || (n_seq <= kTile && !mid_fits)) {
+    if (n_seq <= kWave) {
         // 2^rounds >= n_seq >= number of heads
         int rounds = 0;
         while (((int64_t)1 << rounds) < n_seq) ++rounds;
-        hipLaunchKernelGGL(plan_small_kernel, dim3(1), block, 0, stream, d_lengths, n, t_blk, key,
-                           rounds, d_order, d_block_of_seq, d_offset_of_seq, d_block_first, result);
+        hipLaunchKernelGGL(plan_wave_kernel, dim3(1), dim3(kWave), 0, stream, d_lengths, n, t_blk, key, rounds, d_order,
+                           d_block_of_seq, d_offset_of_seq, d_block_first, result);
+    } else if (n_seq <= kWavesMost) {
+        const dim3 waves((uint32_t)std::min<int64_t>((int64_t)1 << 2 * key.half_bits, kPlanWaves * kWave));
+        const auto kernel = n_seq <= kPlanWaves * kWave ? plan_waves_kernel<1> : plan_waves_kernel<2>;
+        hipLaunchKernelGGL(kernel, dim3(1), waves, 0, stream, d_lengths, n, t_blk, key, d_order, d_block_of_seq,
+                           d_offset_of_seq, d_block_first, result);
     } else if (mid_fits) {
         const dim3 sums((uint32_t)l.n_sums), per_item((uint32_t)ceil_div(n_seq, kThreads));
         int32_t* block_at = next;
@@ -1050,9 +1127,9 @@ extern "C" bload_status bload_plan(const int32_t* d_lengths, int64_t n_seq, int3
         hipLaunchKernelGGL(plan_order_kernel<1>, sums, block, 0, stream, d_lengths, n, t_blk, key, d_order,
                            shuffled_len, sum_of, bad_of);
         const int per = (int)ceil_div(n_seq, kMidThreads) | 1;
-        const auto mid = per == 1 ? plan_mid_kernel<1> : per == 3 ? plan_mid_kernel<3> : per == 5 ? plan_mid_kernel<5> : per == 7 ? plan_mid_kernel<7>
+        const auto mid = per == 3 ? plan_mid_kernel<3> : per == 5 ? plan_mid_kernel<5> : per == 7 ? plan_mid_kernel<7>
                          : per == 9 ? plan_mid_kernel<9> : per == 11 ? plan_mid_kernel<11> : plan_mid_kernel<13>;
-        static_assert(kMidPer == 13 && kMidMost <= kMidThreads * kMidPer, "1 to 13 positions per thread");
+        static_assert(kMidPer == 13 && kMidMost <= kMidThreads * kMidPer, "3 to 13 positions per thread");
         hipLaunchKernelGGL(mid, dim3(1), dim3(kMidThreads), 0, stream, shuffled_len, n, t_blk, bad_of, l.n_sums, block_at,
                            offset_at, d_block_first, result);
         hipLaunchKernelGGL(plan_scatter_kernel, per_item, block, 0, stream, d_order, block_at, offset_at, n, d_block_of_seq,

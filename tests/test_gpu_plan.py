@@ -138,6 +138,29 @@ def test_plan_one_workgroup_of_sixteen_waves(n):
         assert e.value.status == bl.ELENGTH
 
 
+# A position to a lane: one wave (up to 64), up to 16 waves of one chunk of 64 positions (1024) or two (2048): both ends of each
+# and of the permutation's domains, chunks of one position, blocks of one sequence, over a chunk's end and over all of them,
+# and sums that leave 32 bits.
+@pytest.mark.parametrize("n", [1, 2, 4, 5, 16, 17, 63, 64, 65, 127, 128, 129, 192, 255, 1023, 1024, 1025, 1088, 2047, 2048, 2049])
+def test_plan_a_position_to_a_lane(n):
+    rng = np.random.default_rng(100 + n)
+    big = 2 ** 31 - 1
+    cases = [(np.ones(n), 1), (np.ones(n), 3), (np.ones(n), 63), (np.ones(n), 64), (np.ones(n), 65), (np.ones(n), n),
+             (np.full(n, 4), 7), (rng.integers(1, 33, size=n), 32), (rng.integers(1, 4, size=n), 300),
+             (np.where(rng.random(n) < 0.03, 500, 1), 500), (np.full(n, big), big), (rng.integers(big // 9, big, size=n), big)]
+    for k, (L, T) in enumerate(cases):
+        L = np.asarray(L).astype(np.int32)
+        print(f"plan n={n} T={T} case {k}", flush=True)
+        assert_plan_equal(gpu_plan(L, T, 7 * n + k), oracle.plan(L, T, oracle.order(n, 7 * n + k)), n)
+    bl = binding()
+    for bad in (0, 301, -2 ** 31, big):
+        L = np.full(n, 300, dtype=np.int32)
+        L[rng.integers(0, n, size=1 + n // 3)] = bad
+        with pytest.raises(bl.BloadError) as e:
+            gpu_plan(L, 300, 1)
+        assert e.value.status == bl.ELENGTH
+
+
 # Jump tiles of 2048, 4096 and 8192 positions (up to 160000 sequences, 2^20, beyond): one position in the last tile, in the
 # last group of 16 or 8 of them, both sides of the line from which on groups are used; the sequences fetch what
 # they get from 2^19 on (unless the order's domain is much larger); blocks that pass over tiles and groups.
