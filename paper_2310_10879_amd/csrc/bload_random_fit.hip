@@ -13,6 +13,7 @@
 //                      seeded positions are cut into chunks, one workgroup each, that
 //                      count their lengths, learn where their part of every list
 //                      begins, and fill it in order
+//                      (up to 4096 sequences rf_prepare_kernel does all of this in one workgroup)
 //   rf_draw_batches_kernel, rf_draw_kernel
 //                      the draws: per placement only (length, free room, how many were left) - no
 //                      global load on the chain
@@ -121,11 +122,10 @@ struct RfMove {
     __device__ __forceinline__ int32_t at(int32_t v) const { return dpp_move<CTRL, ROW_MASK>(v, 0); }
 };
 
-__global__ __launch_bounds__(kRfOffsetThreads) void rf_offsets_kernel(
-    int32_t n_chunks, int32_t t_blk, int32_t* __restrict__ chunk_count, int32_t* __restrict__ first,
-    int32_t* __restrict__ within, int32_t* __restrict__ group_before)
+__device__ __forceinline__ void rf_offsets(int32_t n_chunks, int32_t t_blk, int32_t* chunk_count, int32_t* s_group,
+                                           int32_t* __restrict__ first, int32_t* __restrict__ within,
+                                           int32_t* __restrict__ group_before)
 {
-    __shared__ int32_t s_group[kRfGroups];
     const int lane = lane_id(), wave = wave_id();
     constexpr int kWaves = kRfOffsetThreads / kWave;
     const int groups = (t_blk + kWave - 1) / kWave;
@@ -176,17 +176,48 @@ __global__ __launch_bounds__(kRfOffsetThreads) void rf_offsets_kernel(
     }
 }
 
+__global__ __launch_bounds__(kRfOffsetThreads) void rf_offsets_kernel(
+    int32_t n_chunks, int32_t t_blk, int32_t* __restrict__ chunk_count, int32_t* __restrict__ first,
+    int32_t* __restrict__ within, int32_t* __restrict__ group_before)
+{
+    __shared__ int32_t s_group[kRfGroups];
+    rf_offsets(n_chunks, t_blk, chunk_count, s_group, first, within, group_before);
+}
+
 // Step 3, one workgroup per chunk: its sequences into their lists, in seeded order: tile by
 // tile of 256 positions.  The lanes of a wave that hold the same length find each other by votes on its bits, and the
 // waves take their places in the lists one after another.  (Each thread ranking itself among the keys in front, read
 // from LDS, took 7 us a tile: 29 us at 10^4 sequences.)
+// `waves` waves take turns: the barriers are the workgroup's.
+__device__ __forceinline__ void rf_scatter_tile(int32_t len, int32_t sequence, int bits, int waves, int32_t* s_fill,
+                                                int32_t* __restrict__ entry, uint16_t* __restrict__ sorted_len)
+{
+    const int lane = lane_id(), wave = wave_id();
+    uint64_t same = ~0ull;                       // the lanes with this length
+    for (int b = 0; b < bits; ++b) {
+        const bool one = (len >> b) & 1;
+        const uint64_t vote = __ballot(one);
+        same &= one ? vote : ~vote;
+    }
+    const int rank = (int)__popcll(same & ((1ull << lane) - 1ull));
+    for (int w = 0; w < waves; ++w) {
+        __syncthreads();
+        if (wave == w && len) {
+            const int32_t at = s_fill[len - 1] + rank;
+            if ((same >> lane) == 1ull) s_fill[len - 1] = at + 1;        // the last of them
+            entry[at] = sequence;
+            sorted_len[at] = (uint16_t)len;
+        }
+    }
+}
+
 __global__ __launch_bounds__(kThreads) void rf_scatter_kernel(
     const int32_t* __restrict__ seeded, const int32_t* __restrict__ seeded_len, int32_t n_seq,
     int32_t t_blk, int32_t per_chunk, const int32_t* __restrict__ chunk_start, int32_t* __restrict__ entry,
     uint16_t* __restrict__ sorted_len)
 {
     __shared__ int32_t s_fill[kRfMaxT];         // next free place of every list, for this chunk
-    const int tid = (int)threadIdx.x, lane = lane_id(), wave = wave_id();
+    const int tid = (int)threadIdx.x;
     const int lengths_kept = ((t_blk + kWave - 1) / kWave) * kWave;
     const int bits = 32 - __clz(t_blk);
     for (int e = tid; e < lengths_kept; e += kThreads) s_fill[e] = chunk_start[(int64_t)blockIdx.x * kRfMaxT + e];
@@ -196,22 +227,70 @@ __global__ __launch_bounds__(kThreads) void rf_scatter_kernel(
         const int64_t p = tile + tid;
         const int32_t len = p < hi ? seeded_len[p] : 0;
         const int32_t sequence = p < hi ? seeded[p] : 0;
-        uint64_t same = ~0ull;                   // the lanes with this length
-        for (int b = 0; b < bits; ++b) {
-            const bool one = (len >> b) & 1;
-            const uint64_t vote = __ballot(one);
-            same &= one ? vote : ~vote;
+        rf_scatter_tile(len, sequence, bits, kThreads / kWave, s_fill, entry, sorted_len);
+    }
+}
+
+// All steps for at most kRfPrepareMost sequences, in one workgroup: a position to a thread, kRfPrepareTiles times, the one
+// chunk's counts in LDS, and the walks of the order as look-ups in a table of the permutation's domain (one compute unit
+// would pay for the longest walk of every wave).  Bound by barriers and latencies; what it saves is four launches: a call for 30
+// sequences 44 -> 33 us, 300: 107 -> 95, 1000: 142 -> 125, 4096: 434 -> 421.  (Every further 1024 positions cost some 2 us
+// of the 16 that it saves at 2048, and beyond 4096 the table is four times as large.)
+constexpr int kRfPrepareTiles = 4;
+constexpr int kRfPrepareMost = kRfPrepareTiles * kRfOffsetThreads;
+
+__global__ __launch_bounds__(kRfOffsetThreads) void rf_prepare_kernel(
+    const int32_t* __restrict__ lengths, int32_t n_seq, int32_t t_blk, OrderKey key, int32_t* __restrict__ first,
+    int32_t* __restrict__ within, int32_t* __restrict__ group_before, int32_t* __restrict__ entry,
+    uint16_t* __restrict__ sorted_len, PlanResult* __restrict__ result)
+{
+    __shared__ int32_t s_fill[kRfMaxT];         // sequences of every length, then the next free place of every list
+    __shared__ int32_t s_group[kRfGroups];
+    __shared__ uint16_t s_step[kRfPrepareMost];
+    __shared__ unsigned long long s_sum;
+    const int tid = (int)threadIdx.x;
+    const int lengths_kept = ((t_blk + kWave - 1) / kWave) * kWave;
+    const int bits = 32 - __clz(t_blk);
+    const int domain = 1 << 2 * key.half_bits;
+    for (int e = tid; e < lengths_kept; e += kRfOffsetThreads) s_fill[e] = 0;
+    for (int x = tid; x < domain; x += kRfOffsetThreads) s_step[x] = (uint16_t)feistel((uint32_t)x, key);
+    if (tid == 0) s_sum = 0;
+    __syncthreads();
+    int32_t sequence[kRfPrepareTiles], len[kRfPrepareTiles];
+    int32_t bad = 0, sum = 0;
+#pragma unroll
+    for (int j = 0; j < kRfPrepareTiles; ++j) {
+        const int p = tid + j * kRfOffsetThreads;
+        sequence[j] = len[j] = 0;
+        if (p < n_seq) {
+            int i = s_step[p];
+            while (i >= n_seq) i = s_step[i];
+            const int32_t found = lengths[i];
+            sequence[j] = i;
+            if (found < 1 || found > t_blk) bad = 1;
+            else len[j] = found;
         }
-        const int rank = (int)__popcll(same & ((1ull << lane) - 1ull));
-        for (int w = 0; w < kThreads / kWave; ++w) {
-            __syncthreads();
-            if (wave == w && len) {
-                const int32_t at = s_fill[len - 1] + rank;
-                if ((same >> lane) == 1ull) s_fill[len - 1] = at + 1;        // the last of them
-                entry[at] = sequence;
-                sorted_len[at] = (uint16_t)len;
-            }
-        }
+    }
+#pragma unroll
+    for (int j = 0; j < kRfPrepareTiles; ++j) {
+        sum += len[j];
+        if (len[j]) atomicAdd(&s_fill[len[j] - 1], 1);
+    }
+    if (sum) atomicAdd(&s_sum, (unsigned long long)sum);
+    bad = __syncthreads_or(bad);
+    if (tid == 0) {
+        result->num_blocks = 0;
+        result->total_frames = (int64_t)s_sum;
+        result->bad_length = bad;
+        result->pad_ = 0;
+    }
+    rf_offsets(1, t_blk, s_fill, s_group, first, within, group_before);
+#pragma unroll
+    for (int j = 0; j < kRfPrepareTiles; ++j) {
+        const int here = n_seq - j * kRfOffsetThreads;
+        if (here <= 0) break;
+        rf_scatter_tile(len[j], sequence[j], bits, min((here + kWave - 1) / kWave, kRfOffsetThreads / kWave), s_fill, entry,
+                        sorted_len);
     }
 }
 
@@ -835,15 +914,20 @@ extern "C" bload_status bload_plan_random_fit(const int32_t* d_lengths, int64_t 
     const dim3 block(kThreads);
     const dim3 per_item((uint32_t)ceil_div(n_seq, kThreads));
 
-    hipLaunchKernelGGL(rf_clear_kernel, dim3(1), dim3(1), 0, stream, result);
-    hipLaunchKernelGGL(rf_order_kernel, per_item, block, 0, stream, d_lengths, n, t_blk, key, seeded,
-                       seeded_len, result);
-    hipLaunchKernelGGL(rf_count_kernel, dim3((uint32_t)l.n_chunks), block, 0, stream, seeded_len, n, t_blk,
-                       l.per_chunk, chunk_count);
-    hipLaunchKernelGGL(rf_offsets_kernel, dim3(1), dim3(kRfOffsetThreads), 0, stream, l.n_chunks, t_blk, chunk_count, first,
-                       within, group_before);
-    hipLaunchKernelGGL(rf_scatter_kernel, dim3((uint32_t)l.n_chunks), block, 0, stream, seeded, seeded_len,
-                       n, t_blk, l.per_chunk, chunk_count, entry, sorted_len);
+    if (n_seq <= kRfPrepareMost) {
+        hipLaunchKernelGGL(rf_prepare_kernel, dim3(1), dim3(kRfOffsetThreads), 0, stream, d_lengths, n, t_blk, key, first,
+                           within, group_before, entry, sorted_len, result);
+    } else {
+        hipLaunchKernelGGL(rf_clear_kernel, dim3(1), dim3(1), 0, stream, result);
+        hipLaunchKernelGGL(rf_order_kernel, per_item, block, 0, stream, d_lengths, n, t_blk, key, seeded,
+                           seeded_len, result);
+        hipLaunchKernelGGL(rf_count_kernel, dim3((uint32_t)l.n_chunks), block, 0, stream, seeded_len, n, t_blk,
+                           l.per_chunk, chunk_count);
+        hipLaunchKernelGGL(rf_offsets_kernel, dim3(1), dim3(kRfOffsetThreads), 0, stream, l.n_chunks, t_blk, chunk_count, first,
+                           within, group_before);
+        hipLaunchKernelGGL(rf_scatter_kernel, dim3((uint32_t)l.n_chunks), block, 0, stream, seeded, seeded_len,
+                           n, t_blk, l.per_chunk, chunk_count, entry, sorted_len);
+    }
     // after a length outside [1, t_blk] the last kernels return at once
     const bool batches = n_seq >= kRfBatchLeast && n_seq <= kRfBatchMost;
     // (behind the sorted lengths, 2 of the 8 bytes per sequence that their part of the workspace has)

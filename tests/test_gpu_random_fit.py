@@ -101,6 +101,31 @@ def test_random_fit_plan_packs_and_reduces(n, T, F, kind):
     assert np.array_equal(red.cpu().numpy(), oracle.segment_reduce(src, so, L, D, "i32", "sum"))
 
 
+# Up to 4096 sequences one workgroup prepares everything, 1024 positions at a time: both ends of each and of the permutation's
+# domains.
+@pytest.mark.parametrize("n", [1, 2, 4, 5, 63, 64, 65, 191, 192, 193, 255, 256, 257, 319, 320, 321, 511, 767, 1023, 1024, 1025, 2047,
+                               2048, 2049, 3073, 4095, 4096, 4097])
+@pytest.mark.parametrize("T", [1, 60, 2048, 3000, 8192])
+def test_random_fit_few_sequences(n, T):
+    rng = np.random.default_rng(31 * n + T)
+    part = np.full(n, max(1, T // 50))
+    most = np.full(n, max(1, 3 * T // 4))
+    cases = [np.clip(8 * (1 + rng.pareto(1.5, size=n)), 1, T), rng.integers(1, T, size=n, endpoint=True),
+             T - np.minimum(rng.geometric(0.3, size=n) - 1, T - 1), part, most, np.clip(part + (np.arange(n) == 0), 1, T),
+             np.clip(most - (np.arange(n) == 0), 1, T), np.where(rng.random(n) < 0.8, T, 1), np.ones(n)]
+    for k, L in enumerate(cases):
+        L = np.asarray(L).astype(np.int32)
+        print(f"random fit n={n} T={T} case {k}", flush=True)
+        assert_plan_equal(gpu_random_fit(L, T, n + k), oracle.plan_random_fit(L, T, n + k), n)
+    bl = binding()
+    for bad in (0, T + 1, -2 ** 31):
+        L = np.full(n, T, dtype=np.int32)
+        L[rng.integers(0, n)] = bad
+        with pytest.raises(bl.BloadError) as e:
+            gpu_random_fit(L, T, 1)
+        assert e.value.status == bl.ELENGTH
+
+
 # Draws are made in batches of 64 from 768 to 24576 sequences: both ends, the end of the short trial (4096), blocks of one
 # length per group and of many, lists that end on and beside whole words; lengths that settle in a few rounds, in
 # many, not at all (the trial fails), that stop paying on the way, and of which there are so few that draws keep
