@@ -471,6 +471,12 @@ constexpr int kRfBatchMost = 24576;               // sequences: what is kept of 
 // pay until few sequences are left up to 20 (lengths of some tenth of a block of 40: 218 -> 235 us); lengths near the
 // block's gain half (304 -> 136), heavy-tailed ones in blocks of 3000 40 % (226 -> 138).
 constexpr int kRfBatchLeast = 768;
+// From so few on where what is left nearly all fits or hardly any of it, which the frame total tells: lengths of a fiftieth of
+// the block on average or less (from kRfShortLeast on), or of three quarters of it and more.  256 nearly full blocks 107 -> 70 us
+// a call, 767 271 -> 120; heavy-tailed lengths in blocks of 3000, 320 of them 100 -> 80, 700 184 -> 104.  (At a 41st of the
+// block 320 and 400 exponential lengths took 116 and 133 us, 100 and 118 by the chain; lengths of a tenth 96 and 111 us at 256
+// and 384, 81 and 111 by the chain.)  Where the total tells that batches don't pay, the launch costs 2 us.
+constexpr int kRfFewest = 192, kRfShortLeast = 320, kRfShortPart = 50;
 // The first batch is a trial: it ends, with nothing drawn, if after so many rounds not so many of its draws are settled.
 // Of many sequences it is guessed ahead and lasts longer, which costs 10 us where it fails: 1 % of 4096 draws.
 constexpr int kRfTryRounds = 4, kRfTryDraws = 6, kRfTryLong = 8, kRfTryLongDraws = 16, kRfTryLongFrom = 4096;
@@ -567,6 +573,13 @@ __global__ __launch_bounds__(kRfBatchThreads) void rf_draw_batches_kernel(
     if (bad) {
         if (tid == 0 && host_result) host_result->bad_length = bad;
         return;
+    }
+    if (n_seq < kRfBatchLeast) {
+        const int64_t frames = result->total_frames, most = (int64_t)n_seq * t_blk;
+        if (!(n_seq >= kRfShortLeast && kRfShortPart * frames <= most) && 4 * frames < 3 * most) {
+            if (tid == 0) *state = RfState{0, 0, 0, 0};
+            return;
+        }
     }
     const int groups = (t_blk + kWave - 1) / kWave, kept = groups * kWave;
     const uint16_t* upto = sh.upto + 7;
@@ -929,7 +942,7 @@ extern "C" bload_status bload_plan_random_fit(const int32_t* d_lengths, int64_t 
                            n, t_blk, l.per_chunk, chunk_count, entry, sorted_len);
     }
     // after a length outside [1, t_blk] the last kernels return at once
-    const bool batches = n_seq >= kRfBatchLeast && n_seq <= kRfBatchMost;
+    const bool batches = n_seq >= kRfFewest && n_seq <= kRfBatchMost;
     // (behind the sorted lengths, 2 of the 8 bytes per sequence that their part of the workspace has)
     RfState* state = reinterpret_cast<RfState*>(ws + l.sorted_len + round_up((size_t)n_seq * 2, 16));
     if (batches)
