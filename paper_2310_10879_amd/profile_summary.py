@@ -134,9 +134,10 @@ def main() -> None:
             "|---|---|---|---|---|---|"]
     # kernel families of one library call each: (bench key, kernel name prefix, prefixes of the kernel that
     # runs exactly once per call, source file)
-    families = {"pack": ("pack", "bload::pack_", ("bload::pack_prepare",), "bload_pack.hip"),
-                "reduce": ("segment_reduce", "bload::reduce_", ("bload::reduce_wide", "bload::reduce_narrow"),
-                           "bload_reduce.hip"),
+    families = {"pack": ("pack", "bload::pack_", ("bload::pack_prepare", "bload::pack_direct", "bload::pack_narrow_direct"),
+                         "bload_pack.hip"),
+                "reduce": ("segment_reduce", "bload::reduce_", ("bload::reduce_wide", "bload::reduce_staged", "bload::reduce_flat",
+                                                               "bload::reduce_narrow"), "bload_reduce.hip"),
                 "scan": ("segment_scan", "bload::scan_", ("bload::scan_direct", "bload::scan_staged"), "bload_scan.hip")}
     totals = {k: [0.0, 0.0, 0] for k in families}          # read bytes, written bytes, calls
     names = sorted({k[0] for k in fetch} | {k[0] for k in write})
