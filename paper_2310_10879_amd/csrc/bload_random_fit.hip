@@ -14,6 +14,7 @@
 //                      count their lengths, learn where their part of every list
 //                      begins, and fill it in order
 //                      (up to 4096 sequences rf_prepare_kernel does all of this in one workgroup)
+//                      (up to 64 sequences rf_wave_kernel makes the whole plan)
 //   rf_draw_batches_kernel, rf_draw_kernel
 //                      the draws: per placement only (length, free room, how many were left) - no
 //                      global load on the chain
@@ -233,8 +234,8 @@ __global__ __launch_bounds__(kThreads) void rf_scatter_kernel(
 
 // All steps for at most kRfPrepareMost sequences, in one workgroup: a position to a thread, kRfPrepareTiles times, the one
 // chunk's counts in LDS, and the walks of the order as look-ups in a table of the permutation's domain (one compute unit
-// would pay for the longest walk of every wave).  Bound by barriers and latencies; what it saves is four launches: a call for 30
-// sequences 44 -> 33 us, 300: 107 -> 95, 1000: 142 -> 125, 4096: 434 -> 421.  (Every further 1024 positions cost some 2 us
+// would pay for the longest walk of every wave).  Bound by barriers and latencies; what it saves is four launches: a call for 128
+// sequences 67 -> 56 us, 300: 107 -> 95, 1000: 142 -> 125, 4096: 434 -> 421.  (Every further 1024 positions cost some 2 us
 // of the 16 that it saves at 2048, and beyond 4096 the table is four times as large.)
 constexpr int kRfPrepareTiles = 4;
 constexpr int kRfPrepareMost = kRfPrepareTiles * kRfOffsetThreads;
@@ -815,6 +816,94 @@ __global__ __launch_bounds__(kRfBatchThreads) void rf_draw_batches_kernel(
     if (tid < kRfGroups) group_before[tid] = upto[min(tid, groups) * kWave];
 }
 
+// ---- few sequences ------------------------------------------------------------------
+//
+// The whole plan of at most 64 sequences in one wave and one launch: the sequences lie in the lanes, in ascending order of their
+// lengths and those of one length in seeded order, and what is left of them is a mask.  How many fit is a vote and a count, the
+// k-th of them the lane with k fitting ones below it, and of its length the last one left is taken, as from the lists of
+// L_dict.  No table of lengths, so nothing depends on t_blk.  Bound by the launch, the wait for it (16 us together)
+// and some 30 dependent instructions a draw, 0.13 us where the chain over L_dict takes 0.26: a call for 64
+// sequences in three launches 42 to 51 us (nine, before those: 47 to 63), like this 26; 30: 22.
+__global__ __launch_bounds__(kWave) void rf_wave_kernel(
+    const int32_t* __restrict__ lengths, int32_t n_seq, int32_t t_blk, OrderKey key, uint64_t seed,
+    int32_t* __restrict__ order, int32_t* __restrict__ block_of_seq, int32_t* __restrict__ offset_of_seq,
+    int32_t* __restrict__ block_first, PlanResult* __restrict__ result)
+{
+    const int lane = (int)threadIdx.x;
+    const bool mine = lane < n_seq;
+    int32_t i = 0, len = INT32_MAX;
+    if (key.half_bits > 0) {                             // (a domain of at most 64: every lane has one step of the walks)
+        const int step = (int)feistel((uint32_t)lane & ((1u << 2 * key.half_bits) - 1u), key);
+        i = step;
+        while (__any(mine && i >= n_seq)) {
+            const int on = __shfl(step, i, kWave);
+            if (i >= n_seq) i = on;
+        }
+    }
+    if (mine) len = lengths[i];
+    if (__any(mine && (len < 1 || len > t_blk))) {
+        if (lane == 0) {
+            result->num_blocks = 0;
+            result->total_frames = 0;
+            result->bad_length = 1;
+            result->pad_ = 0;
+        }
+        return;
+    }
+    const int32_t total = __builtin_amdgcn_readlane(wave_scan(mine ? len : 0, RfSum(), RfMove()), kWave - 1);
+
+    int rank = 0;                                        // (lanes without a sequence come last, in their order)
+#pragma unroll 8
+    for (int j = 0; j < kWave; ++j) {
+        const int32_t other = __builtin_amdgcn_readlane(len, j);
+        rank += other < len || (other == len && j < lane) ? 1 : 0;
+    }
+    len = __builtin_amdgcn_ds_permute(rank * 4, len);
+    i = __builtin_amdgcn_ds_permute(rank * 4, i);
+
+    const uint64_t random = splitmix64_at(seed, (uint64_t)(6 + lane));
+    const uint32_t u_lo = (uint32_t)random, u_hi = (uint32_t)(random >> 32);
+    unsigned long long left = ~0ull >> (kWave - n_seq);
+    int32_t room = 0, blocks = 0;
+    int32_t first = 0, place = 0, block = 0, offset = 0; // of block `lane`; of the lane's sequence
+    for (int32_t placed = 0; placed < n_seq; ++placed) {
+        unsigned long long fits = __ballot(len <= room) & left;
+        if (fits == 0) {                                 // a new block: all that is left fits
+            first = lane == blocks ? placed : first;
+            ++blocks;
+            room = t_blk;
+            fits = left;
+        }
+        const uint32_t fit = (uint32_t)__popcll(fits);
+        const uint32_t lo = __builtin_amdgcn_readlane(u_lo, placed), hi = __builtin_amdgcn_readlane(u_hi, placed);
+        const uint32_t k = (uint32_t)(((uint64_t)hi * fit + ((uint64_t)lo * fit >> 32)) >> 32);
+        const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(fits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)fits, 0u));
+        const unsigned long long chosen = __ballot(below == k) & fits;
+        const int32_t length = __builtin_amdgcn_readlane(len, __ffsll((long long)chosen) - 1);
+        const int last = kWave - 1 - __clzll((long long)(__ballot(len == length) & left));
+        if (lane == last) {
+            place = placed;
+            block = blocks - 1;
+            offset = t_blk - room;
+        }
+        left &= ~(1ull << last);
+        room -= length;
+    }
+    if (mine) {
+        order[place] = i;
+        block_of_seq[i] = block;
+        offset_of_seq[i] = offset;
+        if (lane < blocks) block_first[lane] = first;
+    }
+    if (lane == 0) {
+        block_first[blocks] = n_seq;
+        result->num_blocks = blocks;
+        result->total_frames = total;
+        result->bad_length = 0;
+        result->pad_ = 0;
+    }
+}
+
 __global__ __launch_bounds__(kThreads) void rf_assign_kernel(
     const RfPick* __restrict__ pick, const int32_t* __restrict__ first,
     const int32_t* __restrict__ entry, int32_t n_seq, int32_t t_blk, const int32_t* __restrict__ block_first,
@@ -927,33 +1016,38 @@ extern "C" bload_status bload_plan_random_fit(const int32_t* d_lengths, int64_t 
     const dim3 block(kThreads);
     const dim3 per_item((uint32_t)ceil_div(n_seq, kThreads));
 
-    if (n_seq <= kRfPrepareMost) {
-        hipLaunchKernelGGL(rf_prepare_kernel, dim3(1), dim3(kRfOffsetThreads), 0, stream, d_lengths, n, t_blk, key, first,
-                           within, group_before, entry, sorted_len, result);
+    if (n_seq <= kWave) {
+        hipLaunchKernelGGL(rf_wave_kernel, dim3(1), dim3(kWave), 0, stream, d_lengths, n, t_blk, key, seed, d_order,
+                           d_block_of_seq, d_offset_of_seq, d_block_first, pinned ? pinned : result);
     } else {
-        hipLaunchKernelGGL(rf_clear_kernel, dim3(1), dim3(1), 0, stream, result);
-        hipLaunchKernelGGL(rf_order_kernel, per_item, block, 0, stream, d_lengths, n, t_blk, key, seeded,
-                           seeded_len, result);
-        hipLaunchKernelGGL(rf_count_kernel, dim3((uint32_t)l.n_chunks), block, 0, stream, seeded_len, n, t_blk,
-                           l.per_chunk, chunk_count);
-        hipLaunchKernelGGL(rf_offsets_kernel, dim3(1), dim3(kRfOffsetThreads), 0, stream, l.n_chunks, t_blk, chunk_count, first,
-                           within, group_before);
-        hipLaunchKernelGGL(rf_scatter_kernel, dim3((uint32_t)l.n_chunks), block, 0, stream, seeded, seeded_len,
-                           n, t_blk, l.per_chunk, chunk_count, entry, sorted_len);
+        if (n_seq <= kRfPrepareMost) {
+            hipLaunchKernelGGL(rf_prepare_kernel, dim3(1), dim3(kRfOffsetThreads), 0, stream, d_lengths, n, t_blk, key, first,
+                               within, group_before, entry, sorted_len, result);
+        } else {
+            hipLaunchKernelGGL(rf_clear_kernel, dim3(1), dim3(1), 0, stream, result);
+            hipLaunchKernelGGL(rf_order_kernel, per_item, block, 0, stream, d_lengths, n, t_blk, key, seeded,
+                               seeded_len, result);
+            hipLaunchKernelGGL(rf_count_kernel, dim3((uint32_t)l.n_chunks), block, 0, stream, seeded_len, n, t_blk,
+                               l.per_chunk, chunk_count);
+            hipLaunchKernelGGL(rf_offsets_kernel, dim3(1), dim3(kRfOffsetThreads), 0, stream, l.n_chunks, t_blk, chunk_count, first,
+                               within, group_before);
+            hipLaunchKernelGGL(rf_scatter_kernel, dim3((uint32_t)l.n_chunks), block, 0, stream, seeded, seeded_len,
+                               n, t_blk, l.per_chunk, chunk_count, entry, sorted_len);
+        }
+        // after a length outside [1, t_blk] the last kernels return at once
+        const bool batches = n_seq >= kRfFewest && n_seq <= kRfBatchMost;
+        // (behind the sorted lengths, 2 of the 8 bytes per sequence that their part of the workspace has)
+        RfState* state = reinterpret_cast<RfState*>(ws + l.sorted_len + round_up((size_t)n_seq * 2, 16));
+        if (batches)
+            hipLaunchKernelGGL(rf_draw_batches_kernel, dim3(1), dim3(kRfBatchThreads), 0, stream, sorted_len, within,
+                               group_before, state, n, t_blk, seed, pick, d_block_first, result, pinned);
+        const auto draw = t_blk <= kRfRegisterRows * kWave ? rf_draw_kernel<true, false>
+                          : t_blk <= kWave * kWave ? rf_draw_kernel<false, false> : rf_draw_kernel<false, true>;
+        hipLaunchKernelGGL(draw, dim3(1), dim3(kWave), 0, stream, within, group_before, batches ? state : nullptr, n, t_blk,
+                           seed, pick, d_block_first, result, pinned);
+        hipLaunchKernelGGL(rf_assign_kernel, per_item, block, 0, stream, pick, first, entry, n, t_blk, d_block_first, d_order,
+                           d_block_of_seq, d_offset_of_seq, result, pinned);
     }
-    // after a length outside [1, t_blk] the last kernels return at once
-    const bool batches = n_seq >= kRfFewest && n_seq <= kRfBatchMost;
-    // (behind the sorted lengths, 2 of the 8 bytes per sequence that their part of the workspace has)
-    RfState* state = reinterpret_cast<RfState*>(ws + l.sorted_len + round_up((size_t)n_seq * 2, 16));
-    if (batches)
-        hipLaunchKernelGGL(rf_draw_batches_kernel, dim3(1), dim3(kRfBatchThreads), 0, stream, sorted_len, within,
-                           group_before, state, n, t_blk, seed, pick, d_block_first, result, pinned);
-    const auto draw = t_blk <= kRfRegisterRows * kWave ? rf_draw_kernel<true, false>
-                      : t_blk <= kWave * kWave ? rf_draw_kernel<false, false> : rf_draw_kernel<false, true>;
-    hipLaunchKernelGGL(draw, dim3(1), dim3(kWave), 0, stream, within, group_before, batches ? state : nullptr, n, t_blk,
-                       seed, pick, d_block_first, result, pinned);
-    hipLaunchKernelGGL(rf_assign_kernel, per_item, block, 0, stream, pick, first, entry, n, t_blk, d_block_first, d_order,
-                       d_block_of_seq, d_offset_of_seq, result, pinned);
     if (launch_status() != BLOAD_OK) return BLOAD_EHIP;
     PlanResult host{};
     if (!pinned && !hip_ok(hipMemcpyAsync(&host, result, sizeof(host), hipMemcpyDeviceToHost, stream)))

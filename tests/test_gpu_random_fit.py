@@ -101,8 +101,8 @@ def test_random_fit_plan_packs_and_reduces(n, T, F, kind):
     assert np.array_equal(red.cpu().numpy(), oracle.segment_reduce(src, so, L, D, "i32", "sum"))
 
 
-# Up to 4096 sequences one workgroup prepares everything, 1024 positions at a time: both ends of each and of the permutation's
-# domains; and from 192 sequences on draws are made in batches where the lengths are short (from 320 on) or nearly the block's:
+# Up to 64 sequences one wave makes the whole plan.  Up to 4096 one workgroup prepares everything, 1024 positions at a
+# time: both ends of each and of the permutation's domains; and from 192 sequences on draws are made in batches where the lengths are short (from 320 on) or nearly the block's:
 # both ends, and totals at and beside the lines (a fiftieth and three quarters of the block).
 @pytest.mark.parametrize("n", [1, 2, 4, 5, 63, 64, 65, 191, 192, 193, 255, 256, 257, 319, 320, 321, 511, 767, 1023, 1024, 1025, 2047,
                                2048, 2049, 3073, 4095, 4096, 4097])
