@@ -2036,8 +2036,9 @@ extern "C" bload_status bload_segment_reduce(const void* d_packed, const int32_t
     ReducePlan p = reduce_plan(num_blocks, t_blk, feat_dim, dtype, total_slots / n_seq);
     // a workspace that is smaller than the query's answer but holds what another cut needs, in the end the leanest
     const size_t room = d_workspace ? workspace_bytes : 0;
+    // (the flat cut takes it only where it is aligned: cuts that need none leave it alone)
     const ReducePlan flat = flat_plan(num_blocks, t_blk, feat_dim, dtype);
-    if (flat.flat && flat.bytes <= room &&
+    if (flat.flat && flat.bytes <= (aligned_to(d_workspace, 16) ? room : 0) &&
         takes_flat(flat, p, total_slots * feat_dim * elem_size(dtype), feat_dim * elem_size(dtype), elem_size(dtype), total_slots / n_seq))
         p = flat;
     if (room < p.bytes) {

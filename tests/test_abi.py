@@ -125,6 +125,20 @@ def test_reduce_cuts_many_blocks_as_finely_for_short_pieces(lib, B, T, D):
                  ctypes.c_int64(B * T // frames), p, p, ctypes.c_size_t(need - 16), None) == 3
 
 
+@pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="a call that is not refused would be launched on these addresses")
+@pytest.mark.parametrize("B,T,D,dtype,n", [(598, 4993, 2, 3, 1355), (598, 4993, 2, 2, 1355)])
+def test_reduce_leaves_an_unaligned_workspace_alone(lib, B, T, D, dtype, n):
+    """Sizes whose cut in tiles of whole chunks needs no workspace: one that is not aligned is not used, so the call
+    gets as far as its launch (which fails here, without a GPU) with an aligned workspace, an unaligned one and none."""
+    f, p = lib.bload_segment_reduce, ctypes.c_void_p(0x10000)
+    f.restype = ctypes.c_int
+    need = reduce_query(lib)(B, T, D, dtype)
+    assert need > 0
+    for ws, room in ((0x10000, need), (0x10004, need), (0x10008, 0), (None, 0)):
+        assert f(p, p, p, p, ctypes.c_int64(B), ctypes.c_int32(T), ctypes.c_int64(D), dtype, 0, ctypes.c_int64(n), p,
+                 ctypes.c_void_p(ws), ctypes.c_size_t(room), None) == 6
+
+
 def test_argument_checks_need_no_gpu(lib):
     # every call below must be refused on the host, before any HIP call
     vp, i64, i32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32
