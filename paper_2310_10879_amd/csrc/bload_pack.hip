@@ -511,6 +511,11 @@ __global__ __launch_bounds__(kThreads) void pack_wide_kernel(
 // The runs that overlap slots [gs_lo, gs_hi), the last of which that there is lies at or before `slot_hi` - 1, from the plan's tables, a
 // thread to a shuffled position of the blocks that the slots touch: put(index, run), in destination order.  Returns how many there
 // are.  Called by the whole workgroup; what it put is there for all behind a barrier.
+// Of more positions than threads, the one that the slots begin in is searched first, every wave for itself, and only as many
+// are looked at from there on as the slots can hold: a look is five scattered loads, and thousands of workgroups make
+// them (30000 sequences of one 512-byte frame in a block 17.7 us with a run table, 30.7 where 256 positions were tried and 256
+// looked at, 14.4 like this; with 16 or 64 ways 15.4 and 14.8).
+constexpr int kFindWays = 32;
 template <typename Put>
 __device__ __forceinline__ int32_t find_runs(const PackArgs& a, const PlanTables& t, int64_t num_blocks, double inv_t_blk, int64_t gs_lo,
                                              int64_t slot_hi, int64_t gs_hi, Put put)
@@ -521,20 +526,29 @@ __device__ __forceinline__ int32_t find_runs(const PackArgs& a, const PlanTables
     const int64_t b0 = floor_div(gs_lo, T, inv_t_blk), b1 = floor_div(slot_hi - 1, T, inv_t_blk);
     int32_t first = min(max(t.block_first[b0], 0), a.n_seq);
     const int32_t last = min(max(t.block_first[b1 + 1], first), a.n_seq);
-    // of many positions, the last of 256 evenly spaced ones that starts at or before the slots
+    int32_t looks = kThreads;
     if (last - first > kThreads) {
-        const int32_t step = (last - first + kThreads - 1) / kThreads;
-        const int32_t p = first + tid * step;
-        const int before = __syncthreads_count(p < last && run_at_position(t, p, a.n_seq, num_blocks, T).dst <= gs_lo);
-        first += max(before - 1, 0) * step;
+        const int32_t rel = (int32_t)(gs_lo - b0 * T);
+        int32_t above = min(max(t.block_first[b0 + 1], first), last);
+        while (above - first > 1) {
+            const int32_t step = (above - first + kFindWays - 1) / kFindWays, at = lane_id() * step;
+            bool in_front = false;
+            if (lane_id() < kFindWays && at < above - first) {
+                const uint32_t i = (uint32_t)t.order[first + at];
+                in_front = i < (uint32_t)a.n_seq && t.offset_of_seq[i] <= rel;
+            }
+            first += max((int32_t)__popcll(__ballot(in_front)) - 1, 0) * step;
+            above = min(above, first + step);
+        }
+        looks = (int32_t)min((int64_t)kThreads, gs_hi - gs_lo + 1);
     }
     int32_t n = 0;
-    for (int32_t p0 = first; p0 < last; p0 += kThreads) {
+    for (int32_t p0 = first; p0 < last; p0 += looks) {
         Run r{kNoRun, 0, 0, -1, -1, 0};
-        if (p0 + tid < last) r = run_at_position(t, p0 + tid, a.n_seq, num_blocks, T);
+        if (tid < looks && p0 + tid < last) r = run_at_position(t, p0 + tid, a.n_seq, num_blocks, T);
         const bool here = r.dst < gs_hi && r.dst + r.len > gs_lo;
         const uint64_t vote = __ballot(here);
-        const int behind = __syncthreads_or(r.dst >= gs_hi);       // (also a barrier behind the counts of the round before)
+        const int behind = __syncthreads_or(tid < looks && r.dst >= gs_hi);      // (also a barrier behind the counts of the round before)
         if (lane_id() == 0) s_found[wave_id()] = (int32_t)__popcll(vote);
         __syncthreads();
         int32_t at = n + (int32_t)__popcll(vote & ((1ull << lane_id()) - 1ull));
@@ -1024,9 +1038,12 @@ constexpr int kPassGroup = 2;
 // Up to so many workgroups, every one looks up its tile's runs itself, in one launch (pack_direct_kernel): 64 clips of 3 KB frames 11.4 -> 8.2
 // us, 3000 sequences of two 700-byte frames 13.4 -> 9.2, 18 MB of 320-byte frames 23.5 -> 21; 8192 tiles: 19.4 -> 20.4.  Slot tiles:
 // 300 sequences of tokens 10.7 -> 8.0, 400 of 63-byte frames 22.5 -> 16.2, 4 MB of 40-byte frames 14.8 -> 11.9, 3000 full ones of 60
-// bytes 64 -> 62; but not tiles of more than 256 sequences that several workgroups share, each of which would look them all up
-// (20000 sequences of three 64-byte frames in blocks of 6000: 12.3 us, 15.3).
-constexpr int64_t kDirectTiles = 4096;
+// bytes 64 -> 62.  Every workgroup of a slot tile looks up all of its runs, five scattered loads each: with one to a tile 500000 sequences
+// are fine (of one byte each 46 -> 38 us, of two tokens in blocks of 10^6 slots 45.5 -> 42), 600000 are not (of two tokens
+// 48.6 and 52, 900000 75 and 84); where several share a tile, not more than 2^18 looks (20000 sequences of ten 64-byte frames, 21 to a
+// tile, 14.6 us and 17.7, 6000 of ten 250-byte frames, 63, 18.9 and 21.1; 2000 of ten 400-byte frames, 100 to a tile, 11.7 -> 9.3), and
+// no tiles of more than 256 sequences (20000 of one 40-byte frame 13.0 us, 13.5).
+constexpr int64_t kDirectTiles = 4096, kDirectMost = (int64_t)1 << 19, kDirectLooks = (int64_t)1 << 18;
 
 // Sizes the caller cannot know in advance (which tile shape the lengths will choose) are
 // taken at their larger value when `for_query`.
@@ -1171,7 +1188,8 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
                            1.0 / (double)frame_bytes, 1.0 / (double)t_blk);
         return launch_status();
     }
-    if (!l.wide && !two_passes && l.tiles * parts <= kDirectTiles && (parts == 1 || n_seq * 4 <= a.total_slots)) {
+    const bool looks_pay = parts == 1 ? n_seq <= kDirectMost : n_seq * parts <= kDirectLooks && n_seq * 4 <= a.total_slots;
+    if (!l.wide && !two_passes && l.tiles * parts <= kDirectTiles && looks_pay) {
         with_element(a, [&](auto element, auto fused) {
             hipLaunchKernelGGL((pack_narrow_direct_kernel<decltype(element), decltype(fused)::value>), dim3((uint32_t)(l.tiles * parts)),
                                dim3(kThreads), 0, stream, a, t, num_blocks, 1.0 / (double)t_blk, parts);

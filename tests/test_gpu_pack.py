@@ -237,12 +237,13 @@ def test_pack_slot_tiles_in_shares(F, tiles):
 @pytest.mark.parametrize("F", [1, 4, 7, 62, 64, 100, 600])
 def test_pack_looks_runs_up_in_the_plan(F):
     """Calls of few tiles find their runs in the plan's tables: blocks of as many sequences as a workgroup looks at at once,
-    one fewer and one more, of thousands (which it narrows down first), dozens of blocks to a tile, short sequences beside
-    long ones; bytes must be equal."""
+    one fewer and one more, of thousands and of hundreds of thousands (among which it searches its first), many blocks of
+    some hundreds, dozens of blocks to a tile, short sequences beside long ones; bytes must be equal."""
     rng = np.random.default_rng(F)
     some = np.where(rng.random(4000) < 0.97, 1, rng.integers(500, 3000, size=4000))
     for T, L in [(300, np.ones(255)), (300, np.ones(256)), (300, np.ones(257)), (600, np.ones(513)), (6000, np.ones(13001)),
-                 (7000, rng.integers(1, 4, size=9000)), (1, np.ones(3000)), (3, rng.integers(1, 4, size=3000)), (7000, some)]:
+                 (7000, rng.integers(1, 4, size=9000)), (1, np.ones(3000)), (3, rng.integers(1, 4, size=3000)), (7000, some),
+                 (40000, np.ones(33000)), (40000, rng.integers(1, 40, size=5000)), (300000, np.ones(300000)), (1100, rng.integers(1, 5, size=60000))]:
         L = L.astype(np.int32)
         if int(L.sum()) * F > 40_000_000:
             L = L[:max(1, 40_000_000 * len(L) // (int(L.sum()) * F))]
@@ -255,7 +256,8 @@ def test_pack_looks_runs_up_in_the_plan(F):
         assert_packed_equal(out, ref, f"F={F} n={len(L)} T={T}: ")
 
 
-@pytest.mark.parametrize("F,n", [(4096, 4096), (4096, 4097), (9, 4096 * 1024), (9, 4096 * 1024 + 1), (64, 1023 * 1024)])
+@pytest.mark.parametrize("F,n", [(4096, 4096), (4096, 4097), (9, 4096 * 1024), (9, 4096 * 1024 + 1), (64, 1023 * 1024),
+                                 (3, 1 << 19), (3, (1 << 19) + 1)])
 def test_pack_with_and_without_a_run_table(F, n):
-    """The last number of tiles that find their runs themselves and the first that are given them."""
+    """The last number of tiles, and of sequences, that find their runs themselves and the first that are given them."""
     run_case(n, 1, F, "uniform", seed=1)
