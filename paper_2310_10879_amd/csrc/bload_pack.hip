@@ -178,18 +178,41 @@ static_assert(kWideTile / kWideMinFrame + 2 <= kWideRuns, "a tile's runs must fi
 typedef vec16 __attribute__((aligned(1))) vec16_unaligned;
 
 // How the payload passes the caches (pack_traffic).
-enum PackTraffic : int { kPackStream = 0, kPackCached = 1, kPackPlain = 2 };
+enum PackTraffic : int {
+    kPackStream = 0,     // streaming loads and stores
+    kPackCached = 1,     // plain loads (slot tiles)
+    kPackThrough = 2,    // stores go through the XCD's cache at once and stay in the memory-side cache (4 KiB tiles)
+};
+
+// A 16-byte buffer store of device scope (sc1 of its cache policy) writes whole lines through at once, where plain stores leave
+// them as modified lines in the XCD's cache, whose write-back the call's end waits for: 67 MB of 80 floats from a source in
+// memory 32.8 us streamed, 35.0 with plain stores and loads, 32.6 like this.
+constexpr int kDeviceScope = 16;
+constexpr int kRawBuffer = 0x00027000;              // a buffer's fourth word: untyped, addressed in bytes
 
 template <int TRAFFIC>
 __device__ __forceinline__ vec16 load_source(const uint8_t* p)
 {
     const vec16_unaligned* v = reinterpret_cast<const vec16_unaligned*>(p);
-    return TRAFFIC == kPackStream ? __builtin_nontemporal_load(v) : *v;
+    return TRAFFIC == kPackCached ? *v : __builtin_nontemporal_load(v);
 }
+// Vector `at` of the 4 KiB tile that begins at `tile` (the same for the whole wave).
 template <int TRAFFIC>
-__device__ __forceinline__ void store_packed(vec16* p, vec16 v)
+__device__ __forceinline__ void store_packed(vec16* tile, int at, vec16 v)
 {
-    if (TRAFFIC == kPackPlain) *p = v;
+    if (TRAFFIC != kPackThrough) {
+        store_stream(tile + at, v);
+        return;
+    }
+    const __amdgpu_buffer_rsrc_t lines = __builtin_amdgcn_make_buffer_rsrc(tile, 0, kWideTile, kRawBuffer);
+    __builtin_amdgcn_raw_buffer_store_b128(v, lines, 16 * at, 0, kDeviceScope);
+}
+// A vector of a tile that is written in parts, byte by byte where they meet.  Lines in parts do not go through: plain
+// stores let them meet in the XCD's cache first (40 MB of 74-byte frames 37 us with parts written through, 29).
+template <int TRAFFIC>
+__device__ __forceinline__ void store_part(vec16* p, vec16 v)
+{
+    if (TRAFFIC == kPackThrough) *p = v;
     else store_stream(p, v);
 }
 
@@ -227,23 +250,23 @@ __device__ __forceinline__ void write_range(uint8_t* packed, int64_t lo, int64_t
     int v = tid;
     if (ZERO) {
         const vec16 z = {0u, 0u, 0u, 0u};
-        for (; v < nv; v += kThreads) store_packed<TRAFFIC>(d + v, z);
+        for (; v < nv; v += kThreads) store_part<TRAFFIC>(d + v, z);
     } else {
         for (; v + 3 * kThreads < nv; v += 4 * kThreads) {
             const vec16 x0 = load_source<TRAFFIC>(s + 16 * (int64_t)v);
             const vec16 x1 = load_source<TRAFFIC>(s + 16 * (int64_t)(v + kThreads));
             const vec16 x2 = load_source<TRAFFIC>(s + 16 * (int64_t)(v + 2 * kThreads));
             const vec16 x3 = load_source<TRAFFIC>(s + 16 * (int64_t)(v + 3 * kThreads));
-            store_packed<TRAFFIC>(d + v, x0);
-            store_packed<TRAFFIC>(d + v + kThreads, x1);
-            store_packed<TRAFFIC>(d + v + 2 * kThreads, x2);
-            store_packed<TRAFFIC>(d + v + 3 * kThreads, x3);
+            store_part<TRAFFIC>(d + v, x0);
+            store_part<TRAFFIC>(d + v + kThreads, x1);
+            store_part<TRAFFIC>(d + v + 2 * kThreads, x2);
+            store_part<TRAFFIC>(d + v + 3 * kThreads, x3);
         }
-        for (; v < nv; v += kThreads) store_packed<TRAFFIC>(d + v, load_source<TRAFFIC>(s + 16 * (int64_t)v));
+        for (; v < nv; v += kThreads) store_part<TRAFFIC>(d + v, load_source<TRAFFIC>(s + 16 * (int64_t)v));
     }
 }
 
-// The start-table entry of one slot (frame index -1: padding).  Streamed like the payload: plain
+// The start-table entry of one slot (frame index -1: padding).  Streamed like the payload of large tensors: plain
 // stores leave these planes (a gigabyte at 10^8 slots) as modified lines in the memory-side
 // cache, and a consumer that streams the packed tensor right afterwards then reads about a tenth
 // slower (measured: the reduction of 3000 x 320-byte blocks takes 3.98 ms alone and 4.45 ms
@@ -251,7 +274,7 @@ __device__ __forceinline__ void write_range(uint8_t* packed, int64_t lo, int64_t
 template <int TRAFFIC = kPackStream>
 __device__ __forceinline__ void store_slot(const PackArgs& a, int64_t slot, int32_t seq, int32_t fid)
 {
-    if (TRAFFIC == kPackPlain) {
+    if (TRAFFIC == kPackThrough) {
         a.seq_id[slot] = seq;
         a.frame_idx[slot] = fid;
         a.reset[slot] = (uint8_t)(fid == 0);
@@ -342,14 +365,12 @@ __device__ __forceinline__ void write_wide_tile(const PackArgs& a, const WideRun
         int k = run_at(x0);
         const int64_t next_lo = r.lo[k + 1];
         const int64_t lo = k >= 0 ? r.lo[k] : 0, hi = k >= 0 ? r.hi[k] : 0;
-        vec16* dst = reinterpret_cast<vec16*>(a.packed + x0);
-        if (x0 + 16 <= D1 && x0 + 16 <= hi) {                           // inside one run
-            const uint8_t* from = a.src + r.src[k] + (x0 - lo);
-            store_packed<TRAFFIC>(dst, load_source<TRAFFIC>(from));
-        } else if (x0 + 16 <= D1 && x0 >= hi && x0 + 16 <= next_lo) {   // inside a block's zero tail
-            const vec16 z = {0u, 0u, 0u, 0u};
-            store_packed<TRAFFIC>(dst, z);
-        } else {
+        // (one store for whatever a lane's vector is, so that a wave's goes out as whole lines)
+        const bool whole = x0 + 16 <= D1;
+        vec16 v = {0u, 0u, 0u, 0u};
+        if (whole && x0 + 16 <= hi) {                                   // inside one run
+            v = load_source<TRAFFIC>(a.src + r.src[k] + (x0 - lo));
+        } else if (!(whole && x0 >= hi && x0 + 16 <= next_lo)) {        // not inside a block's zero tail
             // a border inside: byte by byte, all of them asked for before the first is stored
             uint32_t bytes[16];
 #pragma unroll
@@ -359,17 +380,15 @@ __device__ __forceinline__ void write_wide_tile(const PackArgs& a, const WideRun
                 bytes[j] = 0;
                 if (k >= 0 && x < r.hi[k] && x < D1) bytes[j] = a.src[r.src[k] + (x - r.lo[k])];
             }
-            if (x0 + 16 <= D1) {
-                vec16 v;
 #pragma unroll
-                for (int w = 0; w < 4; ++w) v[w] = bytes[4 * w] | bytes[4 * w + 1] << 8 | bytes[4 * w + 2] << 16 | bytes[4 * w + 3] << 24;
-                store_packed<TRAFFIC>(dst, v);
-            } else {
+            for (int w = 0; w < 4; ++w) v[w] = bytes[4 * w] | bytes[4 * w + 1] << 8 | bytes[4 * w + 2] << 16 | bytes[4 * w + 3] << 24;
+            if (!whole) {
 #pragma unroll
                 for (int j = 0; j < 16; ++j)
                     if (x0 + j < D1) a.packed[x0 + j] = (uint8_t)bytes[j];
             }
         }
+        if (whole) store_packed<TRAFFIC>(reinterpret_cast<vec16*>(a.packed + D0), (int)((x0 - D0) / 16), v);
     }
     if (table_wave) {
         for (int64_t slot = m_lo + lane_id(); slot < m_hi; slot += kWave) {
@@ -414,7 +433,7 @@ __global__ __launch_bounds__(kThreads) void pack_wide_kernel(
             const int64_t run_lo = g * F;
             if (run_lo <= D0 && run_lo + len * F >= D0 + tile_bytes && D0 + tile_bytes <= total_bytes) {
                 const uint8_t* s = a.src + r.src * F + (D0 - run_lo) + 16 * (int64_t)threadIdx.x;
-                store_packed<TRAFFIC>(reinterpret_cast<vec16*>(a.packed + D0) + threadIdx.x, load_source<TRAFFIC>(s));
+                store_packed<TRAFFIC>(reinterpret_cast<vec16*>(a.packed + D0), (int)threadIdx.x, load_source<TRAFFIC>(s));
                 if (table_wave) {
                     // frames t of this run with D0 <= run_lo + t * F < D1
                     for (int64_t t = floor_div(D0 - run_lo + F - 1, F, inv_frame_bytes) + lane_id();
@@ -427,7 +446,7 @@ __global__ __launch_bounds__(kThreads) void pack_wide_kernel(
             // next most common: the tile lies in the zero tail of the run's block
             if (run_lo + len * F <= D0 && ((int64_t)r.block + 1) * T * F >= D0 + tile_bytes) {
                 const vec16 z = {0u, 0u, 0u, 0u};
-                store_packed<TRAFFIC>(reinterpret_cast<vec16*>(a.packed + D0) + threadIdx.x, z);
+                store_packed<TRAFFIC>(reinterpret_cast<vec16*>(a.packed + D0), (int)threadIdx.x, z);
                 if (table_wave) {
                     for (int64_t slot = floor_div(D0 + F - 1, F, inv_frame_bytes) + lane_id(); slot * F < D1;
                          slot += kWave) {
@@ -1094,19 +1113,22 @@ bload_status pack_check_args(const void* d_src, const int64_t* d_src_offsets, co
 }
 
 // How a call reads its source and writes its payload.
-//   - Packed tensor, source and table of 256 MB in all (the source taken as long as the packed tensor: what the host knows),
-//     4 KiB tiles: plain loads and stores.  Source and payload stay in the memory-side cache, where a consumer finds them.  Pack
-//     and reduction of 3001 sequences of 37 halfs, 86 MB, in turn 89 -> 68 us, 75 where each pack has another source; of 250
-//     sequences of 80 floats, 118 MB, 97 -> 85 and 86; 60 of them 41 -> 37 and 39; with the scan 127 -> 109 and 108.  Packs alone, the same
-//     source again and again: 50 -> 39, 52 -> 49, 11 and 13 us; another source each time 3 to 5 % slower.
-//   - Up to 300 MB: plain loads.  100 floats, 200 MB 82 -> 65 us, 37 halfs, 220 MB 111 -> 88, tokens, 220 MB 238 -> 210;
-//     sources from elsewhere 1 to 4 % slower.  Plain stores as well: 88, 127 and 266 us.
-//   - Larger ones pass by: 1.5 GB of 320-byte frames 595 us, 630 with plain loads, 660 with plain stores as well.
-// Slot tiles never store plainly: five streams of parts of lines (20-byte frames 47 us, 60).
+//   - 4 KiB tiles, packed tensor, source and table of 256 MB in all (the source taken as long as the packed tensor: what the host
+//     knows): the payload is written through and the table plainly, so that a consumer finds both in the memory-side cache.  Pack
+//     and reduction, each pack from another source, before and after: 1000 sequences of 37 halfs, 28 MB, 49 -> 49 us, 3001 of them 92 -> 74, 20 of
+//     video, 65 MB, 52 -> 46, 312 of 128 floats, 76 MB, 61 -> 53.5; with the scan 59 -> 52, 149 -> 124, 100 -> 86, 81 -> 69.
+//   - Their sources are streamed, at any size.  With plain loads the same source again and again comes from the cache (86 MB 48
+//     -> 41 us), but one that is read once pushes out what others left there: behind a kernel that wrote a gigabyte the same
+//     pack takes 67 us, 53 like this, 94 MB of 80 floats 63 and 46, 220 MB 156 and 117.  Larger tensors stream their payload,
+//     too: it would not stay.
+//   - Slot tiles of up to 128 MB of payload: plain loads, since their lanes look for elements here and there: 40 MB of halfs one a
+//     frame 94 -> 66 us where the source is in the cache, 45 MB of 9-byte frames 53 -> 41; where it is not, even; behind a kernel
+//     that wrote a gigabyte 118 and 118, 63 and 64.5, 40 MB of tokens 59 and 63 (160 MB 194 and 216: hence the line).  They stream their stores:
+//     five streams of parts of lines (20-byte frames 47 us, 60 with plain stores).
 static PackTraffic pack_traffic(int64_t total_slots, int64_t total_bytes, bool wide)
 {
-    if (wide && 2 * total_bytes + 10 * total_slots <= ((int64_t)256 << 20)) return kPackPlain;
-    return total_bytes <= ((int64_t)300 << 20) ? kPackCached : kPackStream;
+    if (wide) return 2 * total_bytes + 10 * total_slots <= ((int64_t)256 << 20) ? kPackThrough : kPackStream;
+    return total_bytes <= ((int64_t)128 << 20) ? kPackCached : kPackStream;
 }
 
 template <int TRAFFIC>
@@ -1184,7 +1206,7 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
 
     const PlanTables t{d_src_offsets, d_lengths, d_order, d_block_of_seq, d_offset_of_seq, d_block_first};
     if (l.wide && l.tiles <= kDirectTiles) {
-        hipLaunchKernelGGL(pack_direct_kernel<kPackPlain>, dim3((uint32_t)l.tiles), dim3(kThreads), 0, stream, a, t, num_blocks,
+        hipLaunchKernelGGL(pack_direct_kernel<kPackThrough>, dim3((uint32_t)l.tiles), dim3(kThreads), 0, stream, a, t, num_blocks,
                            1.0 / (double)frame_bytes, 1.0 / (double)t_blk);
         return launch_status();
     }
@@ -1209,8 +1231,7 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
     const uint32_t n_tiles = (uint32_t)l.tiles;
     const PackTraffic traffic = pack_traffic(a.total_slots, a.total_slots * frame_bytes, l.wide);
     if (l.wide) {
-        const auto launch = traffic == kPackPlain ? pack_launch_wide<kPackPlain> : traffic == kPackCached ? pack_launch_wide<kPackCached>
-                                                                                                       : pack_launch_wide<kPackStream>;
+        const auto launch = traffic == kPackThrough ? pack_launch_wide<kPackThrough> : pack_launch_wide<kPackStream>;
         launch(a, runs, first_pos, n_tiles, inv_unit, l.table_tiles == 0 ? 1 : 0, stream);
         if (l.table_tiles > 0)
             hipLaunchKernelGGL((pack_narrow_kernel<uint8_t, false, kPackStream, false, true, kPassGroup>),
