@@ -719,20 +719,25 @@ static int32_t scan_staged_slots(int32_t groups, int32_t t_blk)
 }
 
 // How direct tiles of 32 slots a lane read and write.
-//   - Input that fits the memory-side cache is read with plain loads, from there where it was just written or read: 200 MB,
-//     3104 halfs 122 -> 91 us, 208 bytes 134 -> 100, 320 floats 83 -> 69; up to 30 MB even.
+//   - Input that bload_pack leaves in the memory-side cache (256 MB of packed tensor, source and table) is read with plain loads
+//     from there.  Scans behind a pack of the same tensor: 50 MB of 2048 halfs 43 -> 38 us, 94 MB of 320 bytes 67 -> 52, 640 bytes, 50 MB 78 -> 57; of
+//     an input that lies in memory only 0 to 5 % slower (25 MB of 2048 halfs 21.8 us, 22.9).  Larger input is streamed: up to 256 MB plain
+//     loads gained where the same tensor is scanned again and again (204 MB of 80 floats 89 -> 72 us), but behind a kernel that wrote a
+//     gigabyte the input pushed its lines out: 300 MB of 2048 halfs 124 us streamed, 147; 200 MB of 256 floats 88 and 107.
 //   - Where output lines are written by two workgroups (frames of several slices) or twice by one (frames that are no whole
 //     half lines), in parts, streaming stores send both parts to memory; plain ones meet in the cache.  270 halfs, 1.2
 //     GB: 1034 -> 820 us, 2415 of them 1710 -> 1504, 72 bytes 868 -> 736, 100 floats 504 -> 454; whole lines lose as much by it (256 floats 372
 //     -> 418), and single slices from 192 elements on gain nothing (250 halfs 764 and 780).  Input and output of 300 MB in all stay in
-//     the cache (944 bytes of 50 MB 68 -> 46); more than that would push input out that fits (250 floats, 216 MB: 93 us with
-//     plain loads alone, 117).
+//     the cache (540 bytes, 50 MB 58 -> 42; 400 bytes, 51 MB 35 -> 28, from memory only 31.4 and 33.1); below 40 MB the write-back at
+//     the call's end costs more than that (400 bytes, 26 MB from memory 17.2 us, 20.2).
 static ScanTraffic scan_traffic(int64_t elems, size_t elem, int64_t feat_dim, bool one_slice)
 {
-    const bool cached = elems * (int64_t)elem <= ((int64_t)256 << 20);
+    const int64_t bytes = elems * (int64_t)elem;
+    const bool kept = 2 * bytes + 10 * (elems / feat_dim) <= ((int64_t)256 << 20);
     const bool parts = one_slice ? feat_dim % (kScanLine / 2) != 0 && feat_dim < 192 : feat_dim % kScanLine != 0;
-    if (parts && (!cached || elems * (int64_t)(elem + 4) <= ((int64_t)300 << 20))) return kScanPlain;
-    return cached ? kScanCached : kScanStream;
+    if (parts && bytes > ((int64_t)256 << 20)) return kScanPlain;
+    if (parts && kept && bytes >= ((int64_t)40 << 20) && bytes + 4 * elems <= ((int64_t)300 << 20)) return kScanPlain;
+    return kept ? kScanCached : kScanStream;
 }
 
 // `walk`: a block's tiles go to one workgroup, as long as there are.  `lines`: slices of whole cache lines.
