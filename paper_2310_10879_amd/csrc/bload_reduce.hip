@@ -118,13 +118,6 @@ template <> struct LaneBits<4> { typedef uint32_t T; typedef uint32_t __attribut
 template <> struct LaneBits<2> { typedef uint16_t T; typedef uint16_t __attribute__((aligned(1))) Any; };
 template <> struct LaneBits<1> { typedef uint8_t T; typedef uint8_t Any; };
 
-template <bool STREAM>
-__device__ __forceinline__ vec16 load_any(const uint8_t* p)
-{
-    const vec16_any* v = reinterpret_cast<const vec16_any*>(p);
-    return STREAM ? __builtin_nontemporal_load(v) : *v;
-}
-
 // STREAM: a streaming load, for tensors that do not fit the memory-side cache.  Rows of narrow lanes
 // share cache lines with the rows beside them, which a streaming load would fetch again (78 slots x
 // 271 int32: 174 us, 143 us with plain loads), and what fits the cache is worth keeping there (4300
@@ -625,7 +618,6 @@ struct LaneFlagBytes {
     bool wave_plain;       // the wave holds nothing but valid slots without a start flag
 };
 
-template <bool STREAM>
 __device__ __forceinline__ LaneFlagBytes narrow_flag_bytes(const ReduceArgs& a, const NarrowTile& tile)
 {
     constexpr int SPL = kSlotsPerLane;
@@ -636,8 +628,8 @@ __device__ __forceinline__ LaneFlagBytes narrow_flag_bytes(const ReduceArgs& a, 
     b.valid = vec16{0u, 0u, 0u, 0u};
     b.reset = vec16{0u, 0u, 0u, 0u};
     if (left >= SPL) {
-        b.valid = load_any<STREAM>(a.valid + tile.g0 + pos0);
-        b.reset = load_any<STREAM>(a.reset + tile.g0 + pos0);
+        b.valid = __builtin_nontemporal_load(reinterpret_cast<const vec16_any*>(a.valid + tile.g0 + pos0));
+        b.reset = __builtin_nontemporal_load(reinterpret_cast<const vec16_any*>(a.reset + tile.g0 + pos0));
     }
     // Two kinds of waves are common in packed blocks and need no byte-by-byte look at their
     // flags: nothing but padding (block tails), and nothing but valid slots without a start flag
@@ -749,12 +741,11 @@ struct NarrowRows {
     static constexpr int NV = NarrowStage<ElemT>::NV;
     vec16 v[NV > 0 ? NV : 1];
 
-    template <bool STREAM>
     __device__ __forceinline__ void issue(const ReduceArgs& a, int64_t wave_s0)
     {
-        const uint8_t* row = a.packed + wave_s0 * (int64_t)sizeof(ElemT) + 16 * lane_id();
+        const vec16_any* row = reinterpret_cast<const vec16_any*>(a.packed + wave_s0 * (int64_t)sizeof(ElemT));
 #pragma unroll
-        for (int k = 0; k < NV; ++k) v[k] = load_any<STREAM>(row + 16 * kWave * k);
+        for (int k = 0; k < NV; ++k) v[k] = __builtin_nontemporal_load(row + k * kWave + lane_id());
     }
     __device__ __forceinline__ void finish(vec16* stage, ElemT (&raw)[kSlotsPerLane])
     {
@@ -788,7 +779,7 @@ struct NarrowRows {
 
 // The lane's 16 elements where they do not come as rows; only those of valid slots mean anything.
 // `left` = slots from the lane's first one to the tile's end.
-template <typename ElemT, bool STREAM>
+template <typename ElemT>
 __device__ __forceinline__ void narrow_load(const ReduceArgs& a, int64_t s0, int32_t left, ElemT (&raw)[kSlotsPerLane])
 {
     constexpr int SPL = kSlotsPerLane;
@@ -797,7 +788,7 @@ __device__ __forceinline__ void narrow_load(const ReduceArgs& a, int64_t s0, int
     if (left >= SPL) {
         union { vec16 v[NV > 0 ? NV : 1]; ElemT e[SPL]; } u;
 #pragma unroll
-        for (int k = 0; k < NV; ++k) u.v[k] = load_any<STREAM>(from + 16 * k);
+        for (int k = 0; k < NV; ++k) u.v[k] = __builtin_nontemporal_load(reinterpret_cast<const vec16_any*>(from) + k);
 #pragma unroll
         for (int j = 0; j < SPL; ++j) raw[j] = u.e[j];
     } else if (left > 0) {
@@ -875,7 +866,7 @@ __device__ __forceinline__ void emit_piece(const ReduceArgs& a, int64_t q, int d
     }
 }
 
-template <typename ElemT, bool STREAM>
+template <typename ElemT>
 __global__ __launch_bounds__(kThreads) void reduce_narrow_kernel(ReduceArgs a)
 {
     typedef typename Elem<ElemT>::Acc Acc;
@@ -897,14 +888,14 @@ __global__ __launch_bounds__(kThreads) void reduce_narrow_kernel(ReduceArgs a)
     const int pos0 = tid * SPL;
     const int64_t s0 = g0 + pos0;
     if (tid == 0) s_desc = ChunkDesc{kHeadNone, 0, 0, -1};
-    const LaneFlagBytes bytes = narrow_flag_bytes<STREAM>(a, tile);
+    const LaneFlagBytes bytes = narrow_flag_bytes(a, tile);
     // a wave without a valid slot reads no payload; a wave that lies whole in the tile asks for
     // its rows now, before the flags are looked at
     const bool wave_valid = !bytes.wave_blank;
     const int32_t left = tile.n - pos0;
     const bool by_rows = NarrowStage<ElemT>::NV > 1 && left - (kWave - 1 - lane) * SPL >= SPL;
     NarrowRows<ElemT> rows;
-    if (wave_valid && by_rows) rows.template issue<STREAM>(a, s0 - lane * SPL);
+    if (wave_valid && by_rows) rows.issue(a, s0 - lane * SPL);
     const LaneFlags f = narrow_lane_flags(a, tile, bytes);
     const uint32_t bmask = f.bmask;
     const unsigned long long wave_breaks = __ballot(bmask != 0);
@@ -931,7 +922,7 @@ __global__ __launch_bounds__(kThreads) void reduce_narrow_kernel(ReduceArgs a)
     } else {
         ElemT raw[SPL];
         if (by_rows) rows.finish(s_stage, raw);
-        else narrow_load<ElemT, STREAM>(a, s0, left, raw);
+        else narrow_load<ElemT>(a, s0, left, raw);
         if (wave_breaks == 0) {
             // no break in the whole wave (so every slot is valid): plain sums
 #pragma unroll
@@ -1971,15 +1962,11 @@ static void launch_reduce(const ReducePlan& p, const ReduceArgs& a, hipStream_t 
         else launch_wide<ElemT, 1, false>(p, a, stream);
     } else {
         const dim3 grid((uint32_t)p.total_chunks), block(kThreads);
-        // One element a frame: bytes and halfs are read with plain loads where they fit the memory-side cache with their flags
-        // and sequence ids (60 MB of halfs 61 -> 48 us, of bytes 55 -> 48; twice as many: even); 4-byte elements lose as often
-        // as they gain (60 MB 21.4 and 21.2, 220 MB 65 and 70).
-        constexpr bool kSmall = sizeof(ElemT) <= 2;
-        const bool cached = kSmall && a.total_slots * (int64_t)(sizeof(ElemT) + 6) <= ((int64_t)450 << 20);
-        if (!p.staged && cached)
-            hipLaunchKernelGGL((reduce_narrow_kernel<ElemT, !kSmall>), grid, block, 0, stream, a);
-        else if (!p.staged)
-            hipLaunchKernelGGL((reduce_narrow_kernel<ElemT, true>), grid, block, 0, stream, a);
+        // (One element a frame: streaming loads at any size.  A pack leaves no such tensor in the cache, so plain loads find only
+        // what a reduction before left there (60 MB of halfs 61 -> 48 us), and behind a kernel that wrote a gigabyte they push its
+        // lines out: 64 MB of halfs 68 us, 84, 29 MB of bytes 56 and 66.)
+        if (!p.staged)
+            hipLaunchKernelGGL(reduce_narrow_kernel<ElemT>, grid, block, 0, stream, a);
         else if (p.run)
             hipLaunchKernelGGL((reduce_staged_kernel<ElemT, kStagedSlots, true>), grid, block, 0, stream, a);
         else if (p.slots == kStagedSlots)
