@@ -318,6 +318,14 @@ bload_status bload_pack_check(const int64_t* d_src_offsets, const int32_t* d_len
 size_t bload_segment_reduce_workspace_bytes(int64_t num_blocks, int32_t t_blk, int64_t feat_dim,
                                             bload_dtype dtype);
 
+/* Which of its layouts bload_segment_reduce takes for these sizes with so many bytes of
+ * (aligned) workspace, and into how many chunks of time or tiles it cuts the blocks
+ * (*h_chunks, which may be NULL): BLOAD_REDUCE_NONE and 0 for empty calls and sizes that
+ * it refuses.  For profiling, reports and tests; what it answers may change. */
+enum { BLOAD_REDUCE_NONE = 0, BLOAD_REDUCE_WIDE = 1, BLOAD_REDUCE_STAGED = 2, BLOAD_REDUCE_FLAT = 3, BLOAD_REDUCE_NARROW = 4 };
+int32_t bload_segment_reduce_layout(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, bload_dtype dtype,
+                                    int64_t n_seq, size_t workspace_bytes, int64_t* h_chunks);
+
 bload_status bload_segment_reduce(const void* d_packed, const int32_t* d_seq_id,
                                   const uint8_t* d_reset, const uint8_t* d_valid,
                                   int64_t num_blocks, int32_t t_blk, int64_t feat_dim,

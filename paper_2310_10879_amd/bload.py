@@ -85,6 +85,8 @@ _lib.bload_segment_scan_workspace_bytes.restype = _sz
 _lib.bload_segment_scan_workspace_bytes.argtypes = [_i64, _i32, _i64, ctypes.c_int]
 _lib.bload_segment_reduce_workspace_bytes.restype = _sz
 _lib.bload_segment_reduce_workspace_bytes.argtypes = [_i64, _i32, _i64, ctypes.c_int]
+_lib.bload_segment_reduce_layout.restype = _i32
+_lib.bload_segment_reduce_layout.argtypes = [_i64, _i32, _i64, ctypes.c_int, _i64, _sz, ctypes.POINTER(_i64)]
 _lib.bload_segment_reduce.restype = ctypes.c_int
 _lib.bload_segment_reduce.argtypes = [_vp, _vp, _vp, _vp, _i64, _i32, _i64, ctypes.c_int,
                                       ctypes.c_int, _i64, _vp, _vp, _sz, _vp]
@@ -388,6 +390,21 @@ def bload_segment_scan(packed: torch.Tensor, reset: torch.Tensor, valid: torch.T
                                  _ptr(out, torch.float32), _ptr(workspace), _room(workspace), _stream())
     _check(st)
     return out
+
+
+REDUCE_LAYOUTS = ("none", "wide", "staged", "flat", "narrow")
+
+
+def bload_segment_reduce_layout(num_blocks: int, t_blk: int, feat_dim: int, dtype: str, n_seq: int,
+                                workspace_bytes: int | None = None) -> tuple[str, int]:
+    """Which layout ``bload_segment_reduce`` takes for these sizes, and into how many chunks or tiles it
+    cuts the blocks, with a workspace of that size (default: what its query answers)."""
+    if workspace_bytes is None:
+        workspace_bytes = bload_segment_reduce_workspace_bytes(num_blocks, t_blk, feat_dim, dtype)
+    chunks = _i64(0)
+    layout = _lib.bload_segment_reduce_layout(num_blocks, t_blk, feat_dim, DTYPES[dtype], n_seq, workspace_bytes,
+                                              ctypes.byref(chunks))
+    return REDUCE_LAYOUTS[layout], int(chunks.value)
 
 
 def bload_pack_tile_bytes(n_seq: int, num_blocks: int, t_blk: int, frame_bytes: int,

@@ -1255,7 +1255,7 @@ __global__ __launch_bounds__(kThreads) void reduce_staged_kernel(ReduceArgs a)
 //
 // Frames of few bytes in pieces that are long beside them: a wave takes the bytes of a piece as one flat stream, 16 to a
 // lane, whatever a frame is.  The least common multiple of a frame and a vector is `P` vectors (of 74 bytes: 37, eight
-// frames), and a step is as many whole multiples of that as the wave's lanes hold, once or twice over (NV), so that a lane
+// frames), and a step is as many whole multiples of that as the wave's lanes hold, a vector to each, so that a lane
 // finds the same features of the same frames in every step and adds them up in registers.  Only where a piece ends are
 // the lanes' sums brought together by feature, through LDS.
 // A workgroup takes a piece of one block, or several whole ones, and each of its four waves a quarter of the slots, wherever
@@ -1924,6 +1924,24 @@ static ReducePlan flat_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim,
     return p;
 }
 
+// The cut of a call with `room` bytes of workspace, aligned or not.
+static ReducePlan chosen_plan(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, bload_dtype dtype, int64_t n_seq, size_t room,
+                              bool aligned)
+{
+    const int64_t slots = num_blocks * (int64_t)t_blk, mean = slots / n_seq;
+    const int es = elem_size(dtype);
+    ReducePlan p = reduce_plan(num_blocks, t_blk, feat_dim, dtype, mean);
+    // (the flat cut takes a workspace only where it is aligned: cuts that need none leave it alone)
+    const ReducePlan flat = flat_plan(num_blocks, t_blk, feat_dim, dtype);
+    if (flat.flat && flat.bytes <= (aligned ? room : 0) && takes_flat(flat, p, slots * feat_dim * es, feat_dim * es, es, mean)) p = flat;
+    // a workspace that is smaller than the query's answer but holds what another cut needs, in the end the leanest
+    if (room < p.bytes) {
+        const ReducePlan lean = reduce_plan(num_blocks, t_blk, feat_dim, dtype, mean, true);
+        if (lean.bytes <= room) p = lean;
+    }
+    return p;
+}
+
 template <typename ElemT, int VEC, bool STREAM>
 static void launch_wide(const ReducePlan& p, const ReduceArgs& a, hipStream_t stream)
 {
@@ -2001,6 +2019,18 @@ extern "C" size_t bload_segment_reduce_workspace_bytes(int64_t num_blocks, int32
                              reduce_plan(num_blocks, t_blk, feat_dim, dtype, (int64_t)1 << 40).bytes));
 }
 
+extern "C" int32_t bload_segment_reduce_layout(int64_t num_blocks, int32_t t_blk, int64_t feat_dim, bload_dtype dtype, int64_t n_seq,
+                                               size_t workspace_bytes, int64_t* h_chunks)
+{
+    if (h_chunks) *h_chunks = 0;
+    if (num_blocks <= 0 || t_blk < 1 || feat_dim < 1 || feat_dim >= ((int64_t)1 << 28) || n_seq < 1 || n_seq > BLOAD_MAX_SEQ ||
+        (int)dtype < 0 || (int)dtype > 3 || num_blocks >= ((int64_t)1 << 40) / t_blk)
+        return BLOAD_REDUCE_NONE;
+    const ReducePlan p = chosen_plan(num_blocks, t_blk, feat_dim, dtype, n_seq, workspace_bytes, true);
+    if (h_chunks) *h_chunks = p.total_chunks;
+    return p.flat ? BLOAD_REDUCE_FLAT : p.wide ? BLOAD_REDUCE_WIDE : p.staged ? BLOAD_REDUCE_STAGED : BLOAD_REDUCE_NARROW;
+}
+
 extern "C" bload_status bload_segment_reduce(const void* d_packed, const int32_t* d_seq_id,
                                              const uint8_t* d_reset, const uint8_t* d_valid,
                                              int64_t num_blocks, int32_t t_blk, int64_t feat_dim,
@@ -2020,18 +2050,7 @@ extern "C" bload_status bload_segment_reduce(const void* d_packed, const int32_t
         !aligned_to(d_valid, 16) || !aligned_to(d_out, 8))
         return BLOAD_EALIGN;
 
-    ReducePlan p = reduce_plan(num_blocks, t_blk, feat_dim, dtype, total_slots / n_seq);
-    // a workspace that is smaller than the query's answer but holds what another cut needs, in the end the leanest
-    const size_t room = d_workspace ? workspace_bytes : 0;
-    // (the flat cut takes it only where it is aligned: cuts that need none leave it alone)
-    const ReducePlan flat = flat_plan(num_blocks, t_blk, feat_dim, dtype);
-    if (flat.flat && flat.bytes <= (aligned_to(d_workspace, 16) ? room : 0) &&
-        takes_flat(flat, p, total_slots * feat_dim * elem_size(dtype), feat_dim * elem_size(dtype), elem_size(dtype), total_slots / n_seq))
-        p = flat;
-    if (room < p.bytes) {
-        const ReducePlan lean = reduce_plan(num_blocks, t_blk, feat_dim, dtype, total_slots / n_seq, true);
-        if (lean.bytes <= room) p = lean;
-    }
+    const ReducePlan p = chosen_plan(num_blocks, t_blk, feat_dim, dtype, n_seq, d_workspace ? workspace_bytes : 0, aligned_to(d_workspace, 16));
     if (p.total_chunks * ceil_div(feat_dim, kThreads) > INT32_MAX) return BLOAD_EOVERFLOW;
     if (p.wide && ceil_div(p.total_chunks, (kThreads >> p.row_lanes_log2) >> p.split) *
                       ceil_div(p.n_vec, 1 << p.row_lanes_log2) > INT32_MAX)

@@ -125,6 +125,23 @@ def test_reduce_cuts_many_blocks_as_finely_for_short_pieces(lib, B, T, D):
                  ctypes.c_int64(B * T // frames), p, p, ctypes.c_size_t(need - 16), None) == 3
 
 
+def test_reduce_layout_tells_what_is_taken(lib):
+    f = lib.bload_segment_reduce_layout
+    f.restype = ctypes.c_int32
+    f.argtypes = [ctypes.c_int64, ctypes.c_int32, ctypes.c_int64, ctypes.c_int, ctypes.c_int64, ctypes.c_size_t,
+                  ctypes.POINTER(ctypes.c_int64)]
+    n = ctypes.c_int64(-1)
+    wide, staged, flat, narrow, much = 1, 2, 3, 4, 1 << 40
+    for sizes, room, want in (((180, 600, 37632, 0, 1000), 0, (wide, 180)), ((34576, 3000, 80, 2, 50000), much, (flat, 34576)),
+                              ((34576, 3000, 80, 2, 30000000), much, (wide, 34576 * 3)), ((857, 777, 16, 2, 200000), much, (staged, 857 * 3)),
+                              ((324084, 5000, 1, 3, 10 ** 6), much, (narrow, 2 * 324084)),
+                              ((160, 8001, 11, 2, 400), much, (flat, 1120)), ((160, 8001, 11, 2, 400), 0, (staged, 160))):
+        assert (f(*sizes, room, n), n.value) == want, sizes
+    for sizes in ((0, 600, 8, 0, 9), (5, 0, 8, 0, 9), (5, 8, 0, 0, 9), (5, 8, 8, 7, 9), (5, 8, 8, 0, 0), (1 << 39, 3, 8, 0, 9)):
+        assert f(*sizes, much, n) == 0 and n.value == 0
+    assert f(5, 8, 8, 0, 9, much, None) > 0
+
+
 @pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="a call that is not refused would be launched on these addresses")
 @pytest.mark.parametrize("B,T,D,dtype,n", [(598, 4993, 2, 3, 1355), (598, 4993, 2, 2, 1355)])
 def test_reduce_leaves_an_unaligned_workspace_alone(lib, B, T, D, dtype, n):

@@ -469,21 +469,32 @@ def test_reduce_short_pieces_over_chunk_borders(B, T, dtype, op):
     assert np.all(np.abs(got[:n_seg].astype(np.float64) - want.astype(np.float64)) <= bound)
 
 
-# Frames whose whole multiples are at most 64 vectors, in long pieces: a wave takes a piece's bytes as one stream.  Blocks cut
-# into several workgroups' shares and several blocks to a workgroup, segments that begin and end around the quarters that
-# the waves take, padding there as well, pieces of fewer frames than a step and of whole steps, the tensor's last bytes (no
-# whole vector).  The lanes' trees of four lose 2 units of roundoff of sum |x|, the result's rounding one, as does the oracle's.
-@pytest.mark.parametrize("dtype,op", [("f32", "mean"), ("i32", "sum"), ("u8", "mean"), ("f16", "sum")])
-@pytest.mark.parametrize("B,T,frame_bytes", [(40, 8001, 44), (3, 60000, 76), (1, 70001, 188), (6000, 33, 124), (1100, 300, 48),
-                                             (300, 7000, 8), (1030, 160, 128), (150, 3000, 128), (1025, 777, 64)])
-def test_reduce_flat_streams(B, T, frame_bytes, dtype, op):
+# Frames whose whole multiples are at most 64 vectors, in long pieces: a wave takes a piece's bytes as one stream.  In every
+# type several blocks to a workgroup (chunks < B), whole blocks and blocks cut into a few and into many shares (chunks >
+# B), segments that begin and end around the quarters that the waves take, padding there as well, pieces of fewer frames
+# than a step and of whole steps, several lanes to a feature and several features to a lane (from 33 on), the tensor's last
+# bytes (also no whole vector), tensors beyond the memory-side cache.  The lanes' trees of four lose 2 units of roundoff of sum |x|,
+# the result's rounding one, as does the oracle's.
+@pytest.mark.parametrize("dtype,B,T,D,chunks", [
+    ("u8", 2300, 400, 44, 1150), ("u8", 2300, 400, 128, 1150), ("f16", 3000, 600, 37, 1500), ("f16", 2300, 400, 62, 1150),
+    ("f16", 2301, 401, 30, 1151), ("f32", 2100, 600, 11, 1050), ("i32", 2100, 600, 11, 1050),
+    ("u8", 1100, 300, 48, 1100), ("u8", 1301, 777, 63, 1301), ("f16", 1100, 300, 24, 1100), ("f16", 1025, 777, 32, 1025),
+    ("f32", 1100, 300, 12, 1100), ("f32", 1030, 160, 32, 1030), ("f32", 1400, 600, 64, 1400), ("i32", 1100, 300, 12, 1100),
+    ("i32", 1400, 600, 64, 1400),
+    ("u8", 160, 8001, 47, 1120), ("u8", 300, 7000, 8, 900), ("f16", 160, 8001, 22, 1120), ("f16", 300, 7000, 4, 900),
+    ("f32", 160, 8001, 11, 1120), ("f32", 300, 7000, 2, 900), ("i32", 160, 8001, 11, 1120), ("i32", 300, 7000, 2, 900),
+    ("u8", 3, 60000, 76, 834), ("f16", 15, 60000, 38, 1035), ("f32", 15, 60000, 19, 1035), ("i32", 15, 60000, 19, 1035),
+    ("u8", 5500, 600, 86, 2750), ("f16", 5500, 600, 43, 2750), ("i32", 5500, 600, 23, 2750)])
+def test_reduce_flat_streams(dtype, B, T, D, chunks):
     bl = binding()
-    rng = np.random.default_rng(B + T + frame_bytes)
-    D = frame_bytes // bl.ELEM_BYTES[dtype]
+    op = {"f32": "mean", "i32": "sum", "u8": "mean", "f16": "sum"}[dtype]
+    rng = np.random.default_rng(B + T + D)
     valid, reset = np.ones((B, T), np.uint8), np.zeros((B, T), np.uint8)
-    at = np.unique(np.clip([T * w // 4 + k for w in range(5) for k in (-17, -1, 0, 1, 2, 16)], 1, T - 1))
+    tile = T * -(-B // chunks) if chunks <= B else -(-T // (chunks // B))         # a workgroup's slots
+    at = np.unique([(t0 + tile * w // 4 + k) % T for t0 in range(0, max(tile, T), tile) for w in range(5) for k in (-17, -1, 0, 1, 2, 16)])
     for b in range(B):
-        reset[b, rng.choice(at, size=int(rng.integers(0, 4)))] = 1 if b * frame_bytes % 3 else 0
+        if b % 3:
+            reset[b, rng.choice(at, size=int(rng.integers(0, 4)))] = 1
         if b % 5 == 1:
             valid[b, int(rng.choice(at)):][:int(rng.integers(1, 12))] = 0
     reset &= valid
@@ -496,8 +507,8 @@ def test_reduce_flat_streams(B, T, frame_bytes, dtype, op):
     absval = np.abs(src.astype(np.float32)).reshape(B, T, D)
     scale, _ = oracle.segment_reduce_packed(absval, seq_id, reset, valid, D, "f32", op, n_seg)
 
-    ws = bl.bload_segment_reduce_workspace_bytes(B, T, D, dtype)
-    print(f"flat B={B} T={T} {frame_bytes} bytes {dtype} segments {n_seg} workspace {ws}", flush=True)
+    print(f"flat B={B} T={T} D={D} {dtype} segments {n_seg}", flush=True)
+    assert bl.bload_segment_reduce_layout(B, T, D, dtype, n_seg) == ("flat", chunks)
     got = bl.bload_segment_reduce(to_dev(src), to_dev(seq_id), to_dev(reset), to_dev(valid), B, T, D, dtype, op, n_seg).cpu().numpy()
     if dtype == "i32":
         assert np.array_equal(got, want)
