@@ -1265,6 +1265,10 @@ __global__ __launch_bounds__(kThreads) void reduce_staged_kernel(ReduceArgs a)
 constexpr int kFlatSlots = 8000;           // of a workgroup, at most: a wave's quarter and its neighbours' flags are 64 words
 constexpr int kFlatGroups = 512;           // of 16 slots' flags
 constexpr int kFlatLoads = 4;              // steps asked for at a time (8 take registers from half the waves: 5 to 40 % slower)
+// Waves per SIMD that its registers are held to.  int32, whose sums take two registers each, needs 66 of them: held to the 64 of eight
+// waves it kept three in memory (600 MB of 44-byte frames in pieces of 500 frames 117 us, 103 with seven waves; 15 MB of 48 bytes 12.1
+// and 11.7).
+template <typename ElemT> constexpr int kFlatWaves = std::is_same<ElemT, int32_t>::value ? 7 : 8;
 constexpr int kWaves = kThreads / kWave;
 static_assert(kFlatSlots / kWaves + 1 + 32 <= kWave * 32, "a wave's slots: a word of flags per lane");
 static_assert((kFlatSlots / kWaves * (kWaves - 1)) / 32 + kWave <= kFlatGroups / 2, "the words that the last wave reads");
@@ -1342,7 +1346,7 @@ constexpr int kFlatByteFrames = 8;         // of bytes, a step holds so many fra
 static_assert((kFlatSlots / kWaves + 1 + kFlatByteFrames - 1) / kFlatByteFrames * 255 < 1 << 16, "a piece's bytes add up in 16 bits");
 
 template <typename ElemT, bool STREAM>
-__global__ __launch_bounds__(kThreads, 8) void reduce_flat_kernel(ReduceArgs a)
+__global__ __launch_bounds__(kThreads, kFlatWaves<ElemT>) void reduce_flat_kernel(ReduceArgs a)
 {
     typedef typename Elem<ElemT>::Acc Acc;
     typedef typename TileSum<ElemT>::T Part;
