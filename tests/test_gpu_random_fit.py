@@ -127,7 +127,8 @@ def test_random_fit_few_sequences(n, T):
         assert e.value.status == bl.ELENGTH
 
 
-# Draws are made in batches of 64 from 768 to 24576 sequences: both ends, the end of the short trial (4096), blocks of one
+# Draws are made in batches of 64 from 768 to 24576 sequences, and from 192 on where the frame total says so: both ends (767
+# sequences are drawn so by their total, 768 in any case), the end of the short trial (4096), blocks of one
 # length per group and of many, lists that end on and beside whole words; lengths that settle in a few rounds, in
 # many, not at all (the trial fails), that stop paying on the way, and of which there are so few that draws keep
 # meeting on the same ones.
