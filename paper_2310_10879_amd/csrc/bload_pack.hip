@@ -55,7 +55,6 @@ constexpr int64_t kNoRun = INT64_MAX;
 
 struct PackArgs {
     const uint8_t* src;
-    const Run* runs;          // [n_seq], by shuffled position
     int32_t n_seq;
     int32_t t_blk;
     int64_t frame_bytes;
@@ -585,7 +584,6 @@ __device__ __forceinline__ int32_t find_runs(const PackArgs& a, const PlanTables
 // The same in one launch, for calls of few tiles: every workgroup looks up the runs of its tile in the plan's tables by itself, a
 // thread to a shuffled position of the blocks that it touches.  Bound by latency: four look-ups one after the other here, against
 // three and a launch there.
-template <int TRAFFIC>
 __global__ __launch_bounds__(kThreads) void pack_direct_kernel(PackArgs a, PlanTables t, int64_t num_blocks, double inv_frame_bytes,
                                                                double inv_t_blk)
 {
@@ -607,8 +605,9 @@ __global__ __launch_bounds__(kThreads) void pack_direct_kernel(PackArgs a, PlanT
         }
     });
     __syncthreads();
-    write_wide_tile<TRAFFIC>(a, runs_here, n + 1, D0, D1, m_lo, m_hi, wave_id() == 0, inv_frame_bytes);
+    write_wide_tile<kPackThrough>(a, runs_here, n + 1, D0, D1, m_lo, m_hi, wave_id() == 0, inv_frame_bytes);      // (16 MB at most)
 }
+
 // ----------------------------------------------------------------- narrow
 
 constexpr int kNarrowSlots = kTableSlots;            // slots per workgroup
@@ -1175,7 +1174,6 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
     int32_t* first_pos_table = reinterpret_cast<int32_t*>(ws + l.table_off);
     PackArgs a;
     a.src = static_cast<const uint8_t*>(d_src);
-    a.runs = runs;
     a.n_seq = (int32_t)n_seq;
     a.t_blk = t_blk;
     a.frame_bytes = frame_bytes;
@@ -1206,7 +1204,7 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
 
     const PlanTables t{d_src_offsets, d_lengths, d_order, d_block_of_seq, d_offset_of_seq, d_block_first};
     if (l.wide && l.tiles <= kDirectTiles) {
-        hipLaunchKernelGGL(pack_direct_kernel<kPackThrough>, dim3((uint32_t)l.tiles), dim3(kThreads), 0, stream, a, t, num_blocks,
+        hipLaunchKernelGGL(pack_direct_kernel, dim3((uint32_t)l.tiles), dim3(kThreads), 0, stream, a, t, num_blocks,
                            1.0 / (double)frame_bytes, 1.0 / (double)t_blk);
         return launch_status();
     }
