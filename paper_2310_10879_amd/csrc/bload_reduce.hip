@@ -1265,10 +1265,11 @@ __global__ __launch_bounds__(kThreads) void reduce_staged_kernel(ReduceArgs a)
 constexpr int kFlatSlots = 8000;           // of a workgroup, at most: a wave's quarter and its neighbours' flags are 64 words
 constexpr int kFlatGroups = 512;           // of 16 slots' flags
 constexpr int kFlatLoads = 4;              // steps asked for at a time (8 take registers from half the waves: 5 to 40 % slower)
-// Waves per SIMD that its registers are held to.  int32, whose sums take two registers each, needs 66 of them: held to the 64 of eight
-// waves it kept three in memory (600 MB of 44-byte frames in pieces of 500 frames 117 us, 103 with seven waves; 15 MB of 48 bytes 12.1
-// and 11.7).
-template <typename ElemT> constexpr int kFlatWaves = std::is_same<ElemT, int32_t>::value ? 7 : 8;
+// int32, whose sums take two registers each, looks at its flags in LDS again for every piece: with two words of them in registers,
+// as the others have them, it needs 66 of the 64 that eight waves per SIMD leave, and kept them in memory instead (364 MB of
+// 36-byte frames in pieces of 620 frames 72.2 us, 64.1 like this; with seven waves 64.4, but 254 MB of 80-byte frames, whose 1977
+// workgroups are more than are at work at once then, 59.7 -> 66.7, 59.3 like this).
+template <typename ElemT> constexpr bool kFlatLooksAgain = std::is_same<ElemT, int32_t>::value;
 constexpr int kWaves = kThreads / kWave;
 static_assert(kFlatSlots / kWaves + 1 + 32 <= kWave * 32, "a wave's slots: a word of flags per lane");
 static_assert((kFlatSlots / kWaves * (kWaves - 1)) / 32 + kWave <= kFlatGroups / 2, "the words that the last wave reads");
@@ -1346,7 +1347,7 @@ constexpr int kFlatByteFrames = 8;         // of bytes, a step holds so many fra
 static_assert((kFlatSlots / kWaves + 1 + kFlatByteFrames - 1) / kFlatByteFrames * 255 < 1 << 16, "a piece's bytes add up in 16 bits");
 
 template <typename ElemT, bool STREAM>
-__global__ __launch_bounds__(kThreads, kFlatWaves<ElemT>) void reduce_flat_kernel(ReduceArgs a)
+__global__ __launch_bounds__(kThreads, 8) void reduce_flat_kernel(ReduceArgs a)
 {
     typedef typename Elem<ElemT>::Acc Acc;
     typedef typename TileSum<ElemT>::T Part;
@@ -1416,8 +1417,10 @@ __global__ __launch_bounds__(kThreads, kFlatWaves<ElemT>) void reduce_flat_kerne
     const int32_t lo = n * wave / kWaves, hi = n * (wave + 1) / kWaves;
     const int32_t base = lo & ~31, mine = base + 32 * lane;
     auto below = [&](int32_t slot) { const int32_t k = slot - mine; return k <= 0 ? 0u : k >= 32 ? ~0u : (1u << k) - 1u; };
-    const uint32_t brk = reinterpret_cast<const uint32_t*>(s_break)[(base >> 5) + lane] | ~below(hi + 1);
-    const uint32_t val = reinterpret_cast<const uint32_t*>(s_valid)[(base >> 5) + lane] & below(hi);
+    auto breaks = [&]() { return reinterpret_cast<const uint32_t*>(s_break)[(base >> 5) + lane] | ~below(hi + 1); };
+    auto valids = [&]() { return reinterpret_cast<const uint32_t*>(s_valid)[(base >> 5) + lane] & below(hi); };
+    constexpr bool kAgain = kFlatLooksAgain<ElemT>;
+    const uint32_t kept_breaks = kAgain ? 0u : breaks(), kept_valids = kAgain ? 0u : valids();
     // the first slot from `t` on whose bit is set, INT32_MAX if there is none
     auto find = [&](uint32_t bits, int32_t t) {
         const uint32_t m = bits & ~below(t);
@@ -1439,8 +1442,9 @@ __global__ __launch_bounds__(kThreads, kFlatWaves<ElemT>) void reduce_flat_kerne
     };
 
     for (int32_t t = lo; t < hi;) {
-        t = find(val, t);
+        t = find(kAgain ? valids() : kept_valids, t);
         if (t >= hi) break;
+        const uint32_t brk = kAgain ? breaks() : kept_breaks;
         const int32_t stop = find(brk, t + 1), e = min(stop, hi);
         const bool closed = stop <= hi;
         const bool head_open = t == lo && find(brk, t) != t;
