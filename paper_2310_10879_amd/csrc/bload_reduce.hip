@@ -1764,24 +1764,34 @@ static bool flat_cut(ReducePlan& p, int64_t num_blocks, int32_t t_blk, int64_t f
 // that its bytes have to make up for that against
 //   - staged tiles, which take their time by elements: 250 MB, 58 bytes in pieces of 80 frames 173 -> 69 us, 14 bytes x 80 211
 //     -> 147, 16 bytes x 80 even, 17 bytes x 20 0.4 times as fast; 28 halfs x 130 189 -> 77; 8 bytes of floats x 400 107 -> 76, x 80 123 and 266
-//     (frames of few floats end in many lanes); 16 to 60 MB, less in flight: 22 bytes of halfs x 40 20 and 30; 16 MB of
-//     80-byte frames in blocks of 3000, which both cut, x 160 12 and 14
+//     (frames of few floats end in many lanes).  Tensors of 16 to 50 MB, less in flight: 64 bytes of floats x 59 33.7 -> 21.5, 80 x 43 32.5
+//     -> 20.9, but 22 bytes of halfs x 40 20 and 30, 84 of floats x 37 17 and 20, 24 x 116 18 and 22; 16 MB of 80-byte frames in blocks
+//     of 3000, which both cut, x 160 12 and 14; and not where a tile takes several blocks that would be a workgroup each (1949 blocks
+//     of 8 KB 9.7 us, 12.7)
 //   - wide rows of 4-byte lanes or single elements: 600 MB, 86 bytes of halfs x 40 197 -> 148; 100 bytes of int32 x 80 153 ->
-//     127; but 140 bytes of floats, half the lanes idle here, x 60 43 and 52
+//     127; but 140 bytes of floats, half the lanes idle here, x 60 43 and 52.  Frames of up to 128 bytes of bytes and halfs
+//     in short blocks, which a row walks whole: 72 bytes x 71, 91 MB 32 and 39, 122 x 57, 81 MB 19 and 23, 118 x 27, 240 MB 75 and 85, but 108 x
+//     76, 141 MB 38 -> 32; in blocks that rows cut, 120 x 41, 194 MB 74 -> 57.  Longer ones, whose rows have all their lanes at
+//     work, below 200 MB: 172 bytes x 24, 83 MB 25 and 30, 220 x 39, 94 MB 22 and 25; in blocks that rows cut 236 x 22, 81 MB 34 -> 32, 184 x 22, 164 MB 57 and 63
 //   - wide rows of whole vectors, whose rows wait for each other: 600 MB, 64 bytes x 80 184 -> 117, 208 x 10 176 -> 152, 480 x 20 159 ->
-//     135; 60 MB, 336 bytes x 40 24.5 -> 18, 144 x 20 23 and 30; 16 MB, 384 x 400 12 and 14.
+//     135; 60 MB, 336 bytes x 40 24.5 -> 18, 144 x 20 23 and 30; 16 MB, 384 x 400 12 and 14.  (More than 192 halfs take 30 KB of
+//     LDS here, four or five workgroups to a compute unit: 480 bytes x 28, 56 MB in 1387 workgroups 17 and 23.)
 static bool takes_flat(const ReducePlan& flat, const ReducePlan& other, int64_t total_bytes, int64_t frame_bytes, int es, int64_t mean)
 {
     const int64_t piece = mean * frame_bytes;
+    const bool large = total_bytes >= kFlatLarge, middle = total_bytes >= kFlatMiddle;
     if (!other.wide) {
-        if (total_bytes < kFlatMiddle && flat.n_chunks > 1 && frame_bytes >= 32) return false;
+        if (!middle && (flat.n_chunks > 1 ? frame_bytes >= 32 : flat.total_chunks > other.total_chunks)) return false;
         const int64_t least = es == 1 ? 1100 : es == 2 ? 2000 : frame_bytes < 20 ? 3200 : 1600;
-        return piece >= (total_bytes >= kFlatLarge ? least : least * 8 / 5);
+        return piece >= (large ? least : middle || (es != 4 && frame_bytes <= 64) ? least * 8 / 5 : least * 2);
     }
     if (frame_bytes % 16 == 0)
-        return total_bytes >= kFlatLarge ? piece >= 2000 : total_bytes >= kFlatMiddle && flat.n_chunks == 1 && piece >= 12000;
+        return large ? piece >= 2000 : middle && flat.n_chunks == 1 && piece >= 12000 && (es != 2 || frame_bytes <= 384);
     if (es == 4) return frame_bytes <= 128 && piece >= 5000;
-    return piece >= 3000 && (total_bytes >= kFlatMiddle || frame_bytes <= 128);
+    const bool short_blocks = other.n_chunks == 1;
+    if (large) return piece >= 3800;
+    if (frame_bytes > 128) return middle && !short_blocks && piece >= 5000;
+    return piece >= (short_blocks ? 8000 : 3800);
 }
 
 // Where the workspace holds what borders cut.

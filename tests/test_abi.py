@@ -331,3 +331,19 @@ def test_plan_tables_are_aligned_like_tensors_of_their_own(n):
     assert all(t.storage_offset() % 128 == 0 for t in tables if t.numel())
     ends = [(t.storage_offset(), t.storage_offset() + t.numel()) for t in tables]
     assert all(a[1] <= b[0] for a, b in zip(ends, ends[1:]))
+
+
+# (blocks, slots, elements, type, sequences) of calls that the flat layout would make slower, and of some beside them that it makes faster.
+@pytest.mark.parametrize("sizes,flat", [
+    ((1949, 158, 13, 3, 2767), False), ((1737, 243, 9, 3, 1737), True),             # two blocks to a staged tile; one
+    ((8181, 174, 6, 2, 12195), False), ((6969, 284, 6, 2, 10087), True),            # 24 bytes x 116; x 196
+    ((3320, 140, 122, 0, 17532), False), ((7892, 84, 61, 1, 11292), False),         # nearly whole rows of 4-byte lanes
+    ((11971, 109, 54, 1, 17145), True), ((7279, 222, 60, 1, 38612), True),          # longer pieces; blocks that rows cut
+    ((13859, 35, 86, 1, 24385), False), ((2773, 42, 240, 1, 4083), False),          # rows of a wave; 480 bytes of halfs
+    ((3746, 53, 84, 2, 5535), False), ((34576, 3000, 80, 2, 50000), True), ((1981, 777, 37, 1, 3960), True)])
+def test_reduce_takes_the_flat_layout_where_it_is_the_faster(lib, sizes, flat):
+    f = lib.bload_segment_reduce_layout
+    f.restype = ctypes.c_int32
+    f.argtypes = [ctypes.c_int64, ctypes.c_int32, ctypes.c_int64, ctypes.c_int, ctypes.c_int64, ctypes.c_size_t,
+                  ctypes.POINTER(ctypes.c_int64)]
+    assert (f(*sizes, 1 << 40, None) == 3) == flat
