@@ -1053,15 +1053,18 @@ constexpr int64_t kTablePassFromSlots = (int64_t)1 << 21;
 // 0.8-1.3 * 10^9 token slots of four length mixes: two tiles 1-3.5 % faster than one, four between 3 %
 // slower and 2 % faster, eight 40 % slower.
 constexpr int kPassGroup = 2;
-// Up to so many workgroups, every one looks up its tile's runs itself, in one launch (pack_direct_kernel): 64 clips of 3 KB frames 11.4 -> 8.2
-// us, 3000 sequences of two 700-byte frames 13.4 -> 9.2, 18 MB of 320-byte frames 23.5 -> 21; 8192 tiles: 19.4 -> 20.4.  Slot tiles:
+// Up to so many workgroups, every one looks up its tile's runs itself, in one launch.  4 KiB tiles (pack_direct_kernel): as many as are at
+// work at once, since those behind them wait for look-ups that the others had hidden by then: 64 clips of 3 KB frames 11.4 -> 8.2 us, 8 MB
+// of 6 KB frames in a sequence of 5 MB 10.4 and 8.5, but 9 MB of 5 KB frames in three 10.6 and 11.5, 16 MB in one 11.0 and 14.3.  Where runs are
+// shorter than 16 KiB on average, the other way has its table of runs to make and several of them in every tile: 7.8 MB of 276-byte frames in 1453
+// sequences 15.7 -> 12.5, 11 MB of 289 bytes in 902 15.1 -> 14.3, 3000 sequences of two 700-byte frames 13.4 -> 9.2; 8192 tiles: 19.4 -> 20.4.  Slot tiles:
 // 300 sequences of tokens 10.7 -> 8.0, 400 of 63-byte frames 22.5 -> 16.2, 4 MB of 40-byte frames 14.8 -> 11.9, 3000 full ones of 60
 // bytes 64 -> 62.  Every workgroup of a slot tile looks up all of its runs, five scattered loads each: with one to a tile 500000 sequences
 // are fine (of one byte each 46 -> 38 us, of two tokens in blocks of 10^6 slots 45.5 -> 42), 600000 are not (of two tokens
 // 48.6 and 52, 900000 75 and 84); where several share a tile, not more than 2^18 looks (20000 sequences of ten 64-byte frames, 21 to a
 // tile, 14.6 us and 17.7, 6000 of ten 250-byte frames, 63, 18.9 and 21.1; 2000 of ten 400-byte frames, 100 to a tile, 11.7 -> 9.3), and
 // no tiles of more than 256 sequences (20000 of one 40-byte frame 13.0 us, 13.5).
-constexpr int64_t kDirectTiles = 4096, kDirectMost = (int64_t)1 << 19, kDirectLooks = (int64_t)1 << 18;
+constexpr int64_t kDirectWide = 2048, kDirectRun = 16384, kDirectTiles = 4096, kDirectMost = (int64_t)1 << 19, kDirectLooks = (int64_t)1 << 18;
 
 // Sizes the caller cannot know in advance (which tile shape the lengths will choose) are
 // taken at their larger value when `for_query`.
@@ -1203,7 +1206,8 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
     const bool two_passes = frame_bytes == 4 && aligned_to(d_src, 4) && a.total_slots >= kTablePassFromSlots;
 
     const PlanTables t{d_src_offsets, d_lengths, d_order, d_block_of_seq, d_offset_of_seq, d_block_first};
-    if (l.wide && l.tiles <= kDirectTiles) {
+    const bool short_runs = a.total_slots * frame_bytes < n_seq * kDirectRun;
+    if (l.wide && l.tiles <= (short_runs ? kDirectTiles : kDirectWide)) {
         hipLaunchKernelGGL(pack_direct_kernel, dim3((uint32_t)l.tiles), dim3(kThreads), 0, stream, a, t, num_blocks,
                            1.0 / (double)frame_bytes, 1.0 / (double)t_blk);
         return launch_status();

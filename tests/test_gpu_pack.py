@@ -257,7 +257,7 @@ def test_pack_looks_runs_up_in_the_plan(F):
 
 
 @pytest.mark.parametrize("F,n", [(4096, 4096), (4096, 4097), (9, 4096 * 1024), (9, 4096 * 1024 + 1), (64, 1023 * 1024),
-                                 (3, 1 << 19), (3, (1 << 19) + 1)])
+                                 (65536, 128), (65536, 129), (3, 1 << 19), (3, (1 << 19) + 1)])
 def test_pack_with_and_without_a_run_table(F, n):
     """The last number of tiles, and of sequences, that find their runs themselves and the first that are given them."""
     run_case(n, 1, F, "uniform", seed=1)
