@@ -332,26 +332,28 @@ __global__ __launch_bounds__(kThreads) void pack_prepare_kernel(
     if (idx < n_table_tiles) first_pos_table[idx] = entry_of(idx * kTableSlots);
 }
 
-// The runs of a 4 KiB tile, looked up side by side.
+// The runs of some 4 KiB tiles in a row, looked up side by side.
+template <int TILES>
 struct WideRuns {
-    int64_t lo[kWideRuns + 1];     // first packed byte of the run; INT64_MAX: no run
-    int64_t hi[kWideRuns];         // one past its last packed byte
-    int64_t src[kWideRuns];        // source byte that goes to `lo`
-    int32_t seq[kWideRuns];
+    static constexpr int kMost = TILES * kWideRuns;
+    int64_t lo[kMost + 1];         // first packed byte of the run; INT64_MAX: no run
+    int64_t hi[kMost];             // one past its last packed byte
+    int64_t src[kMost];            // source byte that goes to `lo`
+    int32_t seq[kMost];
 };
 
-// Packed bytes [D0, D1) of a tile whose runs, `n` at most and in destination order, are known, and the start-table entries of
-// slots [m_lo, m_hi) if `table_wave`.  Every thread finds the run of its own 16 bytes.
-template <int TRAFFIC>
-__device__ __forceinline__ void write_wide_tile(const PackArgs& a, const WideRuns& r, int32_t n, int64_t D0, int64_t D1,
-                                                int64_t m_lo, int64_t m_hi, bool table_wave, double inv_frame_bytes)
+// Packed bytes [D0, D1) of tiles whose runs, `n` at most and in destination order, are known, and the start-table entries of
+// slots [m_lo, m_hi) if `table_wave`.  Every thread finds the run of its own 16 bytes of each tile.
+template <int TRAFFIC, int TILES>
+__device__ __forceinline__ void write_wide_tiles(const PackArgs& a, const WideRuns<TILES>& r, int32_t n, int64_t D0, int64_t D1,
+                                                 int64_t m_lo, int64_t m_hi, bool table_wave, double inv_frame_bytes)
 {
     const int64_t F = a.frame_bytes;
     const int tid = (int)threadIdx.x;
     // last gathered run that starts at or before packed byte x, -1 if none
     // (a binary search over the first `span` entries, span = a power of two that covers them)
     int span = 1;
-    while (span < min(n, kWideRuns)) span <<= 1;
+    while (span < min(n, WideRuns<TILES>::kMost)) span <<= 1;
     auto run_at = [&](int64_t x) {
         int k = -1;
         for (int step = span >> 1; step >= 1; step >>= 1)
@@ -360,16 +362,20 @@ __device__ __forceinline__ void write_wide_tile(const PackArgs& a, const WideRun
         return k;
     };
 
-    for (int64_t x0 = D0 + 16 * (int64_t)tid; x0 < D1; x0 += 16 * (int64_t)kThreads) {
+    vec16 out[TILES];
+    bool whole[TILES];
+#pragma unroll
+    for (int u = 0; u < TILES; ++u) {
+        const int64_t x0 = D0 + 16 * (int64_t)(u * kThreads + tid);
+        out[u] = vec16{0u, 0u, 0u, 0u};
+        whole[u] = x0 + 16 <= D1;
+        if (x0 >= D1) continue;
         int k = run_at(x0);
         const int64_t next_lo = r.lo[k + 1];
         const int64_t lo = k >= 0 ? r.lo[k] : 0, hi = k >= 0 ? r.hi[k] : 0;
-        // (one store for whatever a lane's vector is, so that a wave's goes out as whole lines)
-        const bool whole = x0 + 16 <= D1;
-        vec16 v = {0u, 0u, 0u, 0u};
-        if (whole && x0 + 16 <= hi) {                                   // inside one run
-            v = load_source<TRAFFIC>(a.src + r.src[k] + (x0 - lo));
-        } else if (!(whole && x0 >= hi && x0 + 16 <= next_lo)) {        // not inside a block's zero tail
+        if (whole[u] && x0 + 16 <= hi) {                                // inside one run
+            out[u] = load_source<TRAFFIC>(a.src + r.src[k] + (x0 - lo));
+        } else if (!(whole[u] && x0 >= hi && x0 + 16 <= next_lo)) {     // not inside a block's zero tail
             // a border inside: byte by byte, all of them asked for before the first is stored
             uint32_t bytes[16];
 #pragma unroll
@@ -380,15 +386,18 @@ __device__ __forceinline__ void write_wide_tile(const PackArgs& a, const WideRun
                 if (k >= 0 && x < r.hi[k] && x < D1) bytes[j] = a.src[r.src[k] + (x - r.lo[k])];
             }
 #pragma unroll
-            for (int w = 0; w < 4; ++w) v[w] = bytes[4 * w] | bytes[4 * w + 1] << 8 | bytes[4 * w + 2] << 16 | bytes[4 * w + 3] << 24;
-            if (!whole) {
+            for (int w = 0; w < 4; ++w) out[u][w] = bytes[4 * w] | bytes[4 * w + 1] << 8 | bytes[4 * w + 2] << 16 | bytes[4 * w + 3] << 24;
+            if (!whole[u]) {
 #pragma unroll
                 for (int j = 0; j < 16; ++j)
                     if (x0 + j < D1) a.packed[x0 + j] = (uint8_t)bytes[j];
             }
         }
-        if (whole) store_packed<TRAFFIC>(reinterpret_cast<vec16*>(a.packed + D0), (int)((x0 - D0) / 16), v);
     }
+    // (one store for whatever a lane's vector is, so that a wave's goes out as whole lines)
+#pragma unroll
+    for (int u = 0; u < TILES; ++u)
+        if (whole[u]) store_packed<TRAFFIC>(reinterpret_cast<vec16*>(a.packed + D0) + u * kThreads, tid, out[u]);
     if (table_wave) {
         for (int64_t slot = m_lo + lane_id(); slot < m_hi; slot += kWave) {
             const int64_t x = slot * F;
@@ -500,7 +509,7 @@ __global__ __launch_bounds__(kThreads) void pack_wide_kernel(
     // k-th shuffled position from p on), so that the cost does not grow with their number, and
     // every thread then finds the run of its own 16 bytes.  A frame of kWideMinFrame bytes or
     // more puts at most kWideTile / kWideMinFrame + 2 runs into a tile.
-    __shared__ WideRuns runs_here;
+    __shared__ WideRuns<1> runs_here;
     const int tid = (int)threadIdx.x;
     if (tid <= kWideRuns) {
         int64_t lo = INT64_MAX, hi = 0, from = 0;
@@ -523,7 +532,7 @@ __global__ __launch_bounds__(kThreads) void pack_wide_kernel(
         }
     }
     __syncthreads();
-    write_wide_tile<TRAFFIC>(a, runs_here, p_next - p + 2, D0, D1, m_lo, m_hi, table_wave, inv_frame_bytes);
+    write_wide_tiles<TRAFFIC>(a, runs_here, p_next - p + 2, D0, D1, m_lo, m_hi, table_wave, inv_frame_bytes);
 }
 
 // The runs that overlap slots [gs_lo, gs_hi), the last of which that there is lies at or before `slot_hi` - 1, from the plan's tables, a
@@ -581,23 +590,26 @@ __device__ __forceinline__ int32_t find_runs(const PackArgs& a, const PlanTables
     return n;
 }
 
-// The same in one launch, for calls of few tiles: every workgroup looks up the runs of its tile in the plan's tables by itself, a
-// thread to a shuffled position of the blocks that it touches.  Bound by latency: four look-ups one after the other here, against
-// three and a launch there.
+// The same in one launch, for calls of few tiles: every workgroup looks up the runs of its tile, or of two in a row, in the plan's tables
+// by itself, a thread to a shuffled position of the blocks that it touches.  Bound by latency: four look-ups one after the other here,
+// against three and a launch there.
+template <int TILES>
 __global__ __launch_bounds__(kThreads) void pack_direct_kernel(PackArgs a, PlanTables t, int64_t num_blocks, double inv_frame_bytes,
                                                                double inv_t_blk)
 {
+    constexpr int kMost = WideRuns<TILES>::kMost;
+    static_assert(TILES * kWideTile / kWideMinFrame + 2 <= kMost, "the tiles' runs must fit their table");
     const int64_t F = a.frame_bytes, total_bytes = a.total_slots * F;
     const uint32_t tile = xcd_contiguous(blockIdx.x, gridDim.x);
-    const int64_t D0 = (int64_t)tile * kWideTile, D1 = min(D0 + kWideTile, total_bytes);
+    const int64_t D0 = (int64_t)tile * (TILES * kWideTile), D1 = min(D0 + TILES * kWideTile, total_bytes);
     const int64_t gs_lo = floor_div(D0, F, inv_frame_bytes);              // first slot touched
     const int64_t gs_hi = floor_div(D1 + F - 1, F, inv_frame_bytes);      // one past the last
     const int64_t m_lo = gs_lo + ((gs_lo * F < D0) ? 1 : 0), m_hi = min(gs_hi, a.total_slots);
-    __shared__ WideRuns runs_here;
+    __shared__ WideRuns<TILES> runs_here;
     const int tid = (int)threadIdx.x;
-    if (tid <= kWideRuns) runs_here.lo[tid] = INT64_MAX;
+    for (int k = tid; k <= kMost; k += kThreads) runs_here.lo[k] = INT64_MAX;
     const int32_t n = find_runs(a, t, num_blocks, inv_t_blk, gs_lo, m_hi, gs_hi, [&](int32_t at, const Run& r) {
-        if (at < kWideRuns) {
+        if (at < kMost) {
             runs_here.lo[at] = r.dst * F;
             runs_here.hi[at] = (r.dst + r.len) * F;
             runs_here.src[at] = r.src * F;
@@ -605,7 +617,7 @@ __global__ __launch_bounds__(kThreads) void pack_direct_kernel(PackArgs a, PlanT
         }
     });
     __syncthreads();
-    write_wide_tile<kPackThrough>(a, runs_here, n + 1, D0, D1, m_lo, m_hi, wave_id() == 0, inv_frame_bytes);      // (16 MB at most)
+    write_wide_tiles<kPackThrough>(a, runs_here, n + 1, D0, D1, m_lo, m_hi, wave_id() == 0, inv_frame_bytes);      // (16 MB at most)
 }
 
 // ----------------------------------------------------------------- narrow
@@ -1053,18 +1065,17 @@ constexpr int64_t kTablePassFromSlots = (int64_t)1 << 21;
 // 0.8-1.3 * 10^9 token slots of four length mixes: two tiles 1-3.5 % faster than one, four between 3 %
 // slower and 2 % faster, eight 40 % slower.
 constexpr int kPassGroup = 2;
-// Up to so many workgroups, every one looks up its tile's runs itself, in one launch.  4 KiB tiles (pack_direct_kernel): as many as are at
-// work at once, since those behind them wait for look-ups that the others had hidden by then: 64 clips of 3 KB frames 11.4 -> 8.2 us, 8 MB
-// of 6 KB frames in a sequence of 5 MB 10.4 and 8.5, but 9 MB of 5 KB frames in three 10.6 and 11.5, 16 MB in one 11.0 and 14.3.  Where runs are
-// shorter than 16 KiB on average, the other way has its table of runs to make and several of them in every tile: 7.8 MB of 276-byte frames in 1453
-// sequences 15.7 -> 12.5, 11 MB of 289 bytes in 902 15.1 -> 14.3, 3000 sequences of two 700-byte frames 13.4 -> 9.2; 8192 tiles: 19.4 -> 20.4.  Slot tiles:
+// Up to so many tiles, every workgroup looks up its runs itself, in one launch.  4 KiB tiles (pack_direct_kernel): 64 clips of 3 KB frames
+// 11.4 -> 8.2 us, 3000 sequences of two 700-byte frames 13.4 -> 9.2; 8192 tiles: 19.4 -> 20.4.  Beyond kDirectAtOnce tiles, as many as
+// are at work at once, a workgroup takes two: those of a second round would wait for their look-ups alone (16 MB in one
+// sequence 12.6 us in two launches, 14.6 with a tile each, 12.3 like this; 13 MB in ten 12.4, 12.7, 10.7; 9 MB in three 12.4, 12.0, 9.7).  Slot tiles:
 // 300 sequences of tokens 10.7 -> 8.0, 400 of 63-byte frames 22.5 -> 16.2, 4 MB of 40-byte frames 14.8 -> 11.9, 3000 full ones of 60
 // bytes 64 -> 62.  Every workgroup of a slot tile looks up all of its runs, five scattered loads each: with one to a tile 500000 sequences
 // are fine (of one byte each 46 -> 38 us, of two tokens in blocks of 10^6 slots 45.5 -> 42), 600000 are not (of two tokens
 // 48.6 and 52, 900000 75 and 84); where several share a tile, not more than 2^18 looks (20000 sequences of ten 64-byte frames, 21 to a
 // tile, 14.6 us and 17.7, 6000 of ten 250-byte frames, 63, 18.9 and 21.1; 2000 of ten 400-byte frames, 100 to a tile, 11.7 -> 9.3), and
 // no tiles of more than 256 sequences (20000 of one 40-byte frame 13.0 us, 13.5).
-constexpr int64_t kDirectWide = 2048, kDirectRun = 16384, kDirectTiles = 4096, kDirectMost = (int64_t)1 << 19, kDirectLooks = (int64_t)1 << 18;
+constexpr int64_t kDirectAtOnce = 2048, kDirectTiles = 4096, kDirectMost = (int64_t)1 << 19, kDirectLooks = (int64_t)1 << 18;
 
 // Sizes the caller cannot know in advance (which tile shape the lengths will choose) are
 // taken at their larger value when `for_query`.
@@ -1206,10 +1217,10 @@ bload_status pack_enqueue(const PackLayout& l, const void* d_src, const int64_t*
     const bool two_passes = frame_bytes == 4 && aligned_to(d_src, 4) && a.total_slots >= kTablePassFromSlots;
 
     const PlanTables t{d_src_offsets, d_lengths, d_order, d_block_of_seq, d_offset_of_seq, d_block_first};
-    const bool short_runs = a.total_slots * frame_bytes < n_seq * kDirectRun;
-    if (l.wide && l.tiles <= (short_runs ? kDirectTiles : kDirectWide)) {
-        hipLaunchKernelGGL(pack_direct_kernel, dim3((uint32_t)l.tiles), dim3(kThreads), 0, stream, a, t, num_blocks,
-                           1.0 / (double)frame_bytes, 1.0 / (double)t_blk);
+    if (l.wide && l.tiles <= kDirectTiles) {
+        const bool pairs = l.tiles > kDirectAtOnce;
+        hipLaunchKernelGGL(pairs ? pack_direct_kernel<2> : pack_direct_kernel<1>, dim3((uint32_t)ceil_div(l.tiles, pairs ? 2 : 1)), dim3(kThreads),
+                           0, stream, a, t, num_blocks, 1.0 / (double)frame_bytes, 1.0 / (double)t_blk);
         return launch_status();
     }
     const bool looks_pay = parts == 1 ? n_seq <= kDirectMost : n_seq * parts <= kDirectLooks && n_seq * 4 <= a.total_slots;

@@ -257,7 +257,26 @@ def test_pack_looks_runs_up_in_the_plan(F):
 
 
 @pytest.mark.parametrize("F,n", [(4096, 4096), (4096, 4097), (9, 4096 * 1024), (9, 4096 * 1024 + 1), (64, 1023 * 1024),
-                                 (65536, 128), (65536, 129), (3, 1 << 19), (3, (1 << 19) + 1)])
+                                 (4096, 2048), (4096, 2049), (3, 1 << 19), (3, (1 << 19) + 1)])
 def test_pack_with_and_without_a_run_table(F, n):
     """The last number of tiles, and of sequences, that find their runs themselves and the first that are given them."""
     run_case(n, 1, F, "uniform", seed=1)
+
+
+@pytest.mark.parametrize("tiles", [2048, 2049, 3001, 4096])
+@pytest.mark.parametrize("F", [65, 100, 600, 5000, 30004])
+def test_pack_pairs_of_tiles(F, tiles):
+    """Beyond 2048 tiles of 4 KiB in one launch a workgroup takes two in a row: runs over many tiles, 150 sequences of one frame behind
+    one another (more than two tiles of small frames hold), zero tails, blocks that end inside a tile, odd numbers of tiles."""
+    T = tiles * 4096 // (3 * F)
+    ones = min(150, T // 6)
+    L = np.array(3 * ([T // 3] + [1] * ones + [T // 3]), dtype=np.int32)
+    ref_plan = oracle.plan(L, T, np.arange(len(L), dtype=np.int32))
+    assert ref_plan.num_blocks == 3 and tiles - 100 < -(-3 * T * F // 4096) <= tiles
+    assert binding().bload_pack_tile_bytes(len(L), 3, T, F, True) == 4096
+    so = workloads.src_offsets(L)
+    src = workloads.tagged_source(L, F)
+    ref = oracle.pack(src, so, L, ref_plan, F)
+    print(f"pack pairs F={F} tiles={-(-3 * T * F // 4096)}", flush=True)
+    out = gpu_pack_guarded(src, so, L, upload_plan(ref_plan, len(L)), F)
+    assert_packed_equal(out, ref, f"F={F} tiles={tiles}: ")
