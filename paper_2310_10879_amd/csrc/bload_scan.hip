@@ -727,16 +727,17 @@ static int32_t scan_staged_slots(int32_t groups, int32_t t_blk)
 //   - Where output lines are written by two workgroups (frames of several slices) or twice by one (frames that are no whole
 //     half lines), in parts, streaming stores send both parts to memory; plain ones meet in the cache.  270 halfs, 1.2
 //     GB: 1034 -> 820 us, 2415 of them 1710 -> 1504, 72 bytes 868 -> 736, 100 floats 504 -> 454; whole lines lose as much by it (256 floats 372
-//     -> 418), and single slices from 192 elements on gain nothing (250 halfs 764 and 780).  Input and output of 300 MB in all stay in
-//     the cache (540 bytes, 50 MB 58 -> 42; 400 bytes, 51 MB 35 -> 28, from memory only 31.4 and 33.1); below 40 MB the write-back at
-//     the call's end costs more than that (400 bytes, 26 MB from memory 17.2 us, 20.2).
+//     -> 418), and single slices from 192 elements on gain nothing (250 halfs 764 and 780).  Of single slices, input and output of 300 MB in
+//     all stay in the cache, too (400 bytes, 51 MB 35 -> 28 us, 98 bytes, 57 MB 92 -> 74, also from memory 76 halfs, 74 MB 70 -> 61, but 400 bytes
+//     31.4 and 33.1); below 40 MB the write-back at the call's end costs more than that (400 bytes, 26 MB from memory 17.2 us, 20.2).
+//     Several slices are streamed there: 1273 halfs, 53 MB 51 us and 60 with plain stores, 3279, 76 MB 65 and 74, 2008 floats, 104 MB 53 and 56.
 static ScanTraffic scan_traffic(int64_t elems, size_t elem, int64_t feat_dim, bool one_slice)
 {
     const int64_t bytes = elems * (int64_t)elem;
     const bool kept = 2 * bytes + 10 * (elems / feat_dim) <= ((int64_t)256 << 20);
     const bool parts = one_slice ? feat_dim % (kScanLine / 2) != 0 && feat_dim < 192 : feat_dim % kScanLine != 0;
     if (parts && bytes > ((int64_t)256 << 20)) return kScanPlain;
-    if (parts && kept && bytes >= ((int64_t)40 << 20) && bytes + 4 * elems <= ((int64_t)300 << 20)) return kScanPlain;
+    if (one_slice && parts && kept && bytes >= ((int64_t)40 << 20) && bytes + 4 * elems <= ((int64_t)300 << 20)) return kScanPlain;
     return kept ? kScanCached : kScanStream;
 }
 
