@@ -185,10 +185,10 @@ def run_workload(args, wid: int, cold_sets: int = 0) -> dict:
         "phases_ms": {"plan": plan_ms, "pack": pack_ms, "segment_reduce": reduce_ms},
         # the planner is a latency-bound chain: per sequence it costs
         "plan_ns_per_sequence": plan_ms * 1e6 / max(1, N),
-        # the whole call: pack_prepare_kernel, the copy kernel and, for 4 KiB tiles over 2^21 slots or more,
-        # the pass that writes the start table (pack_narrow_kernel<unsigned char, false, false>)
-        "pack": dict(roofline_block(("pack_wide_kernel + start-table pass" if slots >= 1 << 21 else "pack_wide_kernel")
-                                    if wide else "pack_narrow_kernel", bytes_pack, pack_ms,
+        # the whole call: pack_direct_kernel up to 4096 tiles of 4 KiB, else pack_prepare_kernel, the copy kernel and, for such
+        # tiles over 2^21 slots or more, the pass that writes the start table (pack_narrow_kernel<unsigned char, false, false>)
+        "pack": dict(roofline_block("pack_narrow_kernel" if not wide else "pack_direct_kernel" if slots * F <= 1 << 24 else
+                                    "pack_wide_kernel + start-table pass" if slots >= 1 << 21 else "pack_wide_kernel", bytes_pack, pack_ms,
                                     measured_traffic(w.wid, "pack") if whole else None),
                      frames_per_s=local_frames / (pack_ms * 1e-3), min_ms=float(ms[:, 1].min()),
                      median_ms=float(np.median(ms[:, 1]))),

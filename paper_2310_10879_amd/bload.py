@@ -412,5 +412,5 @@ def bload_segment_reduce_layout(num_blocks: int, t_blk: int, feat_dim: int, dtyp
 def bload_pack_tile_bytes(n_seq: int, num_blocks: int, t_blk: int, frame_bytes: int,
                           src_aligned_16: bool = True) -> int:
     """4096 if ``bload_pack`` cuts the packed tensor into 4 KiB tiles for these sizes
-    (pack_wide_kernel), 0 if into tiles of 1024 slots (pack_narrow_kernel)."""
+    (pack_wide_kernel, pack_direct_kernel), 0 if into tiles of 1024 slots (pack_narrow_kernel, pack_narrow_direct_kernel)."""
     return int(_lib.bload_pack_tile_bytes(n_seq, num_blocks, t_blk, frame_bytes, int(src_aligned_16)))
