@@ -164,11 +164,15 @@ class Plan:
 
 
 def _new_plan(n: int, t_blk: int, dev) -> Plan:
-    # (one allocation: four take 5.2 us of the some 46 that plan, pack and reduction of a small batch take, this 3.8; every table begins
-    # at a multiple of 512 bytes, as one of its own would: side by side without gaps 2.9)
-    gap = -n % 128
-    tables = torch.empty(4 * n + 3 * gap + 1, dtype=torch.int32, device=dev).split_with_sizes((n, gap, n, gap, n, gap, n + 1))
-    return Plan(tables[0], tables[2], tables[4], tables[6], 0, 0, t_blk)
+    # (one allocation: four take 5.2 us of the some 46 that plan, pack and reduction of a small batch take, this 2.9, or 3.8 where the
+    # tables need gaps to begin at multiples of 256 bytes, as device memory of their own would)
+    gap = -n % 64
+    tables = torch.empty(4 * n + 3 * gap + 1, dtype=torch.int32, device=dev)
+    if gap:
+        order, _, block_of_seq, _, offset_of_seq, _, block_first = tables.split_with_sizes((n, gap, n, gap, n, gap, n + 1))
+    else:
+        order, block_of_seq, offset_of_seq, block_first = tables.split_with_sizes((n, n, n, n + 1))
+    return Plan(order, block_of_seq, offset_of_seq, block_first, 0, 0, t_blk)
 
 
 def bload_plan(lengths: torch.Tensor, t_blk: int, seed: int, workspace: torch.Tensor | None = None,
